@@ -183,6 +183,9 @@ struct xdg_basis_s {
     xdg::DevBuf sqrt_d;         // double [n_sym+1] sqrt(c), then [n_sym+1] 1/sqrt(c)
     xdg::DevBuf sqrt_f;         // float, same layout
     xdg::DeviceSearch dsearch;
+    // workspace of expect_szsz (which waits for its results), used under the lock
+    std::mutex measure_mu;
+    xdg::DevBuf measure_ws;
 };
 
 namespace xdg {
