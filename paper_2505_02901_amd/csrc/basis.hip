@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "device_common.hpp"
@@ -149,16 +150,37 @@ size_t lds_limit() {
 __host__ __device__ static inline size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
 // ------------------------------------------------------------ enumeration --
+// Candidates: for every segment, prefix | low << shift over the integers
+// `low` of `bits` bits and k set bits, ascending; ascending segments, so that
+// candidate number r is ascending too.  What a representative must look like
+// keeps the list short:
+//   sublattice coding: its top block is the minimal top of its own content (26
+//     of 512 contents on the 6x6 lattice): one segment per such content, the
+//     sites below it free.  4.2e8 candidates instead of 9.1e9 there.
+//   a full ring: the lowest site is up (else the state shifted down is
+//     smaller) and the top one down, unless all sites agree: one segment of
+//     N - 2 free sites, a quarter of the states.
+//   otherwise: one segment, all states.
+struct EnumSeg {
+    uint64_t base;      // number of the segment's first candidate
+    uint64_t prefix;
+    uint64_t k;
+};
+
 template <class W>
 struct EnumArgs {
-    int N, n_up, n_sym;
+    int N, n_sym;
+    int bits, shift, n_seg;
+    const EnumSeg *segs;       // [n_seg + 1], the last one's base is the total
     uint64_t total, n_chunks;
-    uint32_t chunk_len;
+    uint32_t chunk_len;        // a multiple of 32
     const uint64_t *binom;     // [65][65]
     uint32_t *counts;          // [n_chunks] (count pass)
-    const uint64_t *offsets;   // [n_chunks] (fill pass; NULL = rank itself)
+    uint32_t *keep;            // [chunk_len / 32][n_chunks] kept candidates, or null
+    const uint64_t *offsets;   // [n_chunks] (fill passes; NULL = the number itself)
     W *reps;
     uint16_t *stab;
+    uint64_t dim;
     const double2 *chi;
     const AffineElem *aff;
     const uint64_t *bytetab;
@@ -173,17 +195,50 @@ struct EnumArgs {
     int stage_sub;
 };
 
-template <class W, int KIND, bool FILL>
-__global__ __launch_bounds__(256) void k_enum(EnumArgs<W> A) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const double2 *chi = A.chi;
-    const AffineElem *aff = A.aff;
-    SubCtx C{A.mintop, A.cand_off, A.cand_list, A.sp, A.tperm, A.n_s, A.m, A.pb};
-    if constexpr (KIND != K_U1) {
+template <class W>
+struct Candidates {
+    const EnumArgs<W> &A;
+    int seg;
+    W low;
+    uint64_t r, end;    // this candidate's number, and the segment's end
+    __device__ __forceinline__ Candidates(const EnumArgs<W> &A_, uint64_t r0) : A(A_), r(r0) {
+        int lo = 0, hi = A.n_seg - 1;   // last segment with base <= r0
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (A.segs[mid].base <= r0) lo = mid; else hi = mid - 1;
+        }
+        seg = lo;
+        end = A.segs[seg + 1].base;
+        low = unrank_colex<W>(r0 - A.segs[seg].base, A.bits, (int)A.segs[seg].k, A.binom);
+    }
+    __device__ __forceinline__ W state() const { return (W)A.segs[seg].prefix | (low << A.shift); }
+    __device__ __forceinline__ void next() {
+        if (++r < end) {
+            low = next_same_popcount<W>(low);
+        } else {
+            ++seg;
+            end = A.segs[seg + 1].base;
+            low = (W(1) << A.segs[seg].k) - 1;   // every segment is shorter than W here
+        }
+    }
+};
+
+constexpr int ENUM_BLOCK = 1024;   // 16 waves share the staged tables
+
+// Representative test of the enumeration with the tables in LDS.
+template <class W, int KIND>
+struct RepTest {
+    const EnumArgs<W> &A;
+    const double2 *chi;
+    const AffineElem *aff;
+    SubCtx C;
+    __device__ __forceinline__ RepTest(const EnumArgs<W> &A_, unsigned char *smem) : A(A_) {
+        C = SubCtx{A.mintop, A.cand_off, A.cand_list, A.sp, A.tperm, A.n_s, A.m, A.pb};
         double2 *lchi = reinterpret_cast<double2 *>(smem);
         size_t off = align16(sizeof(double2) * A.n_sym);
         for (int g = threadIdx.x; g < A.n_sym; g += blockDim.x) lchi[g] = A.chi[g];
         chi = lchi;
+        aff = A.aff;
         if constexpr (KIND == K_AFF) {
             AffineElem *laff = reinterpret_cast<AffineElem *>(smem + off);
             for (int g = threadIdx.x; g < A.n_sym; g += blockDim.x) laff[g] = A.aff[g];
@@ -191,65 +246,103 @@ __global__ __launch_bounds__(256) void k_enum(EnumArgs<W> A) {
         }
         if constexpr (KIND == K_SUB) {
             if (A.stage_sub) {
+                auto copy = [&](auto *src, uint32_t n) {
+                    auto *dst = reinterpret_cast<std::remove_const_t<std::remove_pointer_t<decltype(src)>> *>(smem + off);
+                    off = align16(off + sizeof(*src) * (size_t)n);
+                    for (uint32_t e = threadIdx.x; e < n; e += blockDim.x) dst[e] = src[e];
+                    return dst;
+                };
                 const uint32_t NV = (uint32_t)A.n_s << A.m;
-                uint16_t *lmt = reinterpret_cast<uint16_t *>(smem + off);
-                off = align16(off + 2 * NV);
-                uint32_t *lco = reinterpret_cast<uint32_t *>(smem + off);
-                off = align16(off + 4 * (NV + 1));
-                uint16_t *lcl = reinterpret_cast<uint16_t *>(smem + off);
-                for (uint32_t e = threadIdx.x; e < NV; e += blockDim.x) lmt[e] = A.mintop[e];
-                for (uint32_t e = threadIdx.x; e <= NV; e += blockDim.x) lco[e] = A.cand_off[e];
-                for (uint32_t e = threadIdx.x; e < A.n_cand; e += blockDim.x) lcl[e] = A.cand_list[e];
-                off = align16(off + 2 * (size_t)A.n_cand);
-                const uint32_t GS = (uint32_t)A.n_sym * A.n_s;
-                uint32_t *lsp = reinterpret_cast<uint32_t *>(smem + off);
-                off = align16(off + 4 * (size_t)GS);
-                uint16_t *ltp = reinterpret_cast<uint16_t *>(smem + off);
-                const uint32_t TP = (uint32_t)A.n_perm * 2u << A.pb;
-                for (uint32_t e = threadIdx.x; e < GS; e += blockDim.x) lsp[e] = A.sp[e];
-                for (uint32_t e = threadIdx.x; e < TP; e += blockDim.x) ltp[e] = A.tperm[e];
-                C.mintop = lmt;
-                C.cand_off = lco;
-                C.cand_list = lcl;
-                C.sp = lsp;
-                C.tperm = ltp;
+                C.mintop = copy(A.mintop, NV);
+                C.cand_off = copy(A.cand_off, NV + 1);
+                C.cand_list = copy(A.cand_list, A.n_cand);
+                C.sp = copy(A.sp, (uint32_t)A.n_sym * A.n_s);
+                C.tperm = copy(A.tperm, (uint32_t)A.n_perm * 2u << A.pb);
             }
         }
         __syncthreads();
     }
+    // s is the representative of an orbit that carries a symmetric state (the
+    // stabiliser sum of chi is nonzero); st = |Stab(s)|
+    __device__ __forceinline__ bool operator()(W s, int &st) const {
+        double cr, ci;
+        bool rep;
+        if constexpr (KIND == K_AFF)
+            rep = aff_is_rep<W>(aff, A.n_sym, A.N, s, chi, st, cr, ci);
+        else if constexpr (KIND == K_SUB)
+            rep = sub_is_rep<W>(C, s, chi, st, cr, ci);
+        else
+            rep = tab_is_rep<W>(A.bytetab, A.n_bchunks, A.n_sym, s, chi, st, cr, ci);
+        return rep && (cr * cr + ci * ci > 0.25);
+    }
+};
+
+// A lane per chunk of candidates: how many are kept and, with A.keep, which
+// (FILL = false); the kept ones at their place, tested again (FILL = true,
+// byte tables, whose bits would take more memory than the index).
+template <class W, int KIND, bool FILL>
+__global__ __launch_bounds__(ENUM_BLOCK) void k_enum(EnumArgs<W> A) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const RepTest<W, KIND> test(A, smem);
     const uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= A.n_chunks) return;
     const uint64_t r0 = c * A.chunk_len;
     const uint64_t r1 = r0 + A.chunk_len < A.total ? r0 + A.chunk_len : A.total;
-    W s = unrank_colex<W>(r0, A.N, A.n_up, A.binom);
-    uint64_t pos = FILL ? (A.offsets ? A.offsets[c] : r0) : 0;
-    uint32_t cnt = 0;
+    Candidates<W> cand(A, r0);
+    uint64_t pos = FILL ? A.offsets[c] : 0;
+    uint32_t cnt = 0, bits = 0;
     for (uint64_t r = r0; r < r1; ++r) {
-        bool keep = true;
-        int st = 1;
-        if constexpr (KIND != K_U1) {
-            double cr, ci;
-            bool rep;
-            if constexpr (KIND == K_AFF)
-                rep = aff_is_rep<W>(aff, A.n_sym, A.N, s, chi, st, cr, ci);
-            else if constexpr (KIND == K_SUB)
-                rep = sub_is_rep<W>(C, s, chi, st, cr, ci);
-            else
-                rep = tab_is_rep<W>(A.bytetab, A.n_bchunks, A.n_sym, s, chi, st, cr, ci);
-            // the orbit carries a symmetric state iff the stabiliser sum of chi is nonzero
-            keep = rep && (cr * cr + ci * ci > 0.25);
-        }
-        if (keep) {
+        const W s = cand.state();
+        int st;
+        if (test(s, st)) {
             if constexpr (FILL) {
                 A.reps[pos] = s;
-                if constexpr (KIND != K_U1) A.stab[pos] = (uint16_t)st;
+                A.stab[pos] = (uint16_t)st;
                 ++pos;
             }
             ++cnt;
+            bits |= 1u << (uint32_t)((r - r0) & 31);
         }
-        if (r + 1 < r1) s = next_same_popcount<W>(s);
+        if (!FILL && A.keep && (((r - r0) & 31) == 31 || r + 1 == r1)) {
+            A.keep[((r - r0) >> 5) * A.n_chunks + c] = bits;
+            bits = 0;
+        }
+        if (r + 1 < r1) cand.next();
     }
     if constexpr (!FILL) A.counts[c] = cnt;
+}
+
+// The kept candidates at their place: all of them (U(1)) or those of A.keep.
+template <class W>
+__global__ __launch_bounds__(256) void k_enum_fill(EnumArgs<W> A) {
+    const uint64_t c = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    if (c >= A.n_chunks) return;
+    const uint64_t r0 = c * A.chunk_len;
+    const uint64_t r1 = r0 + A.chunk_len < A.total ? r0 + A.chunk_len : A.total;
+    Candidates<W> cand(A, r0);
+    uint64_t pos = A.offsets ? A.offsets[c] : r0;
+    for (uint64_t b0 = r0; b0 < r1; b0 += 32) {
+        const uint64_t b1 = b0 + 32 < r1 ? b0 + 32 : r1;
+        const uint32_t bits = A.keep ? A.keep[((b0 - r0) >> 5) * A.n_chunks + c] : ~0u;
+        for (uint64_t r = b0; r < b1; ++r) {
+            if ((bits >> (uint32_t)(r - b0)) & 1u) A.reps[pos++] = cand.state();
+            if (r + 1 < r1) cand.next();
+        }
+    }
+}
+
+// |Stab| of every basis state (all lanes busy, unlike in the count pass,
+// where one candidate in 13 is kept on the 6x6 lattice)
+template <class W, int KIND>
+__global__ __launch_bounds__(ENUM_BLOCK) void k_stab(EnumArgs<W> A) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const RepTest<W, KIND> test(A, smem);
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < A.dim; i += stride) {
+        int st;
+        (void)test(A.reps[i], st);
+        A.stab[i] = (uint16_t)st;
+    }
 }
 
 // ------------------------------------------------------------------- scan --
@@ -434,13 +527,50 @@ int random_fill(int64_t n_scalars, uint64_t seed, int kind, bool single, void *o
 // ------------------------------------------------------------- host side --
 namespace {
 
+// The candidate segments of a block (see EnumSeg), the last one's end included.
+void enum_segments(const xdg_basis_s *b, std::vector<EnumSeg> *segs, int *bits, int *shift) {
+    const int N = b->n_sites, n = b->n_up;
+    *bits = N;
+    *shift = 0;
+    uint64_t acc = 0;
+    auto add = [&](uint64_t prefix, int k) {
+        segs->push_back({acc, prefix, (uint64_t)k});
+        acc += binomial(*bits, k);
+    };
+    const SublatticeTables &S = b->plan.sub;
+    if (b->plan.kind == K_SUB && S.n_s >= 2) {
+        *bits = (S.n_s - 1) * S.m;
+        for (uint32_t c = 0; c < 1u << S.m; ++c) {
+            const int k = n - __builtin_popcount(c);
+            if (k < 0 || k > *bits || S.mintop[((size_t)(S.n_s - 1) << S.m) + c] != c) continue;
+            add((uint64_t)c << *bits, k);
+        }
+    } else if (b->plan.kind == K_AFF && b->plan.ring && N >= 3 && n > 0 && n < N) {
+        *bits = N - 2;
+        *shift = 1;
+        add(1, n - 1);
+    } else {
+        add(0, n);
+    }
+    segs->push_back({acc, 0, 0});
+}
+
 template <class W>
 int enumerate(xdg_basis_s *b, DevBuf &binom_d) {
-    const int N = b->n_sites, n = b->n_up, kind = b->plan.kind;
-    const uint64_t total = binomial(N, n);
+    const int kind = b->plan.kind;
     EnumArgs<W> A{};
-    A.N = N;
-    A.n_up = n;
+    std::vector<EnumSeg> segs;
+    enum_segments(b, &segs, &A.bits, &A.shift);
+    const uint64_t total = segs.back().base;
+    if (total == 0) {
+        b->dim = 0;
+        return XDG_OK;
+    }
+    DevBuf segs_d;
+    XDG_RETURN_IF(segs_d.upload(segs.data(), segs.size() * sizeof(EnumSeg)));
+    A.segs = segs_d.as<EnumSeg>();
+    A.n_seg = (int)segs.size() - 1;
+    A.N = b->n_sites;
     A.n_sym = b->n_sym;
     A.total = total;
     A.binom = binom_d.as<uint64_t>();
@@ -459,9 +589,11 @@ int enumerate(xdg_basis_s *b, DevBuf &binom_d) {
     A.n_perm = b->plan.sub.n_perm;
     A.n_cand = (uint32_t)b->plan.sub.cand_list.size();
 
-    const uint64_t lanes_target = (uint64_t)device_cu_count() * 1024;
+    // a lane per chunk: enough lanes for the chip twice over, chunks long
+    // enough to pay for their first state
+    const uint64_t lanes_target = (uint64_t)device_cu_count() * 4096;
     uint64_t cl = total / lanes_target;
-    cl = std::max<uint64_t>(16, std::min<uint64_t>(4096, cl));
+    cl = std::max<uint64_t>(32, std::min<uint64_t>(4096, cl)) / 32 * 32;
     A.chunk_len = (uint32_t)cl;
     A.n_chunks = (total + cl - 1) / cl;
 
@@ -481,43 +613,44 @@ int enumerate(xdg_basis_s *b, DevBuf &binom_d) {
             }
         }
     }
-    const int block = 256;
-    const uint64_t grid = (A.n_chunks + block - 1) / block;
-    if (grid > 0x7fffffffull) {
+    auto blocks_of = [](uint64_t lanes, int block) { return (lanes + block - 1) / block; };
+    if (blocks_of(A.n_chunks, 256) > 0x7fffffffull) {
         set_error("enumeration grid too large");
         return XDG_EINVAL;
     }
-    auto kcount = k_enum<W, K_U1, false>;
-    auto kfill = k_enum<W, K_U1, true>;
+    const unsigned grid = (unsigned)blocks_of(A.n_chunks, ENUM_BLOCK);
+    const unsigned fill_grid = (unsigned)blocks_of(A.n_chunks, 256);
+    void (*kcount)(EnumArgs<W>) = nullptr, (*kfill)(EnumArgs<W>) = nullptr,
+        (*kstab)(EnumArgs<W>) = nullptr;
     if (kind == K_AFF) {
         kcount = k_enum<W, K_AFF, false>;
-        kfill = k_enum<W, K_AFF, true>;
+        kstab = k_stab<W, K_AFF>;
     } else if (kind == K_SUB) {
         kcount = k_enum<W, K_SUB, false>;
-        kfill = k_enum<W, K_SUB, true>;
+        kstab = k_stab<W, K_SUB>;
     } else if (kind == K_TAB) {
         kcount = k_enum<W, K_TAB, false>;
         kfill = k_enum<W, K_TAB, true>;
     }
-    if (lds > 65536) {
-        XDG_TRY_HIP(hipFuncSetAttribute((const void *)kcount,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        XDG_TRY_HIP(hipFuncSetAttribute((const void *)kfill,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    }
+    for (auto f : {kcount, kfill, kstab})
+        if (f && lds > 65536)
+            XDG_TRY_HIP(hipFuncSetAttribute((const void *)f,
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
 
-    DevBuf counts, offsets, tiles, tot;
+    DevBuf counts, offsets, tiles, tot, keep;
     uint64_t dim;
     if (kind == K_U1) {
         dim = total;
     } else {
         XDG_RETURN_IF(counts.alloc(sizeof(uint32_t) * A.n_chunks));
         XDG_RETURN_IF(offsets.alloc(sizeof(uint64_t) * A.n_chunks));
+        if (kind != K_TAB) XDG_RETURN_IF(keep.alloc(cl / 8 * A.n_chunks));
         const uint64_t n_tiles = (A.n_chunks + 1023) / 1024;
         XDG_RETURN_IF(tiles.alloc(sizeof(uint64_t) * n_tiles));
         XDG_RETURN_IF(tot.alloc(sizeof(uint64_t)));
         A.counts = counts.as<uint32_t>();
-        hipLaunchKernelGGL(kcount, dim3((unsigned)grid), dim3(block), lds, 0, A);
+        A.keep = keep.as<uint32_t>();
+        hipLaunchKernelGGL(kcount, dim3(grid), dim3(ENUM_BLOCK), lds, 0, A);
         XDG_TRY_HIP(hipGetLastError());
         hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)n_tiles), dim3(1024), 0, 0,
                            counts.as<uint32_t>(), A.n_chunks, tiles.as<uint64_t>());
@@ -541,7 +674,18 @@ int enumerate(xdg_basis_s *b, DevBuf &binom_d) {
     if (kind != K_U1) XDG_RETURN_IF(b->stab.alloc(sizeof(uint16_t) * dim));
     A.reps = b->reps.as<W>();
     A.stab = b->stab.as<uint16_t>();
-    hipLaunchKernelGGL(kfill, dim3((unsigned)grid), dim3(block), lds, 0, A);
+    A.dim = dim;
+    if (kfill) {
+        hipLaunchKernelGGL(kfill, dim3(grid), dim3(ENUM_BLOCK), lds, 0, A);
+    } else {
+        hipLaunchKernelGGL(k_enum_fill<W>, dim3(fill_grid), dim3(256), 0, 0, A);
+        XDG_TRY_HIP(hipGetLastError());
+        if (kstab) {
+            const unsigned g = (unsigned)std::min<uint64_t>(blocks_of(dim, ENUM_BLOCK),
+                                                            (uint64_t)device_cu_count() * 2);
+            hipLaunchKernelGGL(kstab, dim3(g), dim3(ENUM_BLOCK), lds, 0, A);
+        }
+    }
     XDG_TRY_HIP(hipGetLastError());
     XDG_TRY_HIP(hipDeviceSynchronize());
     return XDG_OK;
