@@ -62,9 +62,18 @@ int launch_dispatch(int kind, bool wide, bool single, bool acc64, bool cplx, int
     return XDG_EINVAL;
 }
 
-SectorDesc make_desc(const xdg_ham_s *h, bool single, const void *x, void *y) {
-    const xdg_basis_s *b = h->basis;
+// The sector the products run in: the relabelled one where there is one.
+const xdg_basis_s *product_basis(const xdg_ham_s *h) {
+    return h->basis->inner ? h->basis->inner.get() : h->basis;
+}
+
+// relabelled: through the relabelled sector where there is one
+SectorDesc make_desc(const xdg_ham_s *h, bool single, const void *x, void *y,
+                     bool relabelled = true) {
+    const xdg_basis_s *b = relabelled ? product_basis(h) : h->basis;
+    const BondSet &bonds = b == h->basis ? h->bonds : h->inner_bonds;
     SectorDesc d{};
+    d.umap = b == h->basis ? nullptr : h->basis->umap.as<uint32_t>();
     d.reps = b->reps.p;
     d.stab = b->stab.as<uint16_t>();
     d.dim = b->dim;
@@ -97,19 +106,15 @@ SectorDesc make_desc(const xdg_ham_s *h, bool single, const void *x, void *y) {
     d.pb = b->plan.sub.pb;
     d.n_perm = b->plan.sub.n_perm;
     d.n_cand = (uint32_t)b->plan.sub.cand_list.size();
-    d.subf = b->plan.kind == K_SUB && sub_packed_ok(d.n_s, d.m, d.pb) && h->bonds_x.p;
-    d.bx = d.subf ? h->bonds_x.as<BondX>() : nullptr;
-    d.bonds = single ? h->bonds_f.p : h->bonds_d.p;
+    d.subf = b->plan.kind == K_SUB && sub_packed_ok(d.n_s, d.m, d.pb) && bonds.x.p;
+    d.bx = d.subf ? bonds.x.as<BondX>() : nullptr;
+    d.bonds = single ? bonds.f.p : bonds.d.p;
     d.chi = single ? b->chi_f.p : b->chi_d.p;
     d.sqrtt = single ? b->sqrt_f.p : b->sqrt_d.p;
     double jq = 0.0;
     for (double j : h->jz) jq += 0.25 * j;
     d.jz_quarter = jq;
-    d.ring_bonds = h->n_bonds == b->n_sites;
-    for (int i = 0; i < h->n_bonds && d.ring_bonds; ++i) {
-        const int p = h->sites[2 * i], q = h->sites[2 * i + 1], r = (i + 1) % b->n_sites;
-        d.ring_bonds = (p == i && q == r) || (p == r && q == i);
-    }
+    d.ring_bonds = bonds.ring;
     d.x = x;
     d.y = y;
     return d;
@@ -153,11 +158,20 @@ template <class W, class T>
 __global__ __launch_bounds__(256) void k_xr_scatter(const W *reps, int64_t dim, int spr,
                                                    const T *x, T *xr, const uint32_t *rtab,
                                                    RankLayout L, int B, const uint64_t *top,
-                                                   uint64_t slots) {
+                                                   uint64_t slots, const uint32_t *umap) {
     const int64_t stride = (int64_t)gridDim.x * 256;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < dim; i += stride) {
         const uint64_t r = top_rank<W>(rtab, L, B, top, reps[i]);
         if (r >= slots) continue;   // never for a basis state
+        if (umap) {                 // relabelled sector: the caller's position and sign
+            const uint32_t u = gld(umap + i);
+            const int64_t p = (int64_t)(u & 0x7FFFFFFFu);
+            for (int c = 0; c < spr; ++c) {
+                const T v = x[p * spr + c];
+                xr[r * spr + c] = u >> 31 ? -v : v;
+            }
+            continue;
+        }
         for (int c = 0; c < spr; ++c) xr[r * spr + c] = x[i * spr + c];
     }
 }
@@ -171,7 +185,8 @@ __global__ __launch_bounds__(256) void k_zero32(uint32_t *p, uint64_t n) {
 // wait for the last launch that read it, (re)allocate and zero it when the
 // layout changes (not under graph capture), then scatter x.
 int xr_prepare(xdg_ham_s *h, const void *x, const Form &f, hipStream_t st, bool *capturing) {
-    const xdg_basis_s *b = h->basis;
+    const xdg_basis_s *b = product_basis(h);
+    const uint32_t *umap = b == h->basis ? nullptr : h->basis->umap.as<uint32_t>();
     const int spr = (int)f.cols * (f.cplx_kernel ? 2 : 1);
     const size_t tsz = f.single ? 4 : 8;
     const size_t slot_bytes = (size_t)spr * tsz;
@@ -207,23 +222,23 @@ int xr_prepare(xdg_ham_s *h, const void *x, const Form &f, hipStream_t st, bool 
             hipLaunchKernelGGL((k_xr_scatter<uint64_t, float>), dim3(g), dim3(256), 0, st,
                                b->reps.as<uint64_t>(), b->dim, spr, (const float *)x,
                                h->xr_buf.as<float>(), b->xr_rtab.as<uint32_t>(), b->rank, b->xr_bits, top,
-                               b->xr_slots);
+                               b->xr_slots, umap);
         else
             hipLaunchKernelGGL((k_xr_scatter<uint64_t, double>), dim3(g), dim3(256), 0, st,
                                b->reps.as<uint64_t>(), b->dim, spr, (const double *)x,
                                h->xr_buf.as<double>(), b->xr_rtab.as<uint32_t>(), b->rank, b->xr_bits, top,
-                               b->xr_slots);
+                               b->xr_slots, umap);
     } else {
         if (f.single)
             hipLaunchKernelGGL((k_xr_scatter<uint32_t, float>), dim3(g), dim3(256), 0, st,
                                b->reps.as<uint32_t>(), b->dim, spr, (const float *)x,
                                h->xr_buf.as<float>(), b->xr_rtab.as<uint32_t>(), b->rank, b->xr_bits, top,
-                               b->xr_slots);
+                               b->xr_slots, umap);
         else
             hipLaunchKernelGGL((k_xr_scatter<uint32_t, double>), dim3(g), dim3(256), 0, st,
                                b->reps.as<uint32_t>(), b->dim, spr, (const double *)x,
                                h->xr_buf.as<double>(), b->xr_rtab.as<uint32_t>(), b->rank, b->xr_bits, top,
-                               b->xr_slots);
+                               b->xr_slots, umap);
     }
     XDG_TRY_HIP(hipGetLastError());
     return XDG_OK;
@@ -240,7 +255,7 @@ int pick_nv(int64_t remaining, int cap) {
 // LDS bytes the apply kernel stages for this form, whether the sublattice
 // tables fit with them, and whether two workgroups fit one compute unit
 void apply_lds(const xdg_ham_s *h, int dtype, size_t *lds, int *stage_sub, int *occ_ok) {
-    const xdg_basis_s *b = h->basis;
+    const xdg_basis_s *b = product_basis(h);
     const bool tsingle = dtype_single(dtype) && (b->plan.flags & XDG_FLAG_F32_ACCUMULATE);
     const SectorDesc d = make_desc(h, tsingle, nullptr, nullptr);
     size_t n = tsingle ? stage_bytes<float>(d, b->plan.kind, 1)
@@ -257,7 +272,7 @@ void apply_lds(const xdg_ham_s *h, int dtype, size_t *lds, int *stage_sub, int *
 
 int apply_launch(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, hipStream_t st,
                  const LaunchCfg *cfg) {
-    const xdg_basis_s *b = h->basis;
+    const xdg_basis_s *b = product_basis(h);
     Form f;
     XDG_RETURN_IF(form_of(b, dtype, nvec, &f));
     if (b->dim == 0) return XDG_OK;
@@ -357,7 +372,7 @@ int apply_tuned(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, h
         lock.unlock();
         return apply_launch(h, x, y, nvec, dtype, st, &c);
     }
-    const xdg_basis_s *b = h->basis;
+    const xdg_basis_s *b = product_basis(h);
     Form f;
     XDG_RETURN_IF(form_of(b, dtype, nvec, &f));
     const int64_t need = (b->dim + APPLY_BLOCK - 1) / APPLY_BLOCK;
@@ -486,7 +501,9 @@ int ham_count_nnz(xdg_ham_s *h, int64_t *nnz) {
     XDG_RETURN_IF(cnt.alloc(sizeof(unsigned long long)));
     XDG_TRY_HIP(hipMemset(cnt.p, 0, sizeof(unsigned long long)));
     ApplyArgs A{};
-    A.one = make_desc(h, false, nullptr, nullptr);
+    // in the caller's labels: with repeated bonds the terms of a row depend on
+    // which state of its orbit stands for it
+    A.one = make_desc(h, false, nullptr, nullptr, false);
     A.count = cnt.as<unsigned long long>();
     A.stage_sub = 1;
     size_t lds = stage_bytes<double>(A.one, b->plan.kind, 1);
@@ -537,8 +554,13 @@ int batch_plan_host(int n, xdg_ham_s *const *hams, const void *const *xs, void *
         set_error("bad dtype or nvec");
         return XDG_EINVAL;
     }
+    // byte-table blocks run relabelled if all of them can; sublattice blocks
+    // mix freely (one kernel serves both)
+    bool relabelled = true;
+    if (b0->plan.kind == K_TAB)
+        for (int i = 0; i < n; ++i) relabelled &= hams[i]->basis->inner != nullptr;
     P->n = n;
-    P->kind = b0->plan.kind;
+    P->kind = relabelled ? product_basis(hams[0])->plan.kind : b0->plan.kind;
     P->wide = b0->wide;
     P->single = dtype_single(dtype);
     P->acc64 = !P->single || !(b0->plan.flags & XDG_FLAG_F32_ACCUMULATE);
@@ -551,7 +573,7 @@ int batch_plan_host(int n, xdg_ham_s *const *hams, const void *const *xs, void *
     size_t lds_full = 0, lds_part = 0;
     uint64_t acc = 0;
     for (int i = 0; i < n; ++i) {
-        const SectorDesc d = make_desc(hams[i], P->tsingle, xs[i], ys[i]);
+        const SectorDesc d = make_desc(hams[i], P->tsingle, xs[i], ys[i], relabelled);
         const uint64_t tiles = (hams[i]->basis->dim + P->tile_rows - 1) / P->tile_rows;
         if (acc + tiles >= 0xFFFFFFFFull) {
             set_error("too many row tiles in the batch");

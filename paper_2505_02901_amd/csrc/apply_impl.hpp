@@ -89,6 +89,9 @@ struct SectorDesc {
     int xr_bits;                 // sites below the top block
     const uint32_t *xr_rtab;     // the rank tables' rows for the chunks below it, 4-byte entries
     int xr_rows;                 // rows of xr_rtab
+    // relabelled sector: position in x and y of the orbit of basis state k,
+    // bit 31 where its sign differs (sublattice kind only; null: k itself)
+    const uint32_t *umap;
     const void *x;
     void *y;
 };
@@ -317,6 +320,15 @@ __device__ __forceinline__ typename IndexT<W>::type locate(const SectorDesc &d, 
     }
 }
 
+// Position of basis state k in the caller's vectors; flips the sign of `f`
+// where the caller's symmetric state differs by one.
+template <class A>
+__device__ __forceinline__ int64_t user_pos(const SectorDesc &d, int64_t k, A &f) {
+    const uint32_t v = gld(d.umap + k);
+    f = v >> 31 ? -f : f;
+    return (int64_t)(v & 0x7FFFFFFFu);
+}
+
 // T: storage type of x and y; A: type of the amplitudes and of the per-row
 // accumulation (each output element is rounded to T once, at the store).
 // XR: the terms read the rank-addressed x (sublattice coding, d.xr set);
@@ -346,6 +358,9 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
     for (int v = 0; v < NV * C; ++v) acc[v] = 0;
     A rn = A(1);
     if constexpr (KIND != K_U1) rn = S.rsq[gld(d.stab + row)];
+    int64_t orow = row;
+    if constexpr (KIND == K_SUB)
+        if (d.umap) orow = user_pos<A>(d, row, rn);
     // explicit fused multiply-adds: a complex kernel on a block with real
     // characters (ai = 0) rounds exactly like the real kernel
     auto add = [&](A ar, A ai, const T *xv) {
@@ -368,14 +383,17 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
     // key: the packed sublattice search's key of the term's state, if given
     auto term = [&](const B &bd, W t, const SubKey *key) {
         int u, cnt;
-        const auto idx = locate<W, KIND, A, XR>(d, S, t, u, cnt, key);
+        auto idx = locate<W, KIND, A, XR>(d, S, t, u, cnt, key);
+        A hs = bd.h;
+        if constexpr (KIND == K_SUB && XR == 0)
+            if (d.umap && idx >= 0) idx = user_pos<A>(d, idx, hs);
         if constexpr (PIPE) {
             // the gather is issued for every term (row 0 when the orbit is
             // not in the block: a valid address, never added)
             const bool ok = idx >= 0;
             A ar = 0, ai = 0;
             if (ok) {
-                const A f = bd.h * S.sq[cnt];
+                const A f = hs * S.sq[cnt];
                 if constexpr (XR == 2) {
                     ar = f;   // chi(u) = 1
                 } else {
@@ -396,9 +414,9 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
             return;
         }
         if (idx < 0) return;
-        A ar = bd.h, ai = 0;
+        A ar = hs, ai = 0;
         if constexpr (KIND != K_U1) {
-            const A f = bd.h * S.sq[cnt];   // times 1/sqrt|Stab r| once per row
+            const A f = hs * S.sq[cnt];   // times 1/sqrt|Stab r| once per row
             const auto c = S.chi[u];
             ar = f * c.x;
             if constexpr (CPLX) ai = f * c.y;
@@ -484,7 +502,7 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
             }
         }
     }
-    const size_t base = ((size_t)row * nvec + v0) * C;
+    const size_t base = ((size_t)orow * nvec + v0) * C;
     const A diag = (A)d.jz_quarter - A(0.5) * junq;
 #pragma unroll
     for (int v = 0; v < NV * C; ++v) {
@@ -605,10 +623,13 @@ __device__ __forceinline__ void process_window(const SectorDesc &d, const Staged
             if (has) {
                 const W t = (second ? t1 : t0) ^ flip;
                 int u, cnt;
-                const auto idx = locate<W, KIND, A>(d, S, t, u, cnt);
+                auto idx = locate<W, KIND, A>(d, S, t, u, cnt);
                 if (idx >= 0) {
                     ok = true;
-                    const A f = bd.h * S.sq[cnt];
+                    A hs = bd.h;
+                    if constexpr (KIND == K_SUB)
+                        if (d.umap) idx = user_pos<A>(d, idx, hs);
+                    const A f = hs * S.sq[cnt];
                     const auto c = S.chi[u];
                     ar = f * c.x;
                     if constexpr (CPLX) ai = f * c.y;
@@ -649,8 +670,11 @@ __device__ __forceinline__ void process_window(const SectorDesc &d, const Staged
             const B bd = S.bonds[b];
             if (unequal(sh, bd)) junq += bd.jz;
         }
-        const A rn = S.rsq[gld(d.stab + row)];
-        const size_t base = ((size_t)row * nvec + v0) * C;
+        A rn = S.rsq[gld(d.stab + row)];
+        int64_t orow = row;
+        if constexpr (KIND == K_SUB)
+            if (d.umap) orow = user_pos<A>(d, row, rn);
+        const size_t base = ((size_t)orow * nvec + v0) * C;
         const A diag = (A)d.jz_quarter - A(0.5) * junq;
         const A *acc = h == 0 ? acc0 : acc1;
 #pragma unroll

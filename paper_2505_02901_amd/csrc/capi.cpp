@@ -34,6 +34,52 @@ int guarded(F &&f) {
 
 }  // namespace
 
+namespace xdg {
+
+int upload_bonds(const xdg_basis_s *b, int n_bonds, const int32_t *sites, const double *jz,
+                 const double *jxy, BondSet *out) {
+    const SublatticeTables &sp = b->plan.sub;
+    const bool sub = b->plan.kind == XDG_SEARCH_SUBLATTICE;
+    // device bond order: for sublattice coding, bonds joining the same pair
+    // of blocks are kept together (stable), so that bonds taken one after
+    // the other change the same two blocks of a state
+    std::vector<int> order(n_bonds);
+    for (int i = 0; i < n_bonds; ++i) order[i] = i;
+    if (sub && sp.m > 0) {
+        auto key = [&](int k) {
+            const int p = sites[2 * k] / sp.m, q = sites[2 * k + 1] / sp.m;
+            return std::min(p, q) * 64 + std::max(p, q);
+        };
+        std::stable_sort(order.begin(), order.end(),
+                         [&](int a, int c) { return key(a) < key(c); });
+    }
+    std::vector<BondD> bd(n_bonds);
+    std::vector<BondF> bf(n_bonds);
+    for (int e = 0; e < n_bonds; ++e) {
+        const int i = order[e];
+        bd[e] = BondD{(uint32_t)sites[2 * i], (uint32_t)sites[2 * i + 1], jz[i], 0.5 * jxy[i]};
+        bf[e] = BondF{bd[e].i, bd[e].j, (float)jz[i], (float)(0.5 * jxy[i])};
+    }
+    XDG_RETURN_IF(out->d.upload(bd.data(), sizeof(BondD) * std::max(n_bonds, 1)));
+    XDG_RETURN_IF(out->f.upload(bf.data(), sizeof(BondF) * std::max(n_bonds, 1)));
+    if (sub && sub_packed_ok(sp.n_s, sp.m, sp.pb)) {
+        std::vector<BondX> bx(std::max(n_bonds, 1), BondX{});
+        for (int e = 0; e < n_bonds; ++e) {
+            bondx_site((int)bd[e].i, sp.m, sp.pb, bx[e]);
+            bondx_site((int)bd[e].j, sp.m, sp.pb, bx[e]);
+        }
+        XDG_RETURN_IF(out->x.upload(bx.data(), sizeof(BondX) * bx.size()));
+    }
+    out->ring = n_bonds == b->n_sites;
+    for (int i = 0; i < n_bonds && out->ring; ++i) {
+        const int p = sites[2 * i], q = sites[2 * i + 1], r = (i + 1) % b->n_sites;
+        out->ring = (p == i && q == r) || (p == r && q == i);
+    }
+    return XDG_OK;
+}
+
+}  // namespace xdg
+
 extern "C" {
 
 const char *xdg_version(void) { return "xdg-mi355x 0.1.0 (gfx950, HIP)"; }
@@ -110,6 +156,9 @@ int xdg_create_basis(int n_sites, int n_up, int n_sym, const int32_t *perm, cons
             }
         }
         if (rc == XDG_OK) rc = basis_build_device(b);
+        if (rc == XDG_OK && (!opts || opts->search == XDG_SEARCH_AUTO) &&
+            (!opts || opts->n_sublattices == 0))
+            rc = basis_build_inner(b);
         if (rc != XDG_OK) {
             delete b;
             return rc;
@@ -243,38 +292,11 @@ int xdg_create_hamiltonian(xdg_basis b, int n_bonds, const int32_t *sites, const
         h->sites.assign(sites, sites + 2 * (size_t)n_bonds);
         h->jz.assign(jz, jz + n_bonds);
         h->jxy.assign(jxy, jxy + n_bonds);
-        // device bond order: for sublattice coding, bonds joining the same pair
-        // of blocks are kept together (stable), so that bonds taken one after
-        // the other change the same two blocks of a state
-        std::vector<int> order(n_bonds);
-        for (int i = 0; i < n_bonds; ++i) order[i] = i;
-        if (b->plan.kind == XDG_SEARCH_SUBLATTICE && b->plan.sub.m > 0) {
-            const int m = b->plan.sub.m;
-            auto key = [&](int k) {
-                const int p = sites[2 * k] / m, q = sites[2 * k + 1] / m;
-                return std::min(p, q) * 64 + std::max(p, q);
-            };
-            std::stable_sort(order.begin(), order.end(),
-                             [&](int a, int c) { return key(a) < key(c); });
-        }
-        std::vector<BondD> bd(n_bonds);
-        std::vector<BondF> bf(n_bonds);
-        for (int e = 0; e < n_bonds; ++e) {
-            const int i = order[e];
-            bd[e] = BondD{(uint32_t)sites[2 * i], (uint32_t)sites[2 * i + 1], jz[i], 0.5 * jxy[i]};
-            bf[e] = BondF{bd[e].i, bd[e].j, (float)jz[i], (float)(0.5 * jxy[i])};
-        }
-        int rc = h->bonds_d.upload(bd.data(), sizeof(BondD) * std::max(n_bonds, 1));
-        if (rc == XDG_OK) rc = h->bonds_f.upload(bf.data(), sizeof(BondF) * std::max(n_bonds, 1));
-        const auto &sp = b->plan.sub;
-        if (rc == XDG_OK && b->plan.kind == XDG_SEARCH_SUBLATTICE &&
-            sub_packed_ok(sp.n_s, sp.m, sp.pb)) {
-            std::vector<BondX> bx(std::max(n_bonds, 1), BondX{});
-            for (int e = 0; e < n_bonds; ++e) {
-                bondx_site((int)bd[e].i, sp.m, sp.pb, bx[e]);
-                bondx_site((int)bd[e].j, sp.m, sp.pb, bx[e]);
-            }
-            rc = h->bonds_x.upload(bx.data(), sizeof(BondX) * bx.size());
+        int rc = upload_bonds(b, n_bonds, sites, jz, jxy, &h->bonds);
+        if (rc == XDG_OK && b->inner) {
+            std::vector<int32_t> in(2 * (size_t)n_bonds);
+            for (size_t e = 0; e < in.size(); ++e) in[e] = b->inner_pos[sites[e]];
+            rc = upload_bonds(b->inner.get(), n_bonds, in.data(), jz, jxy, &h->inner_bonds);
         }
         if (rc != XDG_OK) {
             basis_release(h->basis);

@@ -329,6 +329,84 @@ void build_bytes(int N, int n_sym, const int32_t *perm, ByteTables *B) {
 
 }  // namespace
 
+std::vector<int32_t> relabel_group(int N, int n_sym, const int32_t *perm,
+                                   const std::vector<int> &pos) {
+    std::vector<int32_t> out((size_t)n_sym * N);
+    for (int g = 0; g < n_sym; ++g)
+        for (int i = 0; i < N; ++i)
+            out[(size_t)g * N + pos[i]] = pos[perm[(size_t)g * N + i]];
+    return out;
+}
+
+// The partitions of the sites that the group respects: for a transitive group
+// the smallest one joining site 0 with site j, for every j, and the joins of
+// those found.  Of those with four classes of 5 to 10 sites the one with the
+// fewest candidate elements in its search tables is taken.
+std::vector<int> four_block_labels(int N, int n_sym, const int32_t *perm) {
+    if (N % 4 || !sub_packed_ok(4, N / 4, (N / 4 + 1) / 2) || n_sym < 4 || n_sym > 4096) return {};
+    using Classes = std::vector<int>;   // smallest site of each site's class
+    struct Join {
+        std::vector<int> up;
+        int find(int a) {
+            while (up[a] != a) a = up[a] = up[up[a]];
+            return a;
+        }
+    };
+    // the finest respected partition that joins every pair given
+    auto close = [&](std::vector<std::pair<int, int>> pairs) {
+        Join u;
+        for (int i = 0; i < N; ++i) u.up.push_back(i);
+        while (!pairs.empty()) {
+            const auto [a, b] = pairs.back();
+            pairs.pop_back();
+            const int x = u.find(a), y = u.find(b);
+            if (x == y) continue;
+            u.up[std::max(x, y)] = std::min(x, y);
+            for (int g = 0; g < n_sym; ++g) {
+                const int32_t *q = perm + (size_t)g * N;
+                if (u.find(q[a]) != u.find(q[b])) pairs.push_back({q[a], q[b]});
+            }
+        }
+        Classes c(N);
+        for (int i = 0; i < N; ++i) c[i] = u.find(i);
+        return c;
+    };
+    std::vector<Classes> found;
+    auto add = [&](Classes c) {
+        if (std::find(found.begin(), found.end(), c) == found.end()) found.push_back(std::move(c));
+    };
+    for (int j = 1; j < N; ++j) add(close({{0, j}}));
+    for (size_t a = 0; a < found.size() && found.size() < 64; ++a)
+        for (size_t b = 0; b < a && found.size() < 64; ++b) {
+            std::vector<std::pair<int, int>> both;
+            for (int i = 0; i < N; ++i) {
+                both.push_back({i, found[a][i]});
+                both.push_back({i, found[b][i]});
+            }
+            add(close(both));
+        }
+    std::vector<int> best;
+    size_t best_cost = ~(size_t)0;
+    for (const Classes &c : found) {
+        std::map<int, std::vector<int>> blocks;
+        for (int i = 0; i < N; ++i) blocks[c[i]].push_back(i);
+        bool ok = blocks.size() == 4;
+        for (const auto &b : blocks) ok &= (int)b.second.size() == N / 4;
+        if (!ok) continue;
+        std::vector<int> pos(N);
+        int at = 0;
+        for (const auto &b : blocks)
+            for (int i : b.second) pos[i] = at++;
+        SublatticeTables T;
+        build_sublattice(N, n_sym, relabel_group(N, n_sym, perm, pos).data(), 4, &T);
+        if (T.cand_list.size() < best_cost) {
+            best_cost = T.cand_list.size();
+            best = pos;
+        }
+    }
+    return best;
+}
+
 int make_plan(int n_sites, int n_sym, const int32_t *perm, const xdg_basis_opts *opts, Plan *plan,
               bool build_tables) {
     const int want = opts ? opts->search : XDG_SEARCH_AUTO;

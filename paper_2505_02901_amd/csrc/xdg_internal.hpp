@@ -111,6 +111,11 @@ int validate_bonds(int n_sites, int n_sym, const int32_t *perm, int n_bonds, con
                    const double *jz, const double *jxy);
 int make_plan(int n_sites, int n_sym, const int32_t *perm, const xdg_basis_opts *opts, Plan *plan,
               bool build_tables);
+// Site labels in which the group maps four blocks of 5 to 10 consecutive
+// sites onto blocks: pos[i] is the new label of site i.  Empty if there are none.
+std::vector<int> four_block_labels(int n_sites, int n_sym, const int32_t *perm);
+std::vector<int32_t> relabel_group(int n_sites, int n_sym, const int32_t *perm,
+                                   const std::vector<int> &pos);
 uint64_t binomial(int n, int k);
 
 // ---------------------------------------------------------------- basis --
@@ -183,6 +188,14 @@ struct xdg_basis_s {
     xdg::DevBuf sqrt_d;         // double [n_sym+1] sqrt(c), then [n_sym+1] 1/sqrt(c)
     xdg::DevBuf sqrt_f;         // float, same layout
     xdg::DeviceSearch dsearch;
+    // The same sector in site labels that suit the packed sublattice search,
+    // for the products with H (see basis_build_inner): its own
+    // representatives, stabilisers and index.  umap[k]: position in this
+    // basis of the orbit of the inner state k, with bit 31 set where the two
+    // symmetric states differ by a sign.
+    std::unique_ptr<xdg_basis_s> inner;
+    std::vector<int> inner_pos; // inner label of every site
+    xdg::DevBuf umap;           // u32 [dim]
     // workspace of expect_szsz (which waits for its results), used under the lock
     std::mutex measure_mu;
     xdg::DevBuf measure_ws;
@@ -207,15 +220,24 @@ struct LaunchCfg {
 };
 }  // namespace xdg
 
+namespace xdg {
+// Device copies of a bond list in one labelling of the sites.
+struct BondSet {
+    DevBuf d;      // BondD [n_bonds]
+    DevBuf f;      // BondF [n_bonds]
+    DevBuf x;      // BondX [n_bonds] (packed sublattice search only)
+    int ring = 0;  // 1: n_bonds = n_sites and bond b joins sites b and b + 1 mod N
+};
+}  // namespace xdg
+
 struct xdg_ham_s {
     xdg_basis_s *basis = nullptr;
     uint64_t serial = 0;        // unique per created Hamiltonian (cache keys)
     int n_bonds = 0;
     std::vector<int32_t> sites;
     std::vector<double> jz, jxy;
-    xdg::DevBuf bonds_d;        // BondD [n_bonds]
-    xdg::DevBuf bonds_f;        // BondF [n_bonds]
-    xdg::DevBuf bonds_x;        // BondX [n_bonds] (packed sublattice search only)
+    xdg::BondSet bonds;         // in the caller's labels
+    xdg::BondSet inner_bonds;   // in the labels of basis->inner, if any
     int64_t nnz = -1;
     std::mutex tune_mu;         // guards `tuned` (and the tuning runs that fill it)
     std::map<xdg::TuneKey, xdg::LaunchCfg> tuned;
@@ -268,6 +290,10 @@ inline void bondx_site(int i, int m, int pb, BondX &x) {
 }
 
 int basis_build_device(xdg_basis_s *b);                 // enumerate + index
+int basis_build_inner(xdg_basis_s *b);                  // b->inner and b->umap, where they apply
+// Device copies of bonds (labels `sites`) for a basis planned in those labels.
+int upload_bonds(const xdg_basis_s *b, int n_bonds, const int32_t *sites, const double *jz,
+                 const double *jxy, BondSet *out);
 int basis_lookup(xdg_basis_s *b, const uint64_t *d_states, int64_t n, int64_t *d_idx,
                  hipStream_t st);
 int ham_count_nnz(xdg_ham_s *h, int64_t *nnz);

@@ -1,0 +1,104 @@
+"""Products on sectors whose site labels hide four blocks (lattices numbered row
+by row, three-sublattice labels): they run in other labels, so positions, signs
+of real characters and amplitudes all pass through the map between the two."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def X():
+    import paper_2505_02901_amd as X
+    return X
+
+
+def rowmajor(a1, a2, n_up, irrep="A1", j2=0.0, reflections=True):
+    t = W.Torus(a1, a2, blocked=False)
+    sites, jz, jxy = t.j1j2_bonds(1.0, j2)
+    perm, labels = t.symmetry_group(True, reflections)
+    chi = W.gamma_characters(labels, *W.IRREPS_C4V[irrep])
+    return W.Model(f"rows{t.n_sites}_{irrep}", t.n_sites, n_up, sites, 0.7 * jz, jxy, perm, chi)
+
+
+CASES = {
+    "rows36_A1": rowmajor((6, 0), (0, 6), 5, "A1", 0.5),
+    "rows36_B1": rowmajor((6, 0), (0, 6), 4, "B1"),
+    "rows36_A2": rowmajor((6, 0), (0, 6), 4, "A2", 0.5),
+    "rows20_A1": rowmajor((4, 2), (-2, 4), 10, "A1", 0.0, False),
+    "rows20_B1": rowmajor((4, 2), (-2, 4), 9, "B1", 0.0, False),
+    "rows32_B2": rowmajor((4, 4), (-4, 4), 6, "B2"),
+    "rows40_A1": rowmajor((6, 2), (-2, 6), 4, "A1", 0.0, False),
+    "triangle36": W.sublattice_model("triangle3", (6, 0), (0, 6), n_up=4, delta=0.3),
+    "triangle36_odd": W.sublattice_model("triangle3", (6, 0), (0, 6), n_up=5, rot_char=-1.0),
+    "square20_2": W.sublattice_model("square2", (4, 2), (-2, 4)),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_products_match_oracle(X, name):
+    m = CASES[name]
+    b = X.Basis.from_model(m)
+    H = X.Hamiltonian.from_model(b, m)
+    basis = oracle.basis(m)
+    assert np.array_equal(b.states(), basis)
+    for nvec, cplx in ((1, False), (3, False), (2, True), (8, False)):
+        x = W.random_vector(7 + nvec, b.dim, nvec, kind="uniform", complex_=cplx)
+        want = oracle.apply(m, basis, x)
+        want = want if cplx else want.real
+        for dt, tol in ((x.dtype, 1e-12), (np.complex64 if cplx else np.float32, 2e-6)):
+            xt = torch.from_numpy(x.astype(dt)).cuda()
+            y = torch.full_like(xt, 9.0)
+            H.apply(xt, y)
+            err = np.max(np.abs(y.cpu().numpy() - want)) / np.max(np.abs(want))
+            assert err < tol, (name, nvec, dt, err)
+            for shape in (dict(grid=3), dict(occ=0), dict(compact=1), dict(sub_form=2),
+                          dict(xr=1), dict(xr=1, occ=0), dict(nv=1)):
+                z = torch.full_like(xt, 5.0)
+                X.xdg_apply_with_config(H.handle, xt, z, **shape)
+                assert torch.equal(y, z), (name, nvec, dt, shape)
+    # the same block with every element tried for every term
+    t = X.Basis.from_model(m, search=4)
+    T = X.Hamiltonian.from_model(t, m)
+    assert H.nnz == T.nnz
+    x = torch.from_numpy(W.random_vector(1, b.dim, 1, kind="uniform")).cuda()
+    y, z = torch.empty_like(x), torch.empty_like(x)
+    H.apply(x, y)
+    T.apply(x, z)
+    assert float((y - z).abs().max()) < 1e-13 * float(y.abs().max())
+
+
+def test_batches(X):
+    """Relabelled blocks together, and with a complex one that keeps its labels."""
+    models = [CASES["rows20_A1"], CASES["rows20_B1"]]
+    t = W.Torus((4, 2), (-2, 4), blocked=False)
+    perm, labels = t.symmetry_group(True, False)
+    turned = models[0].with_sector(perm, W.gamma_characters(labels, 1j, 1.0))
+    for ms, dt in ((models, torch.float64), (models + [turned], torch.complex128)):
+        bs = [X.Basis.from_model(m) for m in ms]
+        hs = [X.Hamiltonian.from_model(b, m) for b, m in zip(bs, ms)]
+        xs = [torch.randn(b.dim, 3, dtype=dt, device="cuda") for b in bs]
+        for f in (X.xdg_apply_batched, X.xdg_apply_batched_noalloc):
+            ys = [torch.full_like(x, 3.0) for x in xs]
+            f([h.handle for h in hs], xs, ys)
+            for m, x, y in zip(ms, xs, ys):
+                want = oracle.apply(m, oracle.basis(m), x.cpu().numpy())
+                assert np.max(np.abs(y.cpu().numpy() - want)) < 1e-12 * np.max(np.abs(want))
+
+
+def test_lanczos_and_correlations(X):
+    m = CASES["rows20_A1"]
+    b = X.Basis.from_model(m)
+    H = X.Hamiltonian.from_model(b, m)
+    e, psi, _, _ = H.eig0(tol=1e-13, max_iter=200, seed=4)
+    basis = oracle.basis(m)
+    want = oracle.apply(m, basis, psi.cpu().numpy()).real
+    assert np.max(np.abs(want - e * psi.cpu().numpy())) < 1e-5
+    full, amp = oracle.expand_state(m, basis, psi.cpu().numpy())
+    pairs = [(0, 1), (0, 7), (3, 3)]
+    zz = X.xdg_expect_szsz(b.handle, psi, pairs)
+    assert np.max(np.abs(zz - [oracle.szsz_definition(full, amp, *p) for p in pairs])) < 1e-12
