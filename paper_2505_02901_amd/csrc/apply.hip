@@ -152,10 +152,10 @@ int form_of(const xdg_basis_s *b, int dtype, int64_t nvec, Form *f) {
     return XDG_OK;
 }
 
-// Rank-addressed x: row i of x goes to slot top_rank(reps[i]) of xr (spr
-// scalars per row); the other slots hold zeros.
+// Rank-addressed x: row i of x (spr scalars) goes to slot top_rank(reps[i]) of
+// xr (`slot` scalars apart); the other slots hold zeros.
 template <class W, class T>
-__global__ __launch_bounds__(256) void k_xr_scatter(const W *reps, int64_t dim, int spr,
+__global__ __launch_bounds__(256) void k_xr_scatter(const W *reps, int64_t dim, int spr, int slot,
                                                    const T *x, T *xr, const uint32_t *rtab,
                                                    RankLayout L, int B, const uint64_t *top,
                                                    uint64_t slots, const uint32_t *umap) {
@@ -168,17 +168,25 @@ __global__ __launch_bounds__(256) void k_xr_scatter(const W *reps, int64_t dim, 
             const int64_t p = (int64_t)(u & 0x7FFFFFFFu);
             for (int c = 0; c < spr; ++c) {
                 const T v = x[p * spr + c];
-                xr[r * spr + c] = u >> 31 ? -v : v;
+                xr[r * slot + c] = u >> 31 ? -v : v;
             }
             continue;
         }
-        for (int c = 0; c < spr; ++c) xr[r * spr + c] = x[i * spr + c];
+        for (int c = 0; c < spr; ++c) xr[r * slot + c] = x[i * spr + c];
     }
 }
 
 __global__ __launch_bounds__(256) void k_zero32(uint32_t *p, uint64_t n) {
     const uint64_t stride = (uint64_t)gridDim.x * 256;
     for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) p[i] = 0u;
+}
+
+// Columns of a slot of the rank-addressed x: up to eight are padded to a power
+// of two, so that a slot lies in one cache line (the padding is never used).
+int xr_columns(int64_t cols) {
+    int n = 1;
+    while (n < cols) n *= 2;
+    return cols <= 8 ? n : (int)cols;
 }
 
 // Fill the rank-addressed copy of x for this call (caller holds h->xr_mu):
@@ -188,8 +196,9 @@ int xr_prepare(xdg_ham_s *h, const void *x, const Form &f, hipStream_t st, bool 
     const xdg_basis_s *b = product_basis(h);
     const uint32_t *umap = b == h->basis ? nullptr : h->basis->umap.as<uint32_t>();
     const int spr = (int)f.cols * (f.cplx_kernel ? 2 : 1);
+    const int slot = xr_columns(f.cols) * (f.cplx_kernel ? 2 : 1);   // scalars
     const size_t tsz = f.single ? 4 : 8;
-    const size_t slot_bytes = (size_t)spr * tsz;
+    const size_t slot_bytes = (size_t)slot * tsz;
     const size_t need = (size_t)b->xr_slots * slot_bytes;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     XDG_TRY_HIP(hipStreamIsCapturing(st, &cs));
@@ -220,23 +229,23 @@ int xr_prepare(xdg_ham_s *h, const void *x, const Form &f, hipStream_t st, bool 
     if (b->wide) {
         if (f.single)
             hipLaunchKernelGGL((k_xr_scatter<uint64_t, float>), dim3(g), dim3(256), 0, st,
-                               b->reps.as<uint64_t>(), b->dim, spr, (const float *)x,
+                               b->reps.as<uint64_t>(), b->dim, spr, slot, (const float *)x,
                                h->xr_buf.as<float>(), b->xr_rtab.as<uint32_t>(), b->rank, b->xr_bits, top,
                                b->xr_slots, umap);
         else
             hipLaunchKernelGGL((k_xr_scatter<uint64_t, double>), dim3(g), dim3(256), 0, st,
-                               b->reps.as<uint64_t>(), b->dim, spr, (const double *)x,
+                               b->reps.as<uint64_t>(), b->dim, spr, slot, (const double *)x,
                                h->xr_buf.as<double>(), b->xr_rtab.as<uint32_t>(), b->rank, b->xr_bits, top,
                                b->xr_slots, umap);
     } else {
         if (f.single)
             hipLaunchKernelGGL((k_xr_scatter<uint32_t, float>), dim3(g), dim3(256), 0, st,
-                               b->reps.as<uint32_t>(), b->dim, spr, (const float *)x,
+                               b->reps.as<uint32_t>(), b->dim, spr, slot, (const float *)x,
                                h->xr_buf.as<float>(), b->xr_rtab.as<uint32_t>(), b->rank, b->xr_bits, top,
                                b->xr_slots, umap);
         else
             hipLaunchKernelGGL((k_xr_scatter<uint32_t, double>), dim3(g), dim3(256), 0, st,
-                               b->reps.as<uint32_t>(), b->dim, spr, (const double *)x,
+                               b->reps.as<uint32_t>(), b->dim, spr, slot, (const double *)x,
                                h->xr_buf.as<double>(), b->xr_rtab.as<uint32_t>(), b->rank, b->xr_bits, top,
                                b->xr_slots, umap);
     }
@@ -244,11 +253,10 @@ int xr_prepare(xdg_ham_s *h, const void *x, const Form &f, hipStream_t st, bool 
     return XDG_OK;
 }
 
-int pick_nv(int64_t remaining, int cap) {
-    int nv = 8;
-    while (nv > 1 && (nv > remaining || nv > cap)) nv >>= 1;
-    return nv;
-}
+// Vectors of the next pass: a kernel exists for every number up to 8, so that
+// three vectors share one search (two passes of 2 and 1 took 10.7 ms on the
+// 6x6 triangular lattice, 12 of 36 up, FP64).
+int pick_nv(int64_t remaining, int cap) { return (int)std::min<int64_t>(remaining, cap); }
 
 }  // namespace
 
@@ -298,6 +306,7 @@ int apply_launch(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, 
         A.one.xr_top = b->xr_top.as<uint64_t>();
         A.one.xr_top32 = b->xr_top32.as<uint32_t>();
         A.one.xr_slots = b->xr_slots;
+        A.one.xr_cols = xr_columns(f.cols);
         A.one.xr_bits = b->xr_bits;
         A.one.xr_rows = b->xr_rows;
         A.one.xr_rtab = b->xr_rtab.as<uint32_t>();
@@ -327,7 +336,10 @@ int apply_launch(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, 
     }
     A.occ = A.stage_sub ? (c.occ >= 0 ? (c.occ && occ_for(lds)) : occ_for(lds)) : 0;
     A.compact = c.compact > 0 && !xr_on ? 1 : 0;   // the compacted loop reads x itself
-    const int cap = std::min(c.nv > 0 ? c.nv : 8, xr_on ? 2 : 8);
+    const int cap = std::min(c.nv > 0 ? c.nv : 8,
+                             xr_on                          ? xr_max_nv(f.cplx_kernel)
+                             : A.compact && f.cols <= 3 ? 2   // the compacted loop takes two
+                                                        : 8);
     for (int64_t v0 = 0; v0 < f.cols;) {
         const int nv = pick_nv(f.cols - v0, cap);
         A.v0 = (int)v0;

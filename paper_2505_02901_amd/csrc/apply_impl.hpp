@@ -86,6 +86,7 @@ struct SectorDesc {
     const uint64_t *xr_top;      // [2^m] first rank of each top block, ~0 if none
     const uint32_t *xr_top32;    // the same in 4 bytes (0xFFFFFFFF if none), when all fit; or null
     uint64_t xr_slots;           // slots of xr (beyond the last one: not in the block)
+    int xr_cols;                 // columns of a slot (see xr_columns)
     int xr_bits;                 // sites below the top block
     const uint32_t *xr_rtab;     // the rank tables' rows for the chunks below it, 4-byte entries
     int xr_rows;                 // rows of xr_rtab
@@ -405,7 +406,8 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
             // the previous gather (issued one search ago) is added first, so
             // that the new one can land in the same registers
             if (p_ok) add(p_ar, p_ai, p_x);
-            const size_t xb = ((size_t)(ok ? idx : 0) * nvec + v0) * C;
+            const size_t xb =
+                ((size_t)(ok ? idx : 0) * (XR != 0 ? (int64_t)d.xr_cols : nvec) + v0) * C;
 #pragma unroll
             for (int v = 0; v < NV * C; ++v) p_x[v] = gld(XT + xb + v);
             p_ok = ok;
@@ -803,19 +805,21 @@ int launch_sub_xr(bool wide, bool single, bool acc64, bool cplx, int nv, const A
 int launch_sub_xr_trivial(bool wide, bool single, bool acc64, int nv, const ApplyArgs &A,
                           unsigned grid, unsigned block, size_t lds, hipStream_t st);
 
-// XR (the rank-addressed x): passes of at most two vectors.
-template <class W, int KIND, class T, class AC, bool CPLX, bool STAGE, bool OCC, bool CMP,
-          int XR = 0>
+// Kernels with 64 VGPRs, by the accumulator scalars of a lane: with more than
+// two it spills them (complex 8-vector passes: 200 bytes); the rank-addressed
+// kernels up to four.
+constexpr int occ_scalars(int xr) { return xr ? 4 : 2; }
+// Vectors per pass of the rank-addressed kernels: at most eight scalars.
+constexpr int xr_max_nv(bool cplx) { return cplx ? 4 : 8; }
+
+template <class W, int KIND, class T, class AC, bool CPLX, bool STAGE, bool OCC, bool CMP, int XR,
+          int NV = 1>
 void (*apply_kernel(int nv))(ApplyArgs) {
-    switch (nv) {
-        case 1: return k_apply<W, KIND, T, AC, CPLX, 1, STAGE, OCC, CMP, XR>;
-        case 2: return k_apply<W, KIND, T, AC, CPLX, 2, STAGE, OCC, CMP, XR>;
-    }
-    if constexpr (!CMP && XR == 0) {
-        switch (nv) {
-            case 4: return k_apply<W, KIND, T, AC, CPLX, 4, STAGE, OCC, false, 0>;
-            case 8: return k_apply<W, KIND, T, AC, CPLX, 8, STAGE, OCC, false, 0>;
-        }
+    constexpr int most = CMP ? 2 : XR ? xr_max_nv(CPLX) : 8;
+    constexpr int limit = OCC ? occ_scalars(XR) / (CPLX ? 2 : 1) : most;
+    if constexpr (NV <= (limit < most ? limit : most)) {
+        if (nv == NV) return k_apply<W, KIND, T, AC, CPLX, NV, STAGE, OCC, CMP, XR>;
+        return apply_kernel<W, KIND, T, AC, CPLX, STAGE, OCC, CMP, XR, NV + 1>(nv);
     }
     return nullptr;
 }
@@ -828,18 +832,15 @@ constexpr bool has_compact() { return KIND == K_SUB || KIND == K_TAB; }
 template <class W, int KIND, class T, class AC, bool CPLX, bool STAGE, bool OCC>
 void (*apply_kernel_loop(int nv, bool compact))(ApplyArgs) {
     if constexpr (has_compact<KIND>())
-        if (compact && nv <= 2) return apply_kernel<W, KIND, T, AC, CPLX, STAGE, OCC, true>(nv);
-    return apply_kernel<W, KIND, T, AC, CPLX, STAGE, OCC, false>(nv);
+        if (compact && nv <= 2) return apply_kernel<W, KIND, T, AC, CPLX, STAGE, OCC, true, 0>(nv);
+    return apply_kernel<W, KIND, T, AC, CPLX, STAGE, OCC, false, 0>(nv);
 }
 
 template <class W, int KIND, class T, class AC, bool CPLX, int XR>
 int launch_nv(int nv, const ApplyArgs &A, unsigned grid, unsigned block, size_t lds,
               hipStream_t st) {
     void (*f)(ApplyArgs) = nullptr;
-    // only the sublattice kind has tables that may stay in global memory
-    // the 64-VGPR copy only while a lane holds at most two accumulator
-    // scalars: with more it spills them (complex 8-vector passes: 200 bytes)
-    const bool occ = A.occ && nv * (CPLX ? 2 : 1) <= 2;
+    const bool occ = A.occ && nv * (CPLX ? 2 : 1) <= occ_scalars(XR);
     const bool cmp = A.compact != 0;
     if constexpr (XR == 2 && CPLX) {
         set_error("internal: the trivial-character kernels serve real blocks");
@@ -849,13 +850,14 @@ int launch_nv(int nv, const ApplyArgs &A, unsigned grid, unsigned block, size_t 
             f = occ ? apply_kernel<W, KIND, T, AC, CPLX, true, true, false, XR>(nv)
                     : apply_kernel<W, KIND, T, AC, CPLX, true, false, false, XR>(nv);
     } else if (KIND != K_SUB || A.stage_sub)
+        // only the sublattice kind has tables that may stay in global memory
         f = occ ? apply_kernel_loop<W, KIND, T, AC, CPLX, true, true>(nv, cmp)
                 : apply_kernel_loop<W, KIND, T, AC, CPLX, true, false>(nv, cmp);
     else if constexpr (KIND == K_SUB)
         f = apply_kernel_loop<W, KIND, T, AC, CPLX, false, false>(nv, cmp);
     if (!f) {
-        set_error("vectors per pass %d not in {1, 2, 4, 8} (at most 2 with the rank-addressed x, "
-                  "whose tables must be in LDS)", nv);
+        set_error("no kernel for %d vectors per pass (1 to 8; the rank-addressed x: at most eight "
+                  "scalars, tables in LDS)", nv);
         return XDG_EINVAL;
     }
     if (lds > 65536)
@@ -874,24 +876,33 @@ int launch_prec(bool single, bool acc64, int nv, const ApplyArgs &A, unsigned gr
     return launch_nv<W, KIND, float, float, CPLX, XR>(nv, A, grid, block, lds, st);
 }
 
-template <int KIND, int XR = 0>
-int launch_kind_impl(bool wide, bool single, bool acc64, bool cplx, int nv, const ApplyArgs &A,
-                     unsigned grid, unsigned block, size_t lds, hipStream_t st) {
+// One state width (a translation unit each for the sublattice kernels).
+template <class W, int KIND, int XR = 0>
+int launch_width(bool single, bool acc64, bool cplx, int nv, const ApplyArgs &A, unsigned grid,
+                 unsigned block, size_t lds, hipStream_t st) {
     if constexpr (KIND == K_U1) {
         if (cplx) {
             set_error("complex kernel requested for a U(1) block");
             return XDG_EINVAL;
         }
-        return wide ? launch_prec<uint64_t, KIND, false, XR>(single, acc64, nv, A, grid, block, lds, st)
-                    : launch_prec<uint32_t, KIND, false, XR>(single, acc64, nv, A, grid, block, lds, st);
+        return launch_prec<W, KIND, false, XR>(single, acc64, nv, A, grid, block, lds, st);
     } else {
-        if (wide)
-            return cplx ? launch_prec<uint64_t, KIND, true, XR>(single, acc64, nv, A, grid, block, lds, st)
-                        : launch_prec<uint64_t, KIND, false, XR>(single, acc64, nv, A, grid, block, lds, st);
-        return cplx ? launch_prec<uint32_t, KIND, true, XR>(single, acc64, nv, A, grid, block, lds, st)
-                    : launch_prec<uint32_t, KIND, false, XR>(single, acc64, nv, A, grid, block, lds, st);
+        return cplx ? launch_prec<W, KIND, true, XR>(single, acc64, nv, A, grid, block, lds, st)
+                    : launch_prec<W, KIND, false, XR>(single, acc64, nv, A, grid, block, lds, st);
     }
 }
+
+template <int KIND, int XR = 0>
+int launch_kind_impl(bool wide, bool single, bool acc64, bool cplx, int nv, const ApplyArgs &A,
+                     unsigned grid, unsigned block, size_t lds, hipStream_t st) {
+    return wide ? launch_width<uint64_t, KIND, XR>(single, acc64, cplx, nv, A, grid, block, lds, st)
+                : launch_width<uint32_t, KIND, XR>(single, acc64, cplx, nv, A, grid, block, lds, st);
+}
+
+int launch_sub_wide(bool single, bool acc64, bool cplx, int nv, const ApplyArgs &A, unsigned grid,
+                    unsigned block, size_t lds, hipStream_t st);
+int launch_sub_xr_wide(bool single, bool acc64, bool cplx, int nv, const ApplyArgs &A,
+                       unsigned grid, unsigned block, size_t lds, hipStream_t st);
 
 template <int KIND>
 int launch_count_impl(bool wide, const ApplyArgs &A, unsigned grid, unsigned block, size_t lds,

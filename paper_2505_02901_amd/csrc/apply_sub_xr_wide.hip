@@ -1,0 +1,12 @@
+// Instantiation of the sublattice apply kernels that read the rank-addressed x
+// for states wider than 32 bits.
+#include "apply_impl.hpp"
+
+namespace xdg {
+
+int launch_sub_xr_wide(bool single, bool acc64, bool cplx, int nv, const ApplyArgs &A,
+                       unsigned grid, unsigned block, size_t lds, hipStream_t st) {
+    return launch_width<uint64_t, K_SUB, 1>(single, acc64, cplx, nv, A, grid, block, lds, st);
+}
+
+}  // namespace xdg

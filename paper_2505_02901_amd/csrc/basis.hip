@@ -173,10 +173,10 @@ struct EnumArgs {
     int bits, shift, n_seg;
     const EnumSeg *segs;       // [n_seg + 1], the last one's base is the total
     uint64_t total, n_chunks;
-    uint32_t chunk_len;        // a multiple of 32
+    uint32_t chunk_len;        // a multiple of 32 if larger
     const uint64_t *binom;     // [65][65]
     uint32_t *counts;          // [n_chunks] (count pass)
-    uint32_t *keep;            // [chunk_len / 32][n_chunks] kept candidates, or null
+    uint32_t *keep;            // [ceil(chunk_len / 32)][n_chunks] kept candidates, or null
     const uint64_t *offsets;   // [n_chunks] (fill passes; NULL = the number itself)
     W *reps;
     uint16_t *stab;
@@ -223,7 +223,9 @@ struct Candidates {
     }
 };
 
-constexpr int ENUM_BLOCK = 1024;   // 16 waves share the staged tables
+// 16 waves share the staged tables; lists too short to fill the chip that way
+// take workgroups of one wave
+constexpr int ENUM_BLOCK = 1024;
 
 // Representative test of the enumeration with the tables in LDS.
 template <class W, int KIND>
@@ -592,8 +594,8 @@ int enumerate(xdg_basis_s *b, DevBuf &binom_d) {
     // a lane per chunk: enough lanes for the chip twice over, chunks long
     // enough to pay for their first state
     const uint64_t lanes_target = (uint64_t)device_cu_count() * 4096;
-    uint64_t cl = total / lanes_target;
-    cl = std::max<uint64_t>(32, std::min<uint64_t>(4096, cl)) / 32 * 32;
+    uint64_t cl = std::max<uint64_t>(4, std::min<uint64_t>(4096, total / lanes_target));
+    if (cl > 32) cl = cl / 32 * 32;
     A.chunk_len = (uint32_t)cl;
     A.n_chunks = (total + cl - 1) / cl;
 
@@ -618,7 +620,9 @@ int enumerate(xdg_basis_s *b, DevBuf &binom_d) {
         set_error("enumeration grid too large");
         return XDG_EINVAL;
     }
-    const unsigned grid = (unsigned)blocks_of(A.n_chunks, ENUM_BLOCK);
+    const int block =
+        A.n_chunks >= (uint64_t)device_cu_count() * ENUM_BLOCK ? ENUM_BLOCK : 64;
+    const unsigned grid = (unsigned)blocks_of(A.n_chunks, block);
     const unsigned fill_grid = (unsigned)blocks_of(A.n_chunks, 256);
     void (*kcount)(EnumArgs<W>) = nullptr, (*kfill)(EnumArgs<W>) = nullptr,
         (*kstab)(EnumArgs<W>) = nullptr;
@@ -644,13 +648,13 @@ int enumerate(xdg_basis_s *b, DevBuf &binom_d) {
     } else {
         XDG_RETURN_IF(counts.alloc(sizeof(uint32_t) * A.n_chunks));
         XDG_RETURN_IF(offsets.alloc(sizeof(uint64_t) * A.n_chunks));
-        if (kind != K_TAB) XDG_RETURN_IF(keep.alloc(cl / 8 * A.n_chunks));
+        if (kind != K_TAB) XDG_RETURN_IF(keep.alloc(4 * ((cl + 31) / 32) * A.n_chunks));
         const uint64_t n_tiles = (A.n_chunks + 1023) / 1024;
         XDG_RETURN_IF(tiles.alloc(sizeof(uint64_t) * n_tiles));
         XDG_RETURN_IF(tot.alloc(sizeof(uint64_t)));
         A.counts = counts.as<uint32_t>();
         A.keep = keep.as<uint32_t>();
-        hipLaunchKernelGGL(kcount, dim3(grid), dim3(ENUM_BLOCK), lds, 0, A);
+        hipLaunchKernelGGL(kcount, dim3(grid), dim3(block), lds, 0, A);
         XDG_TRY_HIP(hipGetLastError());
         hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)n_tiles), dim3(1024), 0, 0,
                            counts.as<uint32_t>(), A.n_chunks, tiles.as<uint64_t>());
@@ -676,14 +680,14 @@ int enumerate(xdg_basis_s *b, DevBuf &binom_d) {
     A.stab = b->stab.as<uint16_t>();
     A.dim = dim;
     if (kfill) {
-        hipLaunchKernelGGL(kfill, dim3(grid), dim3(ENUM_BLOCK), lds, 0, A);
+        hipLaunchKernelGGL(kfill, dim3(grid), dim3(block), lds, 0, A);
     } else {
         hipLaunchKernelGGL(k_enum_fill<W>, dim3(fill_grid), dim3(256), 0, 0, A);
         XDG_TRY_HIP(hipGetLastError());
         if (kstab) {
-            const unsigned g = (unsigned)std::min<uint64_t>(blocks_of(dim, ENUM_BLOCK),
+            const unsigned g = (unsigned)std::min<uint64_t>(blocks_of(dim, block),
                                                             (uint64_t)device_cu_count() * 2);
-            hipLaunchKernelGGL(kstab, dim3(g), dim3(ENUM_BLOCK), lds, 0, A);
+            hipLaunchKernelGGL(kstab, dim3(g), dim3(block), lds, 0, A);
         }
     }
     XDG_TRY_HIP(hipGetLastError());

@@ -1,0 +1,55 @@
+"""Every number of vectors from 1 to 11 in one product: passes of 1 to 8 vectors,
+with the padded slots of the rank-addressed copy, against single-vector products
+(bitwise: the passes share a search, not a sum)."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def X():
+    import paper_2505_02901_amd as X
+    return X
+
+
+def turned():
+    t = W.Torus((4, 2), (-2, 4))
+    m = W.torus_model((4, 2), (-2, 4), 1.0, 0.0, None, n_up=7)
+    perm, labels = t.symmetry_group(True, False)
+    return m.with_sector(perm, W.gamma_characters(labels, 1j, 1.0))
+
+
+CASES = {
+    "u1": (W.chain_model(12), {}), "ring": (W.chain_model(14, l=0), {}),
+    "ring_complex": (W.chain_model(14, l=3), {}), "wide_ring": (W.chain_model(34, n_up=3, l=1), {}),
+    "square16_table": (W.torus_model((4, 0), (0, 4), 1.0, 0.5, "B1"), {"search": 4}),
+    "square20": (W.torus_model((4, 2), (-2, 4), 1.0, 0.0, "A1", n_up=7, reflections=False), {}),
+    "square20_complex": (turned(), {}),
+    "square36": (W.torus_model((6, 0), (0, 6), 1.0, 0.0, "B1", n_up=5), {}),
+}
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64", "complex64", "complex128"])
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_columns(X, name, dtype):
+    m, kw = CASES[name]
+    b = X.Basis.from_model(m, **kw)
+    dt = getattr(torch, dtype)
+    if b.is_complex and not dt.is_complex:
+        return
+    H = X.Hamiltonian.from_model(b, m)
+    for nvec in range(1, 12):
+        x = torch.randn(b.dim, nvec, dtype=dt, device="cuda")
+        one = torch.stack([H.apply(x[:, v].contiguous(), torch.empty_like(x[:, v].contiguous()))
+                           for v in range(nvec)], 1)
+        for shape in ({}, {"xr": 1}, {"xr": 1, "occ": 0}, {"xr": 1, "nv": 2}, {"nv": 4}, {"compact": 1}):
+            y = torch.full_like(x, 3.0)
+            X.xdg_apply_with_config(H.handle, x, y, **shape)
+            assert torch.equal(y, one), (name, nvec, shape)
+        y = torch.full_like(x, 3.0)
+        X.xdg_apply_batched([H.handle], [x], [y])
+        assert torch.equal(y, one), (name, nvec, "batched")
