@@ -18,6 +18,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "xdg_internal.hpp"
@@ -38,29 +39,31 @@ __device__ inline void block_col_reduce(double *sh, int cols) {
     __syncthreads();
 }
 
-// partials[block][c] = sum over the block's scalars of column c of a*b.
-// The flat scalar index q has column q % cols because the grid stride is a
-// multiple of cols.
+// The vector operations of one workgroup: number lb of the nb that share the
+// vector's n scalars.  They are used by kernels on one vector block (lb =
+// blockIdx.x) and by kernels on many vector blocks at once (below), and give
+// the same bits in both.
+//
+// dot_part: partials[lb][c] = sum over the workgroup's scalars of column c of
+// a*b.  The flat scalar index q has column q % cols because the grid stride
+// is a multiple of cols.
 template <class T>
-__global__ __launch_bounds__(RB) void k_dot(const T *a, const T *b, uint64_t n, int cols,
-                                            double *partials) {
-    __shared__ double sh[RB];
+__device__ __forceinline__ void dot_part(const T *a, const T *b, uint64_t n, int cols,
+                                         double *partials, uint32_t lb, uint32_t nb, double *sh) {
     double acc = 0.0;
-    const uint64_t stride = (uint64_t)gridDim.x * RB;
-    for (uint64_t q = (uint64_t)blockIdx.x * RB + threadIdx.x; q < n; q += stride)
+    const uint64_t stride = (uint64_t)nb * RB;
+    for (uint64_t q = (uint64_t)lb * RB + threadIdx.x; q < n; q += stride)
         acc += (double)a[q] * (double)b[q];
     sh[threadIdx.x] = acc;
     block_col_reduce(sh, cols);
-    if ((int)threadIdx.x < cols) partials[(size_t)blockIdx.x * cols + threadIdx.x] = sh[threadIdx.x];
+    if ((int)threadIdx.x < cols) partials[(size_t)lb * cols + threadIdx.x] = sh[threadIdx.x];
 }
 
 // Fixed-order total of the partials, pairs of columns combined for complex
 // vectors (Re<a,b> = sum re*re + im*im).  mode 0: out = s; 1: out = sqrt(s).
-// hist (may be null) receives the value at row *jdev.
-__global__ __launch_bounds__(RB) void k_finalize(const double *partials, int n_blocks, int cols,
-                                                 int C, int mode, double *out, double *hist,
-                                                 const int *jdev) {
-    __shared__ double sh[RB];
+// hist (may be null) receives the values too.
+__device__ __forceinline__ void total_part(const double *partials, int n_blocks, int cols, int C,
+                                           int mode, double *out, double *hist, double *sh) {
     const int c = threadIdx.x % cols;
     double acc = 0.0;
     for (int blk = threadIdx.x / cols; blk < n_blocks; blk += RB / cols)
@@ -73,22 +76,22 @@ __global__ __launch_bounds__(RB) void k_finalize(const double *partials, int n_b
         if (C == 2) s += sh[v * C + 1];
         const double r = mode == 1 ? sqrt(s) : s;
         out[v] = r;
-        if (hist) hist[(size_t)(*jdev) * (cols / C) + v] = r;
+        if (hist) hist[v] = r;
     }
 }
 
 // w = w - alpha v - beta vprev (FP64, one rounding), partial |w|^2
 template <class T>
-__global__ __launch_bounds__(RB) void k_update(T *w, const T *v, const T *vprev, uint64_t n,
-                                               int cols, int C, const double *alpha,
-                                               const double *beta, double *partials) {
-    __shared__ double sh[RB];
+__device__ __forceinline__ void update_part(T *w, const T *v, const T *vprev, uint64_t n, int cols,
+                                            int C, const double *alpha, const double *beta,
+                                            double *partials, uint32_t lb, uint32_t nb,
+                                            double *sh) {
     double acc = 0.0;
-    const uint64_t stride = (uint64_t)gridDim.x * RB;
+    const uint64_t stride = (uint64_t)nb * RB;
     // cols divides RB, so every scalar of this thread is in column threadIdx.x % cols
     const int vec = (int)(threadIdx.x % cols) / C;
     const double a = alpha[vec], b = vprev ? beta[vec] : 0.0;
-    for (uint64_t q = (uint64_t)blockIdx.x * RB + threadIdx.x; q < n; q += stride) {
+    for (uint64_t q = (uint64_t)lb * RB + threadIdx.x; q < n; q += stride) {
         double x = (double)w[q] - a * (double)v[q];
         if (vprev) x -= b * (double)vprev[q];
         const T r = (T)x;
@@ -97,54 +100,53 @@ __global__ __launch_bounds__(RB) void k_update(T *w, const T *v, const T *vprev,
     }
     sh[threadIdx.x] = acc;
     block_col_reduce(sh, cols);
-    if ((int)threadIdx.x < cols) partials[(size_t)blockIdx.x * cols + threadIdx.x] = sh[threadIdx.x];
+    if ((int)threadIdx.x < cols) partials[(size_t)lb * cols + threadIdx.x] = sh[threadIdx.x];
 }
 
 // dst = src / beta  (zero where beta vanished: invariant subspace)
 template <class T>
-__global__ __launch_bounds__(RB) void k_scale(const T *src, T *dst, uint64_t n, int cols, int C,
-                                              const double *beta) {
-    const uint64_t stride = (uint64_t)gridDim.x * RB;
+__device__ __forceinline__ void scale_part(const T *src, T *dst, uint64_t n, int cols, int C,
+                                           const double *beta, uint32_t lb, uint32_t nb) {
+    const uint64_t stride = (uint64_t)nb * RB;
     // cols divides RB, so every scalar of this thread is in column threadIdx.x % cols
     const double bt = beta[(int)(threadIdx.x % cols) / C];
-    for (uint64_t q = (uint64_t)blockIdx.x * RB + threadIdx.x; q < n; q += stride)
+    for (uint64_t q = (uint64_t)lb * RB + threadIdx.x; q < n; q += stride)
         dst[q] = bt > 0.0 ? (T)((double)src[q] / bt) : T(0);
 }
 
 // One column (a single real vector): four consecutive scalars per thread
-// through one vector load each, the same arithmetic per scalar as the
-// kernels above.  Scalars past the last full group of four go to block 0.
+// through one vector load each, the same arithmetic per scalar as above.
+// Scalars past the last full group of four go to workgroup 0.
 template <class T>
 using Vec4 = T __attribute__((ext_vector_type(4)));
 
 template <class T>
-__global__ __launch_bounds__(RB) void k_dot1(const T *a, const T *b, uint64_t n,
-                                             double *partials) {
-    __shared__ double sh[RB];
+__device__ __forceinline__ void dot1_part(const T *a, const T *b, uint64_t n, double *partials,
+                                          uint32_t lb, uint32_t nb, double *sh) {
     double acc = 0.0;
-    const uint64_t n4 = n / 4, stride = (uint64_t)gridDim.x * RB;
-    for (uint64_t q = (uint64_t)blockIdx.x * RB + threadIdx.x; q < n4; q += stride) {
+    const uint64_t n4 = n / 4, stride = (uint64_t)nb * RB;
+    for (uint64_t q = (uint64_t)lb * RB + threadIdx.x; q < n4; q += stride) {
         const Vec4<T> x = reinterpret_cast<const Vec4<T> *>(a)[q];
         const Vec4<T> y = reinterpret_cast<const Vec4<T> *>(b)[q];
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc += (double)x[e] * (double)y[e];
     }
-    if (blockIdx.x == 0)
+    if (lb == 0)
         for (uint64_t q = 4 * n4 + threadIdx.x; q < n; q += RB) acc += (double)a[q] * (double)b[q];
     sh[threadIdx.x] = acc;
     block_col_reduce(sh, 1);
-    if (threadIdx.x == 0) partials[blockIdx.x] = sh[0];
+    if (threadIdx.x == 0) partials[lb] = sh[0];
 }
 
 template <class T>
-__global__ __launch_bounds__(RB) void k_update1(T *w, const T *v, const T *vprev, uint64_t n,
-                                                const double *alpha, const double *beta,
-                                                double *partials) {
-    __shared__ double sh[RB];
+__device__ __forceinline__ void update1_part(T *w, const T *v, const T *vprev, uint64_t n,
+                                             const double *alpha, const double *beta,
+                                             double *partials, uint32_t lb, uint32_t nb,
+                                             double *sh) {
     double acc = 0.0;
     const double a = alpha[0], b = vprev ? beta[0] : 0.0;
-    const uint64_t n4 = n / 4, stride = (uint64_t)gridDim.x * RB;
-    for (uint64_t q = (uint64_t)blockIdx.x * RB + threadIdx.x; q < n4; q += stride) {
+    const uint64_t n4 = n / 4, stride = (uint64_t)nb * RB;
+    for (uint64_t q = (uint64_t)lb * RB + threadIdx.x; q < n4; q += stride) {
         Vec4<T> x = reinterpret_cast<const Vec4<T> *>(w)[q];
         const Vec4<T> y = reinterpret_cast<const Vec4<T> *>(v)[q];
         Vec4<T> z = {};
@@ -159,7 +161,7 @@ __global__ __launch_bounds__(RB) void k_update1(T *w, const T *v, const T *vprev
         }
         reinterpret_cast<Vec4<T> *>(w)[q] = x;
     }
-    if (blockIdx.x == 0)
+    if (lb == 0)
         for (uint64_t q = 4 * n4 + threadIdx.x; q < n; q += RB) {
             double t = (double)w[q] - a * (double)v[q];
             if (vprev) t -= b * (double)vprev[q];
@@ -169,23 +171,160 @@ __global__ __launch_bounds__(RB) void k_update1(T *w, const T *v, const T *vprev
         }
     sh[threadIdx.x] = acc;
     block_col_reduce(sh, 1);
-    if (threadIdx.x == 0) partials[blockIdx.x] = sh[0];
+    if (threadIdx.x == 0) partials[lb] = sh[0];
 }
 
 template <class T>
-__global__ __launch_bounds__(RB) void k_scale1(const T *src, T *dst, uint64_t n,
-                                               const double *beta) {
+__device__ __forceinline__ void scale1_part(const T *src, T *dst, uint64_t n, const double *beta,
+                                            uint32_t lb, uint32_t nb) {
     const double bt = beta[0];
-    const uint64_t n4 = n / 4, stride = (uint64_t)gridDim.x * RB;
-    for (uint64_t q = (uint64_t)blockIdx.x * RB + threadIdx.x; q < n4; q += stride) {
+    const uint64_t n4 = n / 4, stride = (uint64_t)nb * RB;
+    for (uint64_t q = (uint64_t)lb * RB + threadIdx.x; q < n4; q += stride) {
         Vec4<T> x = reinterpret_cast<const Vec4<T> *>(src)[q];
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[e] = bt > 0.0 ? (T)((double)x[e] / bt) : T(0);
         reinterpret_cast<Vec4<T> *>(dst)[q] = x;
     }
-    if (blockIdx.x == 0)
+    if (lb == 0)
         for (uint64_t q = 4 * n4 + threadIdx.x; q < n; q += RB)
             dst[q] = bt > 0.0 ? (T)((double)src[q] / bt) : T(0);
+}
+
+// ---- one vector block ----
+template <class T>
+__global__ __launch_bounds__(RB) void k_dot(const T *a, const T *b, uint64_t n, int cols,
+                                            double *partials) {
+    __shared__ double sh[RB];
+    dot_part(a, b, n, cols, partials, blockIdx.x, gridDim.x, sh);
+}
+
+__global__ __launch_bounds__(RB) void k_finalize(const double *partials, int n_blocks, int cols,
+                                                 int C, int mode, double *out, double *hist,
+                                                 const int *jdev) {
+    __shared__ double sh[RB];
+    total_part(partials, n_blocks, cols, C, mode, out,
+               hist ? hist + (size_t)(*jdev) * (cols / C) : nullptr, sh);
+}
+
+template <class T>
+__global__ __launch_bounds__(RB) void k_update(T *w, const T *v, const T *vprev, uint64_t n,
+                                               int cols, int C, const double *alpha,
+                                               const double *beta, double *partials) {
+    __shared__ double sh[RB];
+    update_part(w, v, vprev, n, cols, C, alpha, beta, partials, blockIdx.x, gridDim.x, sh);
+}
+
+template <class T>
+__global__ __launch_bounds__(RB) void k_scale(const T *src, T *dst, uint64_t n, int cols, int C,
+                                              const double *beta) {
+    scale_part(src, dst, n, cols, C, beta, blockIdx.x, gridDim.x);
+}
+
+template <class T>
+__global__ __launch_bounds__(RB) void k_dot1(const T *a, const T *b, uint64_t n,
+                                             double *partials) {
+    __shared__ double sh[RB];
+    dot1_part(a, b, n, partials, blockIdx.x, gridDim.x, sh);
+}
+
+template <class T>
+__global__ __launch_bounds__(RB) void k_update1(T *w, const T *v, const T *vprev, uint64_t n,
+                                                const double *alpha, const double *beta,
+                                                double *partials) {
+    __shared__ double sh[RB];
+    update1_part(w, v, vprev, n, alpha, beta, partials, blockIdx.x, gridDim.x, sh);
+}
+
+template <class T>
+__global__ __launch_bounds__(RB) void k_scale1(const T *src, T *dst, uint64_t n,
+                                               const double *beta) {
+    scale1_part(src, dst, n, beta, blockIdx.x, gridDim.x);
+}
+
+// ---- many vector blocks at once ----
+// One launch for an operation on all blocks of a batch.  With a launch per
+// block a step of 20 small blocks was 123 graph nodes of 2-4 us (ring N = 20,
+// all momenta, four vectors each: 540 us per step); the workgroups of all
+// blocks are numbered through, each block keeping the workgroups, and so the
+// order of every sum, that it has alone.
+struct ManyBlock {
+    char *buf;             // vector slots, `slot` bytes apart
+    uint64_t slot, n;      // n: scalars of a vector
+    double *partials;      // [workgroups][cols]
+    double *s;             // its scalars (the same places in every block)
+    uint32_t first, wgs;   // its workgroups: [first, first + wgs)
+};
+struct ManyArgs {
+    const ManyBlock *blk;
+    int n_blk, cols, C;
+};
+
+__device__ __forceinline__ ManyBlock many_block(const ManyArgs &A, uint32_t wg) {
+    int lo = 0, hi = A.n_blk - 1;   // last block with first <= wg
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (A.blk[mid].first <= wg) lo = mid; else hi = mid - 1;
+    }
+    return A.blk[lo];
+}
+template <class T>
+__device__ __forceinline__ T *slot_of(const ManyBlock &b, int slot) {
+    return reinterpret_cast<T *>(b.buf + b.slot * (uint64_t)slot);
+}
+
+// partials of slot va . slot vb
+template <class T, bool ONE>
+__global__ __launch_bounds__(RB) void k_many_dot(ManyArgs A, int va, int vb) {
+    __shared__ double sh[RB];
+    const ManyBlock b = many_block(A, blockIdx.x);
+    const uint32_t lb = blockIdx.x - b.first;
+    if constexpr (ONE)
+        dot1_part(slot_of<T>(b, va), slot_of<T>(b, vb), b.n, b.partials, lb, b.wgs, sh);
+    else
+        dot_part(slot_of<T>(b, va), slot_of<T>(b, vb), b.n, A.cols, b.partials, lb, b.wgs, sh);
+}
+
+// totals into the scalars at `out` (and the history at `hist` >= 0, row *jdev)
+__global__ __launch_bounds__(RB) void k_many_total(ManyArgs A, int mode, int out, int hist,
+                                                   const int *jdev) {
+    __shared__ double sh[RB];
+    const ManyBlock b = A.blk[blockIdx.x];
+    total_part(b.partials, (int)b.wgs, A.cols, A.C, mode, b.s + out,
+               hist >= 0 ? b.s + hist + (size_t)(*jdev) * (A.cols / A.C) : nullptr, sh);
+}
+
+// slot w -= alpha slot v + beta slot vp (vp < 0: none), partial |w|^2
+template <class T, bool ONE>
+__global__ __launch_bounds__(RB) void k_many_update(ManyArgs A, int w, int v, int vp, int alpha,
+                                                    int beta) {
+    __shared__ double sh[RB];
+    const ManyBlock b = many_block(A, blockIdx.x);
+    const uint32_t lb = blockIdx.x - b.first;
+    const T *p = vp < 0 ? nullptr : slot_of<T>(b, vp);
+    if constexpr (ONE)
+        update1_part(slot_of<T>(b, w), slot_of<T>(b, v), p, b.n, b.s + alpha, b.s + beta,
+                     b.partials, lb, b.wgs, sh);
+    else
+        update_part(slot_of<T>(b, w), slot_of<T>(b, v), p, b.n, A.cols, A.C, b.s + alpha,
+                    b.s + beta, b.partials, lb, b.wgs, sh);
+}
+
+// slot dst = slot src / beta; the end of a step (keep >= 0): the scalars at
+// `beta` are copied to `keep` and the step counter advances (nothing in this
+// launch reads either)
+template <class T, bool ONE>
+__global__ __launch_bounds__(RB) void k_many_scale(ManyArgs A, int src, int dst, int beta,
+                                                   int keep, int *jdev) {
+    const ManyBlock b = many_block(A, blockIdx.x);
+    const uint32_t lb = blockIdx.x - b.first;
+    if constexpr (ONE)
+        scale1_part(slot_of<T>(b, src), slot_of<T>(b, dst), b.n, b.s + beta, lb, b.wgs);
+    else
+        scale_part(slot_of<T>(b, src), slot_of<T>(b, dst), b.n, A.cols, A.C, b.s + beta, lb,
+                   b.wgs);
+    if (keep >= 0 && lb == 0 && (int)threadIdx.x < A.cols / A.C)
+        b.s[keep + threadIdx.x] = b.s[beta + threadIdx.x];
+    if (jdev && blockIdx.x == 0 && threadIdx.x == 0) *jdev += 1;
 }
 
 __global__ void k_step_end(int *jdev, double *prev_beta, const double *cur_beta, int nv) {
@@ -505,6 +644,90 @@ struct VecOps {
                                (double *)dst, n, cols, C, beta);
         XDG_TRY_HIP(hipGetLastError());
         return XDG_OK;
+    }
+};
+
+// The vector operations of a batch: n blocks of `slots` vector slots each, in
+// one allocation per kind (a block's slots 256-byte aligned), with `n_scal`
+// scalars per block and a step counter.
+struct ManyOps {
+    bool single;
+    ManyArgs A;
+    uint32_t wgs;          // workgroups of all blocks
+    hipStream_t st;
+    std::vector<ManyBlock> blk;
+    DevBuf buf, parts, scal, desc;
+    int *jdev;
+    size_t n_scal;
+
+    int setup(int n, const int64_t *dims, int cols, int C, bool single_, int slots, size_t n_scal_,
+              hipStream_t st_) {
+        single = single_;
+        st = st_;
+        n_scal = n_scal_;
+        blk.resize(n);
+        wgs = 0;
+        uint64_t bytes = 0;
+        for (int i = 0; i < n; ++i) {
+            ManyBlock &b = blk[i];
+            b.n = (uint64_t)dims[i] * cols;
+            b.slot = ((single ? 4 : 8) * b.n + 255) & ~(uint64_t)255;
+            b.first = wgs;
+            b.wgs = (uint32_t)vec_grid(b.n);
+            wgs += b.wgs;
+            bytes += b.slot * slots;
+        }
+        XDG_RETURN_IF(buf.alloc(bytes));
+        XDG_RETURN_IF(parts.alloc(sizeof(double) * (size_t)wgs * cols));
+        XDG_RETURN_IF(scal.alloc(sizeof(double) * n_scal * n + 16));
+        char *p = buf.as<char>();
+        for (int i = 0; i < n; ++i) {
+            ManyBlock &b = blk[i];
+            b.buf = p;
+            p += b.slot * slots;
+            b.partials = parts.as<double>() + (size_t)b.first * cols;
+            b.s = scal.as<double>() + n_scal * i;
+        }
+        jdev = reinterpret_cast<int *>(scal.as<double>() + n_scal * n);
+        XDG_RETURN_IF(desc.upload(blk.data(), sizeof(ManyBlock) * n));
+        A = ManyArgs{desc.as<ManyBlock>(), n, cols, C};
+        return XDG_OK;
+    }
+    char *vec(int i, int slot) const { return blk[i].buf + blk[i].slot * slot; }
+
+    template <class F>
+    int launch(F &&f) const {
+        // one real vector: the four-wide forms, as for a block alone
+        if (single) {
+            if (A.cols == 1) f(float(), std::true_type()); else f(float(), std::false_type());
+        } else {
+            if (A.cols == 1) f(double(), std::true_type()); else f(double(), std::false_type());
+        }
+        XDG_TRY_HIP(hipGetLastError());
+        return XDG_OK;
+    }
+    int dot(int va, int vb) const {
+        return launch([&](auto t, auto one) {
+            hipLaunchKernelGGL((k_many_dot<decltype(t), decltype(one)::value>), dim3(wgs),
+                               dim3(RB), 0, st, A, va, vb);
+        });
+    }
+    int total(int mode, int out, int hist) const {
+        hipLaunchKernelGGL(k_many_total, dim3(A.n_blk), dim3(RB), 0, st, A, mode, out, hist, jdev);
+        XDG_TRY_HIP(hipGetLastError());
+        return XDG_OK;
+    }
+    int update(int w, int v, int vp, int alpha, int beta) const {
+        return launch([&](auto t, auto one) {
+            hipLaunchKernelGGL((k_many_update<decltype(t), decltype(one)::value>), dim3(wgs),
+                               dim3(RB), 0, st, A, w, v, vp, alpha, beta);
+        });
+    }
+    int scale(int src, int dst, int beta, int keep, int *counter) const {
+        return launch([&](auto t, auto one) {
+            hipLaunchKernelGGL((k_many_scale<decltype(t), decltype(one)::value>), dim3(wgs),
+                               dim3(RB), 0, st, A, src, dst, beta, keep, counter);
+        });
     }
 };
 
@@ -1044,43 +1267,31 @@ int lanczos_batched(int n, xdg_ham_s *const *hams, const void *const *v0s, int64
         XDG_TRY_HIP(hipStreamCreateWithFlags(&own, hipStreamNonBlocking));
         st = own;
     }
-    struct Sec {
-        DevBuf buf, parts, scal;
-        uint64_t nsc;
-        size_t slot;   // bytes between the vector slots of buf
-        VecOps ops;
-        double *cur_a, *cur_b, *prev_b, *hist_a, *hist_b;
-    };
-    std::vector<Sec> S(n);
-    DevBuf jbuf;
-    XDG_RETURN_IF(jbuf.alloc(16));
-    int *jdev = jbuf.as<int>();
+    // slots: v0, v1, v2 (rotating) and w.  Scalars per block: current alpha
+    // and beta, previous beta, then both histories.
+    const int W = 3, nv = (int)nvec;
+    const int cur_a = 0, cur_b = nv, prev_b = 2 * nv, hist_a = 3 * nv,
+              hist_b = hist_a + n_iter * nv;
+    std::vector<int64_t> dims(n);
+    for (int i = 0; i < n; ++i) dims[i] = hams[i]->basis->dim;
+    ManyOps ops;
+    XDG_RETURN_IF(ops.setup(n, dims.data(), cols, C, single, 4,
+                            (size_t)3 * nv + 2 * (size_t)n_iter * nv, st));
     for (int i = 0; i < n; ++i) {
-        Sec &s = S[i];
-        const int64_t D = hams[i]->basis->dim;
-        s.nsc = (uint64_t)D * cols;
-        s.slot = (ssz * s.nsc + 255) & ~(size_t)255;   // 256-byte aligned slots
-        XDG_RETURN_IF(s.buf.alloc(s.slot * 4));   // v0, v1, v2 (rotating) + w
-        s.ops = VecOps{single, cols, C, s.nsc, vec_grid(s.nsc), nullptr, st};
-        XDG_RETURN_IF(s.parts.alloc(sizeof(double) * (size_t)s.ops.grid * MAXC));
-        s.ops.partials = s.parts.as<double>();
-        XDG_RETURN_IF(s.scal.alloc(sizeof(double) * (3 * nvec + 2 * (size_t)n_iter * nvec)));
-        s.cur_a = s.scal.as<double>();
-        s.cur_b = s.cur_a + nvec;
-        s.prev_b = s.cur_b + nvec;
-        s.hist_a = s.prev_b + nvec;
-        s.hist_b = s.hist_a + (size_t)n_iter * nvec;
-        char *v = s.buf.as<char>();
+        char *v = ops.vec(i, 0);
+        const uint64_t nsc = ops.blk[i].n;
         if (v0s && v0s[i])
-            XDG_TRY_HIP(hipMemcpyAsync(v, v0s[i], ssz * s.nsc, hipMemcpyDeviceToDevice, st));
+            XDG_TRY_HIP(hipMemcpyAsync(v, v0s[i], ssz * nsc, hipMemcpyDeviceToDevice, st));
         else
-            XDG_RETURN_IF(random_fill((int64_t)s.nsc, seed + (uint64_t)i, 1, single, v, st));
-        hipLaunchKernelGGL(k_set_scalars, dim3(1), dim3(64), 0, st, jdev, s.prev_b, (int)nvec);
-        XDG_RETURN_IF(s.ops.dot(v, v));
-        XDG_RETURN_IF(s.ops.finalize(1, s.cur_b, nullptr, jdev));
-        XDG_RETURN_IF(s.ops.scale(v, v, s.cur_b));
+            XDG_RETURN_IF(random_fill((int64_t)nsc, seed + (uint64_t)i, 1, single, v, st));
+        hipLaunchKernelGGL(k_set_scalars, dim3(1), dim3(64), 0, st, ops.jdev,
+                           ops.blk[i].s + prev_b, nv);
     }
-    auto vecp = [&](int i, int slot) -> char * { return S[i].buf.as<char>() + S[i].slot * slot; };
+    XDG_TRY_HIP(hipGetLastError());
+    XDG_RETURN_IF(ops.dot(0, 0));
+    XDG_RETURN_IF(ops.total(1, cur_b, -1));
+    XDG_RETURN_IF(ops.scale(0, 0, cur_b, -1, nullptr));
+    auto vecp = [&](int i, int slot) -> char * { return ops.vec(i, slot); };
     // phase p: v = slot p, vprev = slot (p+2)%3 (none at j = 0), next = slot (p+1)%3, w = slot 3
     std::vector<xdg_ham_s *> hv(hams, hams + n);
     auto prepare = [&](int p, BatchPlan *P, uint32_t tile) -> int {
@@ -1109,23 +1320,11 @@ int lanczos_batched(int n, xdg_ham_s *const *hams, const void *const *v0s, int64
     const int best_grid = best_shape.grid;
     auto enqueue_step = [&](int p, bool first) -> int {
         XDG_RETURN_IF(batch_launch(plans[p], best_grid, best_shape.nv, st));
-        for (int i = 0; i < n; ++i) {
-            Sec &s = S[i];
-            char *v = vecp(i, p), *w = vecp(i, 3);
-            char *vp = first ? nullptr : vecp(i, (p + 2) % 3);
-            XDG_RETURN_IF(s.ops.dot(v, w));
-            XDG_RETURN_IF(s.ops.finalize(0, s.cur_a, s.hist_a, jdev));
-            XDG_RETURN_IF(s.ops.update(w, v, vp, s.cur_a, s.prev_b));
-            XDG_RETURN_IF(s.ops.finalize(1, s.cur_b, s.hist_b, jdev));
-            XDG_RETURN_IF(s.ops.scale(w, vecp(i, (p + 1) % 3), s.cur_b));
-            hipLaunchKernelGGL(k_step_end, dim3(1), dim3(64), 0, st, (int *)nullptr, s.prev_b,
-                               s.cur_b, (int)nvec);
-        }
-        // one counter for all blocks; k_step_end with a null counter only copies beta
-        hipLaunchKernelGGL(k_step_end, dim3(1), dim3(64), 0, st, jdev, S[0].prev_b, S[0].cur_b,
-                           (int)nvec);
-        XDG_TRY_HIP(hipGetLastError());
-        return XDG_OK;
+        XDG_RETURN_IF(ops.dot(p, W));
+        XDG_RETURN_IF(ops.total(0, cur_a, hist_a));
+        XDG_RETURN_IF(ops.update(W, p, first ? -1 : (p + 2) % 3, cur_a, prev_b));
+        XDG_RETURN_IF(ops.total(1, cur_b, hist_b));
+        return ops.scale(W, (p + 1) % 3, cur_b, prev_b, ops.jdev);
     };
     XDG_TRY_HIP(hipStreamSynchronize(st));
     const auto t0 = std::chrono::steady_clock::now();
@@ -1175,15 +1374,10 @@ int lanczos_batched(int n, xdg_ham_s *const *hams, const void *const *v0s, int64
         if (graphs[p]) (void)hipGraphDestroy(graphs[p]);
     }
     if (rc == XDG_OK) {
-        std::vector<double> ha((size_t)n_iter * nvec), hb((size_t)n_iter * nvec), a1(n_iter),
-            b1(n_iter), ritz;
+        std::vector<double> all(ops.n_scal * n), a1(n_iter), b1(n_iter), ritz;
+        rc = copy_d2h(all.data(), ops.scal.p, sizeof(double) * all.size(), st);
         for (int i = 0; i < n && rc == XDG_OK; ++i) {
-            if (copy_d2h(ha.data(), S[i].hist_a, sizeof(double) * ha.size(), st) != XDG_OK ||
-                copy_d2h(hb.data(), S[i].hist_b, sizeof(double) * hb.size(), st) != XDG_OK) {
-                set_error("batched lanczos: copy of the tridiagonal matrices failed");
-                rc = XDG_EHIP;
-                break;
-            }
+            const double *ha = all.data() + ops.n_scal * i + hist_a, *hb = ha + (hist_b - hist_a);
             for (int v = 0; v < nvec; ++v) {
                 int m = n_iter;
                 for (int j = 0; j < n_iter; ++j) {
@@ -1330,54 +1524,37 @@ int tpq_micro_batched(int n, xdg_ham_s *const *hams, const void *const *v0s, int
             if (s) (void)hipStreamDestroy(s);
         }
     } own_guard{own};
-    struct Sec {
-        DevBuf buf, parts, scal;
-        uint64_t nsc;
-        size_t slot;
-        VecOps ops;
-        double *ln, *nrm, *vw, *ww, *h_vw, *h_ww;
-    };
-    std::vector<Sec> S(n);
-    DevBuf jbuf;
-    XDG_RETURN_IF(jbuf.alloc(16));
-    int *jdev = jbuf.as<int>();
+    // slots: v and w.  Scalars per block and vector: l N, norm, <v, Hv>,
+    // <Hv, Hv>; then the two histories.
+    const int nv = (int)nvec;
+    const int ln = 0, nrm = nv, vw = 2 * nv, ww = 3 * nv, h_vw = 4 * nv, h_ww = h_vw + n_steps * nv;
+    std::vector<int64_t> dims(n);
+    for (int i = 0; i < n; ++i) dims[i] = hams[i]->basis->dim;
+    ManyOps ops;
+    XDG_RETURN_IF(ops.setup(n, dims.data(), cols, C, single, 2,
+                            (size_t)4 * nv + 2 * (size_t)n_steps * nv, st));
+    std::vector<double> lnv(nvec);
     for (int i = 0; i < n; ++i) {
-        Sec &s = S[i];
-        const int64_t D = hams[i]->basis->dim;
-        s.nsc = (uint64_t)D * cols;
-        s.slot = (ssz * s.nsc + 255) & ~(size_t)255;
-        XDG_RETURN_IF(s.buf.alloc(s.slot * 2));   // v, w
-        s.ops = VecOps{single, cols, C, s.nsc, vec_grid(s.nsc), nullptr, st};
-        XDG_RETURN_IF(s.parts.alloc(sizeof(double) * (size_t)s.ops.grid * MAXC));
-        s.ops.partials = s.parts.as<double>();
-        // per vector: l N, norm, <v, Hv>, <Hv, Hv>; then the two histories
-        XDG_RETURN_IF(s.scal.alloc(sizeof(double) * (4 * (size_t)nvec + 2 * (size_t)n_steps * nvec)));
-        s.ln = s.scal.as<double>();
-        s.nrm = s.ln + nvec;
-        s.vw = s.nrm + nvec;
-        s.ww = s.vw + nvec;
-        s.h_vw = s.ww + nvec;
-        s.h_ww = s.h_vw + (size_t)n_steps * nvec;
-        const std::vector<double> lnv(nvec, l * (double)hams[i]->basis->n_sites);
-        XDG_TRY_HIP(hipMemcpyAsync(s.ln, lnv.data(), sizeof(double) * nvec, hipMemcpyHostToDevice,
-                                   st));
-        char *v = s.buf.as<char>();
+        std::fill(lnv.begin(), lnv.end(), l * (double)hams[i]->basis->n_sites);
+        XDG_RETURN_IF(copy_h2d(ops.blk[i].s + ln, lnv.data(), sizeof(double) * nvec, st));
+        char *v = ops.vec(i, 0);
+        const uint64_t nsc = ops.blk[i].n;
         if (v0s && v0s[i])
-            XDG_TRY_HIP(hipMemcpyAsync(v, v0s[i], ssz * s.nsc, hipMemcpyDeviceToDevice, st));
+            XDG_TRY_HIP(hipMemcpyAsync(v, v0s[i], ssz * nsc, hipMemcpyDeviceToDevice, st));
         else
-            XDG_RETURN_IF(random_fill((int64_t)s.nsc, seed + (uint64_t)i, 1, single, v, st));
-        XDG_RETURN_IF(s.ops.dot(v, v));
-        XDG_RETURN_IF(s.ops.finalize(1, s.nrm, nullptr, jdev));
-        XDG_RETURN_IF(s.ops.scale(v, v, s.nrm));
+            XDG_RETURN_IF(random_fill((int64_t)nsc, seed + (uint64_t)i, 1, single, v, st));
     }
-    hipLaunchKernelGGL(k_set_scalars, dim3(1), dim3(64), 0, st, jdev, S[0].nrm, 0);
+    XDG_RETURN_IF(ops.dot(0, 0));
+    XDG_RETURN_IF(ops.total(1, nrm, -1));
+    XDG_RETURN_IF(ops.scale(0, 0, nrm, -1, nullptr));
+    hipLaunchKernelGGL(k_set_scalars, dim3(1), dim3(64), 0, st, ops.jdev, ops.blk[0].s + nrm, 0);
     XDG_TRY_HIP(hipGetLastError());
     std::vector<xdg_ham_s *> hv(hams, hams + n);
     std::vector<const void *> xs(n);
     std::vector<void *> ys(n);
     for (int i = 0; i < n; ++i) {
-        xs[i] = S[i].buf.as<char>();
-        ys[i] = S[i].buf.as<char>() + S[i].slot;
+        xs[i] = ops.vec(i, 0);
+        ys[i] = ops.vec(i, 1);
     }
     BatchShape shape;
     XDG_RETURN_IF(batch_shape_tuned(n, hv.data(), xs.data(), ys.data(), nvec, dtype, st, &shape));
@@ -1385,20 +1562,13 @@ int tpq_micro_batched(int n, xdg_ham_s *const *hams, const void *const *v0s, int
     XDG_RETURN_IF(batch_prepare(n, hv.data(), xs.data(), ys.data(), nvec, dtype, &plan, shape.tile));
     auto step = [&]() -> int {
         XDG_RETURN_IF(batch_launch(plan, shape.grid, shape.nv, st));
-        for (int i = 0; i < n; ++i) {
-            Sec &s = S[i];
-            char *v = s.buf.as<char>(), *w = v + s.slot;
-            XDG_RETURN_IF(s.ops.dot(v, w));
-            XDG_RETURN_IF(s.ops.finalize(0, s.vw, s.h_vw, jdev));
-            XDG_RETURN_IF(s.ops.dot(w, w));
-            XDG_RETURN_IF(s.ops.finalize(0, s.ww, s.h_ww, jdev));
-            XDG_RETURN_IF(s.ops.update(w, v, nullptr, s.ln, nullptr));   // H v - l N v
-            XDG_RETURN_IF(s.ops.finalize(1, s.nrm, nullptr, jdev));
-            XDG_RETURN_IF(s.ops.scale(w, v, s.nrm));
-        }
-        hipLaunchKernelGGL(k_step_end, dim3(1), dim3(64), 0, st, jdev, S[0].nrm, S[0].nrm, 0);
-        XDG_TRY_HIP(hipGetLastError());
-        return XDG_OK;
+        XDG_RETURN_IF(ops.dot(0, 1));
+        XDG_RETURN_IF(ops.total(0, vw, h_vw));
+        XDG_RETURN_IF(ops.dot(1, 1));
+        XDG_RETURN_IF(ops.total(0, ww, h_ww));
+        XDG_RETURN_IF(ops.update(1, 0, -1, ln, ln));   // H v - l N v
+        XDG_RETURN_IF(ops.total(1, nrm, -1));
+        return ops.scale(1, 0, nrm, -1, ops.jdev);
     };
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -1423,12 +1593,12 @@ int tpq_micro_batched(int n, xdg_ham_s *const *hams, const void *const *v0s, int
     if (exec) (void)hipGraphExecDestroy(exec);
     if (graph) (void)hipGraphDestroy(graph);
     if (rc == XDG_OK) {
-        std::vector<double> hv_((size_t)n_steps * nvec), hw_((size_t)n_steps * nvec);
+        std::vector<double> all(ops.n_scal * n);
+        rc = copy_d2h(all.data(), ops.scal.p, sizeof(double) * all.size(), st);
         for (int i = 0; i < n && rc == XDG_OK; ++i) {
-            rc = copy_d2h(hv_.data(), S[i].h_vw, sizeof(double) * hv_.size(), st);
-            if (rc == XDG_OK) rc = copy_d2h(hw_.data(), S[i].h_ww, sizeof(double) * hw_.size(), st);
+            const double *hv_ = all.data() + ops.n_scal * i + h_vw, *hw_ = hv_ + (h_ww - h_vw);
             const double N = (double)hams[i]->basis->n_sites;
-            for (int v = 0; v < nvec && rc == XDG_OK; ++v)
+            for (int v = 0; v < nvec; ++v)
                 for (int k = 0; k < n_steps; ++k) {
                     u[((size_t)i * nvec + v) * n_steps + k] = hv_[(size_t)k * nvec + v] / N;
                     u2[((size_t)i * nvec + v) * n_steps + k] = hw_[(size_t)k * nvec + v] / (N * N);
