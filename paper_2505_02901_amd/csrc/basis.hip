@@ -76,7 +76,7 @@ struct PinnedStage {
         if (p) (void)hipHostFree(p);
         p = nullptr;
         cap = 0;
-        hipError_t e = hipHostMalloc(&p, n, hipHostMallocDefault);
+        hipError_t e = hipHostMalloc(&p, n, hipHostMallocPortable | hipHostMallocMapped);
         if (e != hipSuccess) {
             p = nullptr;
             (void)hipGetLastError();
@@ -87,7 +87,7 @@ struct PinnedStage {
         return XDG_OK;
     }
 };
-thread_local PinnedStage g_stage;
+thread_local PinnedStage g_stage, g_scalars;
 constexpr size_t STAGE_CHUNK = (size_t)64 << 20;
 }  // namespace
 
@@ -116,6 +116,12 @@ int copy_h2d(void *dst, const void *src, size_t n, hipStream_t st) {
         XDG_TRY_HIP(hipStreamSynchronize(st));
         done += len;
     }
+    return XDG_OK;
+}
+
+int host_scalars(size_t n, double **out) {
+    XDG_RETURN_IF(g_scalars.reserve(n * sizeof(double)));
+    *out = static_cast<double *>(g_scalars.p);
     return XDG_OK;
 }
 

@@ -61,7 +61,7 @@ __device__ __forceinline__ void dot_part(const T *a, const T *b, uint64_t n, int
 
 // Fixed-order total of the partials, pairs of columns combined for complex
 // vectors (Re<a,b> = sum re*re + im*im).  mode 0: out = s; 1: out = sqrt(s).
-// hist (may be null) receives the values too.
+// hist (may be null) receives the values too; they stay in sh[v * C].
 __device__ __forceinline__ void total_part(const double *partials, int n_blocks, int cols, int C,
                                            int mode, double *out, double *hist, double *sh) {
     const int c = threadIdx.x % cols;
@@ -75,9 +75,23 @@ __device__ __forceinline__ void total_part(const double *partials, int n_blocks,
         double s = sh[v * C];
         if (C == 2) s += sh[v * C + 1];
         const double r = mode == 1 ? sqrt(s) : s;
-        out[v] = r;
+        if (out) out[v] = r;
         if (hist) hist[v] = r;
+        sh[v * C] = r;
     }
+}
+
+// one scalar of w - alpha v - beta vprev in FP64, rounded once
+template <class T>
+__device__ __forceinline__ T updated(T w, T v, T vprev, bool has_prev, double a, double b) {
+    double x = (double)w - a * (double)v;
+    if (has_prev) x -= b * (double)vprev;
+    return (T)x;
+}
+// one scalar divided by beta (zero where beta vanished: invariant subspace)
+template <class T>
+__device__ __forceinline__ T scaled(T x, double bt) {
+    return bt > 0.0 ? (T)((double)x / bt) : T(0);
 }
 
 // w = w - alpha v - beta vprev (FP64, one rounding), partial |w|^2
@@ -92,9 +106,7 @@ __device__ __forceinline__ void update_part(T *w, const T *v, const T *vprev, ui
     const int vec = (int)(threadIdx.x % cols) / C;
     const double a = alpha[vec], b = vprev ? beta[vec] : 0.0;
     for (uint64_t q = (uint64_t)lb * RB + threadIdx.x; q < n; q += stride) {
-        double x = (double)w[q] - a * (double)v[q];
-        if (vprev) x -= b * (double)vprev[q];
-        const T r = (T)x;
+        const T r = updated<T>(w[q], v[q], vprev ? vprev[q] : T(0), vprev != nullptr, a, b);
         w[q] = r;
         acc += (double)r * (double)r;
     }
@@ -103,7 +115,7 @@ __device__ __forceinline__ void update_part(T *w, const T *v, const T *vprev, ui
     if ((int)threadIdx.x < cols) partials[(size_t)lb * cols + threadIdx.x] = sh[threadIdx.x];
 }
 
-// dst = src / beta  (zero where beta vanished: invariant subspace)
+// dst = src / beta
 template <class T>
 __device__ __forceinline__ void scale_part(const T *src, T *dst, uint64_t n, int cols, int C,
                                            const double *beta, uint32_t lb, uint32_t nb) {
@@ -111,7 +123,7 @@ __device__ __forceinline__ void scale_part(const T *src, T *dst, uint64_t n, int
     // cols divides RB, so every scalar of this thread is in column threadIdx.x % cols
     const double bt = beta[(int)(threadIdx.x % cols) / C];
     for (uint64_t q = (uint64_t)lb * RB + threadIdx.x; q < n; q += stride)
-        dst[q] = bt > 0.0 ? (T)((double)src[q] / bt) : T(0);
+        dst[q] = scaled<T>(src[q], bt);
 }
 
 // One column (a single real vector): four consecutive scalars per thread
@@ -153,9 +165,7 @@ __device__ __forceinline__ void update1_part(T *w, const T *v, const T *vprev, u
         if (vprev) z = reinterpret_cast<const Vec4<T> *>(vprev)[q];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            double t = (double)x[e] - a * (double)y[e];
-            if (vprev) t -= b * (double)z[e];
-            const T r = (T)t;
+            const T r = updated<T>(x[e], y[e], z[e], vprev != nullptr, a, b);
             x[e] = r;
             acc += (double)r * (double)r;
         }
@@ -163,9 +173,7 @@ __device__ __forceinline__ void update1_part(T *w, const T *v, const T *vprev, u
     }
     if (lb == 0)
         for (uint64_t q = 4 * n4 + threadIdx.x; q < n; q += RB) {
-            double t = (double)w[q] - a * (double)v[q];
-            if (vprev) t -= b * (double)vprev[q];
-            const T r = (T)t;
+            const T r = updated<T>(w[q], v[q], vprev ? vprev[q] : T(0), vprev != nullptr, a, b);
             w[q] = r;
             acc += (double)r * (double)r;
         }
@@ -182,12 +190,12 @@ __device__ __forceinline__ void scale1_part(const T *src, T *dst, uint64_t n, co
     for (uint64_t q = (uint64_t)lb * RB + threadIdx.x; q < n4; q += stride) {
         Vec4<T> x = reinterpret_cast<const Vec4<T> *>(src)[q];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = bt > 0.0 ? (T)((double)x[e] / bt) : T(0);
+        for (int e = 0; e < 4; ++e) x[e] = scaled<T>(x[e], bt);
         reinterpret_cast<Vec4<T> *>(dst)[q] = x;
     }
     if (lb == 0)
         for (uint64_t q = 4 * n4 + threadIdx.x; q < n; q += RB)
-            dst[q] = bt > 0.0 ? (T)((double)src[q] / bt) : T(0);
+            dst[q] = scaled<T>(src[q], bt);
 }
 
 // ---- one vector block ----
@@ -199,11 +207,9 @@ __global__ __launch_bounds__(RB) void k_dot(const T *a, const T *b, uint64_t n, 
 }
 
 __global__ __launch_bounds__(RB) void k_finalize(const double *partials, int n_blocks, int cols,
-                                                 int C, int mode, double *out, double *hist,
-                                                 const int *jdev) {
+                                                 int C, int mode, double *out, double *hist) {
     __shared__ double sh[RB];
-    total_part(partials, n_blocks, cols, C, mode, out,
-               hist ? hist + (size_t)(*jdev) * (cols / C) : nullptr, sh);
+    total_part(partials, n_blocks, cols, C, mode, out, hist, sh);
 }
 
 template <class T>
@@ -239,6 +245,65 @@ template <class T>
 __global__ __launch_bounds__(RB) void k_scale1(const T *src, T *dst, uint64_t n,
                                                const double *beta) {
     scale1_part(src, dst, n, beta, blockIdx.x, gridDim.x);
+}
+
+// Short vectors (at most FUSE_WGS workgroups): the total of the previous
+// kernel's partials is taken by every workgroup itself, in the order of
+// k_finalize, which saves a launch between two kernels of 2-3 us.  Longer
+// ones would read the partials of up to 2048 workgroups 2048 times.
+constexpr int FUSE_WGS = 256;
+
+template <class T, bool ONE>
+__global__ __launch_bounds__(RB) void k_total_update(T *w, const T *v, const T *vprev, uint64_t n,
+                                                     int cols, int C, const double *dots,
+                                                     double *alpha, double *host_alpha,
+                                                     const double *beta, double *partials) {
+    __shared__ double sh[RB];
+    const bool first = blockIdx.x == 0;
+    total_part(dots, gridDim.x, cols, C, 0, first ? alpha : nullptr, first ? host_alpha : nullptr,
+               sh);
+    __syncthreads();
+    const double a = sh[0];   // one vector
+    __syncthreads();
+    if constexpr (ONE)
+        update1_part(w, v, vprev, n, &a, beta, partials, blockIdx.x, gridDim.x, sh);
+    else
+        update_part(w, v, vprev, n, cols, C, &a, beta, partials, blockIdx.x, gridDim.x, sh);
+}
+
+template <class T, bool ONE>
+__global__ __launch_bounds__(RB) void k_total_scale(const T *src, T *dst, uint64_t n, int cols,
+                                                    int C, const double *norms, double *beta,
+                                                    double *host_beta) {
+    __shared__ double sh[RB];
+    const bool first = blockIdx.x == 0;
+    total_part(norms, gridDim.x, cols, C, 1, first ? beta : nullptr, first ? host_beta : nullptr,
+               sh);
+    __syncthreads();
+    const double b = sh[0];
+    if constexpr (ONE)
+        scale1_part(src, dst, n, &b, blockIdx.x, gridDim.x);
+    else
+        scale_part(src, dst, n, cols, C, &b, blockIdx.x, gridDim.x);
+}
+
+// A step of the second pass on known alpha and beta: next = (w - alpha v -
+// beta_prev vprev) / beta with the two roundings of the first pass, and
+// acc += c next in FP64, in one pass over the vectors (before: update, scale
+// and the accumulation apart, nine vector passes instead of six).
+template <class T>
+__global__ __launch_bounds__(RB) void k_ritz_step(const T *w, const T *v, const T *vprev, T *next,
+                                                  double *acc, uint64_t n, const double *alpha,
+                                                  const double *beta_prev, const double *beta,
+                                                  double c) {
+    const uint64_t stride = (uint64_t)gridDim.x * RB;
+    const double a = *alpha, b = vprev ? *beta_prev : 0.0, bt = *beta;
+    for (uint64_t q = (uint64_t)blockIdx.x * RB + threadIdx.x; q < n; q += stride) {
+        const T r = scaled<T>(
+            updated<T>(w[q], v[q], vprev ? vprev[q] : T(0), vprev != nullptr, a, b), bt);
+        next[q] = r;
+        acc[q] = __builtin_fma(c, (double)r, acc[q]);
+    }
 }
 
 // ---- many vector blocks at once ----
@@ -325,12 +390,6 @@ __global__ __launch_bounds__(RB) void k_many_scale(ManyArgs A, int src, int dst,
     if (keep >= 0 && lb == 0 && (int)threadIdx.x < A.cols / A.C)
         b.s[keep + threadIdx.x] = b.s[beta + threadIdx.x];
     if (jdev && blockIdx.x == 0 && threadIdx.x == 0) *jdev += 1;
-}
-
-__global__ void k_step_end(int *jdev, double *prev_beta, const double *cur_beta, int nv) {
-    for (int v = threadIdx.x; v < nv; v += blockDim.x) prev_beta[v] = cur_beta[v];
-    __syncthreads();
-    if (threadIdx.x == 0 && jdev) *jdev += 1;
 }
 
 __global__ void k_set_scalars(int *jdev, double *prev_beta, int nv) {
@@ -594,9 +653,10 @@ struct VecOps {
         XDG_TRY_HIP(hipGetLastError());
         return XDG_OK;
     }
-    int finalize(int mode, double *out, double *hist, const int *jdev) const {
+    // hist (may be null): a second place for the total, device or page-locked host memory
+    int finalize(int mode, double *out, double *hist) const {
         hipLaunchKernelGGL(k_finalize, dim3(1), dim3(RB), 0, st, partials, grid, cols, C, mode,
-                           out, hist, jdev);
+                           out, hist);
         XDG_TRY_HIP(hipGetLastError());
         return XDG_OK;
     }
@@ -644,6 +704,37 @@ struct VecOps {
                                (double *)dst, n, cols, C, beta);
         XDG_TRY_HIP(hipGetLastError());
         return XDG_OK;
+    }
+
+    // the total of the dot product's partials, then the update with it (one
+    // vector, at most FUSE_WGS workgroups); its norm partials go to `norms`
+    bool fusable() const { return cols == C && grid <= FUSE_WGS; }
+    template <class F>
+    int typed(bool one, F &&f) const {
+        if (single) {
+            if (one) f(float(), std::true_type()); else f(float(), std::false_type());
+        } else {
+            if (one) f(double(), std::true_type()); else f(double(), std::false_type());
+        }
+        XDG_TRY_HIP(hipGetLastError());
+        return XDG_OK;
+    }
+    int total_update(void *w, const void *v, const void *vprev, double *alpha, double *host_alpha,
+                     const double *beta, double *norms) const {
+        return typed(vec4(w) && vec4(v) && (!vprev || vec4(vprev)), [&](auto t, auto one) {
+            using T = decltype(t);
+            hipLaunchKernelGGL((k_total_update<T, decltype(one)::value>), dim3(grid), dim3(RB), 0,
+                               st, (T *)w, (const T *)v, (const T *)vprev, n, cols, C, partials,
+                               alpha, host_alpha, beta, norms);
+        });
+    }
+    int total_scale(const void *src, void *dst, const double *norms, double *beta,
+                    double *host_beta) const {
+        return typed(vec4(src) && vec4(dst), [&](auto t, auto one) {
+            using T = decltype(t);
+            hipLaunchKernelGGL((k_total_scale<T, decltype(one)::value>), dim3(grid), dim3(RB), 0,
+                               st, (const T *)src, (T *)dst, n, cols, C, norms, beta, host_beta);
+        });
     }
 };
 
@@ -831,6 +922,85 @@ void tridiag_eigenvalues(int m, const double *alpha, const double *beta, std::ve
     out = d;
 }
 
+// Eigenvalue number k (ascending) of the symmetric tridiagonal matrix by
+// multisection on Sturm counts (the number of negative pivots of T - x is the
+// number of eigenvalues below x; Givens 1954): seven points a round, whose
+// pivots are independent, so a round costs little more than one count and
+// yields three bits.  A full QL run costs O(m^2) square roots for all
+// eigenvalues (m = 32: 57 us, m = 200: 2.0 ms on one core; this: 4 and 30 us).
+// lo, hi (may be NaN): a guess of an enclosing interval, checked.
+static double tridiag_kth(int m, const double *alpha, const double *beta, int k, double lo,
+                          double hi) {
+    double g0 = HUGE_VAL, g1 = -HUGE_VAL, b2max = 0.0, sum = 0.0;
+    static thread_local std::vector<double> b2;
+    b2.assign(m, 0.0);
+    for (int i = 0; i < m; ++i) {
+        const double l = i ? std::fabs(beta[i - 1]) : 0.0, r = i + 1 < m ? std::fabs(beta[i]) : 0.0;
+        g0 = std::min(g0, alpha[i] - l - r);
+        g1 = std::max(g1, alpha[i] + l + r);
+        if (i + 1 < m) b2[i + 1] = beta[i] * beta[i];
+        b2max = std::max(b2max, b2[i]);
+        sum += alpha[i] + l;
+    }
+    if (!std::isfinite(sum) || !std::isfinite(g0) || !std::isfinite(g1)) return NAN;
+    constexpr int P = 7;
+    constexpr double eps = 2.220446049250313e-16;
+    const double tiny = 2.3e-308 * std::max(1.0, b2max);
+    const double norm = std::max(std::fabs(g0), std::fabs(g1));
+    auto counts = [&](const double *x, int *n) {
+        double q[P];
+        int c[P] = {};
+        for (int p = 0; p < P; ++p) q[p] = 1.0;
+        for (int i = 0; i < m; ++i) {
+            const double a = alpha[i], bb = b2[i];
+            for (int p = 0; p < P; ++p) {
+                double v = (a - x[p]) - bb / q[p];
+                v = std::fabs(v) < tiny ? -tiny : v;
+                c[p] += v < 0.0;
+                q[p] = v;
+            }
+        }
+        for (int p = 0; p < P; ++p) n[p] = c[p];
+    };
+    double x[P];
+    int n[P];
+    const double slack = 4.0 * eps * norm + tiny;
+    if (lo <= hi) {
+        for (int p = 0; p < P; ++p) x[p] = p ? hi : lo;
+        counts(x, n);
+        if (!(n[0] <= k)) lo = g0 - slack;
+        if (!(n[1] > k)) hi = g1 + slack;
+    } else {
+        lo = g0 - slack;
+        hi = g1 + slack;
+    }
+    for (int round = 0; round < 100; ++round) {
+        const double w = hi - lo;
+        if (w <= 2.0 * eps * std::max(std::fabs(lo), std::fabs(hi)) || w <= 0.25 * eps * norm)
+            break;
+        for (int p = 0; p < P; ++p) x[p] = lo + w * ((p + 1) / 8.0);
+        counts(x, n);
+        double nl = lo, nh = hi;
+        for (int p = 0; p < P; ++p) {
+            if (n[p] <= k) nl = std::max(nl, x[p]);
+            if (n[P - 1 - p] > k) nh = std::min(nh, x[P - 1 - p]);
+        }
+        if (!(nl < nh) || (nl == lo && nh == hi)) break;
+        lo = nl;
+        hi = nh;
+    }
+    return 0.5 * (lo + hi);
+}
+
+// Eigenvalue number k of the matrix: the lowest ones alone, further ones with all.
+constexpr int KTH_ALONE = 8;
+static double tridiag_eigenvalue(int m, const double *alpha, const double *beta, int k,
+                                 std::vector<double> &all) {
+    if (k < KTH_ALONE) return tridiag_kth(m, alpha, beta, k, NAN, NAN);
+    if ((int)all.size() != m) tridiag_eigenvalues(m, alpha, beta, all);
+    return all[k];
+}
+
 // Eigenvalues (ascending) and the squared first components of their
 // eigenvectors: the nodes and weights of the Gauss quadrature that the
 // Lanczos recurrence defines for the start vector.
@@ -882,16 +1052,19 @@ int lanczos_single(xdg_ham_s *h, const void *v0, int k, double tol, int max_iter
     const int nstore = reorth ? max_iter + 1 : 3;
     XDG_RETURN_IF(bufs.alloc(vstride * nstore));
     XDG_RETURN_IF(wbuf.alloc(vbytes));
-    // scalars: cur_alpha, cur_beta, prev_beta, |w|^2 before and after a first
+    // scalars: the start norm, |w|^2 before and after a first
     // reorthogonalisation pass, hist_alpha[max_iter], hist_beta[max_iter],
-    // coef[2 (max_iter + 1)], then jdev and the skip flag of the second pass
-    XDG_RETURN_IF(scal.alloc(sizeof(double) * (5 + 2 * (size_t)max_iter + 2 * (size_t)(max_iter + 1)) + 16));
-    double *cur_alpha = scal.as<double>(), *cur_beta = cur_alpha + 1, *prev_beta = cur_alpha + 2;
-    double *nrm0 = cur_alpha + 3, *nrm1 = cur_alpha + 4;
-    double *hist_a = cur_alpha + 5, *hist_b = hist_a + max_iter;
+    // coef[2 (max_iter + 1)], then the skip flag of the second pass
+    XDG_RETURN_IF(scal.alloc(sizeof(double) * (3 + 2 * (size_t)max_iter + 2 * (size_t)(max_iter + 1)) + 16));
+    double *start_nrm = scal.as<double>(), *nrm0 = start_nrm + 1, *nrm1 = start_nrm + 2;
+    double *hist_a = start_nrm + 3, *hist_b = hist_a + max_iter;
     double *coef = hist_b + max_iter;
-    int *jdev = reinterpret_cast<int *>(coef + 2 * (size_t)(max_iter + 1));
-    int *skip2 = jdev + 1;
+    int *skip2 = reinterpret_cast<int *>(coef + 2 * (size_t)(max_iter + 1));
+    // the kernels write every alpha and beta here too, so that the host reads
+    // them without a copy once their step has passed
+    double *ha = nullptr;
+    XDG_RETURN_IF(host_scalars(2 * (size_t)max_iter, &ha));
+    double *hb = ha + max_iter;
     VecOps ops{single, C, C, nsc, vec_grid(nsc), nullptr, st};
     XDG_RETURN_IF(parts.alloc(sizeof(double) * (size_t)ops.grid * MAXC));
     ops.partials = parts.as<double>();
@@ -907,38 +1080,94 @@ int lanczos_single(xdg_ham_s *h, const void *v0, int k, double tol, int max_iter
         XDG_TRY_HIP(hipMemcpyAsync(vec(0), v0, vbytes, hipMemcpyDeviceToDevice, st));
     else
         XDG_RETURN_IF(random_fill((int64_t)nsc, seed, 1, single, vec(0), st));
-    hipLaunchKernelGGL(k_set_scalars, dim3(1), dim3(64), 0, st, jdev, prev_beta, 1);
     XDG_RETURN_IF(ops.dot(vec(0), vec(0)));
-    XDG_RETURN_IF(ops.finalize(1, cur_beta, nullptr, jdev));
-    XDG_RETURN_IF(ops.scale(vec(0), vec(0), cur_beta));
+    XDG_RETURN_IF(ops.finalize(1, start_nrm, nullptr));
+    XDG_RETURN_IF(ops.scale(vec(0), vec(0), start_nrm));
+    DevBuf norms;   // fused form: |w|^2 partials beside those of the dot product
+    const bool fused = !reorth && ops.fusable();
+    if (fused) XDG_RETURN_IF(norms.alloc(sizeof(double) * (size_t)ops.grid * MAXC));
 
     // one event pair per iteration around the apply; summed at the end
-    std::vector<hipEvent_t> evs(2 * (size_t)max_iter, nullptr);
-    struct EvGuard {
-        std::vector<hipEvent_t> &e;
-        ~EvGuard() {
-            for (hipEvent_t x : e)
-                if (x) (void)hipEventDestroy(x);
+    struct Events {
+        std::vector<hipEvent_t> e;
+        int at(size_t i, hipEvent_t *out) {
+            while (e.size() <= i) {
+                hipEvent_t x = nullptr;
+                XDG_TRY_HIP(hipEventCreate(&x));
+                e.push_back(x);
+            }
+            *out = e[i];
+            return XDG_OK;
         }
-    } ev_guard{evs};
-    for (auto &e : evs) XDG_TRY_HIP(hipEventCreate(&e));
-    std::vector<double> ha(max_iter), hb(max_iter), ritz;
-    double prev_k = NAN;
+        ~Events() {
+            for (hipEvent_t x : e) (void)hipEventDestroy(x);
+        }
+    } evs;
+    struct CheckEvent {
+        hipEvent_t e = nullptr;
+        ~CheckEvent() {
+            if (e) (void)hipEventDestroy(e);
+        }
+    } checked;
+    XDG_TRY_HIP(hipEventCreateWithFlags(&checked.e, hipEventDisableTiming));
+    double prev_k = NAN, last_move = NAN;
     int m = 0, status = XDG_ENOCONV;
     bool stop = false;
     double apply_s = 0.0;
+    // The test of iteration j: breakdown anywhere since the last test
+    // truncates the run there; the k-th lowest Ritz value within tol stops it.
+    auto test = [&](int mm) -> int {
+        XDG_TRY_HIP(hipEventSynchronize(checked.e));
+        m = mm;
+        for (int t = std::max(0, mm - 16); t < mm; ++t)
+            if (hb[t] <= 1e-13 * std::max(1.0, std::fabs(ha[t])) || !std::isfinite(hb[t])) {
+                m = t + 1;
+                stop = true;
+                status = XDG_OK;
+                return XDG_OK;
+            }
+        if (tol > 0.0 && mm >= k) {
+            // the k-th value only falls as the matrix grows: look just below the last one
+            const double span = 4.0 * last_move + 1e-13 * std::fabs(prev_k);
+            const double th = tridiag_kth(mm, ha, hb, k - 1, prev_k - span,
+                                          prev_k + 1e-13 * std::fabs(prev_k));
+            if (std::isfinite(prev_k) && std::fabs(th - prev_k) <= tol * std::fabs(th)) {
+                stop = true;
+                status = XDG_OK;
+            }
+            last_move = std::fabs(th - prev_k);
+            prev_k = th;
+        }
+        return XDG_OK;
+    };
+    // Where an iteration is short beside a round trip to the host (about 20
+    // us), the next one is enqueued before the test of the last: at most one
+    // iteration too many runs, and its numbers are not used.
+    const bool ahead = nsc <= (uint64_t)1 << 22;
+    int pending = 0;
     XDG_TRY_HIP(hipStreamSynchronize(st));
     const auto t0 = std::chrono::steady_clock::now();
     int iv = 0, ip = -1, in = 1;   // rotating indices (v, vprev, next) when not reorth
     for (int j = 0; j < max_iter && !stop; ++j) {
         char *v = reorth ? vec(j) : vec(iv);
         char *vp = reorth ? (j ? vec(j - 1) : nullptr) : (ip >= 0 ? vec(ip) : nullptr);
-        XDG_TRY_HIP(hipEventRecord(evs[2 * j], st));
+        char *next = reorth ? vec(j + 1) : vec(in);
+        hipEvent_t e0, e1;
+        XDG_RETURN_IF(evs.at(2 * (size_t)j, &e0));
+        XDG_RETURN_IF(evs.at(2 * (size_t)j + 1, &e1));
+        XDG_TRY_HIP(hipEventRecord(e0, st));
         XDG_RETURN_IF(apply_tuned(h, v, w, 1, dtype, st));
-        XDG_TRY_HIP(hipEventRecord(evs[2 * j + 1], st));
+        XDG_TRY_HIP(hipEventRecord(e1, st));
         XDG_RETURN_IF(ops.dot(v, w));
-        XDG_RETURN_IF(ops.finalize(0, cur_alpha, hist_a, jdev));
-        XDG_RETURN_IF(ops.update(w, v, vp, cur_alpha, prev_beta));
+        const double *beta_prev = j ? hist_b + (j - 1) : nullptr;
+        if (fused) {
+            XDG_RETURN_IF(ops.total_update(w, v, vp, hist_a + j, ha + j, beta_prev,
+                                           norms.as<double>()));
+            XDG_RETURN_IF(ops.total_scale(w, next, norms.as<double>(), hist_b + j, hb + j));
+        } else {
+            XDG_RETURN_IF(ops.finalize(0, hist_a + j, ha + j));
+            XDG_RETURN_IF(ops.update(w, v, vp, hist_a + j, beta_prev));
+        }
         if (reorth) {
             // classical Gram-Schmidt against v_0 .. v_j, FP64 coefficients; the
             // second pass runs only where the first removed more than half of |w|^2
@@ -985,52 +1214,36 @@ int lanczos_single(xdg_ham_s *h, const void *v0, int k, double tol, int max_iter
                 XDG_TRY_HIP(hipGetLastError());
                 return XDG_OK;
             };
-            XDG_RETURN_IF(ops.finalize(0, nrm0, nullptr, jdev));   // |w|^2 from the update
+            XDG_RETURN_IF(ops.finalize(0, nrm0, nullptr));   // |w|^2 from the update
             XDG_RETURN_IF(pass(nullptr));
             XDG_RETURN_IF(ops.dot(w, w));
-            XDG_RETURN_IF(ops.finalize(0, nrm1, nullptr, jdev));
+            XDG_RETURN_IF(ops.finalize(0, nrm1, nullptr));
             hipLaunchKernelGGL(k_dgks, dim3(1), dim3(64), 0, st, nrm0, nrm1, skip2);
             XDG_TRY_HIP(hipGetLastError());
             XDG_RETURN_IF(pass(skip2));
             XDG_RETURN_IF(ops.dot(w, w));
         }
-        XDG_RETURN_IF(ops.finalize(1, cur_beta, hist_b, jdev));
-        hipLaunchKernelGGL(k_step_end, dim3(1), dim3(64), 0, st, jdev, prev_beta, cur_beta, 1);
-        XDG_TRY_HIP(hipGetLastError());
+        if (!fused) XDG_RETURN_IF(ops.finalize(1, hist_b + j, hb + j));
+        if (pending) {   // the iteration before this one
+            XDG_RETURN_IF(test(pending));
+            pending = 0;
+            if (stop) break;
+        }
         m = j + 1;
         if (progress_every() && m % progress_every() == 0) {
             XDG_TRY_HIP(hipStreamSynchronize(st));
             fprintf(stderr, "[xdg] lanczos iteration %d / %d\n", m, max_iter);
         }
-        const bool check = tol > 0.0 || m == max_iter || (m % 16) == 0;
-        if (check) {
-            XDG_RETURN_IF(copy_d2h(ha.data(), hist_a, sizeof(double) * m, st));
-            XDG_RETURN_IF(copy_d2h(hb.data(), hist_b, sizeof(double) * m, st));
-            float ms = 0;
-            // breakdown anywhere since the last check truncates the run there
-            for (int t = std::max(0, m - 16); t < m; ++t)
-                if (hb[t] <= 1e-13 * std::max(1.0, std::fabs(ha[t])) || !std::isfinite(hb[t])) {
-                    m = t + 1;
-                    stop = true;
-                    status = XDG_OK;
-                    break;
-                }
-            if (!stop && tol > 0.0 && m >= k) {
-                tridiag_eigenvalues(m, ha.data(), hb.data(), ritz);
-                const double th = ritz[k - 1];
-                if (std::isfinite(prev_k) && std::fabs(th - prev_k) <= tol * std::fabs(th)) {
-                    stop = true;
-                    status = XDG_OK;
-                }
-                prev_k = th;
-            }
-            (void)ms;
+        if (tol > 0.0 || m == max_iter || (m % 16) == 0) {
+            XDG_TRY_HIP(hipEventRecord(checked.e, st));
+            if (ahead && m < max_iter)
+                pending = m;
+            else
+                XDG_RETURN_IF(test(m));
         }
         if (stop) break;
-        if (reorth) {
-            XDG_RETURN_IF(ops.scale(w, vec(j + 1), cur_beta));
-        } else {
-            XDG_RETURN_IF(ops.scale(w, vec(in), cur_beta));
+        if (!fused) XDG_RETURN_IF(ops.scale(w, next, hist_b + j));
+        if (!reorth) {
             ip = iv;
             iv = in;
             in = (in + 1) % 3;
@@ -1042,16 +1255,17 @@ int lanczos_single(xdg_ham_s *h, const void *v0, int k, double tol, int max_iter
         std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     for (int j = 0; j < m; ++j) {
         float ms = 0;
-        if (hipEventElapsedTime(&ms, evs[2 * j], evs[2 * j + 1]) == hipSuccess) apply_s += 1e-3 * ms;
+        hipEvent_t e0, e1;
+        XDG_RETURN_IF(evs.at(2 * (size_t)j, &e0));
+        XDG_RETURN_IF(evs.at(2 * (size_t)j + 1, &e1));
+        if (hipEventElapsedTime(&ms, e0, e1) == hipSuccess) apply_s += 1e-3 * ms;
     }
-    XDG_RETURN_IF(copy_d2h(ha.data(), hist_a, sizeof(double) * m, st));
-    XDG_RETURN_IF(copy_d2h(hb.data(), hist_b, sizeof(double) * m, st));
     if (tol == 0.0 && !stop) status = XDG_OK;
-    tridiag_eigenvalues(m, ha.data(), hb.data(), ritz);
-    for (int e = 0; e < k; ++e) evals[e] = e < m ? ritz[e] : NAN;
+    std::vector<double> all;
+    for (int e = 0; e < k; ++e) evals[e] = e < m ? tridiag_eigenvalue(m, ha, hb, e, all) : NAN;
     *n_iter = m;
-    if (alpha) std::copy(ha.begin(), ha.begin() + m, alpha);
-    if (beta) std::copy(hb.begin(), hb.begin() + m, beta);
+    if (alpha) std::copy(ha, ha + m, alpha);
+    if (beta) std::copy(hb, hb + m, beta);
     g_t_total = total;
     g_t_apply = apply_s;
     if (t_total) *t_total = total;
@@ -1069,8 +1283,7 @@ int lanczos_single(xdg_ham_s *h, const void *v0, int k, double tol, int max_iter
 void tridiag_eigvec(int m, const double *alpha, const double *beta, int which,
                     std::vector<double> &x, double &theta) {
     std::vector<double> ev;
-    tridiag_eigenvalues(m, alpha, beta, ev);
-    theta = ev[which];
+    theta = tridiag_eigenvalue(m, alpha, beta, which, ev);
     double tnorm = 0.0;
     for (int i = 0; i < m; ++i)
         tnorm = std::max(tnorm, std::fabs(alpha[i]) + (i ? std::fabs(beta[i - 1]) : 0.0) +
@@ -1172,13 +1385,12 @@ int lanczos_eigvec(xdg_ham_s *h, const void *v0, uint64_t seed, int prec, int m,
     XDG_RETURN_IF(bufs.alloc(vstride * 3));
     XDG_RETURN_IF(wbuf.alloc(vbytes));
     XDG_RETURN_IF(acc.alloc(sizeof(double) * nsc));
-    // scalars: nrm, alpha[m], beta[m], zero
-    XDG_RETURN_IF(scal.alloc(sizeof(double) * (2 + 2 * (size_t)m) + 16));
-    double *nrm = scal.as<double>(), *zero = nrm + 1, *al_d = nrm + 2, *be_d = al_d + m;
-    int *jdev = reinterpret_cast<int *>(be_d + m);
-    XDG_TRY_HIP(hipMemsetAsync(scal.p, 0, scal.bytes, st));
-    XDG_RETURN_IF(copy_h2d(al_d, alpha, sizeof(double) * m, st));
-    XDG_RETURN_IF(copy_h2d(be_d, beta, sizeof(double) * m, st));
+    // scalars: nrm, alpha[m], beta[m]
+    XDG_RETURN_IF(scal.alloc(sizeof(double) * (1 + 2 * (size_t)m)));
+    double *nrm = scal.as<double>(), *al_d = nrm + 1, *be_d = al_d + m;
+    std::vector<double> ab(alpha, alpha + m);
+    ab.insert(ab.end(), beta, beta + m);
+    XDG_RETURN_IF(copy_h2d(al_d, ab.data(), sizeof(double) * ab.size(), st));
     XDG_TRY_HIP(hipMemsetAsync(acc.p, 0, acc.bytes, st));
     VecOps ops{single, C, C, nsc, vec_grid(nsc), nullptr, st};
     XDG_RETURN_IF(parts.alloc(sizeof(double) * (size_t)ops.grid * MAXC));
@@ -1191,23 +1403,30 @@ int lanczos_eigvec(xdg_ham_s *h, const void *v0, uint64_t seed, int prec, int m,
     else
         XDG_RETURN_IF(random_fill((int64_t)nsc, seed, 1, single, vec(0), st));
     XDG_RETURN_IF(ops.dot(vec(0), vec(0)));
-    XDG_RETURN_IF(ops.finalize(1, nrm, nullptr, jdev));
+    XDG_RETURN_IF(ops.finalize(1, nrm, nullptr));
     XDG_RETURN_IF(ops.scale(vec(0), vec(0), nrm));
     const int g = vec_grid(nsc);
+    if (single)
+        hipLaunchKernelGGL(k_acc_axpy<float>, dim3(g), dim3(RB), 0, st, acc.as<double>(),
+                           (const float *)vec(0), nsc, c[0]);
+    else
+        hipLaunchKernelGGL(k_acc_axpy<double>, dim3(g), dim3(RB), 0, st, acc.as<double>(),
+                           (const double *)vec(0), nsc, c[0]);
+    XDG_TRY_HIP(hipGetLastError());
     int iv = 0, ip = -1, in = 1;
-    for (int j = 0; j < m; ++j) {
-        char *v = vec(iv);
-        if (single)
-            hipLaunchKernelGGL(k_acc_axpy<float>, dim3(g), dim3(RB), 0, st, acc.as<double>(),
-                               (const float *)v, nsc, c[j]);
-        else
-            hipLaunchKernelGGL(k_acc_axpy<double>, dim3(g), dim3(RB), 0, st, acc.as<double>(),
-                               (const double *)v, nsc, c[j]);
-        XDG_TRY_HIP(hipGetLastError());
-        if (j + 1 == m) break;
+    for (int j = 0; j + 1 < m; ++j) {
+        char *v = vec(iv), *vp = ip >= 0 ? vec(ip) : nullptr;
         XDG_RETURN_IF(apply_tuned(h, v, w, 1, dtype, st));
-        XDG_RETURN_IF(ops.update(w, v, ip >= 0 ? vec(ip) : nullptr, al_d + j, j ? be_d + j - 1 : zero));
-        XDG_RETURN_IF(ops.scale(w, vec(in), be_d + j));
+        const double *bp = j ? be_d + j - 1 : nullptr;
+        if (single)
+            hipLaunchKernelGGL(k_ritz_step<float>, dim3(g), dim3(RB), 0, st, (const float *)w,
+                               (const float *)v, (const float *)vp, (float *)vec(in),
+                               acc.as<double>(), nsc, al_d + j, bp, be_d + j, c[j + 1]);
+        else
+            hipLaunchKernelGGL(k_ritz_step<double>, dim3(g), dim3(RB), 0, st, (const double *)w,
+                               (const double *)v, (const double *)vp, (double *)vec(in),
+                               acc.as<double>(), nsc, al_d + j, bp, be_d + j, c[j + 1]);
+        XDG_TRY_HIP(hipGetLastError());
         ip = iv;
         iv = in;
         in = (in + 1) % 3;
@@ -1220,7 +1439,7 @@ int lanczos_eigvec(xdg_ham_s *h, const void *v0, uint64_t seed, int prec, int m,
     // psi = acc / |acc|
     VecOps dops{false, 1, 1, nsc, vec_grid(nsc), parts.as<double>(), st};
     XDG_RETURN_IF(dops.dot(acc.p, acc.p));
-    XDG_RETURN_IF(dops.finalize(1, nrm, nullptr, jdev));
+    XDG_RETURN_IF(dops.finalize(1, nrm, nullptr));
     if (single)
         hipLaunchKernelGGL(k_acc_out<float>, dim3(g), dim3(RB), 0, st, acc.as<double>(),
                            (float *)psi, nsc, nrm);
@@ -1391,8 +1610,8 @@ int lanczos_batched(int n, xdg_ham_s *const *hams, const void *const *v0s, int64
                         m = j + 1;
                         break;
                     }
-                tridiag_eigenvalues(m, a1.data(), b1.data(), ritz);
-                evals[(size_t)i * nvec + v] = ritz[0];
+                evals[(size_t)i * nvec + v] =
+                    tridiag_eigenvalue(m, a1.data(), b1.data(), 0, ritz);
             }
         }
     }
@@ -1436,11 +1655,9 @@ int tpq_micro(xdg_ham_s *h, const void *v0, uint64_t seed, int prec, double l, i
 
     DevBuf vbuf, scal, parts;
     XDG_RETURN_IF(vbuf.alloc(2 * vstride));
-    // scalars: <v,Hv>, <Hv,Hv>, norm, l N, unused, histories [2][n_steps], jdev
-    XDG_RETURN_IF(scal.alloc(sizeof(double) * (5 + 2 * (size_t)n_steps) + 16));
-    double *s_vw = scal.as<double>(), *s_ww = s_vw + 1, *s_nrm = s_vw + 2, *s_ln = s_vw + 3;
-    double *s_dummy = s_vw + 4, *h_vw = s_vw + 5, *h_ww = h_vw + n_steps;
-    int *jdev = reinterpret_cast<int *>(h_ww + n_steps);
+    // scalars: norm, l N, histories of <v,Hv> and <Hv,Hv>
+    XDG_RETURN_IF(scal.alloc(sizeof(double) * (2 + 2 * (size_t)n_steps)));
+    double *s_nrm = scal.as<double>(), *s_ln = s_nrm + 1, *h_vw = s_nrm + 2, *h_ww = h_vw + n_steps;
     VecOps ops{single, C, C, nsc, vec_grid(nsc), nullptr, st};
     XDG_RETURN_IF(parts.alloc(sizeof(double) * (size_t)ops.grid * MAXC));
     ops.partials = parts.as<double>();
@@ -1451,24 +1668,20 @@ int tpq_micro(xdg_ham_s *h, const void *v0, uint64_t seed, int prec, double l, i
         XDG_RETURN_IF(random_fill((int64_t)nsc, seed, 1, single, v, st));
     const double ln = l * N;
     XDG_TRY_HIP(hipMemcpyAsync(s_ln, &ln, sizeof(double), hipMemcpyHostToDevice, st));
-    hipLaunchKernelGGL(k_set_scalars, dim3(1), dim3(64), 0, st, jdev, s_dummy, 1);
-    XDG_TRY_HIP(hipGetLastError());
     XDG_RETURN_IF(ops.dot(v, v));
-    XDG_RETURN_IF(ops.finalize(1, s_nrm, nullptr, jdev));
+    XDG_RETURN_IF(ops.finalize(1, s_nrm, nullptr));
     XDG_RETURN_IF(ops.scale(v, v, s_nrm));
     for (int k = 0; k < n_steps; ++k) {
         XDG_RETURN_IF(apply_tuned(h, v, w, 1, dtype, st));
         XDG_RETURN_IF(ops.dot(v, w));
-        XDG_RETURN_IF(ops.finalize(0, s_vw, h_vw, jdev));
+        XDG_RETURN_IF(ops.finalize(0, h_vw + k, nullptr));
         XDG_RETURN_IF(ops.dot(w, w));
-        XDG_RETURN_IF(ops.finalize(0, s_ww, h_ww, jdev));
+        XDG_RETURN_IF(ops.finalize(0, h_ww + k, nullptr));
         if (k + 1 < n_steps) {
             XDG_RETURN_IF(ops.update(w, v, nullptr, s_ln, nullptr));   // w = H v - l N v
-            XDG_RETURN_IF(ops.finalize(1, s_nrm, nullptr, jdev));
+            XDG_RETURN_IF(ops.finalize(1, s_nrm, nullptr));
             XDG_RETURN_IF(ops.scale(w, v, s_nrm));
         }
-        hipLaunchKernelGGL(k_step_end, dim3(1), dim3(64), 0, st, jdev, s_dummy, s_dummy, 1);
-        XDG_TRY_HIP(hipGetLastError());
     }
     std::vector<double> hv(n_steps), hw(n_steps);
     XDG_RETURN_IF(copy_d2h(hv.data(), h_vw, sizeof(double) * n_steps, st));

@@ -105,6 +105,9 @@ uint64_t device_memory_in_use();
 // staging buffer, complete on return.
 int copy_d2h(void *dst, const void *src, size_t n, hipStream_t st);
 int copy_h2d(void *dst, const void *src, size_t n, hipStream_t st);
+// n doubles of page-locked memory that kernels can write and the host read
+// (per thread, grown on demand, valid until the thread's next call)
+int host_scalars(size_t n, double **out);
 
 int validate_group(int n_sites, int n_sym, const int32_t *perm, const double *chi);
 int validate_bonds(int n_sites, int n_sym, const int32_t *perm, int n_bonds, const int32_t *sites,
