@@ -260,6 +260,36 @@ int pick_nv(int64_t remaining, int cap) { return (int)std::min<int64_t>(remainin
 
 }  // namespace
 
+// The few-rows loop serves blocks (or batches) of fewer rows than this.  Its
+// time grows with the rows from the first on, while the row loop takes the
+// time of one lane's chain up to about 3 10^5 rows; measured crossings (FP64,
+// one vector): rings at 6 10^4 (9252 rows 12 against 27 us, 112720 rows 47
+// against 35), sublattice blocks at 9 10^4 (6x6 triangular), 10^5 (4x6) to
+// 1.6 10^5 (6x6 square).  Without a group a term is too cheap to share out
+// (184756 rows: 41 against 13 us): those blocks take small workgroups.
+static int64_t few_rows(int kind) {
+    return kind == K_U1 ? 0 : kind == K_AFF ? 1 << 16 : 3 << 15;
+}
+
+// Its shape: rows per wave (about 128 (row, bond) pairs, two for every lane),
+// the workgroup, and its LDS behind `tables` bytes of staged tables.  False
+// where the terms of even one wave do not fit.
+static bool few_shape(int64_t rows, int n_bonds, bool cplx, bool single_acc, size_t tables,
+                      int *few, int *block, size_t *lds) {
+    const int nb = std::max(n_bonds, 1);
+    *few = std::max(1, std::min(16, 128 / nb));
+    const size_t per_wave = single_acc ? few_bytes<float>(cplx, *few * nb)
+                                       : few_bytes<double>(cplx, *few * nb);
+    const int64_t waves = (rows + *few - 1) / *few;
+    // a workgroup per compute unit at least, as large as that leaves it
+    int w = 1;
+    while (w < 16 && (int64_t)w * device_cu_count() < waves) w *= 2;
+    while (w > 1 && a16(tables) + w * per_wave > lds_budget()) w /= 2;
+    *block = 64 * w;
+    *lds = a16(tables) + w * per_wave;
+    return *lds <= lds_budget();
+}
+
 // LDS bytes the apply kernel stages for this form, whether the sublattice
 // tables fit with them, and whether two workgroups fit one compute unit
 void apply_lds(const xdg_ham_s *h, int dtype, size_t *lds, int *stage_sub, int *occ_ok) {
@@ -336,6 +366,26 @@ int apply_launch(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, 
     }
     A.occ = A.stage_sub ? (c.occ >= 0 ? (c.occ && occ_for(lds)) : occ_for(lds)) : 0;
     A.compact = c.compact > 0 && !xr_on ? 1 : 0;   // the compacted loop reads x itself
+    // few rows: terms shared out over the lanes (never with an explicit shape)
+    int few = 0, few_block = 0;
+    size_t few_lds = 0;
+    if (c.few && b->plan.kind != K_U1 && !xr_on && A.stage_sub && f.cols < (int64_t)1 << 24 &&
+        few_shape(b->dim, h->n_bonds, f.cplx_kernel, f.tsingle, lds, &few, &few_block, &few_lds)) {
+        A.few = few;
+        A.few_off = (uint32_t)a16(lds);
+        A.occ = A.compact = 0;
+        const int64_t per = (int64_t)few * (few_block / 64);
+        const int64_t g = std::min<int64_t>((b->dim + per - 1) / per, 2 * (int64_t)device_cu_count());
+        return launch_dispatch(b->plan.kind, b->wide, f.single, f.acc64, f.cplx_kernel, 1, A,
+                               (unsigned)g, (unsigned)few_block, few_lds, st);
+    }
+    // no group, few rows: nothing to stage, so workgroups small enough for two
+    // on every compute unit
+    unsigned lanes = block, groups = grid;
+    if (c.few && b->plan.kind == K_U1) {
+        while (lanes > 64 && b->dim < (int64_t)2 * lanes * device_cu_count()) lanes /= 2;
+        groups = (unsigned)((b->dim + lanes - 1) / lanes);
+    }
     const int cap = std::min(c.nv > 0 ? c.nv : 8,
                              xr_on                          ? xr_max_nv(f.cplx_kernel)
                              : A.compact && f.cols <= 3 ? 2   // the compacted loop takes two
@@ -351,7 +401,7 @@ int apply_launch(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, 
                                         block, lds, st));
         else
             XDG_RETURN_IF(launch_dispatch(b->plan.kind, b->wide, f.single, f.acc64,
-                                          f.cplx_kernel, nv, A, grid, block, lds, st));
+                                          f.cplx_kernel, nv, A, groups, lanes, lds, st));
         v0 += nv;
     }
     if (xr_on && !capturing) XDG_TRY_HIP(hipEventRecord(h->xr_ev, st));
@@ -390,6 +440,7 @@ int apply_tuned(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, h
     const int64_t need = (b->dim + APPLY_BLOCK - 1) / APPLY_BLOCK;
     if (b->dim < (int64_t)1024 * APPLY_BLOCK) {   // small blocks: one row per lane
         LaunchCfg c{APPLY_BLOCK, (int)std::min<int64_t>(need, 1 << 30), 8};
+        c.few = b->plan.kind == K_U1 || b->dim < few_rows(b->plan.kind);
         h->tuned[key] = c;
         return apply_launch(h, x, y, nvec, dtype, st, &c);
     }
@@ -583,6 +634,32 @@ int batch_plan_host(int n, xdg_ham_s *const *hams, const void *const *xs, void *
     P->tile_rows = tile_rows ? (tile_rows + APPLY_BLOCK - 1) / APPLY_BLOCK * APPLY_BLOCK
                              : 4 * APPLY_BLOCK;
     size_t lds_full = 0, lds_part = 0;
+    // few rows in all: terms shared out over the lanes, about four items per
+    // compute unit
+    P->few = 0;
+    int64_t rows = 0;
+    int most_bonds = 0;
+    for (int i = 0; i < n; ++i) {
+        const SectorDesc d = make_desc(hams[i], P->tsingle, nullptr, nullptr, relabelled);
+        rows += d.dim;
+        most_bonds = std::max(most_bonds, d.n_bonds);
+        lds_full = std::max(lds_full, P->tsingle ? stage_bytes<float>(d, P->kind, 1)
+                                                 : stage_bytes<double>(d, P->kind, 1));
+    }
+    if (rows < few_rows(P->kind) && lds_full <= lds_budget() && P->cols < (int64_t)1 << 24) {
+        int few = 0, block = 0;
+        size_t lds = 0;
+        if (few_shape(rows, most_bonds, P->cplx, P->tsingle, lds_full, &few, &block, &lds)) {
+            const int64_t per = (int64_t)few * (block / 64);
+            const int64_t want = (rows + 4 * (int64_t)device_cu_count() - 1) /
+                                 (4 * (int64_t)device_cu_count());
+            P->few = few;
+            P->few_off = (uint32_t)a16(lds_full);
+            P->few_block = block;
+            P->few_lds = lds;
+            P->tile_rows = (uint32_t)std::max<int64_t>(1, (want + per - 1) / per * per);
+        }
+    }
     uint64_t acc = 0;
     for (int i = 0; i < n; ++i) {
         const SectorDesc d = make_desc(hams[i], P->tsingle, xs[i], ys[i], relabelled);
@@ -594,11 +671,8 @@ int batch_plan_host(int n, xdg_ham_s *const *hams, const void *const *xs, void *
         if (prefix) prefix[i] = (uint32_t)acc;
         acc += tiles;
         if (descs) descs[i] = d;
-        const size_t f1 = P->tsingle ? stage_bytes<float>(d, P->kind, 1)
-                                     : stage_bytes<double>(d, P->kind, 1);
         const size_t f0 = P->tsingle ? stage_bytes<float>(d, P->kind, 0)
                                      : stage_bytes<double>(d, P->kind, 0);
-        lds_full = std::max(lds_full, f1);
         lds_part = std::max(lds_part, f0);
     }
     if (prefix) prefix[n] = (uint32_t)acc;
@@ -637,6 +711,16 @@ int batch_launch_raw(const BatchMeta &P, const SectorDesc *d_descs, const uint32
     A.nvec = P.cols;
     A.stage_sub = P.stage_sub;
     A.occ = P.stage_sub ? occ_for(P.lds) : 0;
+    if (P.few) {   // one launch for all vectors
+        A.few = P.few;
+        A.few_off = P.few_off;
+        A.occ = 0;
+        hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, st, A.queue);
+        XDG_TRY_HIP(hipGetLastError());
+        const unsigned gf = std::min<unsigned>(P.n_tiles, 2u * (unsigned)device_cu_count());
+        return launch_dispatch(P.kind, P.wide, P.single, P.acc64, P.cplx, 1, A, gf,
+                               (unsigned)P.few_block, P.few_lds, st);
+    }
     const unsigned g = (unsigned)(grid > 0 ? grid : apply_grid_for(2));
     for (int64_t v0 = 0; v0 < P.cols;) {
         const int nv = pick_nv(P.cols - v0, nv_cap > 0 ? nv_cap : 8);
@@ -694,6 +778,13 @@ int batch_shape_tuned(int n, xdg_ham_s *const *hams, const void *const *xs, void
         return XDG_OK;
     }
     BatchShape best_shape{apply_grid_for(2), 4 * 1024, 8};
+    BatchMeta meta;
+    XDG_RETURN_IF(batch_plan_host(n, hams, xs, ys, nvec, dtype, &meta, nullptr, nullptr));
+    if (meta.few) {   // its shape follows from the sizes
+        g_shape_cache[key] = best_shape;
+        *out = best_shape;
+        return XDG_OK;
+    }
     hipEvent_t e0, e1;
     XDG_TRY_HIP(hipEventCreate(&e0));
     XDG_TRY_HIP(hipEventCreate(&e1));

@@ -110,6 +110,8 @@ struct ApplyArgs {
     int stage_sub;               // copy sublattice tables into LDS
     int occ;                     // use the 8-waves-per-SIMD variant
     int compact;                 // table searches: wave-compacted term loop
+    int few;                     // rows per wave of the few-rows loop (0: another loop)
+    uint32_t few_off;            // byte offset of its terms behind the staged tables
     unsigned long long *count;   // nnz counting mode (nullptr otherwise)
 };
 
@@ -359,9 +361,6 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
     for (int v = 0; v < NV * C; ++v) acc[v] = 0;
     A rn = A(1);
     if constexpr (KIND != K_U1) rn = S.rsq[gld(d.stab + row)];
-    int64_t orow = row;
-    if constexpr (KIND == K_SUB)
-        if (d.umap) orow = user_pos<A>(d, row, rn);
     // explicit fused multiply-adds: a complex kernel on a block with real
     // characters (ai = 0) rounds exactly like the real kernel
     auto add = [&](A ar, A ai, const T *xv) {
@@ -504,6 +503,11 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
             }
         }
     }
+    // (the caller's position is read here and not before the terms: a register
+    // pair held over the search costs the 64-register copies spills)
+    int64_t orow = row;
+    if constexpr (KIND == K_SUB)
+        if (d.umap) orow = user_pos<A>(d, row, rn);
     const size_t base = ((size_t)orow * nvec + v0) * C;
     const A diag = (A)d.jz_quarter - A(0.5) * junq;
 #pragma unroll
@@ -685,15 +689,124 @@ __device__ __forceinline__ void process_window(const SectorDesc &d, const Staged
     }
 }
 
-// rows [r0, r1) of a sector.  CMP: windows of CMP_ROWS rows per wave (every
-// lane of a wave takes part in its permutes; `first` and `stride` count
-// lanes, so wave w of the launch starts at window w); otherwise a lane per
-// row, reading the rank-addressed x when XR.
-template <class W, int KIND, class T, class A, bool CPLX, int NV, bool CMP, int XR, bool PIPE>
+// --------------------------------------------------------- few-rows loop --
+// A block of few rows leaves most of the chip idle when every lane owns a
+// row, and the time is one lane's chain of n_bonds searches (6x6 triangular
+// lattice, 1772 rows: 1.0 ms).  Here a wave takes `few` rows at once: first
+// its lanes share out the (row, bond) pairs and leave each term's amplitude
+// and position in LDS, then a lane per (row, vector) adds the terms in bond
+// order with the fused multiply-adds of the row loop, so that both loops give
+// the same bits.  All vectors share the search, whatever their number.
+constexpr uint32_t NO_TERM = 0xFFFFFFFFu;
+
+template <class A>
+__host__ __device__ constexpr size_t few_bytes(bool cplx, int terms) {
+    return ((size_t)terms * (sizeof(A) * (cplx ? 2 : 1) + 4) + 15) & ~(size_t)15;
+}
+
+template <class W, int KIND, class T, class A, bool CPLX>
+__device__ __forceinline__ void process_few(const SectorDesc &d, const Staged<A> &S, int64_t r0,
+                                            int64_t r1, int64_t wave, int64_t waves, int few,
+                                            unsigned char *scratch, int64_t nvec) {
+    using B = typename BondT<A>::type;
+    constexpr int C = CPLX ? 2 : 1;
+    const int lane = (int)__lane_id();
+    const uint32_t nb = (uint32_t)d.n_bonds, cols = (uint32_t)nvec;
+    const W *R = reinterpret_cast<const W *>(d.reps);
+    const T *X = reinterpret_cast<const T *>(d.x);
+    T *Y = reinterpret_cast<T *>(d.y);
+    A *amp = reinterpret_cast<A *>(scratch);
+    uint32_t *pos = reinterpret_cast<uint32_t *>(amp + (size_t)few * nb * C);
+    for (int64_t w0 = r0 + wave * few; w0 < r1; w0 += waves * few) {
+        const uint32_t nr = (uint32_t)(r1 - w0 < few ? r1 - w0 : few);
+        for (uint32_t e = lane; e < nr * nb; e += 64) {
+            const uint32_t r = e / nb, b = e - r * nb;
+            const W s = gld(R + w0 + r);
+            const B bd = S.bonds[b];
+            uint32_t at = NO_TERM;
+            if (((s >> bd.i) & 1) != ((s >> bd.j) & 1)) {
+                int u, cnt;
+                auto idx = locate<W, KIND, A>(d, S, s ^ ((W(1) << bd.i) | (W(1) << bd.j)), u, cnt);
+                if (idx >= 0) {
+                    A hs = bd.h;
+                    if constexpr (KIND == K_SUB)
+                        if (d.umap) idx = user_pos<A>(d, idx, hs);
+                    A ar = hs;
+                    if constexpr (KIND != K_U1) {
+                        const A f = hs * S.sq[cnt];
+                        const auto c = S.chi[u];
+                        ar = f * c.x;
+                        if constexpr (CPLX) amp[2 * e + 1] = f * c.y;
+                    }
+                    amp[C * e] = ar;
+                    at = (uint32_t)idx;
+                }
+            }
+            pos[e] = at;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (uint32_t q = lane; q < nr * cols; q += 64) {
+            const uint32_t r = q / cols, v = q - r * cols;
+            const int64_t row = w0 + r;
+            const W s = gld(R + row);
+            A junq = 0, re = 0, im = 0;
+#pragma unroll 4
+            for (uint32_t b = 0; b < nb; ++b) {
+                const B bd = S.bonds[b];
+                const bool off = ((s >> bd.i) & 1) != ((s >> bd.j) & 1);
+                junq = off ? junq + bd.jz : junq;
+                const uint32_t e = r * nb + b, at = pos[e];
+                // no term: position 0 is read and not added
+                const size_t xb = ((size_t)(at == NO_TERM ? 0u : at) * cols + v) * C;
+                const A ar = at == NO_TERM ? A(0) : amp[C * e];
+                const A xr = (A)gld(X + xb);
+                if constexpr (CPLX) {
+                    const A ai = at == NO_TERM ? A(0) : amp[2 * e + 1];
+                    const A xi = (A)gld(X + xb + 1);
+                    const A nr_ = fmadd<A>(-ai, xi, fmadd<A>(ar, xr, re));
+                    const A ni_ = fmadd<A>(ai, xr, fmadd<A>(ar, xi, im));
+                    re = at == NO_TERM ? re : nr_;
+                    im = at == NO_TERM ? im : ni_;
+                } else {
+                    const A n_ = fmadd<A>(ar, xr, re);
+                    re = at == NO_TERM ? re : n_;
+                }
+            }
+            A rn = A(1);
+            if constexpr (KIND != K_U1) rn = S.rsq[gld(d.stab + row)];
+            int64_t orow = row;
+            if constexpr (KIND == K_SUB)
+                if (d.umap) orow = user_pos<A>(d, row, rn);
+            const size_t base = ((size_t)orow * cols + v) * C;
+            const A diag = (A)d.jz_quarter - A(0.5) * junq;
+            gst(Y + base, (T)fmadd<A>(diag, (A)gld(X + base), KIND != K_U1 ? rn * re : re));
+            if constexpr (CPLX)
+                gst(Y + base + 1, (T)fmadd<A>(diag, (A)gld(X + base + 1), KIND != K_U1 ? rn * im : im));
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+enum : int { LOOP_ROW = 0, LOOP_CMP = 1, LOOP_FEW = 2 };
+
+// rows [r0, r1) of a sector.  LOOP_CMP: windows of CMP_ROWS rows per wave
+// (every lane of a wave takes part in its permutes; `first` and `stride`
+// count lanes, so wave w of the launch starts at window w); LOOP_FEW: `few`
+// rows per wave, all vectors; otherwise a lane per row, reading the
+// rank-addressed x when XR.
+template <class W, int KIND, class T, class A, bool CPLX, int NV, int LOOP, int XR, bool PIPE>
 __device__ __forceinline__ void process_range(const SectorDesc &d, const Staged<A> &S, int64_t r0,
                                               int64_t r1, int64_t first, int64_t stride,
-                                              int64_t nvec, int v0) {
-    if constexpr (CMP) {
+                                              int64_t nvec, int v0, int few,
+                                              unsigned char *few_terms) {
+    if constexpr (LOOP == LOOP_FEW) {
+        process_few<W, KIND, T, A, CPLX>(
+            d, S, r0, r1, (first - lane_id()) / 64, stride / 64, few,
+            few_terms + (threadIdx.x / 64) * few_bytes<A>(CPLX, few * d.n_bonds), nvec);
+    } else if constexpr (LOOP == LOOP_CMP) {
         const int64_t wave = (first - lane_id()) / 64, waves = stride / 64;
         for (int64_t w0 = r0 + wave * CMP_ROWS; w0 < r1; w0 += waves * CMP_ROWS)
             process_window<W, KIND, T, A, CPLX, NV>(d, S, w0, r1, nvec, v0);
@@ -720,11 +833,12 @@ __device__ __forceinline__ uint32_t count_row(const SectorDesc &d, const Staged<
 }
 
 template <class W, int KIND, class T, class AC, bool CPLX, int NV, bool STAGE, bool OCC,
-          bool CMP, int XR>
+          int LOOP, int XR>
 __global__ __launch_bounds__(APPLY_BLOCK, OCC ? OCC_WAVES : 1) void k_apply(ApplyArgs A) {
     // the sublattice row loop pipelines its gathers
-    constexpr bool PIPE = KIND == K_SUB && !CMP;
+    constexpr bool PIPE = KIND == K_SUB && LOOP == LOOP_ROW;
     extern __shared__ __align__(16) unsigned char smem[];
+    unsigned char *few_terms = smem + A.few_off;
     __shared__ uint32_t s_tile;
     __shared__ SectorDesc s_desc;
     Staged<AC> S;
@@ -733,9 +847,9 @@ __global__ __launch_bounds__(APPLY_BLOCK, OCC ? OCC_WAVES : 1) void k_apply(Appl
         stage<KIND, AC, STAGE>(d, smem, S);
         __syncthreads();
         const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-        process_range<W, KIND, T, AC, CPLX, NV, CMP, XR, PIPE>(d, S, 0, d.dim,
-                                                (int64_t)blockIdx.x * blockDim.x + threadIdx.x,
-                                                stride, A.nvec, A.v0);
+        process_range<W, KIND, T, AC, CPLX, NV, LOOP, XR, PIPE>(
+            d, S, 0, d.dim, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride, A.nvec, A.v0,
+            A.few, few_terms);
         return;
     }
     // persistent: (sector, row tile) items from one queue
@@ -761,8 +875,8 @@ __global__ __launch_bounds__(APPLY_BLOCK, OCC ? OCC_WAVES : 1) void k_apply(Appl
         const int64_t r0 = (int64_t)(tile - A.tile_prefix[lo]) * A.tile_rows;
         int64_t r1 = r0 + A.tile_rows;
         r1 = r1 < d.dim ? r1 : d.dim;
-        process_range<W, KIND, T, AC, CPLX, NV, CMP, XR, PIPE>(d, S, r0, r1, threadIdx.x, blockDim.x,
-                                                     A.nvec, A.v0);
+        process_range<W, KIND, T, AC, CPLX, NV, LOOP, XR, PIPE>(
+            d, S, r0, r1, threadIdx.x, blockDim.x, A.nvec, A.v0, A.few, few_terms);
         __syncthreads();
     }
 }
@@ -812,14 +926,14 @@ constexpr int occ_scalars(int xr) { return xr ? 4 : 2; }
 // Vectors per pass of the rank-addressed kernels: at most eight scalars.
 constexpr int xr_max_nv(bool cplx) { return cplx ? 4 : 8; }
 
-template <class W, int KIND, class T, class AC, bool CPLX, bool STAGE, bool OCC, bool CMP, int XR,
+template <class W, int KIND, class T, class AC, bool CPLX, bool STAGE, bool OCC, int LOOP, int XR,
           int NV = 1>
 void (*apply_kernel(int nv))(ApplyArgs) {
-    constexpr int most = CMP ? 2 : XR ? xr_max_nv(CPLX) : 8;
+    constexpr int most = LOOP == LOOP_CMP ? 2 : XR ? xr_max_nv(CPLX) : 8;
     constexpr int limit = OCC ? occ_scalars(XR) / (CPLX ? 2 : 1) : most;
     if constexpr (NV <= (limit < most ? limit : most)) {
-        if (nv == NV) return k_apply<W, KIND, T, AC, CPLX, NV, STAGE, OCC, CMP, XR>;
-        return apply_kernel<W, KIND, T, AC, CPLX, STAGE, OCC, CMP, XR, NV + 1>(nv);
+        if (nv == NV) return k_apply<W, KIND, T, AC, CPLX, NV, STAGE, OCC, LOOP, XR>;
+        return apply_kernel<W, KIND, T, AC, CPLX, STAGE, OCC, LOOP, XR, NV + 1>(nv);
     }
     return nullptr;
 }
@@ -832,8 +946,9 @@ constexpr bool has_compact() { return KIND == K_SUB || KIND == K_TAB; }
 template <class W, int KIND, class T, class AC, bool CPLX, bool STAGE, bool OCC>
 void (*apply_kernel_loop(int nv, bool compact))(ApplyArgs) {
     if constexpr (has_compact<KIND>())
-        if (compact && nv <= 2) return apply_kernel<W, KIND, T, AC, CPLX, STAGE, OCC, true, 0>(nv);
-    return apply_kernel<W, KIND, T, AC, CPLX, STAGE, OCC, false, 0>(nv);
+        if (compact && nv <= 2)
+            return apply_kernel<W, KIND, T, AC, CPLX, STAGE, OCC, LOOP_CMP, 0>(nv);
+    return apply_kernel<W, KIND, T, AC, CPLX, STAGE, OCC, LOOP_ROW, 0>(nv);
 }
 
 template <class W, int KIND, class T, class AC, bool CPLX, int XR>
@@ -847,8 +962,10 @@ int launch_nv(int nv, const ApplyArgs &A, unsigned grid, unsigned block, size_t 
         return XDG_EINVAL;
     } else if constexpr (XR != 0) {   // row loop, tables in LDS
         if (A.stage_sub)
-            f = occ ? apply_kernel<W, KIND, T, AC, CPLX, true, true, false, XR>(nv)
-                    : apply_kernel<W, KIND, T, AC, CPLX, true, false, false, XR>(nv);
+            f = occ ? apply_kernel<W, KIND, T, AC, CPLX, true, true, LOOP_ROW, XR>(nv)
+                    : apply_kernel<W, KIND, T, AC, CPLX, true, false, LOOP_ROW, XR>(nv);
+    } else if (A.few && (KIND != K_SUB || A.stage_sub)) {
+        f = k_apply<W, KIND, T, AC, CPLX, 1, true, false, LOOP_FEW, 0>;
     } else if (KIND != K_SUB || A.stage_sub)
         // only the sublattice kind has tables that may stay in global memory
         f = occ ? apply_kernel_loop<W, KIND, T, AC, CPLX, true, true>(nv, cmp)

@@ -220,6 +220,7 @@ struct LaunchCfg {
     int compact = -1;      // table searches: 1 = wave-compacted term loop, 0 / -1 = row loop
     int sub_form = 0;      // sublattice coding: 0 = packed form where it applies, 2 = block form
     int xr = 0;            // sublattice coding: 1 = terms read a rank-addressed copy of x
+    int few = 0;           // 1: few rows (the few-rows loop; small workgroups without a group)
 };
 }  // namespace xdg
 
@@ -314,6 +315,10 @@ struct BatchMeta {
     bool wide = false, single = false, cplx = false, acc64 = true, tsingle = false;
     int64_t cols = 0;
     uint32_t n_tiles = 0, tile_rows = 0;
+    int few = 0;             // rows per wave of the few-rows loop (0: the row loop)
+    uint32_t few_off = 0;
+    int few_block = 0;       // its workgroup and LDS
+    size_t few_lds = 0;
     size_t lds = 0;
     int stage_sub = 1;
 };

@@ -1,0 +1,82 @@
+"""Small blocks, whose terms are shared out over the lanes of a wave: bitwise the
+row loop's products for every search, width, precision and number of vectors,
+alone and in batches (row counts below, at and above a wave's share)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def X():
+    import paper_2505_02901_amd as X
+    return X
+
+
+def turned(n_up):
+    t = W.Torus((4, 2), (-2, 4))
+    m = W.torus_model((4, 2), (-2, 4), 1.0, 0.0, None, n_up=n_up)
+    perm, labels = t.symmetry_group(True, False)
+    return m.with_sector(perm, W.gamma_characters(labels, 1j, 1.0))
+
+
+def long_range(n):
+    """every pair of sites of a ring coupled: more bonds than a pass has pairs"""
+    sites = np.array([(i, j) for i in range(n) for j in range(i)], np.int32)
+    d = np.array([min(i - j, n - i + j) for i, j in sites], float)
+    return W.Model("all_pairs", n, n // 2, sites, 1 / d, 0.5 / d, W.chain_translations(n),
+                   W.momentum_characters(n, 0))
+
+
+CASES = {
+    "u1_6": (W.chain_model(6), {}), "u1_12": (W.chain_model(12, n_up=5), {}),
+    "ring3": (W.chain_model(3, n_up=1, l=0), {}), "ring14": (W.chain_model(14, l=0), {}),
+    "ring15_complex": (W.chain_model(15, n_up=7, l=4), {}), "ring40": (W.chain_model(40, n_up=3, l=1), {}),
+    "ring14_hash": (W.chain_model(14, l=3), {"flags": 4}),
+    "pairs15": (long_range(15), {}), "ring14_fp32": (W.chain_model(14, l=0), {"flags": 2}),
+    "square16_table": (W.torus_model((4, 0), (0, 4), 1.0, 0.5, "B1"), {"search": 4}),
+    "square20": (W.torus_model((4, 2), (-2, 4), 1.0, 0.0, "A1", n_up=7, reflections=False), {}),
+    "square20_complex": (turned(7), {}), "square24_2": (W.torus_model((4, 0), (0, 6), 1.0, 0.5, "A1", n_up=6), {}),
+    "square36": (W.torus_model((6, 0), (0, 6), 1.0, 0.5, "B1", n_up=5), {}),
+    "triangle36": (W.sublattice_model("triangle3", (6, 0), (0, 6), n_up=4), {"search": 3, "n_sublattices": 3}),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_same_bits_as_the_row_loop(X, name):
+    m, kw = CASES[name]
+    b = X.Basis.from_model(m, **kw)
+    H = X.Hamiltonian.from_model(b, m)
+    basis = oracle.basis(m)
+    for dt in (torch.float32, torch.float64, torch.complex64, torch.complex128):
+        if b.is_complex and not dt.is_complex:
+            continue
+        for nvec in (1, 3, 8, 70):
+            x = torch.randn(b.dim, nvec, dtype=dt, device="cuda")
+            y, z = torch.full_like(x, 3.0), torch.full_like(x, 4.0)
+            H.apply(x, y)
+            X.xdg_apply_with_config(H.handle, x, z)
+            assert torch.equal(y, z), (name, dt, nvec)
+            if nvec == 3:
+                want = oracle.apply(m, basis, x.cpu().numpy())
+                tol = 1e-12 if dt in (torch.float64, torch.complex128) else 2e-6
+                assert np.max(np.abs(y.cpu().numpy() - want)) < tol * np.max(np.abs(want)), (name, dt)
+
+
+@pytest.mark.parametrize("nvec", [1, 5, 8])
+def test_batches(X, nvec):
+    ms = [W.chain_model(n, l=l) for n, l in ((14, 3), (20, 1), (14, 0), (9, 2), (16, 5), (4, 2))]
+    bs = [X.Basis.from_model(m) for m in ms]
+    hs = [X.Hamiltonian.from_model(b, m) for b, m in zip(bs, ms)]
+    xs = [torch.randn(b.dim, nvec, dtype=torch.complex128, device="cuda") for b in bs]
+    for f in (X.xdg_apply_batched, X.xdg_apply_batched_noalloc, X.xdg_apply_batched):
+        ys = [torch.full_like(x, 3.0) for x in xs]
+        f([h.handle for h in hs], xs, ys)
+        for h, x, y in zip(hs, xs, ys):
+            z = torch.empty_like(x)
+            X.xdg_apply_with_config(h.handle, x, z)
+            assert torch.equal(y, z)
