@@ -263,7 +263,7 @@ template <> struct IndexT<uint32_t> { using type = int32_t; };
 // search is on).  XR: the position is the slot in the rank-addressed x
 // (sublattice coding with d.xr set); XR = 2: every character is 1, so the
 // search does not keep the element (u is left unset).
-template <class W, int KIND, class T, int XR = 0>
+template <class W, int KIND, class T, int XR = 0, bool PACKED = false>
 __device__ __forceinline__ typename IndexT<W>::type locate(const SectorDesc &d, const Staged<T> &S,
                                                            W t, int &u, int &cnt,
                                                            const SubKey *key = nullptr) {
@@ -282,6 +282,8 @@ __device__ __forceinline__ typename IndexT<W>::type locate(const SectorDesc &d, 
                 ring_search<W>(S.ring_gidx, d.ring, d.n_sites, t, rep, u, cnt);
             else
                 aff_search<W>(S.aff, d.n_sym, d.n_sites, t, rep, u, cnt);
+        } else if constexpr (KIND == K_SUB && PACKED) {
+            sub_search_packed<W, XR != 2>(S.sub, S.amask, *key, rep, u, cnt);
         } else if constexpr (KIND == K_SUB) {
             if (S.subf) {
                 if (key)
@@ -339,8 +341,9 @@ __device__ __forceinline__ int64_t user_pos(const SectorDesc &d, int64_t k, A &f
 // exactly 1).  PIPE: each term's gather is added at the next term of the row
 // (or after its last bond), so that its latency overlaps the next search;
 // the same fused multiply-adds in the same order.
+// PACKED: the block runs the packed sublattice search with its bond records.
 template <class W, int KIND, class T, class A, bool CPLX, int NV, int XR = 0,
-          bool PIPE = false>
+          bool PIPE = false, bool PACKED = false>
 __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A> &S, int64_t row,
                                             int64_t nvec, int v0) {
     using B = typename BondT<A>::type;
@@ -383,7 +386,7 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
     // key: the packed sublattice search's key of the term's state, if given
     auto term = [&](const B &bd, W t, const SubKey *key) {
         int u, cnt;
-        auto idx = locate<W, KIND, A, XR>(d, S, t, u, cnt, key);
+        auto idx = locate<W, KIND, A, XR, PACKED>(d, S, t, u, cnt, key);
         A hs = bd.h;
         if constexpr (KIND == K_SUB && XR == 0)
             if (d.umap && idx >= 0) idx = user_pos<A>(d, idx, hs);
@@ -470,7 +473,7 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
         // neighbouring index words.
         bool done = false;
         if constexpr (KIND == K_SUB) {
-            if (S.subf && d.bx) {
+            if (PACKED || (S.subf && d.bx)) {
                 // packed form: the bond comes with scalar loads, the term's key
                 // is the row's key with the bond's bits flipped
                 const SubKey kr = sub_key<W>(s, d.m, d.pb);
@@ -490,7 +493,8 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
                 done = true;
             }
         }
-        if (!done) {
+        if constexpr (!PACKED)
+          if (!done) {
             for (int b = 0; b < nb; ++b) {
                 const B bd = S.bonds[b];
                 if (((s >> bd.i) & 1) == ((s >> bd.j) & 1)) continue;
@@ -790,13 +794,14 @@ __device__ __forceinline__ void process_few(const SectorDesc &d, const Staged<A>
     }
 }
 
-enum : int { LOOP_ROW = 0, LOOP_CMP = 1, LOOP_FEW = 2 };
+enum : int { LOOP_ROW = 0, LOOP_CMP = 1, LOOP_FEW = 2, LOOP_PACKED = 3 };
 
 // rows [r0, r1) of a sector.  LOOP_CMP: windows of CMP_ROWS rows per wave
 // (every lane of a wave takes part in its permutes; `first` and `stride`
 // count lanes, so wave w of the launch starts at window w); LOOP_FEW: `few`
 // rows per wave, all vectors; otherwise a lane per row, reading the
-// rank-addressed x when XR.
+// rank-addressed x when XR.  LOOP_PACKED: the lane-per-row loop of a single
+// block in the packed sublattice form and nothing else (see launch_nv).
 template <class W, int KIND, class T, class A, bool CPLX, int NV, int LOOP, int XR, bool PIPE>
 __device__ __forceinline__ void process_range(const SectorDesc &d, const Staged<A> &S, int64_t r0,
                                               int64_t r1, int64_t first, int64_t stride,
@@ -812,7 +817,7 @@ __device__ __forceinline__ void process_range(const SectorDesc &d, const Staged<
             process_window<W, KIND, T, A, CPLX, NV>(d, S, w0, r1, nvec, v0);
     } else {
         for (int64_t row = r0 + first; row < r1; row += stride)
-            process_row<W, KIND, T, A, CPLX, NV, XR, PIPE>(d, S, row, nvec, v0);
+            process_row<W, KIND, T, A, CPLX, NV, XR, PIPE, LOOP == LOOP_PACKED>(d, S, row, nvec, v0);
     }
 }
 
@@ -836,13 +841,13 @@ template <class W, int KIND, class T, class AC, bool CPLX, int NV, bool STAGE, b
           int LOOP, int XR>
 __global__ __launch_bounds__(APPLY_BLOCK, OCC ? OCC_WAVES : 1) void k_apply(ApplyArgs A) {
     // the sublattice row loop pipelines its gathers
-    constexpr bool PIPE = KIND == K_SUB && LOOP == LOOP_ROW;
+    constexpr bool PIPE = KIND == K_SUB && (LOOP == LOOP_ROW || LOOP == LOOP_PACKED);
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char *few_terms = smem + A.few_off;
     __shared__ uint32_t s_tile;
     __shared__ SectorDesc s_desc;
     Staged<AC> S;
-    if (A.descs == nullptr) {
+    if (LOOP == LOOP_PACKED || A.descs == nullptr) {
         const SectorDesc &d = A.one;
         stage<KIND, AC, STAGE>(d, smem, S);
         __syncthreads();
@@ -853,8 +858,8 @@ __global__ __launch_bounds__(APPLY_BLOCK, OCC ? OCC_WAVES : 1) void k_apply(Appl
         return;
     }
     // persistent: (sector, row tile) items from one queue
-    int cur = -1;
-    for (;;) {
+    if constexpr (LOOP != LOOP_PACKED)
+    for (int cur = -1;;) {
         if (threadIdx.x == 0) s_tile = atomicAdd(A.queue, 1u);
         __syncthreads();
         const uint32_t tile = s_tile;
@@ -957,7 +962,16 @@ int launch_nv(int nv, const ApplyArgs &A, unsigned grid, unsigned block, size_t 
     void (*f)(ApplyArgs) = nullptr;
     const bool occ = A.occ && nv * (CPLX ? 2 : 1) <= occ_scalars(XR);
     const bool cmp = A.compact != 0;
-    if constexpr (XR == 2 && CPLX) {
+    // One block in the packed form: a kernel of that loop alone.  The general
+    // one holds the searches of every form twice (single and batched) and
+    // keeps 46 vector and 86 scalar registers of its 64-register copy in
+    // memory.
+    if constexpr (KIND == K_SUB && !(XR == 2 && CPLX))
+        if (!A.descs && A.stage_sub && A.one.subf && A.one.bx && !cmp && !A.few)
+            f = occ ? apply_kernel<W, KIND, T, AC, CPLX, true, true, LOOP_PACKED, XR>(nv)
+                    : apply_kernel<W, KIND, T, AC, CPLX, true, false, LOOP_PACKED, XR>(nv);
+    if (f) {
+    } else if constexpr (XR == 2 && CPLX) {
         set_error("internal: the trivial-character kernels serve real blocks");
         return XDG_EINVAL;
     } else if constexpr (XR != 0) {   // row loop, tables in LDS
