@@ -106,7 +106,11 @@ SectorDesc make_desc(const xdg_ham_s *h, bool single, const void *x, void *y,
     d.pb = b->plan.sub.pb;
     d.n_perm = b->plan.sub.n_perm;
     d.n_cand = (uint32_t)b->plan.sub.cand_list.size();
-    d.subf = b->plan.kind == K_SUB && sub_packed_ok(d.n_s, d.m, d.pb) && bonds.x.p;
+    d.subf = b->plan.kind == K_SUB && b->plan.sub.packed() && bonds.x.p;
+    d.pk_tab = b->t_pktab.as<uint32_t>();
+    d.pk_cand = b->t_pkcand.as<uint16_t>();
+    d.n_pk = (uint32_t)b->plan.sub.pk_cand.size();
+    d.pk_nb = b->plan.sub.pk_nb;
     d.bx = d.subf ? bonds.x.as<BondX>() : nullptr;
     d.bonds = single ? bonds.f.p : bonds.d.p;
     d.chi = single ? b->chi_f.p : b->chi_d.p;

@@ -73,6 +73,10 @@ struct SectorDesc {
     int n_s, m, pb, n_perm;
     uint32_t n_cand;
     int subf;                    // sublattice tables in the packed form (staged kernels)
+    const uint32_t *pk_tab;      // its block table and candidate lists
+    const uint16_t *pk_cand;
+    uint32_t n_pk;
+    int pk_nb;
     const BondX *bx;             // per-bond data of the packed form [n_bonds]
     const void *bonds;           // BondD / BondF [n_bonds]
     const void *chi;             // double2 / float2 [n_sym]
@@ -119,6 +123,10 @@ __host__ __device__ constexpr size_t a16(size_t x) { return (x + 15) & ~(size_t)
 
 __host__ __device__ inline size_t sub_table_bytes(const SectorDesc &d) {
     const size_t NV = (size_t)d.n_s << d.m;
+    // packed form: one more element and its permutation, and 128 bytes to align the permutations
+    if (d.subf)
+        return a16(4 * NV) + a16(2 * (size_t)d.n_pk) + 16 * ((size_t)d.n_sym + 1) +
+               a16(4 * ((size_t)d.n_perm + 1) << d.pb) + 128;
     return a16(2 * NV) + a16(4 * (NV + 1)) + a16(2 * (size_t)d.n_cand) +
            a16(4 * (size_t)d.n_sym * d.n_s) +
            a16(2 * (size_t)d.n_perm * 2 * ((size_t)1 << d.pb));
@@ -146,8 +154,6 @@ __host__ __device__ inline size_t stage_bytes(const SectorDesc &d, int kind, int
         n += a16(rank_table_bytes(d));
         if (kind == K_AFF) n += a16(sizeof(AffineElem) * d.n_sym) + a16(4 * (size_t)d.n_sites);
         if (kind == K_SUB && stage_sub) n += sub_table_bytes(d);
-        // packed form: alignment of the permutation tables
-        if (kind == K_SUB && stage_sub && d.subf) n += 128;
         if (kind == K_SUB && stage_sub && d.xr) n += a16(xr_top_bytes(d));
     }
     return n;
@@ -163,8 +169,8 @@ struct Staged {
     const int16_t *ring_gidx;
     const void *rtab;
     SubCtx sub;
-    bool subf;             // packed sublattice search (sub.sp holds the packed entries)
-    uint32_t amask;        // ~(4E - 1)
+    bool subf;             // packed sublattice search
+    PackedCtx pk;
     const uint64_t *xr_top;   // first rank of each top block (rank-addressed x)
     const uint32_t *xr_top32; // the same in 4 bytes (xr_w32) at the same place
     bool xr_w32;
@@ -186,6 +192,10 @@ __device__ inline void stage(const SectorDesc &d, unsigned char *smem, Staged<T>
     using B = typename BondT<T>::type;
     using T2 = typename Vec2<T>::type;
     size_t off = 0;
+    // packed sublattice search: the elements' entries come first, so that
+    // their LDS addresses fit the 16 bits of a candidate
+    if constexpr (KIND == K_SUB && STAGE)
+        if (d.subf) off = 16 * ((size_t)d.n_sym + 1);
     S.bonds = stage_copy(smem, off, reinterpret_cast<const B *>(d.bonds), d.n_bonds);
     S.sub = SubCtx{d.mintop, d.cand_off, d.cand_list, d.sp, d.tperm, d.n_s, d.m, d.pb};
     S.subf = false;
@@ -212,28 +222,45 @@ __device__ inline void stage(const SectorDesc &d, unsigned char *smem, Staged<T>
             if constexpr (STAGE) {
                 const size_t NV = (size_t)d.n_s << d.m;
                 const size_t ntp = (size_t)d.n_perm * 2 * ((size_t)1 << d.pb);
-                S.sub.mintop = stage_copy(smem, off, d.mintop, NV);
-                S.sub.cand_off = stage_copy(smem, off, d.cand_off, NV + 1);
-                S.sub.cand_list = stage_copy(smem, off, d.cand_list, d.n_cand);
                 if (d.subf) {
-                    // permutation tables at a 128-byte aligned LDS address,
-                    // then the packed (element, block) entries pointing there
                     const uint32_t base =
                         (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+                    S.pk.tab = base + (uint32_t)off;
+                    stage_copy(smem, off, d.pk_tab, NV);
+                    S.pk.list = base + (uint32_t)off;
+                    uint16_t *cand = reinterpret_cast<uint16_t *>(smem + off);
+                    off = a16(off + 2 * (size_t)d.n_pk);
+                    for (uint32_t e = threadIdx.x; e < d.n_pk; e += blockDim.x)
+                        cand[e] = (uint16_t)(d.pk_cand[e] + base);
+                    // permutation tables at a 128-byte aligned LDS address,
+                    // and behind them one whose images are all 2^m: the
+                    // padding element's
                     off += (128u - ((base + (uint32_t)off) & 127u)) & 127u;
                     const uint32_t tpa = base + (uint32_t)off;
-                    S.sub.tperm = stage_copy(smem, off, d.tperm, ntp);
-                    const size_t nsp = (size_t)d.n_sym * d.n_s;
-                    uint32_t *sq = reinterpret_cast<uint32_t *>(smem + off);
-                    off = a16(off + 4 * nsp);
-                    for (size_t e = threadIdx.x; e < nsp; e += blockDim.x) {
-                        const uint32_t w = d.sp[e];
+                    uint16_t *tp = reinterpret_cast<uint16_t *>(smem + off);
+                    const size_t E = (size_t)1 << d.pb;
+                    off = a16(off + 2 * (ntp + 2 * E));
+                    for (size_t e = threadIdx.x; e < ntp + 2 * E; e += blockDim.x)
+                        tp[e] = e < ntp       ? d.tperm[e]
+                                : e < ntp + E ? (uint16_t)(1u << d.m)
+                                              : (uint16_t)0;
+                    // the (element, block) entries: the tables' address or'ed
+                    // with seven times the source block
+                    const size_t nsp = (size_t)d.n_sym * 4;
+                    S.pk.sp = base;
+                    uint32_t *sq = reinterpret_cast<uint32_t *>(smem);
+                    for (size_t e = threadIdx.x; e < nsp + 4; e += blockDim.x) {
+                        const uint32_t w = e < nsp ? d.sp[e] : (uint32_t)ntp << 8;
                         sq[e] = (tpa + 2u * (w >> 8)) | (7u * ((w & 0xFFu) / (uint32_t)d.m));
                     }
-                    S.sub.sp = sq;
-                    S.amask = ~((4u << d.pb) - 1u);
+                    S.pk.amask = ~((4u << d.pb) - 1u);
+                    S.pk.m = d.m;
+                    S.pk.nb = d.pk_nb;
                     S.subf = true;
                 } else {
+                    S.sub.mintop = stage_copy(smem, off, d.mintop, NV);
+                    S.sub.cand_off = stage_copy(smem, off, d.cand_off, NV + 1);
+                    S.sub.cand_list = stage_copy(smem, off, d.cand_list, d.n_cand);
                     S.sub.sp = stage_copy(smem, off, d.sp, (size_t)d.n_sym * d.n_s);
                     S.sub.tperm = stage_copy(smem, off, d.tperm, ntp);
                 }
@@ -283,14 +310,13 @@ __device__ __forceinline__ typename IndexT<W>::type locate(const SectorDesc &d, 
             else
                 aff_search<W>(S.aff, d.n_sym, d.n_sites, t, rep, u, cnt);
         } else if constexpr (KIND == K_SUB && PACKED) {
-            sub_search_packed<W, XR != 2>(S.sub, S.amask, *key, rep, u, cnt);
+            sub_search_packed<W, XR != 2>(S.pk, *key, rep, u, cnt);
         } else if constexpr (KIND == K_SUB) {
             if (S.subf) {
                 if (key)
-                    sub_search_packed<W, XR != 2>(S.sub, S.amask, *key, rep, u, cnt);
+                    sub_search_packed<W, XR != 2>(S.pk, *key, rep, u, cnt);
                 else
-                    sub_search_packed<W, XR != 2>(S.sub, S.amask, sub_key<W>(t, d.m, d.pb), rep,
-                                                  u, cnt);
+                    sub_search_packed<W, XR != 2>(S.pk, sub_key<W>(t, d.m, d.pb), rep, u, cnt);
             } else if (d.n_s == 4)
                 sub_search<W, 4>(S.sub, t, rep, u, cnt);
             else

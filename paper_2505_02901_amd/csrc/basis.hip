@@ -984,6 +984,8 @@ int basis_build_device(xdg_basis_s *b) {
         XDG_RETURN_IF(b->t_candoff.upload(P.sub.cand_off.data(), P.sub.cand_off.size() * 4));
         XDG_RETURN_IF(b->t_candlist.upload(P.sub.cand_list.data(),
                                            std::max<size_t>(2, P.sub.cand_list.size() * 2)));
+        XDG_RETURN_IF(b->t_pktab.upload(P.sub.pk_tab.data(), P.sub.pk_tab.size() * 4));
+        XDG_RETURN_IF(b->t_pkcand.upload(P.sub.pk_cand.data(), P.sub.pk_cand.size() * 2));
     }
     if (P.kind == K_TAB)
         XDG_RETURN_IF(b->t_bytes.upload(P.bytes.tab.data(), P.bytes.tab.size() * 8));
@@ -1074,7 +1076,7 @@ int basis_build_inner(xdg_basis_s *b) {
     const Plan &P = b->plan;
     if (b->dim < 1 || b->dim >= 0x7FFFFFFF || (P.flags & XDG_FLAG_HASH_INDEX)) return XDG_OK;
     if (P.kind != K_TAB &&
-        !(P.kind == K_SUB && !sub_packed_ok(P.sub.n_s, P.sub.m, P.sub.pb)))
+        !(P.kind == K_SUB && !P.sub.packed()))
         return XDG_OK;
     for (int g = 0; g < b->n_sym; ++g)
         if (std::fabs(b->chi[2 * g]) != 1.0 || b->chi[2 * g + 1] != 0.0) return XDG_OK;
@@ -1099,7 +1101,7 @@ int basis_build_inner(xdg_basis_s *b) {
     if (rc == XDG_OK) rc = bad.alloc(sizeof(uint32_t));
     if (rc == XDG_ENOMEM) return XDG_OK;   // no room: the caller's labels serve
     XDG_RETURN_IF(rc);
-    if (in->dim != b->dim || !in->n_rwords) return XDG_OK;
+    if (in->dim != b->dim || !in->n_rwords || !in->plan.sub.packed()) return XDG_OK;
     UserMapArgs A{};
     for (int i = 0; i < b->n_sites; ++i) A.site_bit[i] = (uint8_t)pos[i];
     A.N = b->n_sites;

@@ -62,7 +62,7 @@ int upload_bonds(const xdg_basis_s *b, int n_bonds, const int32_t *sites, const 
     }
     XDG_RETURN_IF(out->d.upload(bd.data(), sizeof(BondD) * std::max(n_bonds, 1)));
     XDG_RETURN_IF(out->f.upload(bf.data(), sizeof(BondF) * std::max(n_bonds, 1)));
-    if (sub && sub_packed_ok(sp.n_s, sp.m, sp.pb)) {
+    if (sub && sp.packed()) {
         std::vector<BondX> bx(std::max(n_bonds, 1), BondX{});
         for (int e = 0; e < n_bonds; ++e) {
             bondx_site((int)bd[e].i, sp.m, sp.pb, bx[e]);

@@ -633,10 +633,21 @@ __device__ __forceinline__ bool sub_is_rep(const SubCtx &C, W s, const double2 *
 // extract of the packed word at w's low five bits and one and-or with w give
 // a table address.  Every candidate's top block is the minimal top, so the
 // three lower image blocks (at most 30 bits) decide as one 32-bit word.
+//
+// The search takes a candidate list in two steps.  Of every candidate only the
+// image's second block is formed (two half-table reads) and the smallest kept
+// with a bit for each candidate reaching it, two candidates a turn; the two
+// lower blocks are formed for those alone.  On the 6x6 lattice at half filling
+// a wave takes 5.5 candidates per bond (the most of any lane) but only 1.6 of
+// them reach the second block's minimum; at quarter filling 21.6 and 2.6.
+// Forming whole images for all candidates took 26 vector instructions each
+// (now 10.5 and, for those reaching it, 23): 6x6 J1-J2, Gamma A1, FP32, 23.8 ->
+// 19.2 ms; 6x6 square, 12 of 36 up, FP64, 3.4 -> 2.3 ms.
 typedef __attribute__((address_space(3))) const uint16_t lds_u16;
+typedef __attribute__((address_space(3))) const uint32_t lds_u32;
 
-// A state's key for the packed search: its four block-table indices
-// e_k = k 2^m + chunk_k and its two packed words.
+// A state's key for the packed search: the byte offsets of its four
+// block-table entries, 4 (k 2^m + chunk_k), and its two packed words.
 struct SubKey {
     uint32_t e[4];
     uint32_t lo2, hi2;
@@ -651,7 +662,7 @@ __device__ __forceinline__ SubKey sub_key(W t, int m, int pb) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const uint32_t c = chunk_of<W>(t, k, m, vmask);
-        K.e[k] = k * V + c;
+        K.e[k] = 4u * (k * V + c);
         K.lo2 |= ((c & (E - 1)) << 1) << (7 * k);
         K.hi2 |= ((E + (c >> pb)) << 1) << (7 * k);
     }
@@ -668,59 +679,86 @@ __device__ __forceinline__ SubKey sub_key_flip(const SubKey &K, const BondX &x) 
     return T;
 }
 
-// C.sp holds the packed (element, block) entries; amask = ~(4E - 1).
+// LDS addresses of the packed tables: SublatticeTables::pk_tab and pk_cand
+// (there the addresses of the elements' entries), and the entries, four words
+// for each element.
+struct PackedCtx {
+    uint32_t tab, list, sp;
+    uint32_t amask;            // ~(4E - 1)
+    int m, nb;
+};
+
 // KEEP_U = false: the element reaching the minimum is not kept (u = 0).
 template <class W, bool KEEP_U = true>
-__device__ __forceinline__ void sub_search_packed(const SubCtx &C, uint32_t amask,
-                                                  const SubKey &K, W &best, int &u, int &cnt) {
+__device__ __forceinline__ void sub_search_packed(const PackedCtx &C, const SubKey &K, W &best,
+                                                  int &u, int &cnt) {
     const int m = C.m;
-    const uint32_t *e = K.e;
-    const uint32_t lo2 = K.lo2, hi2 = K.hi2;
-    uint32_t mv[4];
+    const uint32_t lo2 = K.lo2, hi2 = K.hi2, amask = C.amask;
+    const uint32_t low = (1u << (31 - m)) - 1u;   // a word's bits below its minimal top
+    uint32_t w[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) mv[k] = C.mintop[e[k]];
-    const uint32_t mt = min(min(mv[0], mv[1]), min(mv[2], mv[3]));
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    for (int k = 0; k < 4; ++k) w[k] = *(lds_u32 *)(C.tab + K.e[k]);
+    // the smallest word: the minimal top, and the list of the lowest block
+    // reaching it (lists lie in block order); the second smallest tells
+    // whether another block reaches it too
+    const uint32_t a0 = min(w[0], w[1]), a1 = max(w[0], w[1]);
+    const uint32_t b0 = min(w[2], w[3]), b1 = max(w[2], w[3]);
+    const uint32_t wm = min(a0, b0), second = min(max(a0, b0), min(a1, b1));
     uint32_t bl = 0xFFFFFFFFu, bu = 0x7fffffffu, bc = 0;
-    auto candidate = [&](uint32_t g) {
-        const u32x4 w = *reinterpret_cast<const u32x4 *>(C.sp + 4 * g);
-        uint32_t v[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            // the fields are below 4E: bitop3 table 0xE4 takes wa's bits
-            // under amask and the field's below it
-            const uint32_t wa = w[a];
-            const uint32_t la =
-                __builtin_amdgcn_bitop3_b32(wa, __builtin_amdgcn_ubfe(lo2, wa, 7), amask, 0xE4);
-            const uint32_t ha =
-                __builtin_amdgcn_bitop3_b32(wa, __builtin_amdgcn_ubfe(hi2, wa, 7), amask, 0xE4);
-            // the two halves set disjoint bits: an add keeps the sum in 32 bits
-            v[a] = (uint32_t)*(lds_u16 *)la + (uint32_t)*(lds_u16 *)ha;
-        }
-        const uint32_t img = (((v[2] << m) | v[1]) << m) | v[0];
-        const bool lt = img < bl, eq = img == bl;
-        if constexpr (KEEP_U) bu = lt ? g : bu;
-        bc = lt ? 1u : bc + (eq ? 1u : 0u);
-        bl = lt ? img : bl;
+    // image of one block from its entry: the fields are below 4E, so bitop3
+    // table 0xE4 takes the entry's bits under amask and the field's below it;
+    // the two halves set disjoint bits
+    auto block = [&](uint32_t wa) -> uint32_t {
+        const uint32_t la =
+            __builtin_amdgcn_bitop3_b32(wa, __builtin_amdgcn_ubfe(lo2, wa, 7), amask, 0xE4);
+        const uint32_t ha =
+            __builtin_amdgcn_bitop3_b32(wa, __builtin_amdgcn_ubfe(hi2, wa, 7), amask, 0xE4);
+        return (uint32_t)*(lds_u16 *)la + (uint32_t)*(lds_u16 *)ha;
     };
-    // the list of the lowest block reaching mt (most terms have one such
-    // block): one paired read of its offsets, then one loop
-    const bool h0 = mv[0] == mt, h1 = mv[1] == mt, h2 = mv[2] == mt;
-    const uint32_t ef = h0 ? e[0] : h1 ? e[1] : h2 ? e[2] : e[3];
-    const uint32_t q0 = C.cand_off[ef], n = C.cand_off[ef + 1] - q0;
-    const uint16_t *cl = C.cand_list + q0;
-    for (uint32_t i = 0; i < n; ++i) candidate(cl[i]);
-    // the lists of further blocks reaching mt
-    const int kf = h0 ? 0 : h1 ? 1 : h2 ? 2 : 3;
+    auto list = [&](uint32_t word) {
+        uint32_t p = C.list + 4u * ((word & low) >> C.nb);
+        uint32_t left = word & ((1u << C.nb) - 1u);
+        do {   // 16 pairs at a time (a bit for each candidate, the first one highest)
+            const uint32_t n = min(left, 16u);
+            uint32_t b2 = bl >> (2 * m), mask = 0;
+            for (uint32_t i = 0; i < n; ++i) {
+                const uint32_t e0 = *(lds_u16 *)(p + 4 * i), e1 = *(lds_u16 *)(p + 4 * i + 2);
+                const uint32_t v0 = block(*(lds_u32 *)(e0 + 8));
+                const uint32_t v1 = block(*(lds_u32 *)(e1 + 8));
+                uint32_t mn = min(min(b2, v0), v1);
+                // nothing about mn is derived from v0 and v1 below: one
+                // three-input minimum; v + ~mn is negative where v = mn, and
+                // alignbit shifts its sign into the mask
+                asm("" : "+v"(mn));
+                mask = mn == b2 ? mask : 0u;
+                mask = __builtin_amdgcn_alignbit(mask, v0 + ~mn, 31);
+                mask = __builtin_amdgcn_alignbit(mask, v1 + ~mn, 31);
+                b2 = mn;
+            }
+            const uint32_t pl = p + 4 * n - 64;
+            while (mask) {
+                const uint32_t z = (uint32_t)__builtin_clz(mask);
+                mask ^= 0x80000000u >> z;
+                const uint32_t e = *(lds_u16 *)(pl + 2 * z);
+                const uint32_t w0 = *(lds_u32 *)e, w1 = *(lds_u32 *)(e + 4);
+                const uint32_t img = (((b2 << m) | block(w1)) << m) | block(w0);
+                const bool lt = img < bl, eq = img == bl;
+                if constexpr (KEEP_U) bu = lt ? e : bu;
+                bc = lt ? 1u : bc + (eq ? 1u : 0u);
+                bl = lt ? img : bl;
+            }
+            left -= n;
+            p += 64;
+        } while (left);
+    };
+    list(wm);
+    if (second <= (wm | low)) {
 #pragma unroll
-    for (int k = 1; k < 4; ++k) {
-        if (k > kf && mv[k] == mt) {
-            const uint32_t r1 = C.cand_off[e[k] + 1];
-            for (uint32_t q = C.cand_off[e[k]]; q < r1; ++q) candidate(C.cand_list[q]);
-        }
+        for (int k = 1; k < 4; ++k)
+            if ((w[k] ^ wm) - 1u < low) list(w[k]);   // the same top, another list
     }
-    best = ((W)mt << (3 * m)) | (W)bl;
-    u = KEEP_U ? (int)bu : 0;
+    best = ((W)(wm >> (31 - m)) << (3 * m)) | (W)bl;
+    u = KEEP_U ? (int)((bu - C.sp) >> 4) : 0;
     cnt = (int)bc;
 }
 

@@ -305,6 +305,26 @@ void build_sublattice(int N, int n_sym, const int32_t *perm, int n_s, Sublattice
         T->cand_list.insert(T->cand_list.end(), lists[e].begin(), lists[e].end());
     }
     T->cand_off.back() = (uint32_t)T->cand_list.size();
+    // packed form, where its fields hold everything
+    // (2048: more than the kernels' own shared data before the entries)
+    if (!sub_packed_ok(n_s, m, pb) || 16 * (n_sym + 1) + 2048 > 65536) return;
+    size_t longest = 1, pairs = 0;
+    for (const auto &L : lists) {
+        longest = std::max(longest, (L.size() + 1) / 2);
+        pairs += (L.size() + 1) / 2;
+    }
+    int nb = 1;
+    while (((size_t)1 << nb) <= longest) ++nb;
+    if (nb > 31 - m || pairs >= (size_t)1 << (31 - m - nb)) return;
+    T->pk_nb = nb;
+    for (size_t e = 0; e < lists.size(); ++e) {
+        const auto &L = lists[e];
+        const uint32_t top_bits = L.empty() ? (uint32_t)V : T->mintop[e];
+        T->pk_tab.push_back(top_bits << (31 - m) | (uint32_t)(T->pk_cand.size() / 2) << nb |
+                            (uint32_t)((L.size() + 1) / 2));
+        for (uint16_t g : L) T->pk_cand.push_back((uint16_t)(g * 16));
+        if (L.size() & 1) T->pk_cand.push_back((uint16_t)(n_sym * 16));
+    }
 }
 
 void build_bytes(int N, int n_sym, const int32_t *perm, ByteTables *B) {

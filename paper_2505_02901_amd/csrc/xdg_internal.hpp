@@ -69,6 +69,16 @@ struct SublatticeTables {
     std::vector<uint16_t> mintop;    // [n_s][2^m]
     std::vector<uint32_t> cand_off;  // [n_s * 2^m + 1]
     std::vector<uint16_t> cand_list; // [cand_off.back()]
+    // Packed form (four blocks, see sub_search_packed; empty where it does not
+    // apply): one word per (block, content) holding the minimal top (m + 1
+    // bits; 2^m: no element), the place of its candidate list in pairs and
+    // the list's pairs (pk_nb bits); the lists as byte offsets of the
+    // elements' 16-byte entries, padded to pairs with element n_sym, which no
+    // image beats.
+    std::vector<uint32_t> pk_tab;    // [n_s][2^m]
+    std::vector<uint16_t> pk_cand;
+    int pk_nb = 0;
+    bool packed() const { return !pk_tab.empty(); }
 };
 
 // Generic byte tables: tab[g][c][v] = image bits of byte c of t having value v.
@@ -186,6 +196,7 @@ struct xdg_basis_s {
     // sublattice tables on the device: t_pid = u32 [n_sym][n_s], the offset of
     // the block permutation's tables in t_tperm << 8 | first bit of the source block
     xdg::DevBuf t_pid, t_tperm, t_mintop, t_candoff, t_candlist, t_bytes, t_aff, t_ring;
+    xdg::DevBuf t_pktab, t_pkcand;   // packed form of the sublattice tables
     xdg::DevBuf chi_d;          // double2 [n_sym]
     xdg::DevBuf chi_f;          // float2 [n_sym]
     xdg::DevBuf sqrt_d;         // double [n_sym+1] sqrt(c), then [n_sym+1] 1/sqrt(c)
@@ -276,7 +287,8 @@ __host__ __device__ constexpr bool sub_packed_ok(int n_s, int m, int pb) {
 
 // Per-bond data of the packed sublattice search, in device bond order, read
 // with scalar loads: the two sites as a mask, and the bits that exchanging
-// them flips in a state's packed words and in its four block-table indices.
+// them flips in a state's packed words and in the byte offsets of its four
+// block-table entries.
 struct BondX {
     uint64_t flip;
     uint32_t plo, phi;
@@ -286,7 +298,7 @@ struct BondX {
 inline void bondx_site(int i, int m, int pb, BondX &x) {
     const int q = i / m, p = i - q * m;
     x.flip |= 1ull << i;
-    x.ek[q] |= 1u << p;
+    x.ek[q] |= 4u << p;
     if (p < pb)
         x.plo |= 1u << (7 * q + 1 + p);
     else
