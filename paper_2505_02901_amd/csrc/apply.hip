@@ -156,16 +156,21 @@ int form_of(const xdg_basis_s *b, int dtype, int64_t nvec, Form *f) {
     return XDG_OK;
 }
 
-// Rank-addressed x: row i of x (spr scalars) goes to slot top_rank(reps[i]) of
-// xr (`slot` scalars apart); the other slots hold zeros.
+// Rank-addressed x: row i of x (spr scalars) goes to the slot of reps[i]
+// (block_slot in the packed form, top_rank otherwise) of xr (`slot` scalars apart); the other slots hold zeros.
 template <class W, class T>
 __global__ __launch_bounds__(256) void k_xr_scatter(const W *reps, int64_t dim, int spr, int slot,
                                                    const T *x, T *xr, const uint32_t *rtab,
                                                    RankLayout L, int B, const uint64_t *top,
-                                                   uint64_t slots, const uint32_t *umap) {
+                                                   uint64_t slots, const uint32_t *umap,
+                                                   const uint32_t *xb_ent, const uint32_t *xb_off,
+                                                   const uint2 *xb_top) {
     const int64_t stride = (int64_t)gridDim.x * 256;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < dim; i += stride) {
-        const uint64_t r = top_rank<W>(rtab, L, B, top, reps[i]);
+        const W s = reps[i];
+        const uint64_t r = xb_ent ? block_slot(xb_ent, xb_off, xb_top, B / 3, (uint32_t)(s >> B),
+                                               (uint32_t)s & ((1u << B) - 1u))
+                                  : top_rank<W>(rtab, L, B, top, s);
         if (r >= slots) continue;   // never for a basis state
         if (umap) {                 // relabelled sector: the caller's position and sign
             const uint32_t u = gld(umap + i);
@@ -235,23 +240,27 @@ int xr_prepare(xdg_ham_s *h, const void *x, const Form &f, hipStream_t st, bool 
             hipLaunchKernelGGL((k_xr_scatter<uint64_t, float>), dim3(g), dim3(256), 0, st,
                                b->reps.as<uint64_t>(), b->dim, spr, slot, (const float *)x,
                                h->xr_buf.as<float>(), b->xr_rtab.as<uint32_t>(), b->rank, b->xr_bits, top,
-                               b->xr_slots, umap);
+                               b->xr_slots, umap, b->xb_ent.as<uint32_t>(),
+                               b->xb_off.as<uint32_t>(), b->xb_top.as<uint2>());
         else
             hipLaunchKernelGGL((k_xr_scatter<uint64_t, double>), dim3(g), dim3(256), 0, st,
                                b->reps.as<uint64_t>(), b->dim, spr, slot, (const double *)x,
                                h->xr_buf.as<double>(), b->xr_rtab.as<uint32_t>(), b->rank, b->xr_bits, top,
-                               b->xr_slots, umap);
+                               b->xr_slots, umap, b->xb_ent.as<uint32_t>(),
+                               b->xb_off.as<uint32_t>(), b->xb_top.as<uint2>());
     } else {
         if (f.single)
             hipLaunchKernelGGL((k_xr_scatter<uint32_t, float>), dim3(g), dim3(256), 0, st,
                                b->reps.as<uint32_t>(), b->dim, spr, slot, (const float *)x,
                                h->xr_buf.as<float>(), b->xr_rtab.as<uint32_t>(), b->rank, b->xr_bits, top,
-                               b->xr_slots, umap);
+                               b->xr_slots, umap, b->xb_ent.as<uint32_t>(),
+                               b->xb_off.as<uint32_t>(), b->xb_top.as<uint2>());
         else
             hipLaunchKernelGGL((k_xr_scatter<uint32_t, double>), dim3(g), dim3(256), 0, st,
                                b->reps.as<uint32_t>(), b->dim, spr, slot, (const double *)x,
                                h->xr_buf.as<double>(), b->xr_rtab.as<uint32_t>(), b->rank, b->xr_bits, top,
-                               b->xr_slots, umap);
+                               b->xr_slots, umap, b->xb_ent.as<uint32_t>(),
+                               b->xb_off.as<uint32_t>(), b->xb_top.as<uint2>());
     }
     XDG_TRY_HIP(hipGetLastError());
     return XDG_OK;
@@ -336,7 +345,11 @@ int apply_launch(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, 
     // rank-addressed x: when its tables fit in LDS with the others
     bool xr_on = c.xr && b->xr_slots && b->plan.kind == K_SUB, capturing = false;
     if (xr_on) {
-        A.one.xr = b->xr_top.p;   // the copy is set below; non-null for the LDS size
+        A.one.xr = b->reps.p;     // the copy is set below; non-null for the LDS size
+        A.one.xb_ent = b->xb_ent.as<uint32_t>();
+        A.one.xb_off = b->xb_off.as<uint32_t>();
+        A.one.xb_top = b->xb_top.as<uint2>();
+        A.one.xb_w32 = b->xr_slots <= 0xFFFFFFFFull;
         A.one.xr_top = b->xr_top.as<uint64_t>();
         A.one.xr_top32 = b->xr_top32.as<uint32_t>();
         A.one.xr_slots = b->xr_slots;
@@ -351,6 +364,7 @@ int apply_launch(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, 
             A.one.xr = nullptr;
             A.one.xr_top = nullptr;
             A.one.xr_top32 = nullptr;
+            A.one.xb_ent = nullptr;
         }
     }
     std::unique_lock<std::mutex> xr_lock;

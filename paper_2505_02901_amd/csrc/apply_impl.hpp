@@ -94,6 +94,10 @@ struct SectorDesc {
     int xr_bits;                 // sites below the top block
     const uint32_t *xr_rtab;     // the rank tables' rows for the chunks below it, 4-byte entries
     int xr_rows;                 // rows of xr_rtab
+    // packed form: the slots of block_slot instead (null: the ranks above)
+    const uint32_t *xb_ent, *xb_off;
+    const uint2 *xb_top;
+    int xb_w32;
     // relabelled sector: position in x and y of the orbit of basis state k,
     // bit 31 where its sign differs (sublattice kind only; null: k itself)
     const uint32_t *umap;
@@ -135,12 +139,17 @@ __host__ __device__ inline size_t sub_table_bytes(const SectorDesc &d) {
 __host__ __device__ inline size_t rank_table_bytes(const SectorDesc &d) {
     if (!d.rwords) return 0;
     // the rank-addressed x reads only its 4-byte rows of the chunks below the top block
+    if (d.xr && d.xb_ent) return 0;
     if (d.xr) return ((size_t)d.xr_rows << d.rl.cb) * 4;
     return ((size_t)d.rl.rows << d.rl.cb) * (d.rl.e32 ? 4 : 8);
 }
 
 // bytes of the first-rank table of the rank-addressed x in LDS
 __host__ __device__ inline size_t xr_top_bytes(const SectorDesc &d) {
+    if (d.xb_ent) {   // entries, offsets, tops
+        const size_t m1 = (size_t)d.m + 1;
+        return a16((size_t)4 << d.m) + a16(4 * m1 * m1 * m1) + ((size_t)8 << d.m);
+    }
     return ((size_t)1 << d.m) * (d.xr_top32 ? 4 : 8);
 }
 
@@ -171,6 +180,7 @@ struct Staged {
     SubCtx sub;
     bool subf;             // packed sublattice search
     PackedCtx pk;
+    SlotCtx slot;          // rank-addressed x of a packed sector
     const uint64_t *xr_top;   // first rank of each top block (rank-addressed x)
     const uint32_t *xr_top32; // the same in 4 bytes (xr_w32) at the same place
     bool xr_w32;
@@ -267,7 +277,24 @@ __device__ inline void stage(const SectorDesc &d, unsigned char *smem, Staged<T>
                 // the first-rank table at one LDS address whatever its entry
                 // size (both pointers always address LDS here: LDS reads)
                 unsigned char *tp = smem + off;
-                if (d.xr) {
+                if (d.xr && d.xb_ent) {
+                    const uint32_t base =
+                        (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+                    const uint32_t m1 = (uint32_t)d.m + 1, V = 1u << d.m;
+                    S.slot.ent = base + (uint32_t)off;
+                    stage_copy(smem, off, d.xb_ent, V);
+                    const uint32_t oa = base + (uint32_t)off;
+                    stage_copy(smem, off, d.xb_off, (size_t)m1 * m1 * m1);
+                    S.slot.top = base + (uint32_t)off;
+                    uint2 *lt = reinterpret_cast<uint2 *>(smem + off);
+                    for (uint32_t e = threadIdx.x; e < V; e += blockDim.x) {
+                        const uint2 t = d.xb_top[e];
+                        lt[e] = make_uint2(t.x, t.y + oa);
+                    }
+                    off = a16(off + 8 * (size_t)V);
+                    S.slot.m = d.m;
+                    S.slot.w32 = d.xb_w32 != 0;
+                } else if (d.xr) {
                     if (d.xr_top32)
                         stage_copy(smem, off, d.xr_top32, (size_t)1 << d.m);
                     else
@@ -309,14 +336,13 @@ __device__ __forceinline__ typename IndexT<W>::type locate(const SectorDesc &d, 
                 ring_search<W>(S.ring_gidx, d.ring, d.n_sites, t, rep, u, cnt);
             else
                 aff_search<W>(S.aff, d.n_sym, d.n_sites, t, rep, u, cnt);
-        } else if constexpr (KIND == K_SUB && PACKED) {
-            sub_search_packed<W, XR != 2>(S.pk, *key, rep, u, cnt);
         } else if constexpr (KIND == K_SUB) {
-            if (S.subf) {
-                if (key)
-                    sub_search_packed<W, XR != 2>(S.pk, *key, rep, u, cnt);
-                else
-                    sub_search_packed<W, XR != 2>(S.pk, sub_key<W>(t, d.m, d.pb), rep, u, cnt);
+            if (PACKED || S.subf) {
+                uint32_t top, low;
+                sub_search_packed<XR != 2>(S.pk, key ? *key : sub_key<W>(t, d.m, d.pb), top, low,
+                                           u, cnt);
+                if constexpr (XR != 0) return (I)block_slot_lds(S.slot, top, low);
+                rep = ((W)top << (3 * d.m)) | (W)low;
             } else if (d.n_s == 4)
                 sub_search<W, 4>(S.sub, t, rep, u, cnt);
             else
@@ -326,6 +352,11 @@ __device__ __forceinline__ typename IndexT<W>::type locate(const SectorDesc &d, 
         }
         if constexpr (KIND == K_SUB && XR != 0) {
             // the slot of rep in the rank-addressed x (zeros unless rep is a basis state)
+            if (d.xb_ent) {
+                const int B = 3 * d.m;
+                return (I)block_slot_lds(S.slot, (uint32_t)(rep >> B),
+                                         (uint32_t)rep & ((1u << B) - 1u));
+            }
             const uint32_t *T32 = static_cast<const uint32_t *>(S.rtab);
             const uint64_t r = S.xr_w32
                                    ? top_rank32<W>(T32, d.rl, d.xr_bits, S.xr_top32, rep)
@@ -404,7 +435,10 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
             }
         }
     };
-    bool p_ok = false;   // PIPE: the pending term
+    // PIPE: the pending term.  ALL: every term has a slot (packed form of the
+    // rank-addressed x), so none is tested; the first one pending adds 0 * 0.
+    constexpr bool ALL = PACKED && XR != 0;
+    bool p_ok = ALL;
     A p_ar = 0, p_ai = 0;
     T p_x[NV * C];
 #pragma unroll
@@ -419,7 +453,7 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
         if constexpr (PIPE) {
             // the gather is issued for every term (row 0 when the orbit is
             // not in the block: a valid address, never added)
-            const bool ok = idx >= 0;
+            const bool ok = ALL || idx >= 0;
             A ar = 0, ai = 0;
             if (ok) {
                 const A f = hs * S.sq[cnt];
@@ -433,12 +467,12 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
             }
             // the previous gather (issued one search ago) is added first, so
             // that the new one can land in the same registers
-            if (p_ok) add(p_ar, p_ai, p_x);
+            if (ALL || p_ok) add(p_ar, p_ai, p_x);
             const size_t xb =
                 ((size_t)(ok ? idx : 0) * (XR != 0 ? (int64_t)d.xr_cols : nvec) + v0) * C;
 #pragma unroll
             for (int v = 0; v < NV * C; ++v) p_x[v] = gld(XT + xb + v);
-            p_ok = ok;
+            p_ok = ALL || ok;
             p_ar = ar;
             p_ai = ai;
             return;
@@ -513,8 +547,7 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
                     term(bd, s ^ fl, &kt);
                 }
                 if constexpr (PIPE) {
-                    if (p_ok) add(p_ar, p_ai, p_x);
-                    p_ok = false;
+                    if (ALL || p_ok) add(p_ar, p_ai, p_x);
                 }
                 done = true;
             }
@@ -528,7 +561,7 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
                 term(bd, s ^ ((W(1) << bd.i) | (W(1) << bd.j)), nullptr);
             }
             if constexpr (PIPE) {
-                if (p_ok) add(p_ar, p_ai, p_x);
+                if (ALL || p_ok) add(p_ar, p_ai, p_x);
                 p_ok = false;
             }
         }

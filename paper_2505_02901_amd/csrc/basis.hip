@@ -830,6 +830,46 @@ int build_xr(xdg_basis_s *b, const void *T, const RankLayout &L, W first, W last
         top[c] = acc;
         acc += binomial(B, k);
     }
+    if (S.packed()) {   // the slots of block_slot
+        if (acc >= 1ull << 40) return XDG_OK;
+        std::vector<uint32_t> ent(V), off((size_t)(m + 1) * (m + 1) * (m + 1), 0);
+        std::vector<uint32_t> seen(m + 1, 0);
+        for (uint32_t v = 0; v < V; ++v) {
+            const int p = __builtin_popcount(v);
+            ent[v] = slot_entry(seen[p]++, (uint32_t)binomial(m, p), p, m);
+        }
+        for (int pc = 0; pc <= m; ++pc) {
+            uint64_t o = 0;
+            for (int p2 = 0; p2 <= m; ++p2)
+                for (int p1 = 0; p1 <= m; ++p1) {
+                    const int p0 = b->n_up - pc - p2 - p1;
+                    if (p0 < 0 || p0 > m) continue;
+                    off[((size_t)pc * (m + 1) + p2) * (m + 1) + p1] = (uint32_t)o;
+                    o += binomial(m, p2) * binomial(m, p1) * binomial(m, p0);
+                }
+        }
+        std::vector<uint2> tops(V);
+        for (uint32_t c = 0; c < V; ++c) {
+            const uint64_t t = top[c] == ~0ull ? 0 : top[c];
+            const uint32_t row = 4u * (uint32_t)(__builtin_popcount(c) * (m + 1) * (m + 1));
+            tops[c] = make_uint2((uint32_t)t, (uint32_t)(t >> 32) << 24 | row);
+        }
+        auto in = [&](W s) {
+            const uint32_t c = (uint32_t)((uint64_t)s >> B);
+            return top[c] != ~0ull && block_slot(ent.data(), off.data(), tops.data(), m, c,
+                                                 (uint32_t)s & ((1u << B) - 1u)) < acc;
+        };
+        if (!in(first) || !in(last)) {
+            set_error("internal: a representative lies outside the slot space");
+            return XDG_EINVAL;
+        }
+        XDG_RETURN_IF(b->xb_ent.upload(ent.data(), 4 * ent.size()));
+        XDG_RETURN_IF(b->xb_off.upload(off.data(), 4 * off.size()));
+        XDG_RETURN_IF(b->xb_top.upload(tops.data(), 8 * tops.size()));
+        b->xr_slots = acc;
+        b->xr_bits = B;
+        return XDG_OK;
+    }
     std::vector<uint32_t> low;
     const int rows = L.e32 ? xr_lower_rows(L, static_cast<const uint32_t *>(T), B, b->n_up, low)
                            : xr_lower_rows(L, static_cast<const uint64_t *>(T), B, b->n_up, low);

@@ -189,6 +189,7 @@ struct xdg_basis_s {
     // the slots up to the last basis state and the sites below the top block
     xdg::DevBuf xr_top, xr_top32;   // xr_top32: u32 copy when every first rank fits
     xdg::DevBuf xr_rtab;        // u32 rows of the rank tables for the chunks below the top block
+    xdg::DevBuf xb_ent, xb_off, xb_top;   // packed form: its slots (see block_slot)
     uint64_t xr_slots = 0;      // 0: not available
     int xr_bits = 0;
     int xr_rows = 0;            // rows of xr_rtab
