@@ -119,6 +119,10 @@ SectorDesc make_desc(const xdg_ham_s *h, bool single, const void *x, void *y,
     for (double j : h->jz) jq += 0.25 * j;
     d.jz_quarter = jq;
     d.ring_bonds = bonds.ring;
+    d.u1_adj = b->u1_adj.as<uint32_t>();
+    // far exchanges: Lin's tables (device memory) for a few of them, the rank
+    // tables (LDS) where they are more than an eighth of the bonds
+    d.u1_rank = b->plan.kind == K_U1 && 8 * bonds.far > h->n_bonds;
     d.x = x;
     d.y = y;
     return d;

@@ -59,6 +59,8 @@ struct SectorDesc {
     int n_up;
     const uint32_t *lin;         // Lin tables (U(1))
     int nlo;
+    const uint32_t *u1_adj;      // U(1): C(i, k) [n_sites][n_up + 1]
+    int u1_rank;                 // U(1): stage the rank tables for far exchanges
     int n_sites, n_sym, n_bonds;
     const AffineElem *aff;
     int ring;                    // 0, 1 (all rotations), 2 (and all reflections)
@@ -137,7 +139,7 @@ __host__ __device__ inline size_t sub_table_bytes(const SectorDesc &d) {
 }
 
 __host__ __device__ inline size_t rank_table_bytes(const SectorDesc &d) {
-    if (!d.rwords) return 0;
+    if (!d.rwords && !d.u1_rank) return 0;
     // the rank-addressed x reads only its 4-byte rows of the chunks below the top block
     if (d.xr && d.xb_ent) return 0;
     if (d.xr) return ((size_t)d.xr_rows << d.rl.cb) * 4;
@@ -157,6 +159,8 @@ __host__ __device__ inline size_t xr_top_bytes(const SectorDesc &d) {
 template <class T>
 __host__ __device__ inline size_t stage_bytes(const SectorDesc &d, int kind, int stage_sub) {
     size_t n = a16(sizeof(typename BondT<T>::type) * d.n_bonds);
+    if (kind == K_U1)
+        n += a16(4 * (size_t)d.n_sites * (d.n_up + 1)) + a16(rank_table_bytes(d));
     if (kind != K_U1) {
         n += a16(sizeof(typename Vec2<T>::type) * d.n_sym);
         n += a16(sizeof(T) * 2 * (d.n_sym + 1));
@@ -177,6 +181,7 @@ struct Staged {
     const AffineElem *aff;
     const int16_t *ring_gidx;
     const void *rtab;
+    const uint32_t *adj;   // U(1): see process_row_u1
     SubCtx sub;
     bool subf;             // packed sublattice search
     PackedCtx pk;
@@ -212,6 +217,11 @@ __device__ inline void stage(const SectorDesc &d, unsigned char *smem, Staged<T>
     S.xr_top = d.xr_top;
     S.xr_top32 = d.xr_top32;
     S.xr_w32 = d.xr_top32 != nullptr;
+    if constexpr (KIND == K_U1) {
+        S.adj = stage_copy(smem, off, d.u1_adj, (size_t)d.n_sites * (d.n_up + 1));
+        S.rtab = stage_copy(smem, off, reinterpret_cast<const uint32_t *>(d.rtab),
+                            rank_table_bytes(d) / 4);
+    }
     if constexpr (KIND != K_U1) {
         S.chi = stage_copy(smem, off, reinterpret_cast<const T2 *>(d.chi), d.n_sym);
         const T *ls = stage_copy(smem, off, reinterpret_cast<const T *>(d.sqrtt), 2 * (d.n_sym + 1));
@@ -398,11 +408,94 @@ __device__ __forceinline__ int64_t user_pos(const SectorDesc &d, int64_t k, A &f
 // exactly 1).  PIPE: each term's gather is added at the next term of the row
 // (or after its last bond), so that its latency overlaps the next search;
 // the same fused multiply-adds in the same order.
+// A row of a block without a group.  All lanes take the same bond, whose data
+// are scalars: neighbouring rows agree in their upper sites, so most of a
+// wave's gathers are consecutive.  Exchanging sites i and i + 1 moves the
+// position by C(i, k), k the up spins below i (the colex rank's Pascal step),
+// read from LDS; far exchanges take the rank of the new state.  The loads of
+// U bonds are in flight together.  Walking each lane's own bonds with two Lin
+// table reads before every gather kept the vector memory units busy with 64
+// separate lines an instruction (ring N = 28, 40 M rows, FP64: 1.87 ms).
+template <class W, class T, class A, int NV>
+__device__ __forceinline__ void process_row_u1(const SectorDesc &d, const Staged<A> &S,
+                                               int64_t row, int64_t nvec, int v0) {
+    using B = typename BondT<A>::type;
+    constexpr int U = NV <= 2 ? 4 : NV <= 4 ? 2 : 1;
+    const W s = gld(reinterpret_cast<const W *>(d.reps) + row);
+    const W pairs = s ^ (s >> 1);   // bit i: sites i and i + 1 differ
+    const uint32_t r32 = (uint32_t)row;   // positions are below 2^32
+    const T *X = reinterpret_cast<const T *>(d.x) + v0;
+    T *Y = reinterpret_cast<T *>(d.y);
+    const int nb = d.n_bonds;
+    const uint32_t stride = (uint32_t)d.n_up + 1u, cols = (uint32_t)nvec;
+    A junq = 0, acc[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) acc[v] = 0;
+    for (int b0 = 0; b0 < nb; b0 += U) {
+        bool off[U];
+        A h[U];
+        T xv[U][NV];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            off[k] = false;
+            h[k] = 0;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) xv[k][v] = T(0);
+            if (b0 + k >= nb) continue;
+            const B bd = sld(reinterpret_cast<const B *>(d.bonds) + b0 + k);
+            const uint32_t lo = bd.i < bd.j ? bd.i : bd.j, hi = bd.i < bd.j ? bd.j : bd.i;
+            h[k] = bd.h;
+            const W bit = W(1) << lo;
+            uint32_t at;
+            if (hi == lo + 1) {
+                off[k] = (pairs & bit) != 0;
+                const W under = s & (bit - 1);
+                const uint32_t below = (uint32_t)(sizeof(W) == 4 ? __popc((uint32_t)under)
+                                                                 : __popcll((uint64_t)under));
+                const uint32_t move = S.adj[lo * stride + below];
+                // up if the spin at lo is: row + move, else row - move
+                const uint32_t neg =
+                    sizeof(W) == 4 ? (uint32_t)__builtin_amdgcn_sbfe((int)~(uint32_t)s, lo, 1)
+                                   : ((s & bit) ? 0u : ~0u);
+                at = (move ^ neg) + (r32 - neg);
+            } else {
+                const W mask = bit | (W(1) << hi), both = s & mask;
+                off[k] = both != 0 && both != mask;
+                at = r32;
+                if (off[k]) {
+                    if (d.u1_rank) {
+                        at = (uint32_t)colex_rank<W>(S.rtab, d.rl, s ^ mask);
+                    } else {
+                        int u, cnt;
+                        at = (uint32_t)locate<W, K_U1, A>(d, S, s ^ mask, u, cnt);
+                    }
+                }
+            }
+            at = off[k] ? at : r32;   // spins equal: the own row is read and not added
+            junq = fmadd<A>(off[k] ? A(1) : A(0), bd.jz, junq);
+            const T *q = X + (uint64_t)at * cols;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) xv[k][v] = gld(q + v);
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+                acc[v] = fmadd<A>(h[k], off[k] ? (A)xv[k][v] : A(0), acc[v]);
+    }
+    const size_t base = (size_t)row * nvec + v0;
+    const A diag = (A)d.jz_quarter - A(0.5) * junq;
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+        gst(Y + base + v, (T)fmadd<A>(diag, (A)gld(X + (size_t)row * nvec + v), acc[v]));
+}
+
 // PACKED: the block runs the packed sublattice search with its bond records.
 template <class W, int KIND, class T, class A, bool CPLX, int NV, int XR = 0,
           bool PIPE = false, bool PACKED = false>
 __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A> &S, int64_t row,
                                             int64_t nvec, int v0) {
+    static_assert(KIND != K_U1, "process_row_u1");
     using B = typename BondT<A>::type;
     constexpr int C = CPLX ? 2 : 1;
     const W s = gld(reinterpret_cast<const W *>(d.reps) + row);
@@ -419,8 +512,7 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
     A acc[NV * C];
 #pragma unroll
     for (int v = 0; v < NV * C; ++v) acc[v] = 0;
-    A rn = A(1);
-    if constexpr (KIND != K_U1) rn = S.rsq[gld(d.stab + row)];
+    A rn = S.rsq[gld(d.stab + row)];
     // explicit fused multiply-adds: a complex kernel on a block with real
     // characters (ai = 0) rounds exactly like the real kernel
     auto add = [&](A ar, A ai, const T *xv) {
@@ -478,13 +570,11 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
             return;
         }
         if (idx < 0) return;
-        A ar = hs, ai = 0;
-        if constexpr (KIND != K_U1) {
-            const A f = hs * S.sq[cnt];   // times 1/sqrt|Stab r| once per row
-            const auto c = S.chi[u];
-            ar = f * c.x;
-            if constexpr (CPLX) ai = f * c.y;
-        }
+        const A f = hs * S.sq[cnt];   // times 1/sqrt|Stab r| once per row
+        const auto c = S.chi[u];
+        const A ar = f * c.x;
+        A ai = 0;
+        if constexpr (CPLX) ai = f * c.y;
         // 32-bit states: positions below 2^31, one 32 x 32 -> 64-bit multiply-add
         const size_t xb = sizeof(W) == 4
                               ? (uint64_t)(uint32_t)idx * (uint32_t)(nvec * C) + (uint64_t)(v0 * C)
@@ -502,7 +592,7 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
             }
         }
     };
-    if constexpr (KIND == K_AFF || KIND == K_U1) {
+    if constexpr (KIND == K_AFF) {
         // Cheap searches: per group of 32 bonds, a mask of the bonds with
         // unequal spins, walked lowest first (the order of the plain bond
         // loop), so that a wave iterates over its lanes' active bonds only.
@@ -575,8 +665,7 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
     const A diag = (A)d.jz_quarter - A(0.5) * junq;
 #pragma unroll
     for (int v = 0; v < NV * C; ++v) {
-        const A off = KIND != K_U1 ? rn * acc[v] : acc[v];
-        gst(Y + base + v, (T)fmadd<A>(diag, (A)gld(X + base + v), off));
+        gst(Y + base + v, (T)fmadd<A>(diag, (A)gld(X + base + v), rn * acc[v]));
     }
 }
 
@@ -876,6 +965,9 @@ __device__ __forceinline__ void process_range(const SectorDesc &d, const Staged<
             process_window<W, KIND, T, A, CPLX, NV>(d, S, w0, r1, nvec, v0);
     } else {
         for (int64_t row = r0 + first; row < r1; row += stride)
+            if constexpr (KIND == K_U1)
+                process_row_u1<W, T, A, NV>(d, S, row, nvec, v0);
+            else
             process_row<W, KIND, T, A, CPLX, NV, XR, PIPE, LOOP == LOOP_PACKED>(d, S, row, nvec, v0);
     }
 }

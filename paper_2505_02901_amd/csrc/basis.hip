@@ -564,7 +564,7 @@ void enum_segments(const xdg_basis_s *b, std::vector<EnumSeg> *segs, int *bits, 
 }
 
 template <class W>
-int enumerate(xdg_basis_s *b, DevBuf &binom_d) {
+int enumerate(xdg_basis_s *b, const std::vector<uint64_t> &binom) {
     const int kind = b->plan.kind;
     EnumArgs<W> A{};
     std::vector<EnumSeg> segs;
@@ -574,14 +574,18 @@ int enumerate(xdg_basis_s *b, DevBuf &binom_d) {
         b->dim = 0;
         return XDG_OK;
     }
-    DevBuf segs_d;
-    XDG_RETURN_IF(segs_d.upload(segs.data(), segs.size() * sizeof(EnumSeg)));
-    A.segs = segs_d.as<EnumSeg>();
+    DevBuf consts;
+    DevView segs_v, binom_v;
+    UploadArena ar;
+    ar.add(segs_v, segs.data(), segs.size() * sizeof(EnumSeg));
+    ar.add(binom_v, binom.data(), binom.size() * 8);
+    XDG_RETURN_IF(ar.commit(consts));
+    A.segs = segs_v.as<EnumSeg>();
     A.n_seg = (int)segs.size() - 1;
     A.N = b->n_sites;
     A.n_sym = b->n_sym;
     A.total = total;
-    A.binom = binom_d.as<uint64_t>();
+    A.binom = binom_v.as<uint64_t>();
     A.chi = b->chi_d.as<double2>();
     A.aff = b->t_aff.as<AffineElem>();
     A.bytetab = b->t_bytes.as<uint64_t>();
@@ -647,31 +651,28 @@ int enumerate(xdg_basis_s *b, DevBuf &binom_d) {
             XDG_TRY_HIP(hipFuncSetAttribute((const void *)f,
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
 
-    DevBuf counts, offsets, tiles, tot, keep;
+    DevBuf temp;
     uint64_t dim;
     if (kind == K_U1) {
         dim = total;
     } else {
-        XDG_RETURN_IF(counts.alloc(sizeof(uint32_t) * A.n_chunks));
-        XDG_RETURN_IF(offsets.alloc(sizeof(uint64_t) * A.n_chunks));
-        if (kind != K_TAB) XDG_RETURN_IF(keep.alloc(4 * ((cl + 31) / 32) * A.n_chunks));
+        // one allocation: total, tile sums, offsets, counts, kept bits
         const uint64_t n_tiles = (A.n_chunks + 1023) / 1024;
-        XDG_RETURN_IF(tiles.alloc(sizeof(uint64_t) * n_tiles));
-        XDG_RETURN_IF(tot.alloc(sizeof(uint64_t)));
-        A.counts = counts.as<uint32_t>();
-        A.keep = keep.as<uint32_t>();
+        const uint64_t keep_words = kind == K_TAB ? 0 : (cl + 31) / 32 * A.n_chunks;
+        XDG_RETURN_IF(temp.alloc(8 * (1 + n_tiles + A.n_chunks) + 4 * (A.n_chunks + keep_words)));
+        uint64_t *tot = temp.as<uint64_t>(), *tiles = tot + 1, *offsets = tiles + n_tiles;
+        A.counts = reinterpret_cast<uint32_t *>(offsets + A.n_chunks);
+        A.keep = keep_words ? A.counts + A.n_chunks : nullptr;
         hipLaunchKernelGGL(kcount, dim3(grid), dim3(block), lds, 0, A);
         XDG_TRY_HIP(hipGetLastError());
         hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)n_tiles), dim3(1024), 0, 0,
-                           counts.as<uint32_t>(), A.n_chunks, tiles.as<uint64_t>());
-        hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, 0, tiles.as<uint64_t>(),
-                           n_tiles, tot.as<uint64_t>());
+                           A.counts, A.n_chunks, tiles);
+        hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, 0, tiles, n_tiles, tot);
         hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)n_tiles), dim3(1024), 0, 0,
-                           counts.as<uint32_t>(), A.n_chunks, tiles.as<uint64_t>(),
-                           offsets.as<uint64_t>());
+                           A.counts, A.n_chunks, tiles, offsets);
         XDG_TRY_HIP(hipGetLastError());
-        XDG_RETURN_IF(copy_d2h(&dim, tot.p, sizeof dim, nullptr));
-        A.offsets = offsets.as<uint64_t>();
+        XDG_RETURN_IF(copy_d2h(&dim, tot, sizeof dim, nullptr));
+        A.offsets = offsets;
     }
     if (dim >= 0xFFFFFFFFull) {
         set_error("block dimension %llu needs 64-bit indices (limit 2^32 - 1)",
@@ -863,9 +864,11 @@ int build_xr(xdg_basis_s *b, const void *T, const RankLayout &L, W first, W last
             set_error("internal: a representative lies outside the slot space");
             return XDG_EINVAL;
         }
-        XDG_RETURN_IF(b->xb_ent.upload(ent.data(), 4 * ent.size()));
-        XDG_RETURN_IF(b->xb_off.upload(off.data(), 4 * off.size()));
-        XDG_RETURN_IF(b->xb_top.upload(tops.data(), 8 * tops.size()));
+        UploadArena ar;
+        ar.add(b->xb_ent, ent.data(), 4 * ent.size());
+        ar.add(b->xb_off, off.data(), 4 * off.size());
+        ar.add(b->xb_top, tops.data(), 8 * tops.size());
+        XDG_RETURN_IF(ar.commit(b->xb_buf));
         b->xr_slots = acc;
         b->xr_bits = B;
         return XDG_OK;
@@ -923,7 +926,9 @@ int build_rank(xdg_basis_s *b) {
         set_error("internal: colex chunk tables disagree with the colex rank");
         return XDG_EINVAL;
     }
-    XDG_RETURN_IF(b->rtab.upload(T, tbytes));
+    UploadArena ar;
+    ar.add(b->rtab, T, tbytes);
+    XDG_RETURN_IF(ar.commit(b->rank_buf));
     XDG_RETURN_IF(b->rwords.alloc(8 * n_words));
     XDG_TRY_HIP(hipMemset(b->rwords.p, 0, 8 * n_words));
     const int block = 256;
@@ -967,7 +972,27 @@ int build_lin(xdg_basis_s *b) {
     }
     b->lin_nlo = nlo;
     b->lin_nhi = nhi;
-    return b->lin.upload(t.data(), t.size() * sizeof(uint32_t));
+    // for the products: position changes of neighbouring sites' exchanges, and
+    // the chunk tables of the colex rank, which is the position
+    std::vector<uint32_t> adj((size_t)N * (n + 1));
+    for (int i = 0; i < N; ++i)
+        for (int k = 0; k <= n; ++k)
+            adj[(size_t)i * (n + 1) + k] =
+                (uint32_t)std::min<uint64_t>(binomial(i, k), 0xFFFFFFFFull);
+    UploadArena ar;
+    ar.add(b->lin, t.data(), t.size() * sizeof(uint32_t));
+    ar.add(b->u1_adj, adj.data(), adj.size() * 4);
+    b->rank = rank_layout(N, n, b->wide, (uint64_t)b->dim - 1);
+    std::vector<uint32_t> T32;
+    std::vector<uint64_t> T64;
+    if (b->rank.e32) {
+        rank_tables<uint32_t>(N, n, b->rank, T32);
+        ar.add(b->rtab, T32.data(), T32.size() * 4);
+    } else {
+        rank_tables<uint64_t>(N, n, b->rank, T64);
+        ar.add(b->rtab, T64.data(), T64.size() * 8);
+    }
+    return ar.commit(b->tables);
 }
 
 }  // namespace
@@ -976,17 +1001,15 @@ int basis_build_device(xdg_basis_s *b) {
     std::vector<uint64_t> bt(65 * 65);
     for (int a = 0; a <= 64; ++a)
         for (int c = 0; c <= 64; ++c) bt[a * 65 + c] = binomial(a, c);
-    DevBuf binom_d;
-    XDG_RETURN_IF(binom_d.upload(bt.data(), bt.size() * 8));
-
+    UploadArena ar;
     const Plan &P = b->plan;
     if (b->n_sym) {
-        XDG_RETURN_IF(b->chi_d.upload(b->chi.data(), b->chi.size() * sizeof(double)));
+        ar.add(b->chi_d, b->chi.data(), b->chi.size() * sizeof(double));
         b->chi_trivial = true;
         for (int g = 0; g < b->n_sym; ++g)
             b->chi_trivial &= b->chi[2 * g] == 1.0 && b->chi[2 * g + 1] == 0.0;
         std::vector<float> cf(b->chi.begin(), b->chi.end());
-        XDG_RETURN_IF(b->chi_f.upload(cf.data(), cf.size() * sizeof(float)));
+        ar.add(b->chi_f, cf.data(), cf.size() * sizeof(float));
         std::vector<double> sq(2 * (b->n_sym + 1));
         std::vector<float> sqf(2 * (b->n_sym + 1));
         for (int c = 0; c <= b->n_sym; ++c) {
@@ -995,13 +1018,13 @@ int basis_build_device(xdg_basis_s *b) {
             sqf[c] = (float)sq[c];
             sqf[b->n_sym + 1 + c] = (float)sq[b->n_sym + 1 + c];
         }
-        XDG_RETURN_IF(b->sqrt_d.upload(sq.data(), sq.size() * sizeof(double)));
-        XDG_RETURN_IF(b->sqrt_f.upload(sqf.data(), sqf.size() * sizeof(float)));
+        ar.add(b->sqrt_d, sq.data(), sq.size() * sizeof(double));
+        ar.add(b->sqrt_f, sqf.data(), sqf.size() * sizeof(float));
     }
     if (P.kind == K_AFF) {
-        XDG_RETURN_IF(b->t_aff.upload(P.aff.data(), P.aff.size() * sizeof(AffineElem)));
+        ar.add(b->t_aff, P.aff.data(), P.aff.size() * sizeof(AffineElem));
         if (P.ring)
-            XDG_RETURN_IF(b->t_ring.upload(P.ring_gidx.data(), P.ring_gidx.size() * 2));
+            ar.add(b->t_ring, P.ring_gidx.data(), P.ring_gidx.size() * 2);
     }
     if (P.kind == K_SUB) {
         // device form, one word per (element, block): the offset of the block
@@ -1018,22 +1041,24 @@ int basis_build_device(xdg_basis_s *b) {
             }
             sp[e] = (uint32_t)(to << 8) | so;
         }
-        XDG_RETURN_IF(b->t_pid.upload(sp.data(), sp.size() * 4));
-        XDG_RETURN_IF(b->t_tperm.upload(P.sub.tperm.data(), P.sub.tperm.size() * 2));
-        XDG_RETURN_IF(b->t_mintop.upload(P.sub.mintop.data(), P.sub.mintop.size() * 2));
-        XDG_RETURN_IF(b->t_candoff.upload(P.sub.cand_off.data(), P.sub.cand_off.size() * 4));
-        XDG_RETURN_IF(b->t_candlist.upload(P.sub.cand_list.data(),
-                                           std::max<size_t>(2, P.sub.cand_list.size() * 2)));
-        XDG_RETURN_IF(b->t_pktab.upload(P.sub.pk_tab.data(), P.sub.pk_tab.size() * 4));
-        XDG_RETURN_IF(b->t_pkcand.upload(P.sub.pk_cand.data(), P.sub.pk_cand.size() * 2));
+        ar.add(b->t_pid, sp.data(), sp.size() * 4);
+        ar.add(b->t_tperm, P.sub.tperm.data(), P.sub.tperm.size() * 2);
+        ar.add(b->t_mintop, P.sub.mintop.data(), P.sub.mintop.size() * 2);
+        ar.add(b->t_candoff, P.sub.cand_off.data(), P.sub.cand_off.size() * 4);
+        ar.add(b->t_candlist, P.sub.cand_list.data(),
+                                           std::max<size_t>(2, P.sub.cand_list.size() * 2));
+        ar.add(b->t_pktab, P.sub.pk_tab.data(), P.sub.pk_tab.size() * 4);
+        ar.add(b->t_pkcand, P.sub.pk_cand.data(), P.sub.pk_cand.size() * 2);
     }
     if (P.kind == K_TAB)
-        XDG_RETURN_IF(b->t_bytes.upload(P.bytes.tab.data(), P.bytes.tab.size() * 8));
+        ar.add(b->t_bytes, P.bytes.tab.data(), P.bytes.tab.size() * 8);
+
+    if (b->n_sym) XDG_RETURN_IF(ar.commit(b->tables));
 
     if (b->wide) {
-        XDG_RETURN_IF(enumerate<uint64_t>(b, binom_d));
+        XDG_RETURN_IF(enumerate<uint64_t>(b, bt));
     } else {
-        XDG_RETURN_IF(enumerate<uint32_t>(b, binom_d));
+        XDG_RETURN_IF(enumerate<uint32_t>(b, bt));
     }
     if (P.kind == K_U1) {
         XDG_RETURN_IF(build_lin(b));

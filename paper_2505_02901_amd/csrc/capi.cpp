@@ -70,6 +70,8 @@ int upload_bonds(const xdg_basis_s *b, int n_bonds, const int32_t *sites, const 
         }
         XDG_RETURN_IF(out->x.upload(bx.data(), sizeof(BondX) * bx.size()));
     }
+    out->far = 0;
+    for (int i = 0; i < n_bonds; ++i) out->far += std::abs(sites[2 * i] - sites[2 * i + 1]) != 1;
     out->ring = n_bonds == b->n_sites;
     for (int i = 0; i < n_bonds && out->ring; ++i) {
         const int p = sites[2 * i], q = sites[2 * i + 1], r = (i + 1) % b->n_sites;

@@ -10,6 +10,7 @@
 #include <mutex>
 #include <string>
 #include <tuple>
+#include <utility>
 #include <vector>
 
 #include "xdg.h"
@@ -48,6 +49,33 @@ struct DevBuf {
     int alloc(size_t n);                      // XDG_OK / XDG_ENOMEM
     int upload(const void *host, size_t n);   // alloc + copy
     template <class T> T *as() const { return static_cast<T *>(p); }
+};
+
+// A part of a DevBuf.
+struct DevView {
+    void *p = nullptr;
+    size_t bytes = 0;
+    template <class T> T *as() const { return static_cast<T *>(p); }
+};
+
+// Several host arrays uploaded as one: an allocation and a copy with its wait
+// cost about 25 us each, whatever the size.
+struct UploadArena {
+    std::vector<char> host;
+    std::vector<std::pair<DevView *, size_t>> parts;   // view, offset
+    void add(DevView &v, const void *src, size_t n) {
+        host.resize((host.size() + 255) & ~(size_t)255);
+        parts.push_back({&v, host.size()});
+        v.bytes = n;
+        const char *c = static_cast<const char *>(src);
+        host.insert(host.end(), c, c + n);
+    }
+    int commit(DevBuf &buf) {
+        XDG_RETURN_IF(buf.upload(host.data(), host.size()));
+        for (auto &q : parts)
+            q.first->p = q.first->bytes ? static_cast<char *>(buf.p) + q.second : nullptr;
+        return XDG_OK;
+    }
 };
 
 // ------------------------------------------------------- search tables --
@@ -177,31 +205,35 @@ struct xdg_basis_s {
     xdg::DevBuf stab;           // u16 [dim]  |Stab(s)|
     xdg::DevBuf hash;           // 64-byte lines
     xdg::HashIndex hidx;
-    xdg::DevBuf lin;            // u32 [2^nlo + 2^nhi] Lin tables (U(1))
     // rank index (symmetric blocks): uint2 {count, bits} per 32 colex ranks,
     // and the chunk tables of the colex rank (u64 [nc][n_up + 1][2^cb])
     xdg::DevBuf rwords;
     uint64_t n_rwords = 0;      // 0: the hash index is used
-    xdg::DevBuf rtab;
+    xdg::DevView rtab;
+    xdg::DevBuf rank_buf;       // holds rtab
     xdg::RankLayout rank{};     // layout of rtab (chunks, entry size, row bases)
     // rank-addressed vectors (sublattice coding, see top_rank): first rank of
     // each top block (u64 [2^m], ~0 for a block that is never a minimal top),
     // the slots up to the last basis state and the sites below the top block
     xdg::DevBuf xr_top, xr_top32;   // xr_top32: u32 copy when every first rank fits
     xdg::DevBuf xr_rtab;        // u32 rows of the rank tables for the chunks below the top block
-    xdg::DevBuf xb_ent, xb_off, xb_top;   // packed form: its slots (see block_slot)
+    xdg::DevView xb_ent, xb_off, xb_top;  // packed form: its slots (see block_slot)
+    xdg::DevBuf xb_buf;         // holds them
     uint64_t xr_slots = 0;      // 0: not available
     int xr_bits = 0;
     int xr_rows = 0;            // rows of xr_rtab
     int lin_nlo = 0, lin_nhi = 0;
+    xdg::DevView lin;           // u32 [2^nlo + 2^nhi] Lin tables (U(1))
+    xdg::DevView u1_adj;        // U(1): u32 C(i, k), i < n_sites, k <= n_up (saturated)
+    xdg::DevBuf tables;         // holds the views of this struct
     // sublattice tables on the device: t_pid = u32 [n_sym][n_s], the offset of
     // the block permutation's tables in t_tperm << 8 | first bit of the source block
-    xdg::DevBuf t_pid, t_tperm, t_mintop, t_candoff, t_candlist, t_bytes, t_aff, t_ring;
-    xdg::DevBuf t_pktab, t_pkcand;   // packed form of the sublattice tables
-    xdg::DevBuf chi_d;          // double2 [n_sym]
-    xdg::DevBuf chi_f;          // float2 [n_sym]
-    xdg::DevBuf sqrt_d;         // double [n_sym+1] sqrt(c), then [n_sym+1] 1/sqrt(c)
-    xdg::DevBuf sqrt_f;         // float, same layout
+    xdg::DevView t_pid, t_tperm, t_mintop, t_candoff, t_candlist, t_bytes, t_aff, t_ring;
+    xdg::DevView t_pktab, t_pkcand;   // packed form of the sublattice tables
+    xdg::DevView chi_d;          // double2 [n_sym]
+    xdg::DevView chi_f;          // float2 [n_sym]
+    xdg::DevView sqrt_d;         // double [n_sym+1] sqrt(c), then [n_sym+1] 1/sqrt(c)
+    xdg::DevView sqrt_f;         // float, same layout
     xdg::DeviceSearch dsearch;
     // The same sector in site labels that suit the packed sublattice search,
     // for the products with H (see basis_build_inner): its own
@@ -243,6 +275,7 @@ struct BondSet {
     DevBuf f;      // BondF [n_bonds]
     DevBuf x;      // BondX [n_bonds] (packed sublattice search only)
     int ring = 0;  // 1: n_bonds = n_sites and bond b joins sites b and b + 1 mod N
+    int far = 0;   // bonds whose sites are not neighbouring numbers
 };
 }  // namespace xdg
 

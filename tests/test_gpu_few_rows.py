@@ -80,3 +80,29 @@ def test_batches(X, nvec):
             z = torch.empty_like(x)
             X.xdg_apply_with_config(h.handle, x, z)
             assert torch.equal(y, z)
+
+
+@pytest.mark.parametrize("name", ["chain", "open", "square", "pairs", "wide", "wide_pairs", "one"])
+def test_blocks_without_a_group(X, name):
+    """neighbouring and far exchanges, one and several vectors, 32 bits and more"""
+    def plain(m):
+        return W.Model(m.name, m.n_sites, m.n_up, m.sites, m.jz, 0.3 + m.jxy)
+    m = {"chain": lambda: plain(W.chain_model(13, n_up=5)),
+         "open": lambda: W.Model("open", 11, 6, *W.chain_bonds(11, 1.0, 0.4, periodic=False)),
+         "square": lambda: plain(W.torus_model((4, 0), (0, 4), 1.0, 0.5, "A1", n_up=7)),
+         "pairs": lambda: plain(long_range(10)), "wide": lambda: plain(W.chain_model(33, n_up=3)),
+         "wide_pairs": lambda: plain(W.torus_model((6, 0), (0, 6), 1.0, 0.5, "A1", n_up=3)),
+         "one": lambda: plain(W.chain_model(5, n_up=5))}[name]()
+    b = X.Basis.from_model(m)
+    H = X.Hamiltonian.from_model(b, m)
+    basis = oracle.basis(m)
+    for dt in (torch.float32, torch.float64, torch.complex128):
+        for nvec in (1, 2, 5):
+            x = torch.randn(b.dim, nvec, dtype=dt, device="cuda")
+            y, z = torch.full_like(x, 3.0), torch.full_like(x, 4.0)
+            H.apply(x, y)
+            X.xdg_apply_with_config(H.handle, x, z, nv=1, grid=2)
+            assert torch.equal(y, z), (name, dt, nvec)
+            want = oracle.apply(m, basis, x.cpu().numpy())
+            tol = 2e-6 if dt == torch.float32 else 1e-12
+            assert np.max(np.abs(y.cpu().numpy() - want)) <= tol * max(np.max(np.abs(want)), 1e-3)
