@@ -120,9 +120,11 @@ SectorDesc make_desc(const xdg_ham_s *h, bool single, const void *x, void *y,
     d.jz_quarter = jq;
     d.ring_bonds = bonds.ring;
     d.u1_adj = b->u1_adj.as<uint32_t>();
-    // far exchanges: Lin's tables (device memory) for a few of them, the rank
-    // tables (LDS) where they are more than an eighth of the bonds
-    d.u1_rank = b->plan.kind == K_U1 && 8 * bonds.far > h->n_bonds;
+    if (h->u1_rtab.p) {
+        d.u1_rank = 1;
+        d.rtab = h->u1_rtab.p;
+        d.rl = h->u1_rank;
+    }
     d.x = x;
     d.y = y;
     return d;

@@ -972,8 +972,7 @@ int build_lin(xdg_basis_s *b) {
     }
     b->lin_nlo = nlo;
     b->lin_nhi = nhi;
-    // for the products: position changes of neighbouring sites' exchanges, and
-    // the chunk tables of the colex rank, which is the position
+    // for the products: position changes of neighbouring sites' exchanges
     std::vector<uint32_t> adj((size_t)N * (n + 1));
     for (int i = 0; i < N; ++i)
         for (int k = 0; k <= n; ++k)
@@ -982,16 +981,6 @@ int build_lin(xdg_basis_s *b) {
     UploadArena ar;
     ar.add(b->lin, t.data(), t.size() * sizeof(uint32_t));
     ar.add(b->u1_adj, adj.data(), adj.size() * 4);
-    b->rank = rank_layout(N, n, b->wide, (uint64_t)b->dim - 1);
-    std::vector<uint32_t> T32;
-    std::vector<uint64_t> T64;
-    if (b->rank.e32) {
-        rank_tables<uint32_t>(N, n, b->rank, T32);
-        ar.add(b->rtab, T32.data(), T32.size() * 4);
-    } else {
-        rank_tables<uint64_t>(N, n, b->rank, T64);
-        ar.add(b->rtab, T64.data(), T64.size() * 8);
-    }
     return ar.commit(b->tables);
 }
 
@@ -1207,6 +1196,19 @@ int basis_build_inner(xdg_basis_s *b) {
     b->inner_pos = std::move(pos);
     b->inner = std::move(in);
     return XDG_OK;
+}
+
+// Chunk tables of the colex rank of a block without a group (its positions).
+int u1_rank_tables(const xdg_basis_s *b, DevBuf *tab, RankLayout *L) {
+    *L = rank_layout(b->n_sites, b->n_up, b->wide, (uint64_t)b->dim - 1);
+    if (L->e32) {
+        std::vector<uint32_t> T;
+        rank_tables<uint32_t>(b->n_sites, b->n_up, *L, T);
+        return tab->upload(T.data(), T.size() * 4);
+    }
+    std::vector<uint64_t> T;
+    rank_tables<uint64_t>(b->n_sites, b->n_up, *L, T);
+    return tab->upload(T.data(), T.size() * 8);
 }
 
 int basis_lookup(xdg_basis_s *b, const uint64_t *d_states, int64_t n, int64_t *d_idx,

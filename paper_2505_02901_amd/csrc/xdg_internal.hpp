@@ -287,6 +287,8 @@ struct xdg_ham_s {
     std::vector<double> jz, jxy;
     xdg::BondSet bonds;         // in the caller's labels
     xdg::BondSet inner_bonds;   // in the labels of basis->inner, if any
+    xdg::DevBuf u1_rtab;        // U(1) with many far bonds: rank tables, layout u1_rank
+    xdg::RankLayout u1_rank{};
     int64_t nnz = -1;
     std::mutex tune_mu;         // guards `tuned` (and the tuning runs that fill it)
     std::map<xdg::TuneKey, xdg::LaunchCfg> tuned;
@@ -341,6 +343,7 @@ inline void bondx_site(int i, int m, int pb, BondX &x) {
 
 int basis_build_device(xdg_basis_s *b);                 // enumerate + index
 int basis_build_inner(xdg_basis_s *b);                  // b->inner and b->umap, where they apply
+int u1_rank_tables(const xdg_basis_s *b, DevBuf *tab, RankLayout *L);
 // Device copies of bonds (labels `sites`) for a basis planned in those labels.
 int upload_bonds(const xdg_basis_s *b, int n_bonds, const int32_t *sites, const double *jz,
                  const double *jxy, BondSet *out);
