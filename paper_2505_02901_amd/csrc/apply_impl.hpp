@@ -129,10 +129,8 @@ __host__ __device__ constexpr size_t a16(size_t x) { return (x + 15) & ~(size_t)
 
 __host__ __device__ inline size_t sub_table_bytes(const SectorDesc &d) {
     const size_t NV = (size_t)d.n_s << d.m;
-    // packed form: one more element and its permutation, and 128 bytes to align the permutations
     if (d.subf)
-        return a16(4 * NV) + a16(2 * (size_t)d.n_pk) + 16 * ((size_t)d.n_sym + 1) +
-               a16(4 * ((size_t)d.n_perm + 1) << d.pb) + 128;
+        return packed_entry_bytes(d.n_sym) + packed_table_bytes(d.n_pk, d.n_perm, d.m, d.pb);
     return a16(2 * NV) + a16(4 * (NV + 1)) + a16(2 * (size_t)d.n_cand) +
            a16(4 * (size_t)d.n_sym * d.n_s) +
            a16(2 * (size_t)d.n_perm * 2 * ((size_t)1 << d.pb));
@@ -210,7 +208,7 @@ __device__ inline void stage(const SectorDesc &d, unsigned char *smem, Staged<T>
     // packed sublattice search: the elements' entries come first, so that
     // their LDS addresses fit the 16 bits of a candidate
     if constexpr (KIND == K_SUB && STAGE)
-        if (d.subf) off = 16 * ((size_t)d.n_sym + 1);
+        if (d.subf) off = packed_entry_bytes(d.n_sym);
     S.bonds = stage_copy(smem, off, reinterpret_cast<const B *>(d.bonds), d.n_bonds);
     S.sub = SubCtx{d.mintop, d.cand_off, d.cand_list, d.sp, d.tperm, d.n_s, d.m, d.pb};
     S.subf = false;
@@ -243,39 +241,9 @@ __device__ inline void stage(const SectorDesc &d, unsigned char *smem, Staged<T>
                 const size_t NV = (size_t)d.n_s << d.m;
                 const size_t ntp = (size_t)d.n_perm * 2 * ((size_t)1 << d.pb);
                 if (d.subf) {
-                    const uint32_t base =
-                        (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
-                    S.pk.tab = base + (uint32_t)off;
-                    stage_copy(smem, off, d.pk_tab, NV);
-                    S.pk.list = base + (uint32_t)off;
-                    uint16_t *cand = reinterpret_cast<uint16_t *>(smem + off);
-                    off = a16(off + 2 * (size_t)d.n_pk);
-                    for (uint32_t e = threadIdx.x; e < d.n_pk; e += blockDim.x)
-                        cand[e] = (uint16_t)(d.pk_cand[e] + base);
-                    // permutation tables at a 128-byte aligned LDS address,
-                    // and behind them one whose images are all 2^m: the
-                    // padding element's
-                    off += (128u - ((base + (uint32_t)off) & 127u)) & 127u;
-                    const uint32_t tpa = base + (uint32_t)off;
-                    uint16_t *tp = reinterpret_cast<uint16_t *>(smem + off);
-                    const size_t E = (size_t)1 << d.pb;
-                    off = a16(off + 2 * (ntp + 2 * E));
-                    for (size_t e = threadIdx.x; e < ntp + 2 * E; e += blockDim.x)
-                        tp[e] = e < ntp       ? d.tperm[e]
-                                : e < ntp + E ? (uint16_t)(1u << d.m)
-                                              : (uint16_t)0;
-                    // the (element, block) entries: the tables' address or'ed
-                    // with seven times the source block
-                    const size_t nsp = (size_t)d.n_sym * 4;
-                    S.pk.sp = base;
-                    uint32_t *sq = reinterpret_cast<uint32_t *>(smem);
-                    for (size_t e = threadIdx.x; e < nsp + 4; e += blockDim.x) {
-                        const uint32_t w = e < nsp ? d.sp[e] : (uint32_t)ntp << 8;
-                        sq[e] = (tpa + 2u * (w >> 8)) | (7u * ((w & 0xFFu) / (uint32_t)d.m));
-                    }
-                    S.pk.amask = ~((4u << d.pb) - 1u);
-                    S.pk.m = d.m;
-                    S.pk.nb = d.pk_nb;
+                    const PackedSrc src{d.pk_tab, d.pk_cand, d.sp, d.tperm, d.n_pk, d.pk_nb,
+                                        d.n_sym, d.n_perm, d.m, d.pb};
+                    S.pk = stage_packed(src, smem, off);
                     S.subf = true;
                 } else {
                     S.sub.mintop = stage_copy(smem, off, d.mintop, NV);

@@ -199,6 +199,7 @@ struct EnumArgs {
     int n_s, m, pb, n_perm;
     uint32_t n_cand;
     int stage_sub;
+    PackedSrc packed;          // K_PACKED
 };
 
 template <class W>
@@ -233,6 +234,12 @@ struct Candidates {
 // take workgroups of one wave
 constexpr int ENUM_BLOCK = 1024;
 
+// Sublattice coding in the packed form with every character 1: a candidate is
+// kept where the packed search returns it, whatever its stabiliser.  The test
+// by early exits takes each lane through lists of its own (6x6 lattice, Gamma
+// A1: count pass 11.0 -> 8.8 ms, k_stab 0.43 -> 0.17 ms).
+constexpr int K_PACKED = 5;
+
 // Representative test of the enumeration with the tables in LDS.
 template <class W, int KIND>
 struct RepTest {
@@ -240,7 +247,14 @@ struct RepTest {
     const double2 *chi;
     const AffineElem *aff;
     SubCtx C;
+    PackedCtx P;
     __device__ __forceinline__ RepTest(const EnumArgs<W> &A_, unsigned char *smem) : A(A_) {
+        if constexpr (KIND == K_PACKED) {
+            size_t at = packed_entry_bytes(A.n_sym);
+            P = stage_packed(A.packed, smem, at);
+            __syncthreads();
+            return;
+        }
         C = SubCtx{A.mintop, A.cand_off, A.cand_list, A.sp, A.tperm, A.n_s, A.m, A.pb};
         double2 *lchi = reinterpret_cast<double2 *>(smem);
         size_t off = align16(sizeof(double2) * A.n_sym);
@@ -273,13 +287,19 @@ struct RepTest {
     // s is the representative of an orbit that carries a symmetric state (the
     // stabiliser sum of chi is nonzero); st = |Stab(s)|
     __device__ __forceinline__ bool operator()(W s, int &st) const {
-        double cr, ci;
-        bool rep;
+        if constexpr (KIND == K_PACKED) {
+            uint32_t top, low;
+            int u;
+            sub_search_packed<false>(P, sub_key<W>(s, A.m, A.pb), top, low, u, st);
+            return (((W)top << (3 * A.m)) | (W)low) == s;
+        }
+        double cr = 0.0, ci = 0.0;
+        bool rep = false;
         if constexpr (KIND == K_AFF)
             rep = aff_is_rep<W>(aff, A.n_sym, A.N, s, chi, st, cr, ci);
         else if constexpr (KIND == K_SUB)
             rep = sub_is_rep<W>(C, s, chi, st, cr, ci);
-        else
+        else if constexpr (KIND == K_TAB)
             rep = tab_is_rep<W>(A.bytetab, A.n_bchunks, A.n_sym, s, chi, st, cr, ci);
         return rep && (cr * cr + ci * ci > 0.25);
     }
@@ -625,6 +645,16 @@ int enumerate(xdg_basis_s *b, const std::vector<uint64_t> &binom) {
             }
         }
     }
+    bool packed = kind == K_SUB && b->chi_trivial && b->plan.sub.packed();
+    if (packed) {
+        const SublatticeTables &S = b->plan.sub;
+        A.packed = PackedSrc{b->t_pktab.as<uint32_t>(), b->t_pkcand.as<uint16_t>(), A.sp, A.tperm,
+                             (uint32_t)S.pk_cand.size(), S.pk_nb, b->n_sym, A.n_perm, A.m, A.pb};
+        const size_t need = packed_entry_bytes(b->n_sym) +
+                            packed_table_bytes(A.packed.n_cand, A.n_perm, A.m, A.pb);
+        packed = need <= lds_limit();
+        if (packed) lds = need;
+    }
     auto blocks_of = [](uint64_t lanes, int block) { return (lanes + block - 1) / block; };
     if (blocks_of(A.n_chunks, 256) > 0x7fffffffull) {
         set_error("enumeration grid too large");
@@ -639,6 +669,9 @@ int enumerate(xdg_basis_s *b, const std::vector<uint64_t> &binom) {
     if (kind == K_AFF) {
         kcount = k_enum<W, K_AFF, false>;
         kstab = k_stab<W, K_AFF>;
+    } else if (packed) {
+        kcount = k_enum<W, K_PACKED, false>;
+        kstab = k_stab<W, K_PACKED>;
     } else if (kind == K_SUB) {
         kcount = k_enum<W, K_SUB, false>;
         kstab = k_stab<W, K_SUB>;

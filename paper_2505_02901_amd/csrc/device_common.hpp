@@ -688,6 +688,67 @@ struct PackedCtx {
     int m, nb;
 };
 
+// The tables in device memory, and their staging: the elements' entries at the
+// start of the LDS area (their addresses fit the 16 bits of a candidate), the
+// rest from `off` on, which moves behind it.  Every lane of the workgroup
+// takes part; the caller synchronises.
+struct PackedSrc {
+    const uint32_t *tab;
+    const uint16_t *cand;
+    const uint32_t *sp;
+    const uint16_t *tperm;
+    uint32_t n_cand;
+    int nb, n_sym, n_perm, m, pb;
+};
+// one entry more than elements: the padding element's
+__host__ __device__ constexpr size_t packed_entry_bytes(int n_sym) {
+    return 16 * ((size_t)n_sym + 1);
+}
+// (its permutation, and 128 bytes to align the permutations)
+__host__ __device__ constexpr size_t packed_table_bytes(uint32_t n_cand, int n_perm, int m, int pb) {
+    auto a16 = [](size_t x) { return (x + 15) & ~(size_t)15; };
+    return a16((size_t)16 << m) + a16(2 * (size_t)n_cand) +
+           a16(4 * ((size_t)n_perm + 1) << pb) + 128;
+}
+__device__ inline PackedCtx stage_packed(const PackedSrc &P, unsigned char *smem, size_t &off) {
+    auto a16 = [](size_t x) { return (x + 15) & ~(size_t)15; };
+    const uint32_t base =
+        (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+    PackedCtx C;
+    const uint32_t NV = 4u << P.m;
+    C.tab = base + (uint32_t)off;
+    uint32_t *tab = reinterpret_cast<uint32_t *>(smem + off);
+    off = a16(off + 4 * (size_t)NV);
+    for (uint32_t e = threadIdx.x; e < NV; e += blockDim.x) tab[e] = P.tab[e];
+    C.list = base + (uint32_t)off;
+    uint16_t *cand = reinterpret_cast<uint16_t *>(smem + off);
+    off = a16(off + 2 * (size_t)P.n_cand);
+    for (uint32_t e = threadIdx.x; e < P.n_cand; e += blockDim.x)
+        cand[e] = (uint16_t)(P.cand[e] + base);
+    // permutation tables at a 128-byte aligned address, and behind them one
+    // whose images are all 2^m: the padding element's
+    off += (128u - ((base + (uint32_t)off) & 127u)) & 127u;
+    const uint32_t tpa = base + (uint32_t)off;
+    uint16_t *tp = reinterpret_cast<uint16_t *>(smem + off);
+    const uint32_t E = 1u << P.pb, ntp = (uint32_t)P.n_perm * 2u * E;
+    off = a16(off + 2 * ((size_t)ntp + 2 * E));
+    for (uint32_t e = threadIdx.x; e < ntp + 2 * E; e += blockDim.x)
+        tp[e] = e < ntp ? P.tperm[e] : e < ntp + E ? (uint16_t)(1u << P.m) : (uint16_t)0;
+    // the (element, block) entries: the tables' address or'ed with seven
+    // times the source block
+    const uint32_t nsp = (uint32_t)P.n_sym * 4u;
+    C.sp = base;
+    uint32_t *sq = reinterpret_cast<uint32_t *>(smem);
+    for (uint32_t e = threadIdx.x; e < nsp + 4; e += blockDim.x) {
+        const uint32_t w = e < nsp ? P.sp[e] : ntp << 8;
+        sq[e] = (tpa + 2u * (w >> 8)) | (7u * ((w & 0xFFu) / (uint32_t)P.m));
+    }
+    C.amask = ~((4u << P.pb) - 1u);
+    C.m = P.m;
+    C.nb = P.nb;
+    return C;
+}
+
 // Slot of a representative in the rank-addressed x of a packed sector: top
 // block c, lower blocks v2, v1, v0 (low = v2 v1 v0).  Ordered by c, then by
 // the set bits p2 and p1 of v2 and v1 (p0 follows), then by the ranks r of v2,

@@ -42,3 +42,37 @@ def test_every_filling(X, name):
             orbit = np.array([[sum(((int(s) >> int(g[i])) & 1) << i for i in range(n)) == int(s)
                                for g in m.perm] for s in want[:64]]).sum(axis=1)
             assert np.array_equal(b.stabilisers(0, min(64, b.dim)), orbit), (name, up)
+
+
+# four blocks of 5 to 10 sites (both state widths): the packed search with
+# characters 1, the general one with others; few and half-filled blocks
+PACKED = {
+    "20_A1": ((4, 2), (-2, 4), "A1", (0, 1, 2, 7, 10, 19, 20)), "20_B1": ((4, 2), (-2, 4), None, (1, 2, 7, 10)),
+    "24_A1": ((4, 0), (0, 6), "A1", (1, 4, 12)), "32_A1": ((4, 4), (-4, 4), "A1", (1, 4, 5, 28)),
+    "36_A1": ((6, 0), (0, 6), "A1", (1, 2, 4, 32)), "36_B1": ((6, 0), (0, 6), "B1", (2, 4)),
+    "40_A1": ((6, 2), (-2, 6), "A1", (1, 2, 3, 4)),
+}
+
+
+@pytest.mark.parametrize("name", sorted(PACKED))
+def test_packed_blocks(X, name):
+    l1, l2, gamma, ups = PACKED[name]
+    for up in ups:
+        refl = l1[1] == 0 or l1[0] == l1[1]
+        m = W.torus_model(l1, l2, 1.0, 0.0, "A1" if gamma is None else gamma, n_up=up,
+                          reflections=refl)
+        if gamma is None:   # a turn by a quarter changes the sign
+            perm, labels = W.Torus(l1, l2).symmetry_group(True, False)
+            m = m.with_sector(perm, W.gamma_characters(labels, -1.0, 1.0))
+        b = X.Basis.from_model(m)
+        want = oracle.basis(m)
+        assert np.array_equal(b.states(), want), (name, up, b.dim, len(want))
+        n = m.perm.shape[1]
+        if len(want):
+            count = np.zeros(len(want), int)
+            for g in m.perm:
+                im = np.zeros(len(want), np.uint64)
+                for i in range(n):
+                    im |= ((want.astype(np.uint64) >> np.uint64(int(g[i]))) & np.uint64(1)) << np.uint64(i)
+                count += im == want.astype(np.uint64)
+            assert np.array_equal(b.stabilisers(0, b.dim), count), (name, up)
