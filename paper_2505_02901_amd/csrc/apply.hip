@@ -119,6 +119,8 @@ SectorDesc make_desc(const xdg_ham_s *h, bool single, const void *x, void *y,
     for (double j : h->jz) jq += 0.25 * j;
     d.jz_quarter = jq;
     d.ring_bonds = bonds.ring;
+    d.ring_eq = bonds.ring_eq;
+    d.chi_one = b->chi_trivial;
     d.u1_adj = b->u1_adj.as<uint32_t>();
     if (h->u1_rtab.p) {
         d.u1_rank = 1;
@@ -382,6 +384,7 @@ int apply_launch(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, 
     A.nvec = f.cols;
     size_t lds = f.tsingle ? stage_bytes<float>(A.one, b->plan.kind, 1)
                            : stage_bytes<double>(A.one, b->plan.kind, 1);
+    A.ring = ring_loop_ok(A.one, b->plan.kind, b->wide);
     A.stage_sub = 1;
     if (lds > lds_budget()) {
         A.stage_sub = 0;
@@ -661,11 +664,13 @@ int batch_plan_host(int n, xdg_ham_s *const *hams, const void *const *xs, void *
     // few rows in all: terms shared out over the lanes, about four items per
     // compute unit
     P->few = 0;
+    P->ring = 1;
     int64_t rows = 0;
     int most_bonds = 0;
     for (int i = 0; i < n; ++i) {
         const SectorDesc d = make_desc(hams[i], P->tsingle, nullptr, nullptr, relabelled);
         rows += d.dim;
+        P->ring &= ring_loop_ok(d, P->kind, P->wide);
         most_bonds = std::max(most_bonds, d.n_bonds);
         lds_full = std::max(lds_full, P->tsingle ? stage_bytes<float>(d, P->kind, 1)
                                                  : stage_bytes<double>(d, P->kind, 1));
@@ -735,6 +740,7 @@ int batch_launch_raw(const BatchMeta &P, const SectorDesc *d_descs, const uint32
     A.nvec = P.cols;
     A.stage_sub = P.stage_sub;
     A.occ = P.stage_sub ? occ_for(P.lds) : 0;
+    A.ring = P.ring;
     if (P.few) {   // one launch for all vectors
         A.few = P.few;
         A.few_off = P.few_off;

@@ -15,6 +15,8 @@
 // characters, search tables) are shared by 16 waves.
 #pragma once
 
+#include <type_traits>
+
 #include "device_common.hpp"
 
 namespace xdg {
@@ -85,6 +87,8 @@ struct SectorDesc {
     const void *sqrtt;           // T [2 (n_sym + 1)]: sqrt(c), then 1/sqrt(c)
     double jz_quarter;           // (1/4) sum_b Jz_b: the diagonal of the all-aligned state
     int ring_bonds;              // 1: n_bonds = n_sites and bond b joins sites b and b + 1 mod N
+    int ring_eq;                 // 1: the same, with equal couplings
+    int chi_one;                 // 1: every character is exactly 1
     // rank-addressed x (sublattice coding): slot top_rank(s) of xr holds the
     // row of representative s when s is a basis state, zeros otherwise, so a
     // term reads x without the index lookup (null: through the rank index)
@@ -121,6 +125,7 @@ struct ApplyArgs {
     int occ;                     // use the 8-waves-per-SIMD variant
     int compact;                 // table searches: wave-compacted term loop
     int few;                     // rows per wave of the few-rows loop (0: another loop)
+    int ring;                    // every block takes the ring loop (see ring_loop_ok)
     uint32_t few_off;            // byte offset of its terms behind the staged tables
     unsigned long long *count;   // nnz counting mode (nullptr otherwise)
 };
@@ -153,6 +158,13 @@ __host__ __device__ inline size_t xr_top_bytes(const SectorDesc &d) {
     return ((size_t)1 << d.m) * (d.xr_top32 ? 4 : 8);
 }
 
+// The ring loop (process_ring): a full ring of more than half a state's bits
+// with equal neighbour bonds and the rank index.
+inline bool ring_loop_ok(const SectorDesc &d, int kind, bool wide) {
+    return kind == K_AFF && (d.dim == 0 || (d.ring && d.ring_eq && d.rwords)) &&
+           (wide ? d.n_sites > 32 && d.n_sites < 64 : d.n_sites > 16);
+}
+
 // LDS bytes needed to stage a sector's tables.
 template <class T>
 __host__ __device__ inline size_t stage_bytes(const SectorDesc &d, int kind, int stage_sub) {
@@ -164,6 +176,8 @@ __host__ __device__ inline size_t stage_bytes(const SectorDesc &d, int kind, int
         n += a16(sizeof(T) * 2 * (d.n_sym + 1));
         n += a16(rank_table_bytes(d));
         if (kind == K_AFF) n += a16(sizeof(AffineElem) * d.n_sym) + a16(4 * (size_t)d.n_sites);
+        if (kind == K_AFF && d.ring_eq)
+            n += a16(sizeof(T) * (d.n_sym + 1)) + a16(sizeof(T) * (d.n_bonds + 1));
         if (kind == K_SUB && stage_sub) n += sub_table_bytes(d);
         if (kind == K_SUB && stage_sub && d.xr) n += a16(xr_top_bytes(d));
     }
@@ -178,6 +192,7 @@ struct Staged {
     const T *rsq;      // 1/sqrt(c)
     const AffineElem *aff;
     const int16_t *ring_gidx;
+    const T *hs, *jsum;    // ring loop: see process_ring
     const void *rtab;
     const uint32_t *adj;   // U(1): see process_row_u1
     SubCtx sub;
@@ -200,7 +215,7 @@ __device__ inline E *stage_copy(unsigned char *smem, size_t &off, const E *src, 
 // STAGE: the sublattice tables go to LDS too (otherwise they are read from
 // global memory); a compile-time choice so that every table pointer has a
 // known address space.
-template <int KIND, class T, bool STAGE>
+template <int KIND, class T, bool STAGE, bool RING = false>
 __device__ inline void stage(const SectorDesc &d, unsigned char *smem, Staged<T> &S) {
     using B = typename BondT<T>::type;
     using T2 = typename Vec2<T>::type;
@@ -233,8 +248,29 @@ __device__ inline void stage(const SectorDesc &d, unsigned char *smem, Staged<T>
             int16_t *lg = reinterpret_cast<int16_t *>(smem + off);
             off = a16(off + 4 * (size_t)d.n_sites);
             if (d.ring)
-                for (int e = threadIdx.x; e < 2 * d.n_sites; e += blockDim.x) lg[e] = d.ring_gidx[e];
+                for (int e = threadIdx.x; e < 2 * d.n_sites; e += blockDim.x) {
+                    int from = e;
+                    if constexpr (RING)   // by the site read first (see ring_scan_big)
+                        from = (e + 1) % d.n_sites == 0 ? e + 1 - d.n_sites : e + 1;
+                    lg[e] = d.ring_gidx[from];
+                }
             S.ring_gidx = lg;
+            if constexpr (RING) {
+                const B b0 = *reinterpret_cast<const B *>(d.bonds);
+                T *hs = reinterpret_cast<T *>(smem + off);
+                off = a16(off + sizeof(T) * ((size_t)d.n_sym + 1));
+                T *js = reinterpret_cast<T *>(smem + off);
+                off = a16(off + sizeof(T) * ((size_t)d.n_bonds + 1));
+                for (int e = threadIdx.x; e <= d.n_sym; e += blockDim.x)
+                    hs[e] = b0.h * reinterpret_cast<const T *>(d.sqrtt)[e];
+                for (int e = threadIdx.x; e <= d.n_bonds; e += blockDim.x) {
+                    T sum = 0;
+                    for (int b = 0; b < e; ++b) sum += b0.jz;
+                    js[e] = sum;
+                }
+                S.hs = hs;
+                S.jsum = js;
+            }
         }
         if constexpr (KIND == K_SUB) {
             if constexpr (STAGE) {
@@ -645,6 +681,92 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
         gst(Y + base + v, (T)fmadd<A>(diag, (A)xd[v], rn * acc[v]));
 }
 
+// A row of a full ring with equal neighbour bonds: the terms, their order and
+// every rounding of the general loop, so the results agree bitwise.  What
+// bounds it is the number of vector instructions of a term (32 sites: 112 of
+// them, 88 % of the issue slots in the general loop).  The exchanged pair is
+// made from the lowest set bit of the walls; the amplitudes h sqrt(c) and the
+// sums of k equal Jz are tables, rounded as the loop rounds them; the search
+// tests no rotation length.  TRIV, every character 1: all orbits are in the
+// block and no element is needed, so neither the index bit nor the character
+// is looked at.  Ring N = 32, k = 0, FP32: 1.166 -> 0.974 ms; N = 28, every
+// momentum, complex64 x 8: 6.06 -> 5.71 ms.  (The 64-register copy kept 27
+// vector and 35 scalar registers in memory in the general loop, here 3 and 0.)
+template <class W, class T, class A, bool CPLX, int NV, bool FULL, bool TRIV>
+__device__ __forceinline__ void process_ring(const SectorDesc &d, const Staged<A> &S, int64_t row,
+                                             int64_t nvec, int v0) {
+    constexpr int C = CPLX ? 2 : 1;
+    const int N = FULL ? 8 * (int)sizeof(W) : d.n_sites;
+    const W mask = FULL ? ~W(0) : (W(1) << N) - 1;
+    const W s = gld(reinterpret_cast<const W *>(d.reps) + row);
+    const T *X = reinterpret_cast<const T *>(d.x) + (size_t)v0 * C;
+    T *Y = reinterpret_cast<T *>(d.y) + (size_t)v0 * C;
+    const bool dense = nvec == NV;   // one pass: the row stride is a constant
+    W act = s ^ rot_r<W, FULL>(s, 1, N, mask);   // bit b: the spins of bond b differ
+    const A junq = S.jsum[sizeof(W) == 4 ? __popc((uint32_t)act) : __popcll((uint64_t)act)];
+    A acc[NV * C];
+#pragma unroll
+    for (int v = 0; v < NV * C; ++v) acc[v] = 0;
+    while (act) {
+        const W bit = act & (W(0) - act);
+        act ^= bit;
+        const W t = s ^ (bit | rot_l<W, FULL>(bit, 1, N, mask));
+        W rep;
+        int u, cnt;
+        ring_scan_big<W, FULL, TRIV, true>(t, N, mask, S.ring_gidx, rep, u, cnt);
+        if (d.ring == 2)
+            ring_scan_big<W, FULL, TRIV, false>(rev_n<W>(t, N), N, mask, S.ring_gidx + N, rep, u,
+                                                cnt);
+        typename IndexT<W>::type idx;
+        if constexpr (sizeof(W) == 4) {
+            const uint32_t r = (uint32_t)colex_rank<W>(S.rtab, d.rl, rep);
+            if constexpr (TRIV) {
+                const uint64_t e = gld(reinterpret_cast<const uint64_t *>(d.rwords) + (r >> 5));
+                idx = (int32_t)((uint32_t)e +
+                                __popc((uint32_t)(e >> 32) & ((1u << (r & 31u)) - 1u)));
+            } else {
+                idx = rank_find32(d.rwords, (uint32_t)d.n_rwords, r);
+            }
+        } else if (d.rl.e32) {
+            const uint32_t r = colex_rank_sat<W>(static_cast<const uint32_t *>(S.rtab), d.rl, rep);
+            idx = r == 0xFFFFFFFFu ? -1 : rank_find_r32(d.rwords, (uint32_t)d.n_rwords, r);
+        } else {
+            idx = rank_find(d.rwords, d.n_rwords, colex_rank<W>(S.rtab, d.rl, rep));
+        }
+        if (!(TRIV && sizeof(W) == 4) && idx < 0) continue;
+        const A f = S.hs[cnt];
+        A ar = f, ai = 0;
+        if constexpr (!TRIV) {
+            const auto c = S.chi[u];
+            ar = f * c.x;
+            if constexpr (CPLX) ai = f * c.y;
+        }
+        const size_t at = sizeof(W) == 4 ? (size_t)(uint32_t)idx : (size_t)idx;
+        const T *q = X + (dense ? at * (NV * C)
+                          : sizeof(W) == 4 ? (uint64_t)(uint32_t)at * (uint32_t)(nvec * C)
+                                           : at * (size_t)(nvec * C));
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            if constexpr (CPLX) {
+                const A xr = gld(q + 2 * v), xi = gld(q + 2 * v + 1);
+                acc[2 * v] = fmadd<A>(-ai, xi, fmadd<A>(ar, xr, acc[2 * v]));
+                acc[2 * v + 1] = fmadd<A>(ai, xr, fmadd<A>(ar, xi, acc[2 * v + 1]));
+            } else {
+                acc[v] = fmadd<A>(ar, (A)gld(q + v), acc[v]);
+            }
+        }
+    }
+    const A rn = S.rsq[gld(d.stab + row)];
+    const size_t base = (size_t)row * nvec * C;
+    const A diag = (A)d.jz_quarter - A(0.5) * junq;
+    T xd[NV * C];
+#pragma unroll
+    for (int v = 0; v < NV * C; ++v) xd[v] = gld(X + base + v);
+#pragma unroll
+    for (int v = 0; v < NV * C; ++v)
+        gst(Y + base + v, (T)fmadd<A>(diag, (A)xd[v], rn * acc[v]));
+}
+
 // ------------------------------------------------ wave-compacted term loop --
 // For the table searches (sublattice coding, byte tables) the row loop above
 // takes every bond with all lanes of the wave at once, so on each bond only
@@ -918,14 +1040,15 @@ __device__ __forceinline__ void process_few(const SectorDesc &d, const Staged<A>
     }
 }
 
-enum : int { LOOP_ROW = 0, LOOP_CMP = 1, LOOP_FEW = 2, LOOP_PACKED = 3 };
+enum : int { LOOP_ROW = 0, LOOP_CMP = 1, LOOP_FEW = 2, LOOP_PACKED = 3, LOOP_RING = 4 };
 
 // rows [r0, r1) of a sector.  LOOP_CMP: windows of CMP_ROWS rows per wave
 // (every lane of a wave takes part in its permutes; `first` and `stride`
 // count lanes, so wave w of the launch starts at window w); LOOP_FEW: `few`
 // rows per wave, all vectors; otherwise a lane per row, reading the
 // rank-addressed x when XR.  LOOP_PACKED: the lane-per-row loop of a single
-// block in the packed sublattice form and nothing else (see launch_nv).
+// block in the packed sublattice form and nothing else (see launch_nv);
+// LOOP_RING: the rows of process_ring.
 template <class W, int KIND, class T, class A, bool CPLX, int NV, int LOOP, int XR, bool PIPE>
 __device__ __forceinline__ void process_range(const SectorDesc &d, const Staged<A> &S, int64_t r0,
                                               int64_t r1, int64_t first, int64_t stride,
@@ -935,6 +1058,28 @@ __device__ __forceinline__ void process_range(const SectorDesc &d, const Staged<
         process_few<W, KIND, T, A, CPLX>(
             d, S, r0, r1, (first - lane_id()) / 64, stride / 64, few,
             few_terms + (threadIdx.x / 64) * few_bytes<A>(CPLX, few * d.n_bonds), nvec);
+    } else if constexpr (LOOP == LOOP_RING) {
+        auto rows = [&](auto full, auto one) {
+            for (int64_t row = r0 + first; row < r1; row += stride)
+                process_ring<W, T, A, CPLX, NV, decltype(full)::value, decltype(one)::value>(
+                    d, S, row, nvec, v0);
+        };
+        using std::false_type;
+        using std::true_type;
+        auto form = [&](auto full) {
+            if constexpr (CPLX) {
+                rows(full, false_type{});
+            } else {
+                if (d.chi_one) rows(full, true_type{});
+                else rows(full, false_type{});
+            }
+        };
+        if constexpr (sizeof(W) == 4) {
+            if (d.n_sites == 32) form(true_type{});
+            else form(false_type{});
+        } else {
+            form(false_type{});
+        }
     } else if constexpr (LOOP == LOOP_CMP) {
         const int64_t wave = (first - lane_id()) / 64, waves = stride / 64;
         for (int64_t w0 = r0 + wave * CMP_ROWS; w0 < r1; w0 += waves * CMP_ROWS)
@@ -976,7 +1121,7 @@ __global__ __launch_bounds__(APPLY_BLOCK, OCC ? OCC_WAVES : 1) void k_apply(Appl
     Staged<AC> S;
     if (LOOP == LOOP_PACKED || A.descs == nullptr) {
         const SectorDesc &d = A.one;
-        stage<KIND, AC, STAGE>(d, smem, S);
+        stage<KIND, AC, STAGE, LOOP == LOOP_RING>(d, smem, S);
         __syncthreads();
         const int64_t stride = (int64_t)gridDim.x * blockDim.x;
         process_range<W, KIND, T, AC, CPLX, NV, LOOP, XR, PIPE>(
@@ -999,7 +1144,7 @@ __global__ __launch_bounds__(APPLY_BLOCK, OCC ? OCC_WAVES : 1) void k_apply(Appl
         if (lo != cur) {
             if (threadIdx.x == 0) s_desc = A.descs[lo];
             __syncthreads();
-            stage<KIND, AC, STAGE>(s_desc, smem, S);
+            stage<KIND, AC, STAGE, LOOP == LOOP_RING>(s_desc, smem, S);
             __syncthreads();
             cur = lo;
         }
@@ -1097,6 +1242,10 @@ int launch_nv(int nv, const ApplyArgs &A, unsigned grid, unsigned block, size_t 
         if (!A.descs && A.stage_sub && A.one.subf && A.one.bx && !cmp && !A.few)
             f = occ ? apply_kernel<W, KIND, T, AC, CPLX, true, true, LOOP_PACKED, XR>(nv)
                     : apply_kernel<W, KIND, T, AC, CPLX, true, false, LOOP_PACKED, XR>(nv);
+    if constexpr (KIND == K_AFF)
+        if (A.ring && !A.few)
+            f = occ ? apply_kernel<W, KIND, T, AC, CPLX, true, true, LOOP_RING, XR>(nv)
+                    : apply_kernel<W, KIND, T, AC, CPLX, true, false, LOOP_RING, XR>(nv);
     if (f) {
     } else if constexpr (XR == 2 && CPLX) {
         set_error("internal: the trivial-character kernels serve real blocks");

@@ -77,6 +77,9 @@ int upload_bonds(const xdg_basis_s *b, int n_bonds, const int32_t *sites, const 
         const int p = sites[2 * i], q = sites[2 * i + 1], r = (i + 1) % b->n_sites;
         out->ring = (p == i && q == r) || (p == r && q == i);
     }
+    out->ring_eq = out->ring;
+    for (int i = 1; i < n_bonds && out->ring_eq; ++i)
+        out->ring_eq = jz[i] == jz[0] && jxy[i] == jxy[0];
     return XDG_OK;
 }
 

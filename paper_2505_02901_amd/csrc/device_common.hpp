@@ -380,25 +380,21 @@ __host__ __device__ __forceinline__ void ring_scan_t(W t, int N, const int16_t *
     constexpr int J = sizeof(W) == 4 ? 5 : 6;   // 2^J > the longest run < N
     const W mask = FULL ? ~W(0) : ((W(1) << N) - 1);
     const W z = ~t & mask;
-    W y;
-    if (z == 0 || z == mask) {
-        y = mask;                      // all rotations give the same image
-    } else {
-        W p[J];                        // p[j] = y_{2^j}
-        p[0] = z;
+    // (t = 0 or all ones: y stays the mask, all rotations give the same image)
+    W p[J];                            // p[j] = y_{2^j}
+    p[0] = z;
 #pragma unroll
-        for (int j = 1; j < J; ++j) {
-            const int h = 1 << (j - 1);
-            p[j] = (FULL || h < N) ? (p[j - 1] & rot_l<W, FULL>(p[j - 1], h, N, mask)) : W(0);
-        }
-        y = mask;                      // y_0
+    for (int j = 1; j < J; ++j) {
+        const int h = 1 << (j - 1);
+        p[j] = (FULL || h < N) ? (p[j - 1] & rot_l<W, FULL>(p[j - 1], h, N, mask)) : W(0);
+    }
+    W y = mask;                        // y_0
 #pragma unroll
-        for (int j = J - 1; j >= 0; --j) {
-            const int h = 1 << j;
-            if (FULL || h < N) {
-                const W c = p[j] & rot_l<W, FULL>(y, h, N, mask);
-                y = c ? c : y;
-            }
+    for (int j = J - 1; j >= 0; --j) {
+        const int h = 1 << j;
+        if (FULL || h < N) {
+            const W c = p[j] & rot_l<W, FULL>(y, h, N, mask);
+            y = c ? c : y;
         }
     }
     auto take = [&](int pos, bool first) {
@@ -450,6 +446,62 @@ __host__ __device__ __forceinline__ void ring_search(const int16_t *gidx, int ri
                                                      W &best, int &u, int &cnt) {
     ring_scan<W, true>(t, N, gidx, best, u, cnt);
     if (ring == 2) ring_scan<W, false>(rev_n<W>(t, N), N, gidx + N, best, u, cnt);
+}
+
+// The same search for the ring loop of the products (see process_ring): more
+// than half of W's bits are sites, so every rotation of the doubling is one
+// of the ring and none is tested; gidx[p] is the group index of the rotation
+// that reads t downward from site p.  TRIV: every character is 1 and u is not
+// kept.
+template <class W, bool FULL, bool TRIV, bool FIRST>
+__device__ __forceinline__ void ring_scan_big(W t, int N, W mask, const int16_t *gidx, W &best,
+                                              int &u, int &cnt) {
+    constexpr int J = sizeof(W) == 4 ? 5 : 6;
+    auto rot_and = [&](W v, int h, W with) -> W {   // rotl(v, h) & with, with inside the mask
+        if constexpr (FULL)
+            return rot_l<W, true>(v, h, N, mask) & with;
+        else
+            return ((v << h) | (v >> (N - h))) & with;
+    };
+    W p[J];
+    p[0] = ~t & mask;
+#pragma unroll
+    for (int j = 1; j < J; ++j) p[j] = rot_and(p[j - 1], 1 << (j - 1), p[j - 1]);
+    W y = p[J - 1] ? p[J - 1] : mask;
+#pragma unroll
+    for (int j = J - 2; j >= 0; --j) {
+        const W c = rot_and(y, 1 << j, p[j]);
+        y = c ? c : y;
+    }
+    const W t1 = rot_r<W, FULL>(t, 1, N, mask);
+    auto image = [&](int pos) -> W {   // rotr(t, pos + 1): 0 <= pos < N
+        if constexpr (FULL)
+            return rot_r<W, true>(t1, pos, N, mask);
+        else
+            return ((t1 >> pos) | (t1 << (N - pos))) & mask;
+    };
+    auto low = [](W v) -> int {
+        return sizeof(W) == 4 ? __builtin_ctz((uint32_t)v) : __builtin_ctzll((uint64_t)v);
+    };
+    if constexpr (FIRST) {
+        const int pos = low(y);
+        y &= y - 1;
+        best = image(pos);
+        cnt = 1;
+        u = TRIV ? 0 : gidx[pos];
+    }
+    while (y) {
+        const int pos = low(y);
+        y &= y - 1;
+        const W img = image(pos);
+        const bool lt = img < best, eq = img == best;
+        if constexpr (!TRIV) {
+            const int g = gidx[pos];
+            u = lt || (eq && g < u) ? g : u;
+        }
+        cnt = lt ? 1 : cnt + (eq ? 1 : 0);
+        best = lt ? img : best;
+    }
 }
 
 // Representative test for enumeration: false as soon as some image is smaller.

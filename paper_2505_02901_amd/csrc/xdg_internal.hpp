@@ -275,6 +275,7 @@ struct BondSet {
     DevBuf f;      // BondF [n_bonds]
     DevBuf x;      // BondX [n_bonds] (packed sublattice search only)
     int ring = 0;  // 1: n_bonds = n_sites and bond b joins sites b and b + 1 mod N
+    int ring_eq = 0;   // 1: and all couplings are equal
     int far = 0;   // bonds whose sites are not neighbouring numbers
 };
 }  // namespace xdg
@@ -365,6 +366,7 @@ struct BatchMeta {
     int64_t cols = 0;
     uint32_t n_tiles = 0, tile_rows = 0;
     int few = 0;             // rows per wave of the few-rows loop (0: the row loop)
+    int ring = 0;            // every block takes the ring loop
     uint32_t few_off = 0;
     int few_block = 0;       // its workgroup and LDS
     size_t few_lds = 0;
