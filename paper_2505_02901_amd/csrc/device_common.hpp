@@ -929,6 +929,62 @@ __device__ __forceinline__ void sub_search_packed(const PackedCtx &C, const SubK
     cnt = (int)bc;
 }
 
+// Is t the smallest state of its orbit (top and lower blocks given)?  If so,
+// `same` was called with each element of its stabiliser.  As
+// sub_search_packed, but against t itself: an element whose second block lies
+// below t's ends the test, one above it is done.
+template <class F>
+__device__ __forceinline__ bool sub_rep_packed(const PackedCtx &C, const SubKey &K, uint32_t top,
+                                               uint32_t lower, F &&same) {
+    const int m = C.m;
+    const uint32_t lo2 = K.lo2, hi2 = K.hi2, amask = C.amask;
+    const uint32_t low = (1u << (31 - m)) - 1u;
+    const uint32_t b2 = lower >> (2 * m);
+    bool rep = true;
+    auto block = [&](uint32_t wa) -> uint32_t {   // as in sub_search_packed
+        const uint32_t la =
+            __builtin_amdgcn_bitop3_b32(wa, __builtin_amdgcn_ubfe(lo2, wa, 7), amask, 0xE4);
+        const uint32_t ha =
+            __builtin_amdgcn_bitop3_b32(wa, __builtin_amdgcn_ubfe(hi2, wa, 7), amask, 0xE4);
+        return (uint32_t)*(lds_u16 *)la + (uint32_t)*(lds_u16 *)ha;
+    };
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t word = *(lds_u32 *)(C.tab + K.e[k]);
+        const uint32_t first = word >> (31 - m);
+        rep = rep && first >= top;
+        if (!rep || first != top) continue;   // (not a return: the lanes stay together)
+        uint32_t p = C.list + 4u * ((word & low) >> C.nb);
+        for (uint32_t left = word & ((1u << C.nb) - 1u); left && rep;) {
+            const uint32_t n = min(left, 16u);   // pairs at a time, a bit for each candidate
+            uint32_t least = b2, mask = 0;
+            for (uint32_t i = 0; i < n; ++i) {
+                const uint32_t e0 = *(lds_u16 *)(p + 4 * i), e1 = *(lds_u16 *)(p + 4 * i + 2);
+                const uint32_t v0 = block(*(lds_u32 *)(e0 + 8));
+                const uint32_t v1 = block(*(lds_u32 *)(e1 + 8));
+                least = min(min(least, v0), v1);
+                // v + ~b2 is negative where v <= b2
+                mask = __builtin_amdgcn_alignbit(mask, v0 + ~b2, 31);
+                mask = __builtin_amdgcn_alignbit(mask, v1 + ~b2, 31);
+            }
+            rep = least == b2;
+            const uint32_t pl = p + 4 * n - 64;
+            while (mask && rep) {
+                const uint32_t z = (uint32_t)__builtin_clz(mask);
+                mask ^= 0x80000000u >> z;
+                const uint32_t e = *(lds_u16 *)(pl + 2 * z);
+                const uint32_t w0 = *(lds_u32 *)e, w1 = *(lds_u32 *)(e + 4);
+                const uint32_t img = (((b2 << m) | block(w1)) << m) | block(w0);
+                rep = img >= lower;
+                if (img == lower) same((e - C.sp) >> 4);
+            }
+            left -= n;
+            p += 64;
+        }
+    }
+    return rep;
+}
+
 // ---------------------------------------------------- search: byte tables --
 template <class W>
 __device__ __forceinline__ W tab_image(const uint64_t *tab, int n_chunks, int g, W t) {

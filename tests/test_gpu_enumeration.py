@@ -44,10 +44,11 @@ def test_every_filling(X, name):
             assert np.array_equal(b.stabilisers(0, min(64, b.dim)), orbit), (name, up)
 
 
-# four blocks of 5 to 10 sites (both state widths): the packed search with
-# characters 1, the general one with others; few and half-filled blocks
+# four blocks of 5 to 10 sites (both state widths) in the packed form, with
+# characters 1, signs and complex ones; few and half-filled blocks
 PACKED = {
-    "20_A1": ((4, 2), (-2, 4), "A1", (0, 1, 2, 7, 10, 19, 20)), "20_B1": ((4, 2), (-2, 4), None, (1, 2, 7, 10)),
+    "20_A1": ((4, 2), (-2, 4), "A1", (0, 1, 2, 7, 10, 19, 20)), "20_B1": ((4, 2), (-2, 4), -1.0, (1, 2, 7, 10)),
+    "20_E": ((4, 2), (-2, 4), 1j, (1, 2, 7, 10)),
     "24_A1": ((4, 0), (0, 6), "A1", (1, 4, 12)), "32_A1": ((4, 4), (-4, 4), "A1", (1, 4, 5, 28)),
     "36_A1": ((6, 0), (0, 6), "A1", (1, 2, 4, 32)), "36_B1": ((6, 0), (0, 6), "B1", (2, 4)),
     "40_A1": ((6, 2), (-2, 6), "A1", (1, 2, 3, 4)),
@@ -59,11 +60,11 @@ def test_packed_blocks(X, name):
     l1, l2, gamma, ups = PACKED[name]
     for up in ups:
         refl = l1[1] == 0 or l1[0] == l1[1]
-        m = W.torus_model(l1, l2, 1.0, 0.0, "A1" if gamma is None else gamma, n_up=up,
-                          reflections=refl)
-        if gamma is None:   # a turn by a quarter changes the sign
+        turn = not isinstance(gamma, str)   # the character of a quarter turn
+        m = W.torus_model(l1, l2, 1.0, 0.0, "A1" if turn else gamma, n_up=up, reflections=refl)
+        if turn:
             perm, labels = W.Torus(l1, l2).symmetry_group(True, False)
-            m = m.with_sector(perm, W.gamma_characters(labels, -1.0, 1.0))
+            m = m.with_sector(perm, W.gamma_characters(labels, gamma, 1.0))
         b = X.Basis.from_model(m)
         want = oracle.basis(m)
         assert np.array_equal(b.states(), want), (name, up, b.dim, len(want))
