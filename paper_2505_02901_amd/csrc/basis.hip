@@ -1181,6 +1181,16 @@ int basis_build_inner(xdg_basis_s *b) {
     if (P.kind != K_TAB &&
         !(P.kind == K_SUB && !P.sub.packed()))
         return XDG_OK;
+    // Few rows whose block tables leave 32 KiB of the LDS for the few-rows
+    // loop's terms beside the rank tables (32 KiB at most) take that loop in
+    // either labels and are prepared faster in one (4x6 square, 29606 rows,
+    // FP64: 89 us a product in the caller's labels, 87 in others, and 3.1
+    // against 5.0 ms before it; with 6 of 24 up 57 and 45 us, 2.9 and 4.8 ms).  Tables without that room keep them out of it
+    // (6x6 triangular lattice, 5 of 36 up: 1.99 ms a product, 0.10 in others).
+    if (P.kind == K_SUB && b->dim < (3 << 15) &&
+        6 * ((size_t)P.sub.n_s << P.sub.m) + 2 * P.sub.cand_list.size() + 4 * P.sub.pid.size() +
+                2 * P.sub.tperm.size() + 64 * 1024 < lds_limit())
+        return XDG_OK;
     for (int g = 0; g < b->n_sym; ++g)
         if (std::fabs(b->chi[2 * g]) != 1.0 || b->chi[2 * g + 1] != 0.0) return XDG_OK;
     std::vector<int> pos = four_block_labels(b->n_sites, b->n_sym, b->perm.data());
