@@ -233,9 +233,10 @@ typedef struct xdg_launch_cfg {
                           applies: four blocks of at most 10 sites, tables in LDS), 2 = the
                           block-by-block form (comparisons); both give bitwise the same y */
     int xr;            /* sublattice coding with a rank index: 1 = the terms read x from a
-                          rank-addressed copy (slot = rank of the representative among the
-                          states whose top block is a minimal top; zeros where the
-                          representative is not a basis state), filled by a scatter before
+                          rank-addressed copy (slot = place of the representative among the
+                          states whose top block is a minimal top, ordered in the packed
+                          form by the contents of their blocks and otherwise by rank;
+                          zeros where the representative is not a basis state), filled by a scatter before
                           the launch: one random read per term instead of an index word and
                           x.  The copy is device memory held by the Hamiltonian (slots x the
                           row's bytes; XDG_ENOMEM when it does not fit), set up by a first call

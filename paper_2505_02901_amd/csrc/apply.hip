@@ -284,12 +284,13 @@ int pick_nv(int64_t remaining, int cap) { return (int)std::min<int64_t>(remainin
 // The few-rows loop serves blocks (or batches) of fewer rows than this.  Its
 // time grows with the rows from the first on, while the row loop takes the
 // time of one lane's chain up to about 3 10^5 rows; measured crossings (FP64,
-// one vector): rings at 6 10^4 (9252 rows 12 against 27 us, 112720 rows 47
-// against 35), sublattice blocks at 9 10^4 (6x6 triangular), 10^5 (4x6) to
+// one vector): rings between 3 10^4 and 6 10^4 (9252 rows 12 against 20 us,
+// 32066 rows 20 against 22, 58786 rows 25 against 24, with complex characters
+// 33 against 28), sublattice blocks at 9 10^4 (6x6 triangular), 10^5 (4x6) to
 // 1.6 10^5 (6x6 square).  Without a group a term is too cheap to share out
 // (184756 rows: 41 against 13 us): those blocks take small workgroups.
 static int64_t few_rows(int kind) {
-    return kind == K_U1 ? 0 : kind == K_AFF ? 1 << 16 : 3 << 15;
+    return kind == K_U1 ? 0 : kind == K_AFF ? 3 << 14 : 3 << 15;
 }
 
 // Its shape: rows per wave (about 128 (row, bond) pairs, two for every lane),
