@@ -738,16 +738,22 @@ struct VecOps {
     }
 };
 
-// The vector operations of a batch: n blocks of `slots` vector slots each, in
-// one allocation per kind (a block's slots 256-byte aligned), with `n_scal`
-// scalars per block and a step counter.
+// The vector operations of a batch: n blocks of `slots` vector slots each (a
+// block's slots 256-byte aligned, as many blocks in an allocation as fit
+// ARENA bytes, larger ones alone), with `n_scal` scalars per block and a step
+// counter.
 struct ManyOps {
     bool single;
     ManyArgs A;
     uint32_t wgs;          // workgroups of all blocks
     hipStream_t st;
     std::vector<ManyBlock> blk;
-    DevBuf buf, parts, scal, desc;
+    // (one allocation for 32 blocks of 4.8 GB took 4.4 s on every call after
+    // the first, one per block 0.2 to 4.6 s: N = 32 ring, every momentum, 20
+    // steps of 8 complex FP32 vectors 7.7 against 3.5 s)
+    static constexpr uint64_t ARENA = (uint64_t)256 << 20;
+    std::vector<DevBuf> bufs;
+    DevBuf parts, scal, desc;
     int *jdev;
     size_t n_scal;
 
@@ -758,7 +764,6 @@ struct ManyOps {
         n_scal = n_scal_;
         blk.resize(n);
         wgs = 0;
-        uint64_t bytes = 0;
         for (int i = 0; i < n; ++i) {
             ManyBlock &b = blk[i];
             b.n = (uint64_t)dims[i] * cols;
@@ -766,14 +771,20 @@ struct ManyOps {
             b.first = wgs;
             b.wgs = (uint32_t)vec_grid(b.n);
             wgs += b.wgs;
-            bytes += b.slot * slots;
         }
-        XDG_RETURN_IF(buf.alloc(bytes));
         XDG_RETURN_IF(parts.alloc(sizeof(double) * (size_t)wgs * cols));
         XDG_RETURN_IF(scal.alloc(sizeof(double) * n_scal * n + 16));
-        char *p = buf.as<char>();
-        for (int i = 0; i < n; ++i) {
+        bufs = std::vector<DevBuf>(n);
+        char *p = nullptr;
+        for (int i = 0, last = 0; i < n; ++i) {
             ManyBlock &b = blk[i];
+            if (i >= last) {   // the blocks from i on that share an allocation
+                uint64_t bytes = b.slot * slots;
+                for (last = i + 1; last < n && bytes + blk[last].slot * slots <= ARENA; ++last)
+                    bytes += blk[last].slot * slots;
+                XDG_RETURN_IF(bufs[i].alloc(bytes));
+                p = bufs[i].as<char>();
+            }
             b.buf = p;
             p += b.slot * slots;
             b.partials = parts.as<double>() + (size_t)b.first * cols;
