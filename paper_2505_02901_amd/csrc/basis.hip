@@ -1173,9 +1173,9 @@ __global__ __launch_bounds__(256) void k_map_check(const uint32_t *umap, uint64_
 // products run in labels by those blocks and go through umap.  Only for
 // characters of exactly +-1, so that no product is rounded twice.
 // Measured: 6x6 lattice numbered row by row, 12 of 36 spins up, FP64, one
-// vector 135.3 -> 3.4 ms (2.1 with the two-step packed search); 6x6 triangular
-// lattice in three blocks of 12, 12 of 36 up, three FP64 vectors 25.8 -> 10.7 ms
-// (3.7 with that search, one pass and stores next to each other).
+// vector 135.3 -> 3.4 ms (2.1 with the two-step packed search and block slots);
+// 6x6 triangular lattice in three blocks of 12, 12 of 36 up, three FP64 vectors
+// 25.8 -> 10.7 ms (3.7 with these and one pass for the three vectors).
 int basis_build_inner(xdg_basis_s *b) {
     const Plan &P = b->plan;
     if (b->dim < 1 || b->dim >= 0x7FFFFFFF || (P.flags & XDG_FLAG_HASH_INDEX)) return XDG_OK;
