@@ -168,19 +168,18 @@ inline bool ring_loop_ok(const SectorDesc &d, int kind, bool wide) {
 // LDS bytes needed to stage a sector's tables.
 template <class T>
 __host__ __device__ inline size_t stage_bytes(const SectorDesc &d, int kind, int stage_sub) {
-    size_t n = a16(sizeof(typename BondT<T>::type) * d.n_bonds);
+    // no group: the bonds are read with scalar loads, so any number of them fits
     if (kind == K_U1)
-        n += a16(4 * (size_t)d.n_sites * (d.n_up + 1)) + a16(rank_table_bytes(d));
-    if (kind != K_U1) {
-        n += a16(sizeof(typename Vec2<T>::type) * d.n_sym);
-        n += a16(sizeof(T) * 2 * (d.n_sym + 1));
-        n += a16(rank_table_bytes(d));
-        if (kind == K_AFF) n += a16(sizeof(AffineElem) * d.n_sym) + a16(4 * (size_t)d.n_sites);
-        if (kind == K_AFF && d.ring_eq)
-            n += a16(sizeof(T) * (d.n_sym + 1)) + a16(sizeof(T) * (d.n_bonds + 1));
-        if (kind == K_SUB && stage_sub) n += sub_table_bytes(d);
-        if (kind == K_SUB && stage_sub && d.xr) n += a16(xr_top_bytes(d));
-    }
+        return a16(4 * (size_t)d.n_sites * (d.n_up + 1)) + a16(rank_table_bytes(d));
+    size_t n = a16(sizeof(typename BondT<T>::type) * d.n_bonds);
+    n += a16(sizeof(typename Vec2<T>::type) * d.n_sym);
+    n += a16(sizeof(T) * 2 * (d.n_sym + 1));
+    n += a16(rank_table_bytes(d));
+    if (kind == K_AFF) n += a16(sizeof(AffineElem) * d.n_sym) + a16(4 * (size_t)d.n_sites);
+    if (kind == K_AFF && d.ring_eq)
+        n += a16(sizeof(T) * (d.n_sym + 1)) + a16(sizeof(T) * (d.n_bonds + 1));
+    if (kind == K_SUB && stage_sub) n += sub_table_bytes(d);
+    if (kind == K_SUB && stage_sub && d.xr) n += a16(xr_top_bytes(d));
     return n;
 }
 
@@ -224,7 +223,10 @@ __device__ inline void stage(const SectorDesc &d, unsigned char *smem, Staged<T>
     // their LDS addresses fit the 16 bits of a candidate
     if constexpr (KIND == K_SUB && STAGE)
         if (d.subf) off = packed_entry_bytes(d.n_sym);
-    S.bonds = stage_copy(smem, off, reinterpret_cast<const B *>(d.bonds), d.n_bonds);
+    if constexpr (KIND == K_U1)
+        S.bonds = reinterpret_cast<const B *>(d.bonds);
+    else
+        S.bonds = stage_copy(smem, off, reinterpret_cast<const B *>(d.bonds), d.n_bonds);
     S.sub = SubCtx{d.mintop, d.cand_off, d.cand_list, d.sp, d.tperm, d.n_s, d.m, d.pb};
     S.subf = false;
     S.xr_top = d.xr_top;

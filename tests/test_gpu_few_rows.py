@@ -106,3 +106,27 @@ def test_blocks_without_a_group(X, name):
             want = oracle.apply(m, basis, x.cpu().numpy())
             tol = 2e-6 if dt == torch.float32 else 1e-12
             assert np.max(np.abs(y.cpu().numpy() - want)) <= tol * max(np.max(np.abs(want)), 1e-3)
+
+
+@pytest.mark.parametrize("n,n_up,far", [(42, 40, False), (24, 3, True)])
+def test_many_bonds_without_a_group(X, n, n_up, far):
+    """6700 bonds, whose records take all but 3 KB of a compute unit's LDS:
+    repeated pairs add their couplings"""
+    rng = np.random.default_rng(3)
+    i = rng.integers(0, n - 1, 6700)
+    sites = np.stack([i, (i + (rng.integers(2, n - 1, 6700) if far else 1)) % n], 1).astype(np.int32)
+    m = W.Model("many", n, n_up, sites, rng.uniform(-1, 1, 6700), rng.uniform(-1, 1, 6700))
+    b = X.Basis.from_model(m)
+    H = X.Hamiltonian.from_model(b, m)
+    x = torch.randn(b.dim, dtype=torch.float64, device="cuda")
+    want = oracle.apply(m, oracle.basis(m), x.cpu().numpy()).real
+    s = b.states()
+    assert H.nnz == b.dim + sum(int(np.sum((s >> np.uint64(p) ^ s >> np.uint64(q)) & np.uint64(1)))
+                                for p, q in sites)
+    for run in (lambda y: H.apply(x, y), lambda y: X.xdg_apply_with_config(H.handle, x, y),
+                lambda y: X.xdg_apply_batched([H.handle], [x], [y]),
+                lambda y: X.xdg_apply_batched_noalloc([H.handle], [x], [y])):
+        y = torch.full_like(x, 3.0)
+        run(y)
+        # up to 6701 terms of size max |x|, each rounded once against a sum of that many
+        assert np.max(np.abs(y.cpu().numpy() - want)) < 6701 * 6701 * 1.2e-16 * float(x.abs().max())
