@@ -1144,7 +1144,17 @@ __global__ __launch_bounds__(APPLY_BLOCK, OCC ? OCC_WAVES : 1) void k_apply(Appl
             if (A.tile_prefix[mid] <= tile) lo = mid; else hi = mid - 1;
         }
         if (lo != cur) {
-            if (threadIdx.x == 0) s_desc = A.descs[lo];
+            // no group: a word per lane.  As one lane's copy it held 64 registers,
+            // which cost kernels of three vectors the second workgroup of a compute
+            // unit (ring N = 24, FP32 x 3: 89 -> 67 us); with the searches of the
+            // other kinds the loop spills 8 bytes more instead.
+            if constexpr (KIND == K_U1) {
+                for (uint32_t e = threadIdx.x; e < sizeof(SectorDesc) / 4; e += blockDim.x)
+                    reinterpret_cast<uint32_t *>(&s_desc)[e] =
+                        reinterpret_cast<const uint32_t *>(A.descs + lo)[e];
+            } else {
+                if (threadIdx.x == 0) s_desc = A.descs[lo];
+            }
             __syncthreads();
             stage<KIND, AC, STAGE, LOOP == LOOP_RING>(s_desc, smem, S);
             __syncthreads();
