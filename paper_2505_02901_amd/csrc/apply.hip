@@ -123,7 +123,7 @@ SectorDesc make_desc(const xdg_ham_s *h, bool single, const void *x, void *y,
     d.chi_one = b->chi_trivial;
     d.u1_adj = b->u1_adj.as<uint32_t>();
     if (h->u1_rtab.p) {
-        d.u1_rank = 1;
+        d.u1 = U1_RANK;
         d.rtab = h->u1_rtab.p;
         d.rl = h->u1_rank;
     }
@@ -293,6 +293,63 @@ static int64_t few_rows(int kind) {
     return kind == K_U1 ? 0 : kind == K_AFF ? 3 << 14 : 3 << 15;
 }
 
+// Blocks without a group: is an exchange of sites that are not neighbouring
+// numbers rare (at most one bond in eight)?
+static bool u1_near(const xdg_ham_s *h) { return 8 * h->bonds.far <= h->n_bonds; }
+
+// Far exchanges of blocks without a group go through rank tables in LDS where
+// staging them pays and the state has 32 bits; otherwise through Lin's tables.
+// Measured, FP64, one vector, Lin against rank tables: 4x6 square, 12 up, 2.7 M
+// rows 127 and 121 us; 5x6, 10 up, 30 M rows 1.74 and 1.48 ms; 4x6, 7 up, 0.35 M
+// rows 21 and 23 us; 4x4, 8 up 10.7 and 15.1 us; 6x6, 8 up (64-bit states) 2.14
+// and 2.75 ms.
+bool u1_wants_rank(const xdg_ham_s *h) {
+    const xdg_basis_s *b = h->basis;
+    return !u1_near(h) && !b->wide && b->dim >= 1 << 19;
+}
+
+static size_t bond_bytes(const xdg_ham_s *h) { return a16(sizeof(BondD) * (size_t)h->n_bonds); }
+
+// Which loop a product without a group takes: all lanes on one bond
+// (process_row_u1), or each lane on its own (process_row_own).  The first reads
+// x in order and holds several gathers in flight, but takes every bond, also
+// those whose spins are equal in most rows; so it needs a filling where a bond's
+// spins differ often enough.  `unequal`: percent of the rows in which they do.
+// Measured against the loop over own bonds (times it needs over the other's):
+//   rings, FP64, 1 vector: 1.80 at 52 % (N = 24), 1.34 at 35 % (32, 7 up), 1.01 at
+//     29 % (36, 6 up), 0.93 at 22 % (40, 5 up); 4 vectors 1.52, 1.20, 1.00, 0.83;
+//     8 vectors 1.22 at 52 % (28, 14 up), 1.10 at 44 % (32, 10 up), 0.79 at 35 %;
+//   FP32, 1 vector: 1.08 at 35 %, 0.99 at 32 % (36, 7 up); 8 vectors: 1.23 at 52 %
+//     (24), 1.06 at 39 % (36, 9 up), 0.90 at 35 %;
+//   square lattices, rank tables, FP64, 1 vector: 1.19 at 40 % (5x6, 8 up), 1.07 at
+//     37 % (5x6, 7 up), 0.92 at 31 % (4x8, 6 up); 4 vectors 1.12, 1.06, 0.89; 8
+//     vectors 0.89 at 53 % (4x6); FP32, 1 vector: 1.08 at 48 % (5x5, 9 up), 0.98 at
+//     40 %; 8 vectors 1.11 at 52 %, 0.95 at 44 % (4x8, 10 up);
+//   64-bit states, Lin's tables (6x6): FP64, 1 vector 1.08 at 36 % (8 up), 0.97 at
+//     32 %; 4 vectors 0.90 at 39 % (9 up); FP32 1.07 at 39 %, 0.97 at 36 %;
+//   fewer than 2^19 rows with far bonds: 0.94 (4x6, 7 up) and less;
+//   every pair of 24 sites coupled, 10 up: 0.88.
+static bool u1_own(const xdg_ham_s *h, bool single, int64_t cols) {
+    const xdg_basis_s *b = h->basis;
+    if (b->plan.kind != K_U1 || b->n_sites < 2) return false;
+    const int N = b->n_sites, n = b->n_up;
+    const int unequal = 200 * n * (N - n) / (N * (N - 1));
+    constexpr int never = 101;
+    int least;
+    if (u1_near(h))
+        least = cols <= 4 ? (single ? 33 : 29) : (single ? 39 : 44);
+    else if (b->dim < 1 << 19 || 6 * h->bonds.far > 5 * h->n_bonds)
+        least = never;
+    else if (b->wide)
+        least = cols <= 2 ? (single ? 38 : 36) : never;
+    else if (single)
+        least = cols <= 4 ? 41 : 48;
+    else
+        least = cols <= 2 ? 36 : cols <= 4 ? 38 : never;
+    // the own bonds are picked lane by lane from LDS
+    return unequal < least && bond_bytes(h) <= lds_budget();
+}
+
 // Its shape: rows per wave (about 128 (row, bond) pairs, two for every lane),
 // the workgroup, and its LDS behind `tables` bytes of staged tables.  False
 // where the terms of even one wave do not fit.
@@ -347,6 +404,8 @@ int apply_launch(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, 
     const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(need, gmax));
     ApplyArgs A{};
     A.one = make_desc(h, f.tsingle, x, y);
+    A.own = u1_own(h, f.single, f.cols);
+    if (A.own) A.one.u1 = U1_OWN;
     if (c.sub_form == 2) {
         A.one.subf = 0;
         A.one.bx = nullptr;
@@ -668,8 +727,24 @@ int batch_plan_host(int n, xdg_ham_s *const *hams, const void *const *xs, void *
     P->ring = 1;
     int64_t rows = 0;
     int most_bonds = 0;
+    // no group: the loop that the largest block takes alone
+    P->own = 0;
+    if (P->kind == K_U1) {
+        const xdg_ham_s *most = *std::max_element(
+            hams, hams + n, [](const xdg_ham_s *p, const xdg_ham_s *q) {
+                return p->basis->dim < q->basis->dim;
+            });
+        size_t bonds = 0;
+        for (int i = 0; i < n; ++i) bonds = std::max(bonds, bond_bytes(hams[i]));
+        P->own = u1_own(most, P->single, P->cols) && bonds <= lds_budget();
+    }
+    auto desc = [&](int i, const void *x, void *y) {
+        SectorDesc d = make_desc(hams[i], P->tsingle, x, y, relabelled);
+        if (P->own) d.u1 = U1_OWN;
+        return d;
+    };
     for (int i = 0; i < n; ++i) {
-        const SectorDesc d = make_desc(hams[i], P->tsingle, nullptr, nullptr, relabelled);
+        const SectorDesc d = desc(i, nullptr, nullptr);
         rows += d.dim;
         P->ring &= ring_loop_ok(d, P->kind, P->wide);
         most_bonds = std::max(most_bonds, d.n_bonds);
@@ -692,7 +767,7 @@ int batch_plan_host(int n, xdg_ham_s *const *hams, const void *const *xs, void *
     }
     uint64_t acc = 0;
     for (int i = 0; i < n; ++i) {
-        const SectorDesc d = make_desc(hams[i], P->tsingle, xs[i], ys[i], relabelled);
+        const SectorDesc d = desc(i, xs[i], ys[i]);
         const uint64_t tiles = (hams[i]->basis->dim + P->tile_rows - 1) / P->tile_rows;
         if (acc + tiles >= 0xFFFFFFFFull) {
             set_error("too many row tiles in the batch");
@@ -742,6 +817,7 @@ int batch_launch_raw(const BatchMeta &P, const SectorDesc *d_descs, const uint32
     A.stage_sub = P.stage_sub;
     A.occ = P.stage_sub ? occ_for(P.lds) : 0;
     A.ring = P.ring;
+    A.own = P.own;
     if (P.few) {   // one launch for all vectors
         A.few = P.few;
         A.few_off = P.few_off;

@@ -30,6 +30,11 @@ constexpr int APPLY_BLOCK = XDG_APPLY_BLOCK;
 constexpr int OCC_WAVES = 8;
 constexpr int BLOCKS_PER_1024 = 1024 / APPLY_BLOCK;   // grid scale for smaller workgroups
 
+// The loops over a launch's rows (see process_range).
+enum : int {
+    LOOP_ROW = 0, LOOP_CMP = 1, LOOP_FEW = 2, LOOP_PACKED = 3, LOOP_RING = 4, LOOP_OWN = 5
+};
+
 template <class T> struct Vec2;
 template <> struct Vec2<float> { using type = float2; };
 template <> struct Vec2<double> { using type = double2; };
@@ -45,6 +50,10 @@ __device__ __forceinline__ T fmadd(T a, T b, T c) {
 template <class T> struct BondT;
 template <> struct BondT<float> { using type = BondF; };
 template <> struct BondT<double> { using type = BondD; };
+
+// Blocks without a group: all lanes on one bond, far exchanges through Lin's
+// tables or the rank tables in LDS; or every lane on its own bonds (LOOP_OWN).
+enum : int { U1_LIN = 0, U1_RANK = 1, U1_OWN = 2 };
 
 // Everything one sector needs on the device (type-erased pointers).
 struct SectorDesc {
@@ -62,7 +71,7 @@ struct SectorDesc {
     const uint32_t *lin;         // Lin tables (U(1))
     int nlo;
     const uint32_t *u1_adj;      // U(1): C(i, k) [n_sites][n_up + 1]
-    int u1_rank;                 // U(1): stage the rank tables for far exchanges
+    int u1;                      // U(1): form of the loop, U1_*
     int n_sites, n_sym, n_bonds;
     const AffineElem *aff;
     int ring;                    // 0, 1 (all rotations), 2 (and all reflections)
@@ -126,6 +135,7 @@ struct ApplyArgs {
     int compact;                 // table searches: wave-compacted term loop
     int few;                     // rows per wave of the few-rows loop (0: another loop)
     int ring;                    // every block takes the ring loop (see ring_loop_ok)
+    int own;                     // no group: the loop over own bonds
     uint32_t few_off;            // byte offset of its terms behind the staged tables
     unsigned long long *count;   // nnz counting mode (nullptr otherwise)
 };
@@ -142,7 +152,7 @@ __host__ __device__ inline size_t sub_table_bytes(const SectorDesc &d) {
 }
 
 __host__ __device__ inline size_t rank_table_bytes(const SectorDesc &d) {
-    if (!d.rwords && !d.u1_rank) return 0;
+    if (!d.rwords && d.u1 != U1_RANK) return 0;
     // the rank-addressed x reads only its 4-byte rows of the chunks below the top block
     if (d.xr && d.xb_ent) return 0;
     if (d.xr) return ((size_t)d.xr_rows << d.rl.cb) * 4;
@@ -168,10 +178,13 @@ inline bool ring_loop_ok(const SectorDesc &d, int kind, bool wide) {
 // LDS bytes needed to stage a sector's tables.
 template <class T>
 __host__ __device__ inline size_t stage_bytes(const SectorDesc &d, int kind, int stage_sub) {
-    // no group: the bonds are read with scalar loads, so any number of them fits
-    if (kind == K_U1)
-        return a16(4 * (size_t)d.n_sites * (d.n_up + 1)) + a16(rank_table_bytes(d));
     size_t n = a16(sizeof(typename BondT<T>::type) * d.n_bonds);
+    // no group: one bond for all lanes is read with scalar loads, so any number
+    // of them fits
+    if (kind == K_U1)
+        return d.u1 == U1_OWN
+                   ? n
+                   : a16(4 * (size_t)d.n_sites * (d.n_up + 1)) + a16(rank_table_bytes(d));
     n += a16(sizeof(typename Vec2<T>::type) * d.n_sym);
     n += a16(sizeof(T) * 2 * (d.n_sym + 1));
     n += a16(rank_table_bytes(d));
@@ -214,7 +227,7 @@ __device__ inline E *stage_copy(unsigned char *smem, size_t &off, const E *src, 
 // STAGE: the sublattice tables go to LDS too (otherwise they are read from
 // global memory); a compile-time choice so that every table pointer has a
 // known address space.
-template <int KIND, class T, bool STAGE, bool RING = false>
+template <int KIND, class T, bool STAGE, int LOOP = LOOP_ROW>
 __device__ inline void stage(const SectorDesc &d, unsigned char *smem, Staged<T> &S) {
     using B = typename BondT<T>::type;
     using T2 = typename Vec2<T>::type;
@@ -223,7 +236,7 @@ __device__ inline void stage(const SectorDesc &d, unsigned char *smem, Staged<T>
     // their LDS addresses fit the 16 bits of a candidate
     if constexpr (KIND == K_SUB && STAGE)
         if (d.subf) off = packed_entry_bytes(d.n_sym);
-    if constexpr (KIND == K_U1)
+    if constexpr (KIND == K_U1 && LOOP != LOOP_OWN)
         S.bonds = reinterpret_cast<const B *>(d.bonds);
     else
         S.bonds = stage_copy(smem, off, reinterpret_cast<const B *>(d.bonds), d.n_bonds);
@@ -232,7 +245,7 @@ __device__ inline void stage(const SectorDesc &d, unsigned char *smem, Staged<T>
     S.xr_top = d.xr_top;
     S.xr_top32 = d.xr_top32;
     S.xr_w32 = d.xr_top32 != nullptr;
-    if constexpr (KIND == K_U1) {
+    if constexpr (KIND == K_U1 && LOOP != LOOP_OWN) {
         S.adj = stage_copy(smem, off, d.u1_adj, (size_t)d.n_sites * (d.n_up + 1));
         S.rtab = stage_copy(smem, off, reinterpret_cast<const uint32_t *>(d.rtab),
                             rank_table_bytes(d) / 4);
@@ -252,12 +265,12 @@ __device__ inline void stage(const SectorDesc &d, unsigned char *smem, Staged<T>
             if (d.ring)
                 for (int e = threadIdx.x; e < 2 * d.n_sites; e += blockDim.x) {
                     int from = e;
-                    if constexpr (RING)   // by the site read first (see ring_scan_big)
+                    if constexpr (LOOP == LOOP_RING)   // by the site read first (see ring_scan_big)
                         from = (e + 1) % d.n_sites == 0 ? e + 1 - d.n_sites : e + 1;
                     lg[e] = d.ring_gidx[from];
                 }
             S.ring_gidx = lg;
-            if constexpr (RING) {
+            if constexpr (LOOP == LOOP_RING) {
                 const B b0 = *reinterpret_cast<const B *>(d.bonds);
                 T *hs = reinterpret_cast<T *>(smem + off);
                 off = a16(off + sizeof(T) * ((size_t)d.n_sym + 1));
@@ -469,7 +482,7 @@ __device__ __forceinline__ void process_row_u1(const SectorDesc &d, const Staged
                 off[k] = both != 0 && both != mask;
                 at = r32;
                 if (off[k]) {
-                    if (d.u1_rank) {
+                    if (d.u1 == U1_RANK) {
                         at = (uint32_t)colex_rank<W>(S.rtab, d.rl, s ^ mask);
                     } else {
                         int u, cnt;
@@ -494,6 +507,57 @@ __device__ __forceinline__ void process_row_u1(const SectorDesc &d, const Staged
     T xd[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) xd[v] = gld(X + (size_t)row * nvec + v);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) gst(Y + base + v, (T)fmadd<A>(diag, (A)xd[v], acc[v]));
+}
+
+// A row of a block without a group, each lane walking its own unequal-spin
+// bonds (a mask of 32 bonds at a time, lowest first) with Lin's tables: the
+// same terms in the same order, and the same bits, as process_row_u1.  It waits
+// for two dependent gathers a term, but takes no bond whose spins agree, and so
+// serves fillings and lattices where most do (see u1_own): 6x6, 7 of 36 up,
+// FP64 735 -> 538 us, 3 up 37 -> 12 us; ring N = 40, 5 up, FP32 29 -> 21.7 us.
+template <class W, class T, class A, int NV>
+__device__ __forceinline__ void process_row_own(const SectorDesc &d, const Staged<A> &S,
+                                                int64_t row, int64_t nvec, int v0) {
+    using B = typename BondT<A>::type;
+    const W s = gld(reinterpret_cast<const W *>(d.reps) + row);
+    const T *X = reinterpret_cast<const T *>(d.x) + v0;
+    T *Y = reinterpret_cast<T *>(d.y) + v0;
+    const int nb = d.n_bonds;
+    A junq = 0, acc[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) acc[v] = 0;
+    const W walls = d.ring_bonds ? (s ^ rotr_n<W>(s, 1, d.n_sites)) : W(0);
+    for (int b0 = 0; b0 < nb; b0 += 32) {
+        const int bn = nb - b0 < 32 ? nb - b0 : 32;
+        uint32_t act = 0;
+        if (d.ring_bonds) {   // bond b joins sites b and b + 1: bit b of the walls
+            act = (uint32_t)(walls >> b0) & (bn == 32 ? ~0u : ((1u << bn) - 1u));
+        } else {
+            for (int k = 0; k < bn; ++k) {
+                const B bd = S.bonds[b0 + k];
+                act |= (((uint32_t)(s >> bd.i) ^ (uint32_t)(s >> bd.j)) & 1u) << k;
+            }
+        }
+        while (act) {
+            const int b = b0 + __builtin_ctz(act);
+            act &= act - 1;
+            const B bd = S.bonds[b];
+            junq += bd.jz;
+            int u, cnt;
+            const auto at = locate<W, K_U1, A>(d, S, s ^ ((W(1) << bd.i) | (W(1) << bd.j)), u, cnt);
+            const T *q = X + (sizeof(W) == 4 ? (uint64_t)(uint32_t)at * (uint32_t)nvec
+                                             : (uint64_t)at * (uint64_t)nvec);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) acc[v] = fmadd<A>(bd.h, (A)gld(q + v), acc[v]);
+        }
+    }
+    const size_t base = (size_t)row * nvec;
+    const A diag = (A)d.jz_quarter - A(0.5) * junq;
+    T xd[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) xd[v] = gld(X + base + v);
 #pragma unroll
     for (int v = 0; v < NV; ++v) gst(Y + base + v, (T)fmadd<A>(diag, (A)xd[v], acc[v]));
 }
@@ -1042,15 +1106,13 @@ __device__ __forceinline__ void process_few(const SectorDesc &d, const Staged<A>
     }
 }
 
-enum : int { LOOP_ROW = 0, LOOP_CMP = 1, LOOP_FEW = 2, LOOP_PACKED = 3, LOOP_RING = 4 };
-
 // rows [r0, r1) of a sector.  LOOP_CMP: windows of CMP_ROWS rows per wave
 // (every lane of a wave takes part in its permutes; `first` and `stride`
 // count lanes, so wave w of the launch starts at window w); LOOP_FEW: `few`
 // rows per wave, all vectors; otherwise a lane per row, reading the
 // rank-addressed x when XR.  LOOP_PACKED: the lane-per-row loop of a single
 // block in the packed sublattice form and nothing else (see launch_nv);
-// LOOP_RING: the rows of process_ring.
+// LOOP_RING: the rows of process_ring; LOOP_OWN: those of process_row_own.
 template <class W, int KIND, class T, class A, bool CPLX, int NV, int LOOP, int XR, bool PIPE>
 __device__ __forceinline__ void process_range(const SectorDesc &d, const Staged<A> &S, int64_t r0,
                                               int64_t r1, int64_t first, int64_t stride,
@@ -1088,10 +1150,13 @@ __device__ __forceinline__ void process_range(const SectorDesc &d, const Staged<
             process_window<W, KIND, T, A, CPLX, NV>(d, S, w0, r1, nvec, v0);
     } else {
         for (int64_t row = r0 + first; row < r1; row += stride)
-            if constexpr (KIND == K_U1)
+            if constexpr (LOOP == LOOP_OWN)
+                process_row_own<W, T, A, NV>(d, S, row, nvec, v0);
+            else if constexpr (KIND == K_U1)
                 process_row_u1<W, T, A, NV>(d, S, row, nvec, v0);
             else
-            process_row<W, KIND, T, A, CPLX, NV, XR, PIPE, LOOP == LOOP_PACKED>(d, S, row, nvec, v0);
+                process_row<W, KIND, T, A, CPLX, NV, XR, PIPE, LOOP == LOOP_PACKED>(d, S, row, nvec,
+                                                                                    v0);
     }
 }
 
@@ -1123,7 +1188,7 @@ __global__ __launch_bounds__(APPLY_BLOCK, OCC ? OCC_WAVES : 1) void k_apply(Appl
     Staged<AC> S;
     if (LOOP == LOOP_PACKED || A.descs == nullptr) {
         const SectorDesc &d = A.one;
-        stage<KIND, AC, STAGE, LOOP == LOOP_RING>(d, smem, S);
+        stage<KIND, AC, STAGE, LOOP>(d, smem, S);
         __syncthreads();
         const int64_t stride = (int64_t)gridDim.x * blockDim.x;
         process_range<W, KIND, T, AC, CPLX, NV, LOOP, XR, PIPE>(
@@ -1156,7 +1221,7 @@ __global__ __launch_bounds__(APPLY_BLOCK, OCC ? OCC_WAVES : 1) void k_apply(Appl
                 if (threadIdx.x == 0) s_desc = A.descs[lo];
             }
             __syncthreads();
-            stage<KIND, AC, STAGE, LOOP == LOOP_RING>(s_desc, smem, S);
+            stage<KIND, AC, STAGE, LOOP>(s_desc, smem, S);
             __syncthreads();
             cur = lo;
         }
@@ -1254,6 +1319,10 @@ int launch_nv(int nv, const ApplyArgs &A, unsigned grid, unsigned block, size_t 
         if (!A.descs && A.stage_sub && A.one.subf && A.one.bx && !cmp && !A.few)
             f = occ ? apply_kernel<W, KIND, T, AC, CPLX, true, true, LOOP_PACKED, XR>(nv)
                     : apply_kernel<W, KIND, T, AC, CPLX, true, false, LOOP_PACKED, XR>(nv);
+    if constexpr (KIND == K_U1)
+        if (A.own)
+            f = occ ? apply_kernel<W, KIND, T, AC, CPLX, true, true, LOOP_OWN, XR>(nv)
+                    : apply_kernel<W, KIND, T, AC, CPLX, true, false, LOOP_OWN, XR>(nv);
     if constexpr (KIND == K_AFF)
         if (A.ring && !A.few)
             f = occ ? apply_kernel<W, KIND, T, AC, CPLX, true, true, LOOP_RING, XR>(nv)

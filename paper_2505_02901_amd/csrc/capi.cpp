@@ -303,10 +303,7 @@ int xdg_create_hamiltonian(xdg_basis b, int n_bonds, const int32_t *sites, const
             for (size_t e = 0; e < in.size(); ++e) in[e] = b->inner_pos[sites[e]];
             rc = upload_bonds(b->inner.get(), n_bonds, in.data(), jz, jxy, &h->inner_bonds);
         }
-        // far exchanges of a block without a group: Lin's tables for a few of
-        // them, the rank tables (LDS) where they are more than an eighth
-        if (rc == XDG_OK && b->plan.kind == XDG_SEARCH_U1 && b->dim > 0 &&
-            8 * h->bonds.far > n_bonds)
+        if (rc == XDG_OK && b->plan.kind == XDG_SEARCH_U1 && u1_wants_rank(h))
             rc = u1_rank_tables(b, &h->u1_rtab, &h->u1_rank);
         if (rc != XDG_OK) {
             basis_release(h->basis);

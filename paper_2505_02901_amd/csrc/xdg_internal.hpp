@@ -288,7 +288,7 @@ struct xdg_ham_s {
     std::vector<double> jz, jxy;
     xdg::BondSet bonds;         // in the caller's labels
     xdg::BondSet inner_bonds;   // in the labels of basis->inner, if any
-    xdg::DevBuf u1_rtab;        // U(1) with many far bonds: rank tables, layout u1_rank
+    xdg::DevBuf u1_rtab;        // no group, see u1_wants_rank: rank tables, layout u1_rank
     xdg::RankLayout u1_rank{};
     int64_t nnz = -1;
     std::mutex tune_mu;         // guards `tuned` (and the tuning runs that fill it)
@@ -345,6 +345,7 @@ inline void bondx_site(int i, int m, int pb, BondX &x) {
 int basis_build_device(xdg_basis_s *b);                 // enumerate + index
 int basis_build_inner(xdg_basis_s *b);                  // b->inner and b->umap, where they apply
 int u1_rank_tables(const xdg_basis_s *b, DevBuf *tab, RankLayout *L);
+bool u1_wants_rank(const xdg_ham_s *h);
 // Device copies of bonds (labels `sites`) for a basis planned in those labels.
 int upload_bonds(const xdg_basis_s *b, int n_bonds, const int32_t *sites, const double *jz,
                  const double *jxy, BondSet *out);
@@ -367,6 +368,7 @@ struct BatchMeta {
     uint32_t n_tiles = 0, tile_rows = 0;
     int few = 0;             // rows per wave of the few-rows loop (0: the row loop)
     int ring = 0;            // every block takes the ring loop
+    int own = 0;             // no group: the loop over own bonds
     uint32_t few_off = 0;
     int few_block = 0;       // its workgroup and LDS
     size_t few_lds = 0;
