@@ -281,16 +281,41 @@ int pick_nv(int64_t remaining, int cap) { return (int)std::min<int64_t>(remainin
 
 }  // namespace
 
-// The few-rows loop serves blocks (or batches) of fewer rows than this.  Its
-// time grows with the rows from the first on, while the row loop takes the
-// time of one lane's chain up to about 3 10^5 rows; measured crossings (FP64,
-// one vector): rings between 3 10^4 and 6 10^4 (9252 rows 12 against 20 us,
-// 32066 rows 20 against 22, 58786 rows 25 against 24, with complex characters
-// 33 against 28), sublattice blocks at 9 10^4 (6x6 triangular), 10^5 (4x6) to
-// 1.6 10^5 (6x6 square).  Without a group a term is too cheap to share out
-// (184756 rows: 41 against 13 us): those blocks take small workgroups.
-static int64_t few_rows(int kind) {
-    return kind == K_U1 ? 0 : kind == K_AFF ? 3 << 14 : 3 << 15;
+// The few-rows loop serves blocks (or batches) below a line.  Its time grows
+// with the rows from the first on; the row loop takes the time of one lane's
+// chain, which the terms of a row make long: those touch at most the
+// min(n_up, n_down) sites of the rarer spin.  So the line is in rows times
+// n_sites / min(n_up, n_down) (twice the rows at half filling), and higher
+// where a search is longer (a second scan for reflections; the packed and the
+// byte-table searches by the group's size) and, since the row loop searches
+// once per eight vectors, where there are more of those; it is lower where a
+// wave holds the terms of a single row (more than 64 bonds).  Measured, FP64,
+// one vector, row loop against few-rows loop (us), the line's number behind:
+//   rings: N = 22, 11 up 21.9 and 19.4 (64 K), N = 23, 11 up 23.7 and 24.7 (123 K);
+//     N = 28, 6 and 7 up 15.1 and 11.8 (63 K), 17.6 and 25.9 (169 K); N = 48, 5 up
+//     23.7 and 69.9 (342 K); next neighbours too: N = 22, 11 up 52.5 and 45.0 (64 K),
+//     N = 32, 6 up 31.6 and 55.1 (151 K), N = 36, 5 up 49.8 and 55.3 (75 K);
+//   rings with reflections: N = 24, 12 up 36.6 and 30.8 (114 K), N = 25, 12 up 40.7
+//     and 54.8 (209 K), N = 40, 6 up 38.3 and 63.0 (324 K);
+//   4x6 square, 48 elements: 48 bonds 151 and 117 (114 K), 96 bonds 208 and 166
+//     (74 K), 224 and 253 (100 K); 24 elements, 96 bonds 169 and 284 (145 K);
+//   6x6 square, 36 elements: 210 and 69 (75 K), 192 and 276 (325 K); 288 elements:
+//     897 and 782 (483 K); 40 sites, 160 elements: 469 and 821 (667 K);
+//   6x6 triangular, three blocks (packed inside): 916 and 403 (199 K), 877 and 1292
+//     (633 K); 27 sites by blocks: 824 and 296 (87 K), 586 and 790 (258 K).
+// Without a group a term is too cheap to share out (184756 rows: 41 against
+// 13 us).
+static int64_t few_line(const xdg_basis_s *b, int n_bonds, int64_t cols) {
+    if (b->plan.kind == K_U1) return 0;
+    const int64_t passes = std::min<int64_t>(8, (cols + 7) / 8);
+    if (b->plan.kind == K_AFF)
+        return passes * (n_bonds > 64 ? 40000 : 75000) * (b->plan.ring == 2 ? 2 : 1);
+    const bool by_group = b->plan.kind == K_TAB || b->plan.sub.packed();
+    return passes * std::min<int64_t>(500000, (n_bonds > 64 && !b->wide ? 90000 : 150000) *
+                                                  (int64_t)(by_group ? std::max(1, b->n_sym / 32) : 1));
+}
+static int64_t few_weight(const xdg_basis_s *b) {
+    return b->dim * b->n_sites / std::max(1, std::min(b->n_up, b->n_sites - b->n_up));
 }
 
 // Blocks without a group: is an exchange of sites that are not neighbouring
@@ -527,7 +552,7 @@ int apply_tuned(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, h
     const int64_t need = (b->dim + APPLY_BLOCK - 1) / APPLY_BLOCK;
     if (b->dim < (int64_t)1024 * APPLY_BLOCK) {   // small blocks: one row per lane
         LaunchCfg c{APPLY_BLOCK, (int)std::min<int64_t>(need, 1 << 30), 8};
-        c.few = b->plan.kind == K_U1 || b->dim < few_rows(b->plan.kind);
+        c.few = b->plan.kind == K_U1 || few_weight(b) < few_line(b, h->n_bonds, f.cols);
         h->tuned[key] = c;
         return apply_launch(h, x, y, nvec, dtype, st, &c);
     }
@@ -725,7 +750,7 @@ int batch_plan_host(int n, xdg_ham_s *const *hams, const void *const *xs, void *
     // compute unit
     P->few = 0;
     P->ring = 1;
-    int64_t rows = 0;
+    int64_t rows = 0, weight = 0, line = INT64_MAX;
     int most_bonds = 0;
     // no group: the loop that the largest block takes alone
     P->own = 0;
@@ -745,13 +770,16 @@ int batch_plan_host(int n, xdg_ham_s *const *hams, const void *const *xs, void *
     };
     for (int i = 0; i < n; ++i) {
         const SectorDesc d = desc(i, nullptr, nullptr);
+        const xdg_basis_s *b = relabelled ? product_basis(hams[i]) : hams[i]->basis;
         rows += d.dim;
+        weight += few_weight(b);
+        line = std::min(line, few_line(b, d.n_bonds, P->cols));
         P->ring &= ring_loop_ok(d, P->kind, P->wide);
         most_bonds = std::max(most_bonds, d.n_bonds);
         lds_full = std::max(lds_full, P->tsingle ? stage_bytes<float>(d, P->kind, 1)
                                                  : stage_bytes<double>(d, P->kind, 1));
     }
-    if (rows < few_rows(P->kind) && lds_full <= lds_budget() && P->cols < (int64_t)1 << 24) {
+    if (weight < line && lds_full <= lds_budget() && P->cols < (int64_t)1 << 24) {
         int few = 0, block = 0;
         size_t lds = 0;
         if (few_shape(rows, most_bonds, P->cplx, P->tsingle, lds_full, &few, &block, &lds)) {
