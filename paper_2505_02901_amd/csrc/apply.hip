@@ -704,6 +704,91 @@ int ham_count_nnz(xdg_ham_s *h, int64_t *nnz) {
     return XDG_OK;
 }
 
+static bool runs_packed(const xdg_ham_s *h) {
+    const xdg_basis_s *b = product_basis(h);
+    return b->plan.kind == K_SUB && b->plan.sub.packed();
+}
+
+// One part of a batch: the blocks with runs_packed == Q->packed.
+static int plan_part(int n, xdg_ham_s *const *hams, const void *const *xs, void *const *ys,
+                     const BatchMeta &P, uint32_t tile_rows, SectorDesc *descs, uint32_t *prefix,
+                     BatchPart *Q) {
+    std::vector<int> in;
+    for (int i = 0; i < n; ++i)
+        if (runs_packed(hams[i]) == (Q->packed != 0)) in.push_back(i);
+    Q->n = (int)in.size();
+    Q->kind = product_basis(hams[in[0]])->plan.kind;
+    // rows per work item: a multiple of the workgroup (default four rows per lane)
+    Q->tile_rows = tile_rows ? (tile_rows + APPLY_BLOCK - 1) / APPLY_BLOCK * APPLY_BLOCK
+                             : 4 * APPLY_BLOCK;
+    size_t lds_full = 0, lds_part = 0;
+    // few rows in all: terms shared out over the lanes, about four items per
+    // compute unit
+    Q->ring = 1;
+    int64_t rows = 0, weight = 0, line = INT64_MAX;
+    int most_bonds = 0;
+    if (Q->kind == K_U1) {   // no group: the loop that the largest block takes alone
+        const xdg_ham_s *most = hams[in[0]];
+        size_t bonds = 0;
+        for (int i : in) {
+            if (hams[i]->basis->dim > most->basis->dim) most = hams[i];
+            bonds = std::max(bonds, bond_bytes(hams[i]));
+        }
+        Q->own = u1_own(most, P.single, P.cols) && bonds <= lds_budget();
+    }
+    auto desc = [&](int i, const void *x, void *y) {
+        SectorDesc d = make_desc(hams[i], P.tsingle, x, y);
+        if (Q->own) d.u1 = U1_OWN;
+        return d;
+    };
+    for (int i : in) {
+        const SectorDesc d = desc(i, nullptr, nullptr);
+        const xdg_basis_s *b = product_basis(hams[i]);
+        rows += d.dim;
+        weight += few_weight(b);
+        line = std::min(line, few_line(b, d.n_bonds, P.cols));
+        Q->ring &= ring_loop_ok(d, Q->kind, P.wide);
+        most_bonds = std::max(most_bonds, d.n_bonds);
+        lds_full = std::max(lds_full, P.tsingle ? stage_bytes<float>(d, Q->kind, 1)
+                                                : stage_bytes<double>(d, Q->kind, 1));
+    }
+    if (weight < line && lds_full <= lds_budget() && P.cols < (int64_t)1 << 24) {
+        int few = 0, block = 0;
+        size_t lds = 0;
+        if (few_shape(rows, most_bonds, P.cplx, P.tsingle, lds_full, &few, &block, &lds)) {
+            const int64_t per = (int64_t)few * (block / 64);
+            const int64_t want = (rows + 4 * (int64_t)device_cu_count() - 1) /
+                                 (4 * (int64_t)device_cu_count());
+            Q->few = few;
+            Q->few_off = (uint32_t)a16(lds_full);
+            Q->few_block = block;
+            Q->few_lds = lds;
+            Q->tile_rows = (uint32_t)std::max<int64_t>(1, (want + per - 1) / per * per);
+        }
+    }
+    uint64_t acc = 0;
+    for (int k = 0; k < Q->n; ++k) {
+        const int i = in[k];
+        const SectorDesc d = desc(i, xs[i], ys[i]);
+        const uint64_t tiles = (hams[i]->basis->dim + Q->tile_rows - 1) / Q->tile_rows;
+        if (acc + tiles >= 0xFFFFFFFFull) {
+            set_error("too many row tiles in the batch");
+            return XDG_EINVAL;
+        }
+        if (prefix) prefix[k] = (uint32_t)acc;
+        acc += tiles;
+        if (descs) descs[k] = d;
+        const size_t f0 = P.tsingle ? stage_bytes<float>(d, Q->kind, 0)
+                                    : stage_bytes<double>(d, Q->kind, 0);
+        lds_part = std::max(lds_part, f0);
+    }
+    if (prefix) prefix[Q->n] = (uint32_t)acc;
+    Q->n_tiles = (uint32_t)acc;
+    Q->stage_sub = lds_full <= lds_budget();
+    Q->lds = Q->stage_sub ? lds_full : lds_part;
+    return XDG_OK;
+}
+
 int batch_plan_host(int n, xdg_ham_s *const *hams, const void *const *xs, void *const *ys,
                     int64_t nvec, int dtype, BatchMeta *P, SectorDesc *descs, uint32_t *prefix,
                     uint32_t tile_rows) {
@@ -729,89 +814,29 @@ int batch_plan_host(int n, xdg_ham_s *const *hams, const void *const *xs, void *
         set_error("bad dtype or nvec");
         return XDG_EINVAL;
     }
-    // byte-table blocks run relabelled if all of them can; sublattice blocks
-    // mix freely (one kernel serves both)
-    bool relabelled = true;
-    if (b0->plan.kind == K_TAB)
-        for (int i = 0; i < n; ++i) relabelled &= hams[i]->basis->inner != nullptr;
-    P->n = n;
-    P->kind = relabelled ? product_basis(hams[0])->plan.kind : b0->plan.kind;
     P->wide = b0->wide;
     P->single = dtype_single(dtype);
     P->acc64 = !P->single || !(b0->plan.flags & XDG_FLAG_F32_ACCUMULATE);
     P->tsingle = P->single && !P->acc64;
     P->cplx = any_cplx;
     P->cols = (dtype_complex(dtype) && !any_cplx) ? 2 * nvec : nvec;
-    // rows per work item: a multiple of the workgroup (default four rows per lane)
-    P->tile_rows = tile_rows ? (tile_rows + APPLY_BLOCK - 1) / APPLY_BLOCK * APPLY_BLOCK
-                             : 4 * APPLY_BLOCK;
-    size_t lds_full = 0, lds_part = 0;
-    // few rows in all: terms shared out over the lanes, about four items per
-    // compute unit
-    P->few = 0;
-    P->ring = 1;
-    int64_t rows = 0, weight = 0, line = INT64_MAX;
-    int most_bonds = 0;
-    // no group: the loop that the largest block takes alone
-    P->own = 0;
-    if (P->kind == K_U1) {
-        const xdg_ham_s *most = *std::max_element(
-            hams, hams + n, [](const xdg_ham_s *p, const xdg_ham_s *q) {
-                return p->basis->dim < q->basis->dim;
-            });
-        size_t bonds = 0;
-        for (int i = 0; i < n; ++i) bonds = std::max(bonds, bond_bytes(hams[i]));
-        P->own = u1_own(most, P->single, P->cols) && bonds <= lds_budget();
+    // the parts: every block runs the search that its products run alone, so that
+    // a batch gives the same bits
+    P->n_parts = 0;
+    int placed = 0;
+    for (const bool packed : {true, false}) {
+        int in_part = 0;
+        for (int i = 0; i < n; ++i) in_part += runs_packed(hams[i]) == packed;
+        if (!in_part) continue;
+        BatchPart &Q = P->part[P->n_parts];
+        Q = BatchPart{};
+        Q.packed = packed;
+        Q.first = placed;
+        XDG_RETURN_IF(plan_part(n, hams, xs, ys, *P, tile_rows, descs ? descs + placed : nullptr,
+                                prefix ? prefix + placed + P->n_parts : nullptr, &Q));
+        placed += in_part;
+        ++P->n_parts;
     }
-    auto desc = [&](int i, const void *x, void *y) {
-        SectorDesc d = make_desc(hams[i], P->tsingle, x, y, relabelled);
-        if (P->own) d.u1 = U1_OWN;
-        return d;
-    };
-    for (int i = 0; i < n; ++i) {
-        const SectorDesc d = desc(i, nullptr, nullptr);
-        const xdg_basis_s *b = relabelled ? product_basis(hams[i]) : hams[i]->basis;
-        rows += d.dim;
-        weight += few_weight(b);
-        line = std::min(line, few_line(b, d.n_bonds, P->cols));
-        P->ring &= ring_loop_ok(d, P->kind, P->wide);
-        most_bonds = std::max(most_bonds, d.n_bonds);
-        lds_full = std::max(lds_full, P->tsingle ? stage_bytes<float>(d, P->kind, 1)
-                                                 : stage_bytes<double>(d, P->kind, 1));
-    }
-    if (weight < line && lds_full <= lds_budget() && P->cols < (int64_t)1 << 24) {
-        int few = 0, block = 0;
-        size_t lds = 0;
-        if (few_shape(rows, most_bonds, P->cplx, P->tsingle, lds_full, &few, &block, &lds)) {
-            const int64_t per = (int64_t)few * (block / 64);
-            const int64_t want = (rows + 4 * (int64_t)device_cu_count() - 1) /
-                                 (4 * (int64_t)device_cu_count());
-            P->few = few;
-            P->few_off = (uint32_t)a16(lds_full);
-            P->few_block = block;
-            P->few_lds = lds;
-            P->tile_rows = (uint32_t)std::max<int64_t>(1, (want + per - 1) / per * per);
-        }
-    }
-    uint64_t acc = 0;
-    for (int i = 0; i < n; ++i) {
-        const SectorDesc d = desc(i, xs[i], ys[i]);
-        const uint64_t tiles = (hams[i]->basis->dim + P->tile_rows - 1) / P->tile_rows;
-        if (acc + tiles >= 0xFFFFFFFFull) {
-            set_error("too many row tiles in the batch");
-            return XDG_EINVAL;
-        }
-        if (prefix) prefix[i] = (uint32_t)acc;
-        acc += tiles;
-        if (descs) descs[i] = d;
-        const size_t f0 = P->tsingle ? stage_bytes<float>(d, P->kind, 0)
-                                     : stage_bytes<double>(d, P->kind, 0);
-        lds_part = std::max(lds_part, f0);
-    }
-    if (prefix) prefix[n] = (uint32_t)acc;
-    P->n_tiles = (uint32_t)acc;
-    P->stage_sub = lds_full <= lds_budget();
-    P->lds = P->stage_sub ? lds_full : lds_part;
     return XDG_OK;
 }
 
@@ -822,39 +847,40 @@ int batch_prepare(int n, xdg_ham_s *const *hams, const void *const *xs, void *co
         return XDG_EINVAL;
     }
     std::vector<SectorDesc> descs(n);
-    std::vector<uint32_t> prefix(n + 1, 0);
+    std::vector<uint32_t> prefix(n + 2, 0);
     XDG_RETURN_IF(batch_plan_host(n, hams, xs, ys, nvec, dtype, P, descs.data(), prefix.data(),
                                   tile_rows));
     XDG_RETURN_IF(P->descs.upload(descs.data(), sizeof(SectorDesc) * n));
-    XDG_RETURN_IF(P->prefix.upload(prefix.data(), sizeof(uint32_t) * (n + 1)));
+    XDG_RETURN_IF(P->prefix.upload(prefix.data(), sizeof(uint32_t) * (n + P->n_parts)));
     XDG_RETURN_IF(P->queue.alloc(sizeof(uint32_t)));
     return XDG_OK;
 }
 
-int batch_launch_raw(const BatchMeta &P, const SectorDesc *d_descs, const uint32_t *d_prefix,
-                     uint32_t *d_queue, int grid, int nv_cap, hipStream_t st) {
-    if (P.n_tiles == 0) return XDG_OK;
+static int part_launch(const BatchMeta &P, const BatchPart &Q, const SectorDesc *d_descs,
+                       const uint32_t *d_prefix, uint32_t *d_queue, int grid, int nv_cap,
+                       hipStream_t st) {
+    if (Q.n_tiles == 0) return XDG_OK;
     ApplyArgs A{};
     A.descs = d_descs;
     A.tile_prefix = d_prefix;
-    A.n_secs = P.n;
-    A.n_tiles = P.n_tiles;
-    A.tile_rows = P.tile_rows;
+    A.n_secs = Q.n;
+    A.n_tiles = Q.n_tiles;
+    A.tile_rows = Q.tile_rows;
     A.queue = d_queue;
     A.nvec = P.cols;
-    A.stage_sub = P.stage_sub;
-    A.occ = P.stage_sub ? occ_for(P.lds) : 0;
-    A.ring = P.ring;
-    A.own = P.own;
-    if (P.few) {   // one launch for all vectors
-        A.few = P.few;
-        A.few_off = P.few_off;
+    A.stage_sub = Q.stage_sub;
+    A.occ = Q.stage_sub ? occ_for(Q.lds) : 0;
+    A.ring = Q.ring;
+    A.own = Q.own;
+    if (Q.few) {   // one launch for all vectors
+        A.few = Q.few;
+        A.few_off = Q.few_off;
         A.occ = 0;
         hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, st, A.queue);
         XDG_TRY_HIP(hipGetLastError());
-        const unsigned gf = std::min<unsigned>(P.n_tiles, 2u * (unsigned)device_cu_count());
-        return launch_dispatch(P.kind, P.wide, P.single, P.acc64, P.cplx, 1, A, gf,
-                               (unsigned)P.few_block, P.few_lds, st);
+        const unsigned gf = std::min<unsigned>(Q.n_tiles, 2u * (unsigned)device_cu_count());
+        return launch_dispatch(Q.kind, P.wide, P.single, P.acc64, P.cplx, 1, A, gf,
+                               (unsigned)Q.few_block, Q.few_lds, st);
     }
     const unsigned g = (unsigned)(grid > 0 ? grid : apply_grid_for(2));
     for (int64_t v0 = 0; v0 < P.cols;) {
@@ -863,9 +889,20 @@ int batch_launch_raw(const BatchMeta &P, const SectorDesc *d_descs, const uint32
         hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, st, A.queue);
         XDG_TRY_HIP(hipGetLastError());
         XDG_RETURN_IF(
-            launch_dispatch(P.kind, P.wide, P.single, P.acc64, P.cplx, nv, A, g, APPLY_BLOCK,
-                            P.lds, st));
+            launch_dispatch(Q.kind, P.wide, P.single, P.acc64, P.cplx, nv, A, g, APPLY_BLOCK,
+                            Q.lds, st));
         v0 += nv;
+    }
+    return XDG_OK;
+}
+
+// The parts follow each other on the stream and share the queue counter.
+int batch_launch_raw(const BatchMeta &P, const SectorDesc *d_descs, const uint32_t *d_prefix,
+                     uint32_t *d_queue, int grid, int nv_cap, hipStream_t st) {
+    for (int p = 0; p < P.n_parts; ++p) {
+        const BatchPart &Q = P.part[p];
+        XDG_RETURN_IF(part_launch(P, Q, d_descs + Q.first, d_prefix + Q.first + p, d_queue, grid,
+                                  nv_cap, st));
     }
     return XDG_OK;
 }
@@ -915,7 +952,9 @@ int batch_shape_tuned(int n, xdg_ham_s *const *hams, const void *const *xs, void
     BatchShape best_shape{apply_grid_for(2), 4 * 1024, 8};
     BatchMeta meta;
     XDG_RETURN_IF(batch_plan_host(n, hams, xs, ys, nvec, dtype, &meta, nullptr, nullptr));
-    if (meta.few) {   // its shape follows from the sizes
+    bool few = true;
+    for (int p = 0; p < meta.n_parts; ++p) few &= meta.part[p].few != 0;
+    if (few) {   // its shape follows from the sizes
         g_shape_cache[key] = best_shape;
         *out = best_shape;
         return XDG_OK;
@@ -972,30 +1011,25 @@ int batch_shape_tuned(int n, xdg_ham_s *const *hams, const void *const *xs, void
 constexpr int NOALLOC_MAX_SECTORS = 128;
 constexpr size_t NOALLOC_PREFIX_OFF = 256;
 constexpr size_t NOALLOC_DESC_OFF =
-    a16(NOALLOC_PREFIX_OFF + sizeof(uint32_t) * (NOALLOC_MAX_SECTORS + 1));
+    a16(NOALLOC_PREFIX_OFF + sizeof(uint32_t) * (NOALLOC_MAX_SECTORS + 2));
 constexpr size_t NOALLOC_BYTES = NOALLOC_DESC_OFF + sizeof(SectorDesc) * NOALLOC_MAX_SECTORS;
 static __device__ __align__(256) unsigned char scratch[NOALLOC_BYTES];
 
 constexpr int FILL_PER_LAUNCH = 4;
 struct FillArgs {
     SectorDesc d[FILL_PER_LAUNCH];
-    uint32_t prefix[FILL_PER_LAUNCH + 1];
-    int first, count;
-    int last;            // 1: also write prefix[first + count] (the total)
+    uint32_t prefix[FILL_PER_LAUNCH + 2];   // the last launch also writes the entries behind
+    int first, count, n_prefix;
     unsigned char *base;
 };
-static_assert(sizeof(FillArgs) <= 2048, "fill kernel arguments");
+static_assert(sizeof(FillArgs) <= 4096, "fill kernel arguments");
 
 static __global__ void k_fill_batch(FillArgs a) {
     const int i = threadIdx.x;
-    if (i < a.count) {
-        SectorDesc *d = reinterpret_cast<SectorDesc *>(a.base + NOALLOC_DESC_OFF);
-        d[a.first + i] = a.d[i];
+    if (i < a.count)
+        reinterpret_cast<SectorDesc *>(a.base + NOALLOC_DESC_OFF)[a.first + i] = a.d[i];
+    if (i < a.n_prefix)
         reinterpret_cast<uint32_t *>(a.base + NOALLOC_PREFIX_OFF)[a.first + i] = a.prefix[i];
-    }
-    if (i == 0 && a.last)
-        reinterpret_cast<uint32_t *>(a.base + NOALLOC_PREFIX_OFF)[a.first + a.count] =
-            a.prefix[a.count];
 }
 
 static int scratch_address(unsigned char **out) {
@@ -1034,7 +1068,7 @@ int apply_batched_noalloc(int n, xdg_ham_s *const *hams, const void *const *xs,
             return XDG_EINVAL;
         }
     thread_local SectorDesc descs[NOALLOC_MAX_SECTORS];
-    thread_local uint32_t prefix[NOALLOC_MAX_SECTORS + 1];
+    thread_local uint32_t prefix[NOALLOC_MAX_SECTORS + 2];
     BatchShape sh;     // a shape tuned earlier for these blocks, else the default
     const bool tuned = batch_shape_cached(n, hams, nvec, dtype, &sh);
     BatchMeta M;
@@ -1046,9 +1080,9 @@ int apply_batched_noalloc(int n, xdg_ham_s *const *hams, const void *const *xs,
         FillArgs a{};
         a.first = first;
         a.count = std::min(FILL_PER_LAUNCH, n - first);
-        a.last = first + a.count == n;
+        a.n_prefix = a.count + (first + a.count == n ? M.n_parts : 0);
         for (int i = 0; i < a.count; ++i) a.d[i] = descs[first + i];
-        for (int i = 0; i <= a.count; ++i) a.prefix[i] = prefix[first + i];
+        for (int i = 0; i < a.n_prefix; ++i) a.prefix[i] = prefix[first + i];
         a.base = base;
         hipLaunchKernelGGL(k_fill_batch, dim3(1), dim3(64), 0, st, a);
         XDG_TRY_HIP(hipGetLastError());

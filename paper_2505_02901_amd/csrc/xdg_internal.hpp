@@ -360,12 +360,14 @@ int apply_tuned_config(xdg_ham_s *h, int dtype, int64_t nvec, LaunchCfg *out);
 int apply_batched_launch(int n, xdg_ham_s *const *hams, const void *const *xs, void *const *ys,
                          int64_t nvec, int dtype, hipStream_t st, uint32_t *d_queue,
                          int grid, int block);
-// Shape of a batched persistent launch (host side, no device memory).
-struct BatchMeta {
-    int n = 0, kind = 0;
-    bool wide = false, single = false, cplx = false, acc64 = true, tsingle = false;
-    int64_t cols = 0;
+// Shape of a batched persistent launch (host side, no device memory).  The
+// blocks of one search form are a part, a launch of its own: packed sublattice
+// blocks (in their own labels or relabelled), and all others.
+struct BatchPart {
+    int kind = 0, n = 0;
+    int first = 0;           // its blocks' place among the descriptors
     uint32_t n_tiles = 0, tile_rows = 0;
+    int packed = 0;          // every block in the packed sublattice form
     int few = 0;             // rows per wave of the few-rows loop (0: the row loop)
     int ring = 0;            // every block takes the ring loop
     int own = 0;             // no group: the loop over own bonds
@@ -375,6 +377,12 @@ struct BatchMeta {
     size_t lds = 0;
     int stage_sub = 1;
 };
+struct BatchMeta {
+    bool wide = false, single = false, cplx = false, acc64 = true, tsingle = false;
+    int64_t cols = 0;
+    int n_parts = 0;
+    BatchPart part[2];
+};
 // Batched persistent launch plan: device copies of the sector descriptors
 // and the cumulative tile counts; the queue counter is zeroed by a kernel
 // (not a memset) so that the launch can be captured into a graph.
@@ -382,8 +390,9 @@ struct BatchPlan : BatchMeta {
     DevBuf descs, prefix, queue;
 };
 struct SectorDesc;
-// Host planning of a batch: fills M, and (when not null) descs[n] and
-// prefix[n + 1] in host memory.  Allocates nothing.
+// Host planning of a batch: fills M, and (when not null) descs[n], part after
+// part, and prefix[n + n_parts] (n + 2 at most; n_p + 1 entries of each part) in
+// host memory.  Allocates nothing.
 int batch_plan_host(int n, xdg_ham_s *const *hams, const void *const *xs, void *const *ys,
                     int64_t nvec, int dtype, BatchMeta *M, SectorDesc *descs, uint32_t *prefix,
                     uint32_t tile_rows = 0);

@@ -102,3 +102,25 @@ def test_lanczos_and_correlations(X):
     pairs = [(0, 1), (0, 7), (3, 3)]
     zz = X.xdg_expect_szsz(b.handle, psi, pairs)
     assert np.max(np.abs(zz - [oracle.szsz_definition(full, amp, *p) for p in pairs])) < 1e-12
+
+
+def test_mixed_batches_keep_the_bits(X):
+    """Relabelled byte-table blocks beside one that keeps its labels: every block
+    of a batch gets the bits of its own product (the blocks in any order)."""
+    t = W.Torus((4, 2), (-2, 4), blocked=False)
+    perm, labels = t.symmetry_group(True, False)
+    m = CASES["rows20_A1"]
+    turned = m.with_sector(perm, W.gamma_characters(labels, 1j, 1.0))
+    ms = {"r": m, "s": CASES["rows20_B1"], "c": turned}
+    bs = {k: X.Basis.from_model(v) for k, v in ms.items()}
+    hs = {k: X.Hamiltonian.from_model(bs[k], v) for k, v in ms.items()}
+    for order in ("rc", "cr", "rcsc", "ccr", "src"):
+        for dt, nvec in ((torch.complex128, 1), (torch.complex64, 3), (torch.complex128, 8)):
+            xs = [torch.randn(bs[k].dim, nvec, dtype=dt, device="cuda") for k in order]
+            for f in (X.xdg_apply_batched, X.xdg_apply_batched_noalloc):
+                ys = [torch.full_like(x, 3.0) for x in xs]
+                f([hs[k].handle for k in order], xs, ys)
+                for k, x, y in zip(order, xs, ys):
+                    z = torch.full_like(x, 4.0)
+                    hs[k].apply(x, z)
+                    assert torch.equal(y, z), (order, k, dt, nvec, f.__name__)
