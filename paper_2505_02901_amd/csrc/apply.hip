@@ -295,6 +295,9 @@ int pick_nv(int64_t remaining, int cap) { return (int)std::min<int64_t>(remainin
 //     N = 28, 6 and 7 up 15.1 and 11.8 (63 K), 17.6 and 25.9 (169 K); N = 48, 5 up
 //     23.7 and 69.9 (342 K); next neighbours too: N = 22, 11 up 52.5 and 45.0 (64 K),
 //     N = 32, 6 up 31.6 and 55.1 (151 K), N = 36, 5 up 49.8 and 55.3 (75 K);
+//     with eight vectors N = 23, 11 up 31.3 and 25.1 (123 K), N = 28, 7 up 24.1 and
+//     25.8 (169 K), complex N = 25, 9 up 76.9 and 46.7 (227 K), N = 36, 6 up 61 and
+//     73 (324 K);
 //   rings with reflections: N = 24, 12 up 36.6 and 30.8 (114 K), N = 25, 12 up 40.7
 //     and 54.8 (209 K), N = 40, 6 up 38.3 and 63.0 (324 K);
 //   4x6 square, 48 elements: 48 bonds 151 and 117 (114 K), 96 bonds 208 and 166
@@ -305,11 +308,15 @@ int pick_nv(int64_t remaining, int cap) { return (int)std::min<int64_t>(remainin
 //     (633 K); 27 sites by blocks: 824 and 296 (87 K), 586 and 790 (258 K).
 // Without a group a term is too cheap to share out (184756 rows: 41 against
 // 13 us).
-static int64_t few_line(const xdg_basis_s *b, int n_bonds, int64_t cols) {
+static int64_t few_line(const xdg_basis_s *b, int n_bonds, int64_t cols, bool cplx) {
     if (b->plan.kind == K_U1) return 0;
     const int64_t passes = std::min<int64_t>(8, (cols + 7) / 8);
-    if (b->plan.kind == K_AFF)
-        return passes * (n_bonds > 64 ? 40000 : 75000) * (b->plan.ring == 2 ? 2 : 1);
+    if (b->plan.kind == K_AFF) {
+        // (its searches are short enough for the gathers of many vectors to count)
+        const bool twice = b->plan.ring == 2;
+        const int64_t gathers = cols < 8 || twice ? 100 : cplx ? 250 : 160;
+        return std::max(100 * passes, gathers) * (n_bonds > 64 ? 400 : 750) * (twice ? 2 : 1);
+    }
     const bool by_group = b->plan.kind == K_TAB || b->plan.sub.packed();
     return passes * std::min<int64_t>(500000, (n_bonds > 64 && !b->wide ? 90000 : 150000) *
                                                   (int64_t)(by_group ? std::max(1, b->n_sym / 32) : 1));
@@ -481,7 +488,7 @@ int apply_launch(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, 
     // few rows: terms shared out over the lanes (never with an explicit shape)
     int few = 0, few_block = 0;
     size_t few_lds = 0;
-    if (c.few && b->plan.kind != K_U1 && !xr_on && A.stage_sub && f.cols < (int64_t)1 << 24 &&
+    if (c.few && !xr_on && A.stage_sub && f.cols < (int64_t)1 << 24 &&
         few_shape(b->dim, h->n_bonds, f.cplx_kernel, f.tsingle, lds, &few, &few_block, &few_lds)) {
         A.few = few;
         A.few_off = (uint32_t)a16(lds);
@@ -491,11 +498,16 @@ int apply_launch(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, 
         return launch_dispatch(b->plan.kind, b->wide, f.single, f.acc64, f.cplx_kernel, 1, A,
                                (unsigned)g, (unsigned)few_block, few_lds, st);
     }
-    // no group, few rows: nothing to stage, so workgroups small enough for two
-    // on every compute unit
+    // fewer rows than fill the chip.  No group: nothing to stage, so workgroups
+    // small enough for two on every compute unit.  Sublattice coding: one on every
+    // compute unit, of at least 256 lanes, which stage the tables together (4x6
+    // square, 112800 rows, FP64: 120 -> 105 us; 5x5, 104384 rows: 470 -> 418 us).
     unsigned lanes = block, groups = grid;
-    if (c.few && b->plan.kind == K_U1) {
+    if (c.small && b->plan.kind == K_U1) {
         while (lanes > 64 && b->dim < (int64_t)2 * lanes * device_cu_count()) lanes /= 2;
+        groups = (unsigned)((b->dim + lanes - 1) / lanes);
+    } else if (c.small && b->plan.kind == K_SUB && !xr_on) {
+        while (lanes > 256 && 2 * b->dim <= (int64_t)lanes * device_cu_count()) lanes /= 2;
         groups = (unsigned)((b->dim + lanes - 1) / lanes);
     }
     const int cap = std::min(c.nv > 0 ? c.nv : 8,
@@ -552,7 +564,8 @@ int apply_tuned(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, h
     const int64_t need = (b->dim + APPLY_BLOCK - 1) / APPLY_BLOCK;
     if (b->dim < (int64_t)1024 * APPLY_BLOCK) {   // small blocks: one row per lane
         LaunchCfg c{APPLY_BLOCK, (int)std::min<int64_t>(need, 1 << 30), 8};
-        c.few = b->plan.kind == K_U1 || few_weight(b) < few_line(b, h->n_bonds, f.cols);
+        c.small = 1;
+        c.few = few_weight(b) < few_line(b, h->n_bonds, f.cols, f.cplx_kernel);
         h->tuned[key] = c;
         return apply_launch(h, x, y, nvec, dtype, st, &c);
     }
@@ -746,7 +759,7 @@ static int plan_part(int n, xdg_ham_s *const *hams, const void *const *xs, void 
         const xdg_basis_s *b = product_basis(hams[i]);
         rows += d.dim;
         weight += few_weight(b);
-        line = std::min(line, few_line(b, d.n_bonds, P.cols));
+        line = std::min(line, few_line(b, d.n_bonds, P.cols, P.cplx));
         Q->ring &= ring_loop_ok(d, Q->kind, P.wide);
         most_bonds = std::max(most_bonds, d.n_bonds);
         lds_full = std::max(lds_full, P.tsingle ? stage_bytes<float>(d, Q->kind, 1)
@@ -869,6 +882,7 @@ static int part_launch(const BatchMeta &P, const BatchPart &Q, const SectorDesc 
     A.queue = d_queue;
     A.nvec = P.cols;
     A.stage_sub = Q.stage_sub;
+    A.packed = Q.packed;
     A.occ = Q.stage_sub ? occ_for(Q.lds) : 0;
     A.ring = Q.ring;
     A.own = Q.own;

@@ -32,8 +32,16 @@ constexpr int BLOCKS_PER_1024 = 1024 / APPLY_BLOCK;   // grid scale for smaller 
 
 // The loops over a launch's rows (see process_range).
 enum : int {
-    LOOP_ROW = 0, LOOP_CMP = 1, LOOP_FEW = 2, LOOP_PACKED = 3, LOOP_RING = 4, LOOP_OWN = 5
+    LOOP_ROW = 0, LOOP_CMP = 1, LOOP_FEW = 2, LOOP_PACKED = 3, LOOP_RING = 4, LOOP_OWN = 5,
+    LOOP_BLOCKS = 6, LOOP_BATCH_PACKED = 7, LOOP_BATCH_BLOCKS = 8
 };
+// Sublattice searches: either, the packed one, the one by blocks.
+enum : int { FORM_ANY = 0, FORM_PACKED = 1, FORM_BLOCKS = 2 };
+constexpr int form_of_loop(int loop) {
+    return loop == LOOP_PACKED || loop == LOOP_BATCH_PACKED   ? FORM_PACKED
+           : loop == LOOP_BLOCKS || loop == LOOP_BATCH_BLOCKS ? FORM_BLOCKS
+                                                              : FORM_ANY;
+}
 
 template <class T> struct Vec2;
 template <> struct Vec2<float> { using type = float2; };
@@ -136,6 +144,7 @@ struct ApplyArgs {
     int few;                     // rows per wave of the few-rows loop (0: another loop)
     int ring;                    // every block takes the ring loop (see ring_loop_ok)
     int own;                     // no group: the loop over own bonds
+    int packed;                  // batch: every block in the packed sublattice form
     uint32_t few_off;            // byte offset of its terms behind the staged tables
     unsigned long long *count;   // nnz counting mode (nullptr otherwise)
 };
@@ -291,18 +300,32 @@ __device__ inline void stage(const SectorDesc &d, unsigned char *smem, Staged<T>
             if constexpr (STAGE) {
                 const size_t NV = (size_t)d.n_s << d.m;
                 const size_t ntp = (size_t)d.n_perm * 2 * ((size_t)1 << d.pb);
-                if (d.subf) {
+                constexpr int form = form_of_loop(LOOP);
+                auto packed = [&] {
                     const PackedSrc src{d.pk_tab, d.pk_cand, d.sp, d.tperm, d.n_pk, d.pk_nb,
                                         d.n_sym, d.n_perm, d.m, d.pb};
                     S.pk = stage_packed(src, smem, off);
                     S.subf = true;
-                } else {
+                    // unused, but addresses in LDS as in the other form: a pointer
+                    // into either memory makes every table read a flat one (5x6
+                    // square numbered row by row, 15 up, FP64: 2.70 against 2.59 ms)
+                    if constexpr (form == FORM_ANY) {
+                        const uint16_t *lds = reinterpret_cast<const uint16_t *>(smem);
+                        S.sub.mintop = S.sub.cand_list = S.sub.tperm = lds;
+                        S.sub.cand_off = S.sub.sp = reinterpret_cast<const uint32_t *>(smem);
+                    }
+                };
+                auto blocks = [&] {
                     S.sub.mintop = stage_copy(smem, off, d.mintop, NV);
                     S.sub.cand_off = stage_copy(smem, off, d.cand_off, NV + 1);
                     S.sub.cand_list = stage_copy(smem, off, d.cand_list, d.n_cand);
                     S.sub.sp = stage_copy(smem, off, d.sp, (size_t)d.n_sym * d.n_s);
                     S.sub.tperm = stage_copy(smem, off, d.tperm, ntp);
-                }
+                };
+                if constexpr (form == FORM_PACKED) packed();
+                else if constexpr (form == FORM_BLOCKS) blocks();
+                else if (d.subf) packed();
+                else blocks();
                 // the first-rank table at one LDS address whatever its entry
                 // size (both pointers always address LDS here: LDS reads)
                 unsigned char *tp = smem + off;
@@ -345,8 +368,9 @@ template <> struct IndexT<uint32_t> { using type = int32_t; };
 // the packed sublattice search (computed here from t when null and that
 // search is on).  XR: the position is the slot in the rank-addressed x
 // (sublattice coding with d.xr set); XR = 2: every character is 1, so the
-// search does not keep the element (u is left unset).
-template <class W, int KIND, class T, int XR = 0, bool PACKED = false>
+// search does not keep the element (u is left unset).  FORM: the sublattice
+// search of the block, FORM_ANY where the sector tells.
+template <class W, int KIND, class T, int XR = 0, int FORM = FORM_ANY>
 __device__ __forceinline__ typename IndexT<W>::type locate(const SectorDesc &d, const Staged<T> &S,
                                                            W t, int &u, int &cnt,
                                                            const SubKey *key = nullptr) {
@@ -366,7 +390,7 @@ __device__ __forceinline__ typename IndexT<W>::type locate(const SectorDesc &d, 
             else
                 aff_search<W>(S.aff, d.n_sym, d.n_sites, t, rep, u, cnt);
         } else if constexpr (KIND == K_SUB) {
-            if (PACKED || S.subf) {
+            if (FORM == FORM_PACKED || (FORM == FORM_ANY && S.subf)) {
                 uint32_t top, low;
                 sub_search_packed<XR != 2>(S.pk, key ? *key : sub_key<W>(t, d.m, d.pb), top, low,
                                            u, cnt);
@@ -562,9 +586,9 @@ __device__ __forceinline__ void process_row_own(const SectorDesc &d, const Stage
     for (int v = 0; v < NV; ++v) gst(Y + base + v, (T)fmadd<A>(diag, (A)xd[v], acc[v]));
 }
 
-// PACKED: the block runs the packed sublattice search with its bond records.
+// FORM: as for locate (the packed one comes with its bond records).
 template <class W, int KIND, class T, class A, bool CPLX, int NV, int XR = 0,
-          bool PIPE = false, bool PACKED = false>
+          bool PIPE = false, int FORM = FORM_ANY>
 __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A> &S, int64_t row,
                                             int64_t nvec, int v0) {
     static_assert(KIND != K_U1, "process_row_u1");
@@ -601,7 +625,7 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
     };
     // PIPE: the pending term.  ALL: every term has a slot (packed form of the
     // rank-addressed x), so none is tested; the first one pending adds 0 * 0.
-    constexpr bool ALL = PACKED && XR != 0;
+    constexpr bool ALL = FORM == FORM_PACKED && XR != 0;
     bool p_ok = ALL;
     A p_ar = 0, p_ai = 0;
     T p_x[NV * C];
@@ -610,7 +634,7 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
     // key: the packed sublattice search's key of the term's state, if given
     auto term = [&](const B &bd, W t, const SubKey *key) {
         int u, cnt;
-        auto idx = locate<W, KIND, A, XR, PACKED>(d, S, t, u, cnt, key);
+        auto idx = locate<W, KIND, A, XR, FORM>(d, S, t, u, cnt, key);
         A hs = bd.h;
         if constexpr (KIND == K_SUB && XR == 0)
             if (d.umap && idx >= 0) idx = user_pos<A>(d, idx, hs);
@@ -694,8 +718,8 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
         // that neighbouring rows walk similar table entries and look up
         // neighbouring index words.
         bool done = false;
-        if constexpr (KIND == K_SUB) {
-            if (PACKED || (S.subf && d.bx)) {
+        if constexpr (KIND == K_SUB && FORM != FORM_BLOCKS) {
+            if (FORM == FORM_PACKED || (S.subf && d.bx)) {
                 // packed form: the bond comes with scalar loads, the term's key
                 // is the row's key with the bond's bits flipped
                 const SubKey kr = sub_key<W>(s, d.m, d.pb);
@@ -714,8 +738,7 @@ __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A>
                 done = true;
             }
         }
-        if constexpr (!PACKED)
-          if (!done) {
+        if constexpr (FORM != FORM_PACKED) if (!done) {
             for (int b = 0; b < nb; ++b) {
                 const B bd = S.bonds[b];
                 if (((s >> bd.i) & 1) == ((s >> bd.j) & 1)) continue;
@@ -1110,14 +1133,16 @@ __device__ __forceinline__ void process_few(const SectorDesc &d, const Staged<A>
 // (every lane of a wave takes part in its permutes; `first` and `stride`
 // count lanes, so wave w of the launch starts at window w); LOOP_FEW: `few`
 // rows per wave, all vectors; otherwise a lane per row, reading the
-// rank-addressed x when XR.  LOOP_PACKED: the lane-per-row loop of a single
-// block in the packed sublattice form and nothing else (see launch_nv);
+// rank-addressed x when XR.  LOOP_PACKED, LOOP_BLOCKS: the lane-per-row loop of
+// a single block in that sublattice form and nothing else, LOOP_BATCH_*: of a
+// batch of such blocks (see launch_nv);
 // LOOP_RING: the rows of process_ring; LOOP_OWN: those of process_row_own.
 template <class W, int KIND, class T, class A, bool CPLX, int NV, int LOOP, int XR, bool PIPE>
 __device__ __forceinline__ void process_range(const SectorDesc &d, const Staged<A> &S, int64_t r0,
                                               int64_t r1, int64_t first, int64_t stride,
                                               int64_t nvec, int v0, int few,
                                               unsigned char *few_terms) {
+    constexpr int form = form_of_loop(LOOP);
     if constexpr (LOOP == LOOP_FEW) {
         process_few<W, KIND, T, A, CPLX>(
             d, S, r0, r1, (first - lane_id()) / 64, stride / 64, few,
@@ -1155,8 +1180,7 @@ __device__ __forceinline__ void process_range(const SectorDesc &d, const Staged<
             else if constexpr (KIND == K_U1)
                 process_row_u1<W, T, A, NV>(d, S, row, nvec, v0);
             else
-                process_row<W, KIND, T, A, CPLX, NV, XR, PIPE, LOOP == LOOP_PACKED>(d, S, row, nvec,
-                                                                                    v0);
+                process_row<W, KIND, T, A, CPLX, NV, XR, PIPE, form>(d, S, row, nvec, v0);
     }
 }
 
@@ -1180,13 +1204,15 @@ template <class W, int KIND, class T, class AC, bool CPLX, int NV, bool STAGE, b
           int LOOP, int XR>
 __global__ __launch_bounds__(APPLY_BLOCK, OCC ? OCC_WAVES : 1) void k_apply(ApplyArgs A) {
     // the sublattice row loop pipelines its gathers
-    constexpr bool PIPE = KIND == K_SUB && (LOOP == LOOP_ROW || LOOP == LOOP_PACKED);
+    constexpr bool SINGLE = LOOP == LOOP_PACKED || LOOP == LOOP_BLOCKS;
+    constexpr bool BATCH = LOOP == LOOP_BATCH_PACKED || LOOP == LOOP_BATCH_BLOCKS;
+    constexpr bool PIPE = KIND == K_SUB && (LOOP == LOOP_ROW || SINGLE || BATCH);
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char *few_terms = smem + A.few_off;
     __shared__ uint32_t s_tile;
     __shared__ SectorDesc s_desc;
     Staged<AC> S;
-    if (LOOP == LOOP_PACKED || A.descs == nullptr) {
+    if constexpr (!BATCH) if (SINGLE || A.descs == nullptr) {
         const SectorDesc &d = A.one;
         stage<KIND, AC, STAGE, LOOP>(d, smem, S);
         __syncthreads();
@@ -1197,8 +1223,7 @@ __global__ __launch_bounds__(APPLY_BLOCK, OCC ? OCC_WAVES : 1) void k_apply(Appl
         return;
     }
     // persistent: (sector, row tile) items from one queue
-    if constexpr (LOOP != LOOP_PACKED)
-    for (int cur = -1;;) {
+    if constexpr (!SINGLE) for (int cur = -1;;) {
         if (threadIdx.x == 0) s_tile = atomicAdd(A.queue, 1u);
         __syncthreads();
         const uint32_t tile = s_tile;
@@ -1292,57 +1317,69 @@ void (*apply_kernel(int nv))(ApplyArgs) {
     return nullptr;
 }
 
-// The compacted term loop exists for the table searches (sublattice coding,
-// byte tables) with at most two vectors per pass.
-template <int KIND>
-constexpr bool has_compact() { return KIND == K_SUB || KIND == K_TAB; }
-
-template <class W, int KIND, class T, class AC, bool CPLX, bool STAGE, bool OCC>
-void (*apply_kernel_loop(int nv, bool compact))(ApplyArgs) {
-    if constexpr (has_compact<KIND>())
-        if (compact && nv <= 2)
-            return apply_kernel<W, KIND, T, AC, CPLX, STAGE, OCC, LOOP_CMP, 0>(nv);
-    return apply_kernel<W, KIND, T, AC, CPLX, STAGE, OCC, LOOP_ROW, 0>(nv);
-}
-
 template <class W, int KIND, class T, class AC, bool CPLX, int XR>
 int launch_nv(int nv, const ApplyArgs &A, unsigned grid, unsigned block, size_t lds,
               hipStream_t st) {
     void (*f)(ApplyArgs) = nullptr;
     const bool occ = A.occ && nv * (CPLX ? 2 : 1) <= occ_scalars(XR);
-    const bool cmp = A.compact != 0;
-    // One block in the packed form: a kernel of that loop alone.  The general
-    // one holds the searches of every form twice (single and batched) and
-    // keeps 46 vector and 86 scalar registers of its 64-register copy in
-    // memory.
-    if constexpr (KIND == K_SUB && !(XR == 2 && CPLX))
-        if (!A.descs && A.stage_sub && A.one.subf && A.one.bx && !cmp && !A.few)
-            f = occ ? apply_kernel<W, KIND, T, AC, CPLX, true, true, LOOP_PACKED, XR>(nv)
-                    : apply_kernel<W, KIND, T, AC, CPLX, true, false, LOOP_PACKED, XR>(nv);
-    if constexpr (KIND == K_U1)
-        if (A.own)
-            f = occ ? apply_kernel<W, KIND, T, AC, CPLX, true, true, LOOP_OWN, XR>(nv)
-                    : apply_kernel<W, KIND, T, AC, CPLX, true, false, LOOP_OWN, XR>(nv);
-    if constexpr (KIND == K_AFF)
-        if (A.ring && !A.few)
-            f = occ ? apply_kernel<W, KIND, T, AC, CPLX, true, true, LOOP_RING, XR>(nv)
-                    : apply_kernel<W, KIND, T, AC, CPLX, true, false, LOOP_RING, XR>(nv);
-    if (f) {
-    } else if constexpr (XR == 2 && CPLX) {
-        set_error("internal: the trivial-character kernels serve real blocks");
-        return XDG_EINVAL;
-    } else if constexpr (XR != 0) {   // row loop, tables in LDS
-        if (A.stage_sub)
-            f = occ ? apply_kernel<W, KIND, T, AC, CPLX, true, true, LOOP_ROW, XR>(nv)
-                    : apply_kernel<W, KIND, T, AC, CPLX, true, false, LOOP_ROW, XR>(nv);
-    } else if (A.few && (KIND != K_SUB || A.stage_sub)) {
-        f = k_apply<W, KIND, T, AC, CPLX, 1, true, false, LOOP_FEW, 0>;
-    } else if (KIND != K_SUB || A.stage_sub)
-        // only the sublattice kind has tables that may stay in global memory
-        f = occ ? apply_kernel_loop<W, KIND, T, AC, CPLX, true, true>(nv, cmp)
-                : apply_kernel_loop<W, KIND, T, AC, CPLX, true, false>(nv, cmp);
-    else if constexpr (KIND == K_SUB)
-        f = apply_kernel_loop<W, KIND, T, AC, CPLX, false, false>(nv, cmp);
+    // the compacted loop takes passes of one or two vectors, the row loop the others
+    const bool cmp = A.compact && nv <= 2;
+    if constexpr (KIND == K_SUB && !(XR == 2 && CPLX)) {
+        // The row loop of each search, for one block and for a batch, is a kernel of
+        // its own: with both searches and both launches in one it held 128 registers
+        // (one block: packed 47, by blocks 45), and its 64-register copy kept 290
+        // bytes in memory.  5x6 square numbered row by row, 15 up, 2.6 M rows, FP64:
+        // 2.75 ms with both, 2.59 apart; eight vectors 3.70 and 3.04 ms; a batch of
+        // two 4x6 J1-J2 blocks, 9 up: 123 and 118 us.
+        const bool packed = A.descs ? A.packed != 0 : A.one.subf && A.one.bx;
+        auto row = [&](auto loop) {
+            constexpr int L = decltype(loop)::value;
+            f = occ ? apply_kernel<W, KIND, T, AC, CPLX, true, true, L, XR>(nv)
+                    : apply_kernel<W, KIND, T, AC, CPLX, true, false, L, XR>(nv);
+        };
+        if constexpr (XR != 0) {   // single blocks with their tables in LDS
+            if (A.stage_sub && packed)
+                row(std::integral_constant<int, LOOP_PACKED>{});
+            else if (A.stage_sub)
+                row(std::integral_constant<int, LOOP_BLOCKS>{});
+        } else if (!A.stage_sub) {
+            f = cmp ? apply_kernel<W, KIND, T, AC, CPLX, false, false, LOOP_CMP, 0>(nv)
+                    : apply_kernel<W, KIND, T, AC, CPLX, false, false, LOOP_ROW, 0>(nv);
+        } else if (A.few) {
+            f = k_apply<W, KIND, T, AC, CPLX, 1, true, false, LOOP_FEW, 0>;
+        } else if (cmp) {
+            row(std::integral_constant<int, LOOP_CMP>{});
+        } else if (A.descs) {
+            if (packed)
+                row(std::integral_constant<int, LOOP_BATCH_PACKED>{});
+            else
+                row(std::integral_constant<int, LOOP_BATCH_BLOCKS>{});
+        } else if (packed) {
+            row(std::integral_constant<int, LOOP_PACKED>{});
+        } else {
+            row(std::integral_constant<int, LOOP_BLOCKS>{});
+        }
+    } else if constexpr (KIND != K_SUB) {
+        auto row = [&](auto loop) {
+            constexpr int L = decltype(loop)::value;
+            f = occ ? apply_kernel<W, KIND, T, AC, CPLX, true, true, L, 0>(nv)
+                    : apply_kernel<W, KIND, T, AC, CPLX, true, false, L, 0>(nv);
+        };
+        if constexpr (KIND == K_U1) {
+            if (A.own)
+                row(std::integral_constant<int, LOOP_OWN>{});
+            else
+                row(std::integral_constant<int, LOOP_ROW>{});
+        } else if (A.few) {
+            f = k_apply<W, KIND, T, AC, CPLX, 1, true, false, LOOP_FEW, 0>;
+        } else if (KIND == K_AFF && A.ring) {
+            if constexpr (KIND == K_AFF) row(std::integral_constant<int, LOOP_RING>{});
+        } else if (KIND == K_TAB && cmp) {
+            if constexpr (KIND == K_TAB) row(std::integral_constant<int, LOOP_CMP>{});
+        } else {
+            row(std::integral_constant<int, LOOP_ROW>{});
+        }
+    }
     if (!f) {
         set_error("no kernel for %d vectors per pass (1 to 8; the rank-addressed x: at most eight "
                   "scalars, tables in LDS)", nv);

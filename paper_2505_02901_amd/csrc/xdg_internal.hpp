@@ -264,7 +264,8 @@ struct LaunchCfg {
     int compact = -1;      // table searches: 1 = wave-compacted term loop, 0 / -1 = row loop
     int sub_form = 0;      // sublattice coding: 0 = packed form where it applies, 2 = block form
     int xr = 0;            // sublattice coding: 1 = terms read a rank-addressed copy of x
-    int few = 0;           // 1: few rows (the few-rows loop; small workgroups without a group)
+    int small = 0;         // 1: workgroups for a block that does not fill the chip
+    int few = 0;           // 1: the few-rows loop
 };
 }  // namespace xdg
 
