@@ -324,6 +324,7 @@ static int64_t few_line(const xdg_basis_s *b, int n_bonds, int64_t cols, bool cp
 static int64_t few_weight(const xdg_basis_s *b) {
     return b->dim * b->n_sites / std::max(1, std::min(b->n_up, b->n_sites - b->n_up));
 }
+bool below_few_line(const xdg_basis_s *b) { return few_weight(b) < few_line(b, 0, 1, false); }
 
 // Blocks without a group: is an exchange of sites that are not neighbouring
 // numbers rare (at most one bond in eight)?
@@ -633,11 +634,13 @@ int apply_tuned(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, h
                 c.xr = 1;
                 more.push_back(c);
             }
+        const std::string before = get_error();
         for (const LaunchCfg &c : more) {
             float ms = 0;
             if ((rc = time_cfg(c, &ms)) != XDG_OK) {
                 if (c.xr && rc == XDG_ENOMEM) {   // no room for the copy: not a candidate
                     rc = XDG_OK;
+                    set_error("%s", before.c_str());
                     continue;
                 }
                 break;

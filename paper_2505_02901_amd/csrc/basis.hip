@@ -1176,19 +1176,20 @@ __global__ __launch_bounds__(256) void k_map_check(const uint32_t *umap, uint64_
 // vector 135.3 -> 3.4 ms (2.1 with the two-step packed search and block slots);
 // 6x6 triangular lattice in three blocks of 12, 12 of 36 up, three FP64 vectors
 // 25.8 -> 10.7 ms (3.7 with these and one pass for the three vectors).
-int basis_build_inner(xdg_basis_s *b) {
+//
+// wrong: the map does not fit the block (an error of this library's, returned).
+static int build_inner(xdg_basis_s *b, uint32_t *wrong) {
     const Plan &P = b->plan;
     if (b->dim < 1 || b->dim >= 0x7FFFFFFF || (P.flags & XDG_FLAG_HASH_INDEX)) return XDG_OK;
-    if (P.kind != K_TAB &&
-        !(P.kind == K_SUB && !P.sub.packed()))
-        return XDG_OK;
-    // Few rows whose block tables leave 32 KiB of the LDS for the few-rows
-    // loop's terms beside the rank tables (32 KiB at most) take that loop in
-    // either labels and are prepared faster in one (4x6 square, 29606 rows,
-    // FP64: 89 us a product in the caller's labels, 87 in others, and 3.1
-    // against 5.0 ms before it; with 6 of 24 up 57 and 45 us, 2.9 and 4.8 ms).  Tables without that room keep them out of it
-    // (6x6 triangular lattice, 5 of 36 up: 1.99 ms a product, 0.10 in others).
-    if (P.kind == K_SUB && b->dim < (3 << 15) &&
+    if (P.kind != K_TAB && !(P.kind == K_SUB && !P.sub.packed())) return XDG_OK;
+    // Blocks below the few-rows line whose tables leave 32 KiB of the LDS for that
+    // loop's terms beside the rank tables (32 KiB at most) take it in either labels
+    // and are prepared faster in one (4x6 square, 29606 rows, FP64: 89 us a product
+    // in the caller's labels, 87 in others, and 3.1 against 5.0 ms before it; with
+    // 6 of 24 up 57 and 45 us, 2.9 and 4.8 ms: a hundred and more products make up
+    // for that).  Tables without that room keep them out of it (6x6 triangular
+    // lattice, 5 of 36 up: 1.99 ms a product, 0.10 in others).
+    if (P.kind == K_SUB && below_few_line(b) &&
         6 * ((size_t)P.sub.n_s << P.sub.m) + 2 * P.sub.cand_list.size() + 4 * P.sub.pid.size() +
                 2 * P.sub.tperm.size() + 64 * 1024 < lds_limit())
         return XDG_OK;
@@ -1213,7 +1214,6 @@ int basis_build_inner(xdg_basis_s *b) {
     DevBuf umap, bad;
     if (rc == XDG_OK && in->dim == b->dim) rc = umap.alloc(sizeof(uint32_t) * (size_t)b->dim);
     if (rc == XDG_OK) rc = bad.alloc(sizeof(uint32_t));
-    if (rc == XDG_ENOMEM) return XDG_OK;   // no room: the caller's labels serve
     XDG_RETURN_IF(rc);
     if (in->dim != b->dim || !in->n_rwords || !in->plan.sub.packed()) return XDG_OK;
     UserMapArgs A{};
@@ -1245,16 +1245,30 @@ int basis_build_inner(xdg_basis_s *b) {
     hipLaunchKernelGGL(k_map_check, dim3(grid), dim3(256), 0, 0, umap.as<uint32_t>(), A.dim,
                        bad.as<uint32_t>());
     XDG_TRY_HIP(hipGetLastError());
-    uint32_t wrong = 0;
-    XDG_RETURN_IF(copy_d2h(&wrong, bad.p, sizeof wrong, nullptr));
-    if (wrong) {
-        set_error("internal: an orbit of the relabelled sector has no place in the basis");
-        return XDG_EINVAL;
-    }
+    XDG_RETURN_IF(copy_d2h(wrong, bad.p, sizeof *wrong, nullptr));
+    if (*wrong) return XDG_EINVAL;
     std::swap(b->umap.p, umap.p);
     std::swap(b->umap.bytes, umap.bytes);
     b->inner_pos = std::move(pos);
     b->inner = std::move(in);
+    return XDG_OK;
+}
+
+// The caller's block is complete without the inner one: whatever keeps that from
+// being built (no room, a plan or an index that does not apply) leaves the block
+// in the caller's labels and the thread's last error as it was.
+int basis_build_inner(xdg_basis_s *b) {
+    const std::string before = get_error();
+    uint32_t wrong = 0;
+    const int rc = build_inner(b, &wrong);
+    if (rc == XDG_OK) return XDG_OK;
+    if (wrong) {
+        set_error("internal: an orbit of the relabelled sector has no place in the basis");
+        return rc;
+    }
+    (void)hipGetLastError();
+    XDG_TRY_HIP(hipDeviceSynchronize());   // an error that lasts
+    set_error("%s", before.c_str());
     return XDG_OK;
 }
 

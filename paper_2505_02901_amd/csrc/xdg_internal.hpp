@@ -347,6 +347,7 @@ int basis_build_device(xdg_basis_s *b);                 // enumerate + index
 int basis_build_inner(xdg_basis_s *b);                  // b->inner and b->umap, where they apply
 int u1_rank_tables(const xdg_basis_s *b, DevBuf *tab, RankLayout *L);
 bool u1_wants_rank(const xdg_ham_s *h);
+bool below_few_line(const xdg_basis_s *b);   // products take the few-rows loop (up to 64 bonds)
 // Device copies of bonds (labels `sites`) for a basis planned in those labels.
 int upload_bonds(const xdg_basis_s *b, int n_bonds, const int32_t *sites, const double *jz,
                  const double *jxy, BondSet *out);

@@ -124,3 +124,48 @@ def test_mixed_batches_keep_the_bits(X):
                     z = torch.full_like(x, 4.0)
                     hs[k].apply(x, z)
                     assert torch.equal(y, z), (order, k, dt, nvec, f.__name__)
+
+
+def test_creation_under_a_memory_limit(X):
+    """The second labelling is built only where it fits: under any limit that lets
+    the block be made alone it is made, its products are right, and no message of
+    an attempt inside is left behind."""
+    m = W.sublattice_model("triangle3", (6, 0), (0, 6), n_up=9, delta=0.3)
+    alone = dict(search=3, n_sublattices=3)
+    start = X.xdg_set_device_memory_limit(0)
+
+    def make(limit, **kw):
+        X.xdg_set_device_memory_limit(limit)
+        try:
+            b = X.Basis.from_model(m, **kw)
+        except X.XdgError as e:
+            assert e.code == X.XDG_ENOMEM, str(e)
+            b = None
+        return b, X.xdg_set_device_memory_limit(0) - start
+
+    b, one = make(0, **alone)
+    H = X.Hamiltonian.from_model(b, m)
+    x = torch.randn(b.dim, dtype=torch.float64, device="cuda")
+    want = H.apply(x, torch.empty_like(x))
+    del H, b
+    b, both = make(0)
+    del b
+    assert both > 1.5 * one
+    held = set()
+    for limit in np.linspace(one, 2.5 * both, 40).astype(int):
+        b, _ = make(start + int(limit), **alone)
+        fits = b is not None
+        del b
+        assert X.xdg_check_group(0, None) != X.XDG_OK
+        mark = X.xdg_last_error()
+        b, now = make(start + int(limit))
+        assert (b is not None) == fits, limit
+        if not fits:
+            continue
+        assert X.xdg_last_error() == mark, limit
+        held.add(now)
+        H = X.Hamiltonian.from_model(b, m)
+        y = H.apply(x, torch.full_like(x, 3.0))
+        assert float((y - want).abs().max()) < 1e-13 * float(want.abs().max()), limit
+        del H, b
+    assert held == {one, both}, (held, one, both)      # both outcomes occurred
