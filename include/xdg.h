@@ -114,6 +114,16 @@ typedef struct xdg_basis_opts {
 #define XDG_INDEX_HASH 2
 #define XDG_INDEX_RANK 3
 
+/* Second labellings: a block whose site labels hide four blocks of sites that
+ * its group respects holds the same sector in labels by those blocks too, for
+ * the products (its own representatives and index; positions and results stay
+ * the caller's).  It is kept only if it takes at most an eighth of the device
+ * memory left when the block is made, and no failure to build it fails the
+ * block.  A call that lacks memory which such labellings hold makes all blocks
+ * give them up, except those whose products were captured into a graph, and runs
+ * again: products are slower from then on, and sum a row's terms in another
+ * order (results differ in the last bits from those before). */
+
 /* Limit on the device memory the library's own buffers (bases, indices,
  * tables, Lanczos work vectors, batched plans) may hold together, in bytes;
  * 0 removes it.  An allocation beyond it fails with XDG_ENOMEM as if the
@@ -318,7 +328,8 @@ int xdg_lanczos_eigval_batched(int n, const xdg_ham *hams, const void *const *v0
  * psi = sum_j c_j v_j is accumulated in FP64, c the normalised eigenvector
  * (c_0 >= 0) of the Ritz value number `which` (0 = lowest) of the leading
  * n_iter x n_iter block of T.  The vectors v_j equal those of the first pass
- * bit for bit (same kernels, same scalars).
+ * bit for bit (same kernels, same scalars); if the block has given up a second
+ * labelling since, T is computed anew in the caller's labels first.
  *   v0, seed, prec: as passed to xdg_lanczos_eigval (prec XDG_PREC_F64 or
  *       XDG_PREC_F32VEC; the forms with reorthogonalisation are refused);
  *   alpha, beta: host double[n_iter] from xdg_lanczos_eigval;

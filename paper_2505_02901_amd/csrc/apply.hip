@@ -62,18 +62,17 @@ int launch_dispatch(int kind, bool wide, bool single, bool acc64, bool cplx, int
     return XDG_EINVAL;
 }
 
-// The sector the products run in: the relabelled one where there is one.
-const xdg_basis_s *product_basis(const xdg_ham_s *h) {
-    return h->basis->inner ? h->basis->inner.get() : h->basis;
+// The sector the products run in.
+const xdg_basis_s *product_basis(const xdg_ham_s *h, const Relabelled *in) {
+    return in ? in->basis.get() : h->basis;
 }
 
-// relabelled: through the relabelled sector where there is one
-SectorDesc make_desc(const xdg_ham_s *h, bool single, const void *x, void *y,
-                     bool relabelled = true) {
-    const xdg_basis_s *b = relabelled ? product_basis(h) : h->basis;
-    const BondSet &bonds = b == h->basis ? h->bonds : h->inner_bonds;
+SectorDesc make_desc(const xdg_ham_s *h, const Relabelled *in, bool single, const void *x,
+                     void *y) {
+    const xdg_basis_s *b = product_basis(h, in);
+    const BondSet &bonds = in ? h->inner_bonds : h->bonds;
     SectorDesc d{};
-    d.umap = b == h->basis ? nullptr : h->basis->umap.as<uint32_t>();
+    d.umap = in ? in->umap.as<uint32_t>() : nullptr;
     d.reps = b->reps.p;
     d.stab = b->stab.as<uint16_t>();
     d.dim = b->dim;
@@ -209,9 +208,10 @@ int xr_columns(int64_t cols) {
 // Fill the rank-addressed copy of x for this call (caller holds h->xr_mu):
 // wait for the last launch that read it, (re)allocate and zero it when the
 // layout changes (not under graph capture), then scatter x.
-int xr_prepare(xdg_ham_s *h, const void *x, const Form &f, hipStream_t st, bool *capturing) {
-    const xdg_basis_s *b = product_basis(h);
-    const uint32_t *umap = b == h->basis ? nullptr : h->basis->umap.as<uint32_t>();
+int xr_prepare(xdg_ham_s *h, const Relabelled *in, const void *x, const Form &f, hipStream_t st,
+               bool *capturing) {
+    const xdg_basis_s *b = product_basis(h, in);
+    const uint32_t *umap = in ? in->umap.as<uint32_t>() : nullptr;
     const int spr = (int)f.cols * (f.cplx_kernel ? 2 : 1);
     const int slot = xr_columns(f.cols) * (f.cplx_kernel ? 2 : 1);   // scalars
     const size_t tsz = f.single ? 4 : 8;
@@ -223,7 +223,7 @@ int xr_prepare(xdg_ham_s *h, const void *x, const Form &f, hipStream_t st, bool 
     if (!h->xr_ev) XDG_TRY_HIP(hipEventCreateWithFlags(&h->xr_ev, hipEventDisableTiming));
     if (!*capturing) XDG_TRY_HIP(hipStreamWaitEvent(st, h->xr_ev, 0));
     const int gcap = device_cu_count() * 32;
-    if (h->xr_buf.bytes < need || h->xr_slot_bytes != slot_bytes) {
+    if (h->xr_buf.bytes < need || h->xr_slot_bytes != slot_bytes || h->xr_of != b) {
         if (*capturing) {
             set_error("the rank-addressed copy of x is set up by a first call outside graph capture");
             return XDG_EINVAL;
@@ -239,6 +239,7 @@ int xr_prepare(xdg_ham_s *h, const void *x, const Form &f, hipStream_t st, bool 
                            h->xr_buf.as<uint32_t>(), nw);
         XDG_TRY_HIP(hipGetLastError());
         h->xr_slot_bytes = slot_bytes;
+        h->xr_of = b;
     }
     const unsigned g =
         (unsigned)std::min<int64_t>((b->dim + 255) / 256, (int64_t)gcap);
@@ -405,9 +406,10 @@ static bool few_shape(int64_t rows, int n_bonds, bool cplx, bool single_acc, siz
 // LDS bytes the apply kernel stages for this form, whether the sublattice
 // tables fit with them, and whether two workgroups fit one compute unit
 void apply_lds(const xdg_ham_s *h, int dtype, size_t *lds, int *stage_sub, int *occ_ok) {
-    const xdg_basis_s *b = product_basis(h);
+    const RelabelledRef in = relabelled(h, nullptr);
+    const xdg_basis_s *b = product_basis(h, in.get());
     const bool tsingle = dtype_single(dtype) && (b->plan.flags & XDG_FLAG_F32_ACCUMULATE);
-    const SectorDesc d = make_desc(h, tsingle, nullptr, nullptr);
+    const SectorDesc d = make_desc(h, in.get(), tsingle, nullptr, nullptr);
     size_t n = tsingle ? stage_bytes<float>(d, b->plan.kind, 1)
                        : stage_bytes<double>(d, b->plan.kind, 1);
     int st = 1;
@@ -420,9 +422,15 @@ void apply_lds(const xdg_ham_s *h, int dtype, size_t *lds, int *stage_sub, int *
     *occ_ok = st ? occ_for(n) : 0;
 }
 
+bool tables_fit(const xdg_ham_s *h, const Relabelled *in) {
+    return stage_bytes<double>(make_desc(h, in, false, nullptr, nullptr),
+                               product_basis(h, in)->plan.kind, 0) <= lds_budget();
+}
+
 int apply_launch(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, hipStream_t st,
                  const LaunchCfg *cfg) {
-    const xdg_basis_s *b = product_basis(h);
+    const RelabelledRef in = relabelled(h, st);
+    const xdg_basis_s *b = product_basis(h, in.get());
     Form f;
     XDG_RETURN_IF(form_of(b, dtype, nvec, &f));
     if (b->dim == 0) return XDG_OK;
@@ -436,7 +444,7 @@ int apply_launch(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, 
     const int64_t gmax = c.grid > 0 ? c.grid : (int64_t)apply_grid_for(2);
     const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(need, gmax));
     ApplyArgs A{};
-    A.one = make_desc(h, f.tsingle, x, y);
+    A.one = make_desc(h, in.get(), f.tsingle, x, y);
     A.own = u1_own(h, f.single, f.cols);
     if (A.own) A.one.u1 = U1_OWN;
     if (c.sub_form == 2) {
@@ -471,7 +479,7 @@ int apply_launch(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, 
     std::unique_lock<std::mutex> xr_lock;
     if (xr_on) {
         xr_lock = std::unique_lock<std::mutex>(h->xr_mu);
-        XDG_RETURN_IF(xr_prepare(h, x, f, st, &capturing));
+        XDG_RETURN_IF(xr_prepare(h, in.get(), x, f, st, &capturing));
         A.one.xr = h->xr_buf.p;
     }
     A.nvec = f.cols;
@@ -555,11 +563,20 @@ int apply_tuned(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, h
     std::unique_lock<std::mutex> lock(h->tune_mu);
     auto it = h->tuned.find(key);
     if (it != h->tuned.end()) {
-        const LaunchCfg c = it->second;
+        LaunchCfg c = it->second;
+        lock.unlock();
+        const int rc = apply_launch(h, x, y, nvec, dtype, st, &c);
+        if (rc != XDG_ENOMEM || !c.xr) return rc;
+        // the copy was set up for a labelling that has been given up, and there is
+        // no room for another
+        c.xr = 0;
+        lock.lock();
+        h->tuned[key] = c;
         lock.unlock();
         return apply_launch(h, x, y, nvec, dtype, st, &c);
     }
-    const xdg_basis_s *b = product_basis(h);
+    const RelabelledRef in = relabelled(h, st);
+    const xdg_basis_s *b = product_basis(h, in.get());
     Form f;
     XDG_RETURN_IF(form_of(b, dtype, nvec, &f));
     const int64_t need = (b->dim + APPLY_BLOCK - 1) / APPLY_BLOCK;
@@ -694,7 +711,7 @@ int ham_count_nnz(xdg_ham_s *h, int64_t *nnz) {
     ApplyArgs A{};
     // in the caller's labels: with repeated bonds the terms of a row depend on
     // which state of its orbit stands for it
-    A.one = make_desc(h, false, nullptr, nullptr, false);
+    A.one = make_desc(h, nullptr, false, nullptr, nullptr);
     A.count = cnt.as<unsigned long long>();
     A.stage_sub = 1;
     size_t lds = stage_bytes<double>(A.one, b->plan.kind, 1);
@@ -720,20 +737,20 @@ int ham_count_nnz(xdg_ham_s *h, int64_t *nnz) {
     return XDG_OK;
 }
 
-static bool runs_packed(const xdg_ham_s *h) {
-    const xdg_basis_s *b = product_basis(h);
+static bool runs_packed(const xdg_ham_s *h, const Relabelled *in) {
+    const xdg_basis_s *b = product_basis(h, in);
     return b->plan.kind == K_SUB && b->plan.sub.packed();
 }
 
 // One part of a batch: the blocks with runs_packed == Q->packed.
-static int plan_part(int n, xdg_ham_s *const *hams, const void *const *xs, void *const *ys,
-                     const BatchMeta &P, uint32_t tile_rows, SectorDesc *descs, uint32_t *prefix,
-                     BatchPart *Q) {
-    std::vector<int> in;
+static int plan_part(int n, xdg_ham_s *const *hams, const RelabelledRef *in,
+                     const void *const *xs, void *const *ys, const BatchMeta &P,
+                     uint32_t tile_rows, SectorDesc *descs, uint32_t *prefix, BatchPart *Q) {
+    std::vector<int> of;
     for (int i = 0; i < n; ++i)
-        if (runs_packed(hams[i]) == (Q->packed != 0)) in.push_back(i);
-    Q->n = (int)in.size();
-    Q->kind = product_basis(hams[in[0]])->plan.kind;
+        if (runs_packed(hams[i], in[i].get()) == (Q->packed != 0)) of.push_back(i);
+    Q->n = (int)of.size();
+    Q->kind = product_basis(hams[of[0]], in[of[0]].get())->plan.kind;
     // rows per work item: a multiple of the workgroup (default four rows per lane)
     Q->tile_rows = tile_rows ? (tile_rows + APPLY_BLOCK - 1) / APPLY_BLOCK * APPLY_BLOCK
                              : 4 * APPLY_BLOCK;
@@ -744,22 +761,22 @@ static int plan_part(int n, xdg_ham_s *const *hams, const void *const *xs, void 
     int64_t rows = 0, weight = 0, line = INT64_MAX;
     int most_bonds = 0;
     if (Q->kind == K_U1) {   // no group: the loop that the largest block takes alone
-        const xdg_ham_s *most = hams[in[0]];
+        const xdg_ham_s *most = hams[of[0]];
         size_t bonds = 0;
-        for (int i : in) {
+        for (int i : of) {
             if (hams[i]->basis->dim > most->basis->dim) most = hams[i];
             bonds = std::max(bonds, bond_bytes(hams[i]));
         }
         Q->own = u1_own(most, P.single, P.cols) && bonds <= lds_budget();
     }
     auto desc = [&](int i, const void *x, void *y) {
-        SectorDesc d = make_desc(hams[i], P.tsingle, x, y);
+        SectorDesc d = make_desc(hams[i], in[i].get(), P.tsingle, x, y);
         if (Q->own) d.u1 = U1_OWN;
         return d;
     };
-    for (int i : in) {
+    for (int i : of) {
         const SectorDesc d = desc(i, nullptr, nullptr);
-        const xdg_basis_s *b = product_basis(hams[i]);
+        const xdg_basis_s *b = product_basis(hams[i], in[i].get());
         rows += d.dim;
         weight += few_weight(b);
         line = std::min(line, few_line(b, d.n_bonds, P.cols, P.cplx));
@@ -784,7 +801,7 @@ static int plan_part(int n, xdg_ham_s *const *hams, const void *const *xs, void 
     }
     uint64_t acc = 0;
     for (int k = 0; k < Q->n; ++k) {
-        const int i = in[k];
+        const int i = of[k];
         const SectorDesc d = desc(i, xs[i], ys[i]);
         const uint64_t tiles = (hams[i]->basis->dim + Q->tile_rows - 1) / Q->tile_rows;
         if (acc + tiles >= 0xFFFFFFFFull) {
@@ -805,9 +822,9 @@ static int plan_part(int n, xdg_ham_s *const *hams, const void *const *xs, void 
     return XDG_OK;
 }
 
-int batch_plan_host(int n, xdg_ham_s *const *hams, const void *const *xs, void *const *ys,
-                    int64_t nvec, int dtype, BatchMeta *P, SectorDesc *descs, uint32_t *prefix,
-                    uint32_t tile_rows) {
+int batch_plan_host(int n, xdg_ham_s *const *hams, const RelabelledRef *in,
+                    const void *const *xs, void *const *ys, int64_t nvec, int dtype, BatchMeta *P,
+                    SectorDesc *descs, uint32_t *prefix, uint32_t tile_rows) {
     if (n < 1) {
         set_error("batched apply needs at least one block");
         return XDG_EINVAL;
@@ -842,13 +859,14 @@ int batch_plan_host(int n, xdg_ham_s *const *hams, const void *const *xs, void *
     int placed = 0;
     for (const bool packed : {true, false}) {
         int in_part = 0;
-        for (int i = 0; i < n; ++i) in_part += runs_packed(hams[i]) == packed;
+        for (int i = 0; i < n; ++i) in_part += runs_packed(hams[i], in[i].get()) == packed;
         if (!in_part) continue;
         BatchPart &Q = P->part[P->n_parts];
         Q = BatchPart{};
         Q.packed = packed;
         Q.first = placed;
-        XDG_RETURN_IF(plan_part(n, hams, xs, ys, *P, tile_rows, descs ? descs + placed : nullptr,
+        XDG_RETURN_IF(plan_part(n, hams, in, xs, ys, *P, tile_rows,
+                                descs ? descs + placed : nullptr,
                                 prefix ? prefix + placed + P->n_parts : nullptr, &Q));
         placed += in_part;
         ++P->n_parts;
@@ -856,16 +874,16 @@ int batch_plan_host(int n, xdg_ham_s *const *hams, const void *const *xs, void *
     return XDG_OK;
 }
 
-int batch_prepare(int n, xdg_ham_s *const *hams, const void *const *xs, void *const *ys,
-                  int64_t nvec, int dtype, BatchPlan *P, uint32_t tile_rows) {
+int batch_prepare(int n, xdg_ham_s *const *hams, const RelabelledRef *in, const void *const *xs,
+                  void *const *ys, int64_t nvec, int dtype, BatchPlan *P, uint32_t tile_rows) {
     if (n < 1) {
         set_error("batched apply needs at least one block");
         return XDG_EINVAL;
     }
     std::vector<SectorDesc> descs(n);
     std::vector<uint32_t> prefix(n + 2, 0);
-    XDG_RETURN_IF(batch_plan_host(n, hams, xs, ys, nvec, dtype, P, descs.data(), prefix.data(),
-                                  tile_rows));
+    XDG_RETURN_IF(batch_plan_host(n, hams, in, xs, ys, nvec, dtype, P, descs.data(),
+                                  prefix.data(), tile_rows));
     XDG_RETURN_IF(P->descs.upload(descs.data(), sizeof(SectorDesc) * n));
     XDG_RETURN_IF(P->prefix.upload(prefix.data(), sizeof(uint32_t) * (n + P->n_parts)));
     XDG_RETURN_IF(P->queue.alloc(sizeof(uint32_t)));
@@ -957,8 +975,9 @@ bool batch_shape_cached(int n, xdg_ham_s *const *hams, int64_t nvec, int dtype, 
     return true;
 }
 
-int batch_shape_tuned(int n, xdg_ham_s *const *hams, const void *const *xs, void *const *ys,
-                      int64_t nvec, int dtype, hipStream_t st, BatchShape *out) {
+int batch_shape_tuned(int n, xdg_ham_s *const *hams, const RelabelledRef *in,
+                      const void *const *xs, void *const *ys, int64_t nvec, int dtype,
+                      hipStream_t st, BatchShape *out) {
     const auto key = shape_key(n, hams, nvec, dtype);
     std::lock_guard<std::mutex> lock(g_shape_mu);
     auto it = g_shape_cache.find(key);
@@ -968,7 +987,7 @@ int batch_shape_tuned(int n, xdg_ham_s *const *hams, const void *const *xs, void
     }
     BatchShape best_shape{apply_grid_for(2), 4 * 1024, 8};
     BatchMeta meta;
-    XDG_RETURN_IF(batch_plan_host(n, hams, xs, ys, nvec, dtype, &meta, nullptr, nullptr));
+    XDG_RETURN_IF(batch_plan_host(n, hams, in, xs, ys, nvec, dtype, &meta, nullptr, nullptr));
     bool few = true;
     for (int p = 0; p < meta.n_parts; ++p) few &= meta.part[p].few != 0;
     if (few) {   // its shape follows from the sizes
@@ -983,7 +1002,7 @@ int batch_shape_tuned(int n, xdg_ham_s *const *hams, const void *const *xs, void
     int64_t cols = 1;
     auto time_shape = [&](const BatchShape &sh) -> int {
         BatchPlan P;
-        XDG_RETURN_IF(batch_prepare(n, hams, xs, ys, nvec, dtype, &P, sh.tile));
+        XDG_RETURN_IF(batch_prepare(n, hams, in, xs, ys, nvec, dtype, &P, sh.tile));
         cols = P.cols;
         XDG_RETURN_IF(batch_launch(P, sh.grid, sh.nv, st));
         XDG_TRY_HIP(hipEventRecord(e0, st));
@@ -1089,7 +1108,8 @@ int apply_batched_noalloc(int n, xdg_ham_s *const *hams, const void *const *xs,
     BatchShape sh;     // a shape tuned earlier for these blocks, else the default
     const bool tuned = batch_shape_cached(n, hams, nvec, dtype, &sh);
     BatchMeta M;
-    XDG_RETURN_IF(batch_plan_host(n, hams, xs, ys, nvec, dtype, &M, descs, prefix,
+    const std::vector<RelabelledRef> in = relabelled(n, hams, st);
+    XDG_RETURN_IF(batch_plan_host(n, hams, in.data(), xs, ys, nvec, dtype, &M, descs, prefix,
                                   tuned ? sh.tile : 0));
     unsigned char *base = nullptr;
     XDG_RETURN_IF(scratch_address(&base));
@@ -1119,7 +1139,8 @@ int apply_batched_launch(int n, xdg_ham_s *const *hams, const void *const *xs, v
         }
     // plans are cached by the exact argument tuple so that repeated calls
     // (iterative methods) upload nothing; a Hamiltonian enters the key by its
-    // serial number too, since a new one may reuse a freed one's address
+    // serial number too, since a new one may reuse a freed one's address, and by
+    // its labelling, which it may lose (and never gets again)
     struct Key {
         std::vector<const void *> p;
         int64_t nvec;
@@ -1127,24 +1148,26 @@ int apply_batched_launch(int n, xdg_ham_s *const *hams, const void *const *xs, v
         bool operator==(const Key &o) const { return p == o.p && nvec == o.nvec && dtype == o.dtype; }
     };
     thread_local std::vector<std::pair<Key, std::unique_ptr<BatchPlan>>> cache;
+    const std::vector<RelabelledRef> in = relabelled(n, hams, st);
     Key k;
     for (int i = 0; i < n; ++i) {
         k.p.push_back(hams[i]);
         k.p.push_back(reinterpret_cast<const void *>((uintptr_t)hams[i]->serial));
+        k.p.push_back(in[i].get());
         k.p.push_back(xs[i]);
         k.p.push_back(ys[i]);
     }
     k.nvec = nvec;
     k.dtype = dtype;
     BatchShape sh;
-    XDG_RETURN_IF(batch_shape_tuned(n, hams, xs, ys, nvec, dtype, st, &sh));
+    XDG_RETURN_IF(batch_shape_tuned(n, hams, in.data(), xs, ys, nvec, dtype, st, &sh));
     k.p.push_back(reinterpret_cast<const void *>((uintptr_t)sh.tile));
     BatchPlan *P = nullptr;
     for (auto &e : cache)
         if (e.first == k) P = e.second.get();
     if (!P) {
         auto up = std::make_unique<BatchPlan>();
-        XDG_RETURN_IF(batch_prepare(n, hams, xs, ys, nvec, dtype, up.get(), sh.tile));
+        XDG_RETURN_IF(batch_prepare(n, hams, in.data(), xs, ys, nvec, dtype, up.get(), sh.tile));
         if (cache.size() >= 8) cache.erase(cache.begin());
         cache.emplace_back(k, std::move(up));
         P = cache.back().second.get();

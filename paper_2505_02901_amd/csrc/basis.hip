@@ -20,6 +20,14 @@ namespace xdg {
 static std::atomic<uint64_t> g_dev_bytes{0};
 static std::atomic<uint64_t> g_dev_limit{0};
 
+static thread_local uint64_t g_missing = 0;
+
+uint64_t take_missing_memory() {
+    const uint64_t n = g_missing;
+    g_missing = 0;
+    return n;
+}
+
 void set_device_memory_limit(uint64_t bytes) { g_dev_limit.store(bytes); }
 uint64_t device_memory_in_use() { return g_dev_bytes.load(); }
 
@@ -39,6 +47,7 @@ int DevBuf::alloc(size_t n) {
     const uint64_t held = g_dev_bytes.fetch_add(n) + n;
     if (limit && held > limit) {
         g_dev_bytes.fetch_sub(n);
+        g_missing = held - limit;
         set_error("device memory limit: %zu more bytes would bring the library to %llu of %llu",
                   n, (unsigned long long)held, (unsigned long long)limit);
         return XDG_ENOMEM;
@@ -47,6 +56,9 @@ int DevBuf::alloc(size_t n) {
     if (e != hipSuccess) {
         g_dev_bytes.fetch_sub(n);
         p = nullptr;
+        size_t room = 0, all = 0;
+        if (e == hipErrorOutOfMemory && hipMemGetInfo(&room, &all) == hipSuccess)
+            g_missing = n > room ? n - room : 1;
         (void)hipGetLastError();
         set_error("hipMalloc(%zu bytes) failed: %s", n, hipGetErrorString(e));
         return XDG_ENOMEM;
@@ -1177,6 +1189,14 @@ __global__ __launch_bounds__(256) void k_map_check(const uint32_t *umap, uint64_
 // 6x6 triangular lattice in three blocks of 12, 12 of 36 up, three FP64 vectors
 // 25.8 -> 10.7 ms (3.7 with these and one pass for the three vectors).
 //
+static uint64_t basis_bytes(const xdg_basis_s *b) {
+    uint64_t n = 0;
+    for (const DevBuf *d : {&b->reps, &b->stab, &b->hash, &b->rwords, &b->rank_buf, &b->xr_top,
+                            &b->xr_top32, &b->xr_rtab, &b->xb_buf, &b->tables})
+        n += d->bytes;
+    return n;
+}
+
 // wrong: the map does not fit the block (an error of this library's, returned).
 static int build_inner(xdg_basis_s *b, uint32_t *wrong) {
     const Plan &P = b->plan;
@@ -1197,7 +1217,9 @@ static int build_inner(xdg_basis_s *b, uint32_t *wrong) {
         if (std::fabs(b->chi[2 * g]) != 1.0 || b->chi[2 * g + 1] != 0.0) return XDG_OK;
     std::vector<int> pos = four_block_labels(b->n_sites, b->n_sym, b->perm.data());
     if (pos.empty()) return XDG_OK;
-    auto in = std::make_unique<xdg_basis_s>();
+    auto rel = std::make_shared<Relabelled>();
+    rel->basis = std::make_unique<xdg_basis_s>();
+    xdg_basis_s *const in = rel->basis.get();
     in->device = b->device;
     in->n_sites = b->n_sites;
     in->n_up = b->n_up;
@@ -1210,8 +1232,8 @@ static int build_inner(xdg_basis_s *b, uint32_t *wrong) {
     o.n_sublattices = 4;
     o.flags = P.flags;
     int rc = make_plan(in->n_sites, in->n_sym, in->perm.data(), &o, &in->plan, true);
-    if (rc == XDG_OK) rc = basis_build_device(in.get());
-    DevBuf umap, bad;
+    if (rc == XDG_OK) rc = basis_build_device(in);
+    DevBuf &umap = rel->umap, bad;
     if (rc == XDG_OK && in->dim == b->dim) rc = umap.alloc(sizeof(uint32_t) * (size_t)b->dim);
     if (rc == XDG_OK) rc = bad.alloc(sizeof(uint32_t));
     XDG_RETURN_IF(rc);
@@ -1247,10 +1269,16 @@ static int build_inner(xdg_basis_s *b, uint32_t *wrong) {
     XDG_TRY_HIP(hipGetLastError());
     XDG_RETURN_IF(copy_d2h(wrong, bad.p, sizeof *wrong, nullptr));
     if (*wrong) return XDG_EINVAL;
-    std::swap(b->umap.p, umap.p);
-    std::swap(b->umap.bytes, umap.bytes);
-    b->inner_pos = std::move(pos);
-    b->inner = std::move(in);
+    rel->pos = std::move(pos);
+    bad.release();
+    rel->bytes = basis_bytes(in) + umap.bytes;
+    // Device memory that the caller's own vectors may want is beyond the library's
+    // sight, so the labelling stays only where it is a small part of what is left;
+    // the library's own allocations make it give way (give_up_relabelled).
+    size_t room = 0, all = 0;
+    XDG_TRY_HIP(hipMemGetInfo(&room, &all));
+    if (rel->bytes > room / 8) return XDG_OK;
+    offer_relabelled(b, std::move(rel));
     return XDG_OK;
 }
 

@@ -11,18 +11,89 @@ using namespace xdg;
 
 namespace xdg {
 int last_timing(double *total, double *apply);
+
+namespace {
+std::mutex g_inner_mu;
+std::vector<xdg_basis_s *> g_inner_of;   // the blocks that have a second labelling
+}  // namespace
+
+void offer_relabelled(xdg_basis_s *b, RelabelledRef in) {
+    std::lock_guard<std::mutex> all(g_inner_mu);
+    std::lock_guard<std::mutex> lock(b->inner_mu);
+    b->inner = std::move(in);
+    b->has_inner = true;
+    g_inner_of.push_back(b);
 }
+
+static void forget_relabelled(xdg_basis_s *b) {
+    if (!b->has_inner) return;
+    std::lock_guard<std::mutex> all(g_inner_mu);
+    g_inner_of.erase(std::remove(g_inner_of.begin(), g_inner_of.end(), b), g_inner_of.end());
+}
+
+RelabelledRef relabelled(const xdg_ham_s *h, hipStream_t st) {
+    xdg_basis_s *b = h->basis;
+    if (!b->has_inner || !h->inner_bonds.d.p) return nullptr;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    bool captured = false;
+    if (st) {
+        captured = hipStreamIsCapturing(st, &cs) != hipSuccess ||
+                   cs != hipStreamCaptureStatusNone;
+    }
+    std::lock_guard<std::mutex> lock(b->inner_mu);
+    b->inner_captured |= captured && b->inner;
+    return b->inner;
+}
+
+std::vector<RelabelledRef> relabelled(int n, xdg_ham_s *const *hams, hipStream_t st) {
+    std::vector<RelabelledRef> in(n);
+    for (int i = 0; i < n; ++i) in[i] = relabelled(hams[i], st);
+    return in;
+}
+
+bool give_up_relabelled() {
+    const uint64_t missing = take_missing_memory();
+    if (!missing) return false;
+    std::vector<RelabelledRef> gone;   // freed after the locks
+    {
+        std::lock_guard<std::mutex> all(g_inner_mu);
+        uint64_t held = 0;
+        for (xdg_basis_s *b : g_inner_of) {
+            std::lock_guard<std::mutex> lock(b->inner_mu);
+            if (b->inner && !b->inner_captured) held += b->inner->bytes;
+        }
+        if (held < missing) return false;
+        for (xdg_basis_s *b : g_inner_of) {
+            std::lock_guard<std::mutex> lock(b->inner_mu);
+            if (!b->inner || b->inner_captured) continue;
+            gone.push_back(std::move(b->inner));
+            b->inner = nullptr;
+            b->has_inner = false;
+        }
+        g_inner_of.erase(std::remove_if(g_inner_of.begin(), g_inner_of.end(),
+                                        [](xdg_basis_s *b) { return !b->has_inner; }),
+                         g_inner_of.end());
+    }
+    return true;
+}
+
+}  // namespace xdg
 
 namespace {
 
 void basis_release(xdg_basis_s *b) {
-    if (b && b->refs.fetch_sub(1) == 1) delete b;
+    if (b && b->refs.fetch_sub(1) == 1) {
+        forget_relabelled(b);
+        delete b;
+    }
 }
 
 template <class F>
 int guarded(F &&f) {
     try {
-        return f();
+        (void)take_missing_memory();
+        const int rc = f();
+        return rc == XDG_ENOMEM && give_up_relabelled() ? f() : rc;
     } catch (const std::bad_alloc &) {
         set_error("host allocation failed");
         return XDG_ENOMEM;
@@ -298,10 +369,16 @@ int xdg_create_hamiltonian(xdg_basis b, int n_bonds, const int32_t *sites, const
         h->jz.assign(jz, jz + n_bonds);
         h->jxy.assign(jxy, jxy + n_bonds);
         int rc = upload_bonds(b, n_bonds, sites, jz, jxy, &h->bonds);
-        if (rc == XDG_OK && b->inner) {
+        RelabelledRef inner;
+        {
+            std::lock_guard<std::mutex> lock(b->inner_mu);
+            inner = b->inner;
+        }
+        if (rc == XDG_OK && inner) {
             std::vector<int32_t> in(2 * (size_t)n_bonds);
-            for (size_t e = 0; e < in.size(); ++e) in[e] = b->inner_pos[sites[e]];
-            rc = upload_bonds(b->inner.get(), n_bonds, in.data(), jz, jxy, &h->inner_bonds);
+            for (size_t e = 0; e < in.size(); ++e) in[e] = inner->pos[sites[e]];
+            rc = upload_bonds(inner->basis.get(), n_bonds, in.data(), jz, jxy, &h->inner_bonds);
+            if (rc == XDG_OK && !tables_fit(h, inner.get())) h->inner_bonds.d.release();
         }
         if (rc == XDG_OK && b->plan.kind == XDG_SEARCH_U1 && u1_wants_rank(h))
             rc = u1_rank_tables(b, &h->u1_rtab, &h->u1_rank);
@@ -403,7 +480,12 @@ int xdg_apply_with_config(xdg_ham h, const void *x, void *y, int64_t nvec, int d
         c.compact = cfg->compact;
         c.sub_form = cfg->sub_form;
         c.xr = cfg->xr;
-        return apply_launch(h, x, y, nvec, dtype, (hipStream_t)stream, &c);
+        int rc = apply_launch(h, x, y, nvec, dtype, (hipStream_t)stream, &c);
+        if (rc == XDG_ENOMEM && c.xr && h->basis->plan.kind == XDG_SEARCH_TABLE) {
+            c.xr = 0;   // not a form of byte-table blocks: never in the way
+            rc = apply_launch(h, x, y, nvec, dtype, (hipStream_t)stream, &c);
+        }
+        return rc;
     });
 }
 

@@ -1097,6 +1097,7 @@ int lanczos_single(xdg_ham_s *h, const void *v0, int k, double tol, int max_iter
     DevBuf norms;   // fused form: |w|^2 partials beside those of the dot product
     const bool fused = !reorth && ops.fusable();
     if (fused) XDG_RETURN_IF(norms.alloc(sizeof(double) * (size_t)ops.grid * MAXC));
+    if (relabelled(h, nullptr)) h->lanczos_relabelled = true;
 
     // one event pair per iteration around the apply; summed at the end
     struct Events {
@@ -1380,6 +1381,25 @@ int lanczos_eigvec(xdg_ham_s *h, const void *v0, uint64_t seed, int prec, int m,
                       beta[j]);
             return XDG_EINVAL;
         }
+    // The vectors equal those of the first pass only in the labelling it ran in: if
+    // that has been given up since, the matrix of this one takes its place (with the
+    // other's, rounding errors grew to 2.7 times the residual on a 6x6 block).
+    std::vector<double> own_a, own_b;
+    if (h->lanczos_relabelled && !relabelled(h, nullptr)) {
+        own_a.resize(m);
+        own_b.resize(m);
+        double lowest = 0.0;
+        int steps = 0;
+        const double total = g_t_total, apply = g_t_apply;   // (of the caller's first pass)
+        XDG_RETURN_IF(lanczos_single(h, v0, 1, 0.0, m, seed, prec, &lowest, &steps, own_a.data(),
+                                     own_b.data(), st, nullptr, nullptr));
+        g_t_total = total;
+        g_t_apply = apply;
+        if (steps == m) {
+            alpha = own_a.data();
+            beta = own_b.data();
+        }
+    }
     std::vector<double> c;
     double theta = 0.0;
     tridiag_eigvec(m, alpha, beta, which, c, theta);
@@ -1524,6 +1544,7 @@ int lanczos_batched(int n, xdg_ham_s *const *hams, const void *const *v0s, int64
     auto vecp = [&](int i, int slot) -> char * { return ops.vec(i, slot); };
     // phase p: v = slot p, vprev = slot (p+2)%3 (none at j = 0), next = slot (p+1)%3, w = slot 3
     std::vector<xdg_ham_s *> hv(hams, hams + n);
+    const std::vector<RelabelledRef> in = relabelled(n, hv.data(), nullptr);   // to the end of the run
     auto prepare = [&](int p, BatchPlan *P, uint32_t tile) -> int {
         std::vector<const void *> xs(n);
         std::vector<void *> ys(n);
@@ -1531,7 +1552,7 @@ int lanczos_batched(int n, xdg_ham_s *const *hams, const void *const *v0s, int64
             xs[i] = vecp(i, p);
             ys[i] = vecp(i, 3);
         }
-        return batch_prepare(n, hv.data(), xs.data(), ys.data(), nvec, dtype, P, tile);
+        return batch_prepare(n, hv.data(), in.data(), xs.data(), ys.data(), nvec, dtype, P, tile);
     };
     // launch shape of the batched apply (tuned once per set of blocks)
     BatchShape best_shape;
@@ -1542,8 +1563,8 @@ int lanczos_batched(int n, xdg_ham_s *const *hams, const void *const *v0s, int64
             xs[i] = vecp(i, 0);
             ys[i] = vecp(i, 3);
         }
-        XDG_RETURN_IF(batch_shape_tuned(n, hv.data(), xs.data(), ys.data(), nvec, dtype, st,
-                                        &best_shape));
+        XDG_RETURN_IF(batch_shape_tuned(n, hv.data(), in.data(), xs.data(), ys.data(), nvec,
+                                        dtype, st, &best_shape));
     }
     BatchPlan plans[3];
     for (int p = 0; p < 3; ++p) XDG_RETURN_IF(prepare(p, &plans[p], best_shape.tile));
@@ -1781,9 +1802,12 @@ int tpq_micro_batched(int n, xdg_ham_s *const *hams, const void *const *v0s, int
         ys[i] = ops.vec(i, 1);
     }
     BatchShape shape;
-    XDG_RETURN_IF(batch_shape_tuned(n, hv.data(), xs.data(), ys.data(), nvec, dtype, st, &shape));
+    const std::vector<RelabelledRef> in = relabelled(n, hv.data(), nullptr);   // to the end of the run
+    XDG_RETURN_IF(batch_shape_tuned(n, hv.data(), in.data(), xs.data(), ys.data(), nvec, dtype, st,
+                                    &shape));
     BatchPlan plan;
-    XDG_RETURN_IF(batch_prepare(n, hv.data(), xs.data(), ys.data(), nvec, dtype, &plan, shape.tile));
+    XDG_RETURN_IF(batch_prepare(n, hv.data(), in.data(), xs.data(), ys.data(), nvec, dtype, &plan,
+                                shape.tile));
     auto step = [&]() -> int {
         XDG_RETURN_IF(batch_launch(plan, shape.grid, shape.nv, st));
         XDG_RETURN_IF(ops.dot(0, 1));

@@ -189,6 +189,19 @@ struct HashIndex {
 
 }  // namespace xdg
 
+namespace xdg {
+// A sector in site labels that suit the packed sublattice search: its own
+// representatives, stabilisers and index.  umap[k]: position in the caller's
+// basis of the orbit of state k, with bit 31 set where the two symmetric states
+// differ by a sign.
+struct Relabelled {
+    std::unique_ptr<xdg_basis_s> basis;
+    std::vector<int> pos;       // label of every site
+    DevBuf umap;                // u32 [dim]
+    uint64_t bytes = 0;         // device memory of all this
+};
+}  // namespace xdg
+
 struct xdg_basis_s {
     std::atomic<int> refs{1};
     int device = 0;
@@ -235,14 +248,14 @@ struct xdg_basis_s {
     xdg::DevView sqrt_d;         // double [n_sym+1] sqrt(c), then [n_sym+1] 1/sqrt(c)
     xdg::DevView sqrt_f;         // float, same layout
     xdg::DeviceSearch dsearch;
-    // The same sector in site labels that suit the packed sublattice search,
-    // for the products with H (see basis_build_inner): its own
-    // representatives, stabilisers and index.  umap[k]: position in this
-    // basis of the orbit of the inner state k, with bit 31 set where the two
-    // symmetric states differ by a sign.
-    std::unique_ptr<xdg_basis_s> inner;
-    std::vector<int> inner_pos; // inner label of every site
-    xdg::DevBuf umap;           // u32 [dim]
+    // The same sector in other site labels, for the products with H (see
+    // basis_build_inner).  Guarded by inner_mu: it is given up when memory is
+    // short, unless a captured graph holds it.  Whoever launches on it holds a
+    // reference until everything is enqueued (freeing waits for the device).
+    std::mutex inner_mu;
+    std::atomic<bool> has_inner{false};   // without the lock: false is final
+    std::shared_ptr<const xdg::Relabelled> inner;
+    bool inner_captured = false;
     // workspace of expect_szsz (which waits for its results), used under the lock
     std::mutex measure_mu;
     xdg::DevBuf measure_ws;
@@ -288,7 +301,7 @@ struct xdg_ham_s {
     std::vector<int32_t> sites;
     std::vector<double> jz, jxy;
     xdg::BondSet bonds;         // in the caller's labels
-    xdg::BondSet inner_bonds;   // in the labels of basis->inner, if any
+    xdg::BondSet inner_bonds;   // in the labels of basis->inner, if the products use it
     xdg::DevBuf u1_rtab;        // no group, see u1_wants_rank: rank tables, layout u1_rank
     xdg::RankLayout u1_rank{};
     int64_t nnz = -1;
@@ -300,6 +313,8 @@ struct xdg_ham_s {
     std::mutex xr_mu;
     xdg::DevBuf xr_buf;
     size_t xr_slot_bytes = 0;
+    const void *xr_of = nullptr;   // the basis whose slots the copy has
+    std::atomic<bool> lanczos_relabelled{false};   // a first Lanczos pass ran relabelled
     hipEvent_t xr_ev = nullptr;
     ~xdg_ham_s() {
         if (xr_ev) (void)hipEventDestroy(xr_ev);
@@ -344,7 +359,21 @@ inline void bondx_site(int i, int m, int pb, BondX &x) {
 }
 
 int basis_build_device(xdg_basis_s *b);                 // enumerate + index
-int basis_build_inner(xdg_basis_s *b);                  // b->inner and b->umap, where they apply
+int basis_build_inner(xdg_basis_s *b);                  // b->inner, where it applies
+// The labelling that a launch on `st` uses (null: the caller's); under capture
+// it stays from then on.
+using RelabelledRef = std::shared_ptr<const Relabelled>;
+RelabelledRef relabelled(const xdg_ham_s *h, hipStream_t st);
+std::vector<RelabelledRef> relabelled(int n, xdg_ham_s *const *hams, hipStream_t st);
+// Do the tables that products in this labelling cannot do without fit in LDS?
+bool tables_fit(const xdg_ham_s *h, const Relabelled *in);
+// After a call failed for lack of memory on this thread: gives up labellings of
+// all blocks if what they hold covers what was missing.  True: call again.
+bool give_up_relabelled();
+void offer_relabelled(xdg_basis_s *b, RelabelledRef in);
+// Bytes that this thread's last failed allocation lacked (0: none since the
+// last call of this).
+uint64_t take_missing_memory();
 int u1_rank_tables(const xdg_basis_s *b, DevBuf *tab, RankLayout *L);
 bool u1_wants_rank(const xdg_ham_s *h);
 bool below_few_line(const xdg_basis_s *b);   // products take the few-rows loop (up to 64 bonds)
@@ -394,12 +423,13 @@ struct BatchPlan : BatchMeta {
 struct SectorDesc;
 // Host planning of a batch: fills M, and (when not null) descs[n], part after
 // part, and prefix[n + n_parts] (n + 2 at most; n_p + 1 entries of each part) in
-// host memory.  Allocates nothing.
-int batch_plan_host(int n, xdg_ham_s *const *hams, const void *const *xs, void *const *ys,
-                    int64_t nvec, int dtype, BatchMeta *M, SectorDesc *descs, uint32_t *prefix,
-                    uint32_t tile_rows = 0);
-int batch_prepare(int n, xdg_ham_s *const *hams, const void *const *xs, void *const *ys,
-                  int64_t nvec, int dtype, BatchPlan *P, uint32_t tile_rows = 0);
+// host memory.  Allocates nothing.  The caller holds `in` (one of each block)
+// until its last launch of the plan is enqueued.
+int batch_plan_host(int n, xdg_ham_s *const *hams, const RelabelledRef *in,
+                    const void *const *xs, void *const *ys, int64_t nvec, int dtype, BatchMeta *M,
+                    SectorDesc *descs, uint32_t *prefix, uint32_t tile_rows = 0);
+int batch_prepare(int n, xdg_ham_s *const *hams, const RelabelledRef *in, const void *const *xs,
+                  void *const *ys, int64_t nvec, int dtype, BatchPlan *P, uint32_t tile_rows = 0);
 int batch_launch(const BatchPlan &P, int grid, int nv_cap, hipStream_t st);
 // The launch itself on device descriptors, tile prefix and queue counter.
 int batch_launch_raw(const BatchMeta &M, const SectorDesc *d_descs, const uint32_t *d_prefix,
@@ -415,8 +445,9 @@ struct BatchShape {
 };
 // The shape for this set of blocks (nvec, dtype): tuned on the first call by
 // timing launches on xs -> ys (which it overwrites) and cached; locked.
-int batch_shape_tuned(int n, xdg_ham_s *const *hams, const void *const *xs, void *const *ys,
-                      int64_t nvec, int dtype, hipStream_t st, BatchShape *out);
+int batch_shape_tuned(int n, xdg_ham_s *const *hams, const RelabelledRef *in,
+                      const void *const *xs, void *const *ys, int64_t nvec, int dtype,
+                      hipStream_t st, BatchShape *out);
 // The cached shape, if any (no tuning, no allocation); false otherwise.
 bool batch_shape_cached(int n, xdg_ham_s *const *hams, int64_t nvec, int dtype, BatchShape *out);
 int lanczos_single(xdg_ham_s *h, const void *v0, int k, double tol, int max_iter, uint64_t seed,

@@ -169,3 +169,111 @@ def test_creation_under_a_memory_limit(X):
         assert float((y - want).abs().max()) < 1e-13 * float(want.abs().max()), limit
         del H, b
     assert held == {one, both}, (held, one, both)      # both outcomes occurred
+
+
+@pytest.mark.parametrize("short_in", ["first pass", "second pass"])
+def test_second_labelling_is_given_up(X, short_in):
+    """Work that fits beside a block in one labelling still fits: Lanczos runs
+    with less memory left than their vectors take."""
+    m = rowmajor((6, 0), (0, 6), 9, "A1", 0.5)
+    start = X.xdg_set_device_memory_limit(0)
+    b = X.Basis.from_model(m, search=4)      # the block without a second labelling
+    alone = X.xdg_set_device_memory_limit(0) - start
+    del b
+    b = X.Basis.from_model(m)
+    extra = X.xdg_set_device_memory_limit(0) - start - alone
+    assert extra > 8 * b.dim
+    H = X.Hamiltonian.from_model(b, m)
+    x = torch.randn(b.dim, dtype=torch.float64, device="cuda")
+    y, z = torch.empty_like(x), torch.empty_like(x)
+    H.apply(x, y)
+    e0, psi0, _, _ = H.eig0(tol=1e-12, max_iter=80, seed=4)
+    r0 = H.apply(psi0, torch.empty_like(x)) - e0 * psi0
+    vec, small = 8 * b.dim, 1 << 20          # four vectors in the first pass, five in the second
+    assert vec > small
+    room = 4 * vec + small if short_in == "second pass" else 5 * vec + small - extra // 2
+    used = X.xdg_set_device_memory_limit(0)
+    X.xdg_set_device_memory_limit(used + room)
+    try:
+        e, psi, _, _ = H.eig0(tol=1e-12, max_iter=80, seed=4)
+    finally:
+        now = X.xdg_set_device_memory_limit(0)
+    assert now < used - extra // 2
+    assert abs(e - e0) < 1e-11 * abs(e0)
+    r = H.apply(psi, z) - e * psi
+    assert float(r.norm()) <= 2 * float(r0.norm()) + 1e-10
+    H.apply(x, z)
+    assert float((y - z).abs().max()) < 1e-13 * float(y.abs().max())
+    b2 = X.Basis.from_model(m)               # new blocks get one again
+    assert X.xdg_set_device_memory_limit(0) - now > alone + extra // 2
+    del b2
+
+
+def test_captured_products_keep_their_labelling(X):
+    """A block whose products a graph holds does not give its second labelling up."""
+    m = rowmajor((6, 0), (0, 6), 8, "A1", 0.5)
+    b = X.Basis.from_model(m)
+    H = X.Hamiltonian.from_model(b, m)
+    x = torch.randn(b.dim, dtype=torch.float64, device="cuda")
+    y, z = torch.empty_like(x), torch.empty_like(x)
+    H.apply(x, y)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        H.apply(x, z)
+    used = X.xdg_set_device_memory_limit(0)
+    X.xdg_set_device_memory_limit(used + 4 * 8 * b.dim)
+    try:
+        with pytest.raises(X.XdgError) as e:      # four vectors and some: a little too much
+            H.lanczos(k=1, tol=0.0, max_iter=5, seed=1)
+        assert e.value.code == X.XDG_ENOMEM
+    finally:
+        now = X.xdg_set_device_memory_limit(0)
+    assert now == used
+    for k in range(3):
+        x.normal_()
+        H.apply(x, y)
+        z.fill_(3.0)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, z), k
+
+
+def test_threads_while_labellings_go(X):
+    """Products from several threads and streams while another thread's calls make
+    blocks give their labellings up: right before, between and after."""
+    import threading
+
+    m = rowmajor((6, 0), (0, 6), 7, "B1")
+    t = X.Basis.from_model(m, search=4)
+    x = torch.randn(t.dim, 2, dtype=torch.float64, device="cuda")
+    want = X.Hamiltonian.from_model(t, m).apply(x, torch.empty_like(x))
+    blocks = [X.Basis.from_model(m) for _ in range(4)]
+    hams = [X.Hamiltonian.from_model(b, m) for b in blocks]
+    used = X.xdg_set_device_memory_limit(0)
+    bad = []
+
+    def work(k):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            y = torch.empty_like(x)
+            for r in range(20):
+                y.fill_(3.0)
+                hams[(k + r) % 4].apply(x, y, stream=s.cuda_stream)
+                s.synchronize()
+                err = float((y - want).abs().max())
+                if not err < 1e-13 * float(want.abs().max()):
+                    bad.append((k, r, err))
+
+    torch.cuda.synchronize()
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(3)]
+    [th.start() for th in ts]
+    X.xdg_set_device_memory_limit(used + 4 * 8 * t.dim)
+    try:
+        for h in hams:
+            h.lanczos(k=1, tol=0.0, max_iter=4, seed=1)
+    finally:
+        X.xdg_set_device_memory_limit(0)
+        [th.join() for th in ts]
+    assert not bad, bad
+    assert X.xdg_set_device_memory_limit(0) < used
