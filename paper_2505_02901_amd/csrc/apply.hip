@@ -616,7 +616,10 @@ int apply_tuned(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, h
     for (int mult : {1, 2, 4, 8}) {
         const int g = cu * mult * BLOCKS_PER_1024;
         cands.push_back({APPLY_BLOCK, g, 8});
-        if (f.cols > 1) cands.push_back({APPLY_BLOCK, g, (int)std::max<int64_t>(1, f.cols / 2)});
+        // (a number of vectors that an explicit shape may ask for: 1, 2, 4 or 8)
+        int half = 1;
+        while (half < 8 && half < f.cols / 2) half *= 2;
+        if (f.cols > 1 && half < 8) cands.push_back({APPLY_BLOCK, g, half});
     }
     cands.push_back({APPLY_BLOCK, (int)std::min<int64_t>(need, 1 << 30), 8});
     float best = 1e30f;

@@ -53,3 +53,23 @@ def test_columns(X, name, dtype):
         y = torch.full_like(x, 3.0)
         X.xdg_apply_batched([H.handle], [x], [y])
         assert torch.equal(y, one), (name, nvec, "batched")
+
+
+@pytest.mark.parametrize("nvec,dtype", [(3, "float32"), (6, "float64"), (7, "float32"), (18, "float64"),
+                                        (3, "complex128"), (9, "complex64")])
+def test_the_tuned_shape_can_be_asked_for(X, nvec, dtype):
+    """a block large enough to be tuned (1.4 M rows), vector numbers whose half
+    is no power of two or above eight"""
+    m = W.chain_model(28, l=0)
+    b = X.Basis.from_model(m)
+    H = X.Hamiltonian.from_model(b, m)
+    dt = getattr(torch, dtype)
+    x = torch.randn(b.dim, nvec, dtype=dt, device="cuda")
+    y, z = torch.empty_like(x), torch.full_like(x, 5.0)
+    H.apply(x, y)
+    code = {"float64": X.XDG_F64, "float32": X.XDG_F32, "complex128": X.XDG_C128,
+            "complex64": X.XDG_C64}[dtype]
+    cfg = X.xdg_apply_tuned_config(H.handle, code, nvec)
+    assert cfg["nv"] in (1, 2, 4, 8), cfg
+    X.xdg_apply_with_config(H.handle, x, z, **cfg)
+    assert torch.equal(y, z)
