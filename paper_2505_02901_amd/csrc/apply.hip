@@ -208,15 +208,21 @@ int xr_columns(int64_t cols) {
 // Fill the rank-addressed copy of x for this call (caller holds h->xr_mu):
 // wait for the last launch that read it, (re)allocate and zero it when the
 // layout changes (not under graph capture), then scatter x.
+// columns: those of a slot (f.cols itself where a padded copy finds no room).
 int xr_prepare(xdg_ham_s *h, const Relabelled *in, const void *x, const Form &f, hipStream_t st,
-               bool *capturing) {
+               bool *capturing, int *columns) {
     const xdg_basis_s *b = product_basis(h, in);
     const uint32_t *umap = in ? in->umap.as<uint32_t>() : nullptr;
     const int spr = (int)f.cols * (f.cplx_kernel ? 2 : 1);
-    const int slot = xr_columns(f.cols) * (f.cplx_kernel ? 2 : 1);   // scalars
     const size_t tsz = f.single ? 4 : 8;
-    const size_t slot_bytes = (size_t)slot * tsz;
-    const size_t need = (size_t)b->xr_slots * slot_bytes;
+    int slot = xr_columns(f.cols) * (f.cplx_kernel ? 2 : 1);   // scalars
+    size_t slot_bytes = (size_t)slot * tsz, need = (size_t)b->xr_slots * slot_bytes;
+    auto unpadded = [&] {
+        slot = spr;
+        slot_bytes = (size_t)slot * tsz;
+        need = (size_t)b->xr_slots * slot_bytes;
+    };
+    if (h->xr_of == b && h->xr_slot_bytes == (size_t)spr * tsz) unpadded();   // as before
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     XDG_TRY_HIP(hipStreamIsCapturing(st, &cs));
     *capturing = cs != hipStreamCaptureStatusNone;
@@ -231,7 +237,14 @@ int xr_prepare(xdg_ham_s *h, const Relabelled *in, const void *x, const Form &f,
         if (h->xr_buf.bytes < need) {
             h->xr_slot_bytes = 0;
             h->xr_buf.release();   // waits for the device
-            XDG_RETURN_IF(h->xr_buf.alloc(need));
+            const std::string before = get_error();
+            int rc = h->xr_buf.alloc(need);
+            if (rc == XDG_ENOMEM && slot != spr) {
+                unpadded();
+                rc = h->xr_buf.alloc(need);
+                if (rc == XDG_OK) set_error("%s", before.c_str());
+            }
+            XDG_RETURN_IF(rc);
         }
         const uint64_t nw = need / 4;
         const unsigned g = (unsigned)std::min<uint64_t>((nw + 255) / 256, (uint64_t)gcap);
@@ -241,6 +254,7 @@ int xr_prepare(xdg_ham_s *h, const Relabelled *in, const void *x, const Form &f,
         h->xr_slot_bytes = slot_bytes;
         h->xr_of = b;
     }
+    *columns = slot / (f.cplx_kernel ? 2 : 1);
     const unsigned g =
         (unsigned)std::min<int64_t>((b->dim + 255) / 256, (int64_t)gcap);
     const uint64_t *top = b->xr_top.as<uint64_t>();
@@ -479,7 +493,7 @@ int apply_launch(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, 
     std::unique_lock<std::mutex> xr_lock;
     if (xr_on) {
         xr_lock = std::unique_lock<std::mutex>(h->xr_mu);
-        XDG_RETURN_IF(xr_prepare(h, in.get(), x, f, st, &capturing));
+        XDG_RETURN_IF(xr_prepare(h, in.get(), x, f, st, &capturing, &A.one.xr_cols));
         A.one.xr = h->xr_buf.p;
     }
     A.nvec = f.cols;

@@ -73,3 +73,35 @@ def test_the_tuned_shape_can_be_asked_for(X, nvec, dtype):
     assert cfg["nv"] in (1, 2, 4, 8), cfg
     X.xdg_apply_with_config(H.handle, x, z, **cfg)
     assert torch.equal(y, z)
+
+
+def test_a_padded_copy_without_room(X):
+    """Three vectors take slots of four columns, and of three where memory ends
+    between the two."""
+    m, _ = CASES["square36"]
+    b = X.Basis.from_model(m)
+    H = X.Hamiltonian.from_model(b, m)
+    x = torch.randn(b.dim, 3, dtype=torch.float64, device="cuda")
+    ref, y = torch.empty_like(x), torch.full_like(x, 3.0)
+    X.xdg_apply_with_config(H.handle, x, ref)
+    used = X.xdg_set_device_memory_limit(0)
+    X.xdg_apply_with_config(H.handle, x, y, xr=1)
+    padded = X.xdg_set_device_memory_limit(0) - used
+    assert torch.equal(y, ref)
+    H = X.Hamiltonian.from_model(b, m)
+    used = X.xdg_set_device_memory_limit(0)
+    X.xdg_set_device_memory_limit(used + padded * 7 // 8)
+    try:
+        for _ in range(2):
+            y.fill_(3.0)
+            X.xdg_apply_with_config(H.handle, x, y, xr=1)
+            assert torch.equal(y, ref)
+        assert X.xdg_set_device_memory_limit(0) == used + padded * 3 // 4
+    finally:
+        X.xdg_set_device_memory_limit(0)
+    for nvec in (4, 3, 1):               # other slots, and back
+        z = torch.randn(b.dim, nvec, dtype=torch.float64, device="cuda")
+        want, got = torch.empty_like(z), torch.full_like(z, 3.0)
+        X.xdg_apply_with_config(H.handle, z, want)
+        X.xdg_apply_with_config(H.handle, z, got, xr=1)
+        assert torch.equal(want, got), nvec
