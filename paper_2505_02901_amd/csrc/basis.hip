@@ -282,7 +282,8 @@ struct RepTest {
         if constexpr (KIND == K_SUB) {
             if (A.stage_sub) {
                 auto copy = [&](auto *src, uint32_t n) {
-                    auto *dst = reinterpret_cast<std::remove_const_t<std::remove_pointer_t<decltype(src)>> *>(smem + off);
+                    using E = std::remove_const_t<std::remove_pointer_t<decltype(src)>>;
+                    auto *dst = reinterpret_cast<E *>(smem + off);
                     off = align16(off + sizeof(*src) * (size_t)n);
                     for (uint32_t e = threadIdx.x; e < n; e += blockDim.x) dst[e] = src[e];
                     return dst;
@@ -1124,6 +1125,72 @@ int basis_build_device(xdg_basis_s *b) {
     return XDG_OK;
 }
 
+// --------------------------------------------------- second labellings --
+namespace {
+std::mutex g_inner_mu;
+std::vector<xdg_basis_s *> g_inner_of;   // the blocks that have a second labelling
+}  // namespace
+
+void offer_relabelled(xdg_basis_s *b, RelabelledRef in) {
+    std::lock_guard<std::mutex> all(g_inner_mu);
+    std::lock_guard<std::mutex> lock(b->inner_mu);
+    b->inner = std::move(in);
+    b->has_inner = true;
+    g_inner_of.push_back(b);
+}
+
+void forget_relabelled(xdg_basis_s *b) {
+    if (!b->has_inner) return;
+    std::lock_guard<std::mutex> all(g_inner_mu);
+    g_inner_of.erase(std::remove(g_inner_of.begin(), g_inner_of.end(), b), g_inner_of.end());
+}
+
+RelabelledRef relabelled(const xdg_ham_s *h, hipStream_t st) {
+    xdg_basis_s *b = h->basis;
+    if (!b->has_inner || !h->inner_bonds.d.p) return nullptr;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    bool captured = false;
+    if (st) {
+        captured = hipStreamIsCapturing(st, &cs) != hipSuccess ||
+                   cs != hipStreamCaptureStatusNone;
+    }
+    std::lock_guard<std::mutex> lock(b->inner_mu);
+    b->inner_captured |= captured && b->inner;
+    return b->inner;
+}
+
+std::vector<RelabelledRef> relabelled(int n, xdg_ham_s *const *hams, hipStream_t st) {
+    std::vector<RelabelledRef> in(n);
+    for (int i = 0; i < n; ++i) in[i] = relabelled(hams[i], st);
+    return in;
+}
+
+bool give_up_relabelled() {
+    const uint64_t missing = take_missing_memory();
+    if (!missing) return false;
+    std::vector<RelabelledRef> gone;   // freed after the locks
+    {
+        std::lock_guard<std::mutex> all(g_inner_mu);
+        uint64_t held = 0;
+        for (xdg_basis_s *b : g_inner_of) {
+            std::lock_guard<std::mutex> lock(b->inner_mu);
+            if (b->inner && !b->inner_captured) held += b->inner->bytes;
+        }
+        if (held < missing) return false;
+        for (xdg_basis_s *b : g_inner_of) {
+            std::lock_guard<std::mutex> lock(b->inner_mu);
+            if (!b->inner || b->inner_captured) continue;
+            gone.push_back(std::move(b->inner));
+            b->inner = nullptr;
+            b->has_inner = false;
+        }
+        g_inner_of.erase(std::remove_if(g_inner_of.begin(), g_inner_of.end(),
+                                        [](xdg_basis_s *b) { return !b->has_inner; }),
+                         g_inner_of.end());
+    }
+    return true;
+}
+
 // ------------------------------------------------------- inner labelling --
 namespace {
 
@@ -1198,7 +1265,7 @@ static uint64_t basis_bytes(const xdg_basis_s *b) {
 }
 
 // wrong: the map does not fit the block (an error of this library's, returned).
-static int build_inner(xdg_basis_s *b, uint32_t *wrong) {
+static int build_inner(xdg_basis_s *b, bool few_rows, uint32_t *wrong) {
     const Plan &P = b->plan;
     if (b->dim < 1 || b->dim >= 0x7FFFFFFF || (P.flags & XDG_FLAG_HASH_INDEX)) return XDG_OK;
     if (P.kind != K_TAB && !(P.kind == K_SUB && !P.sub.packed())) return XDG_OK;
@@ -1209,7 +1276,7 @@ static int build_inner(xdg_basis_s *b, uint32_t *wrong) {
     // 6 of 24 up 57 and 45 us, 2.9 and 4.8 ms: a hundred and more products make up
     // for that).  Tables without that room keep them out of it (6x6 triangular
     // lattice, 5 of 36 up: 1.99 ms a product, 0.10 in others).
-    if (P.kind == K_SUB && below_few_line(b) &&
+    if (P.kind == K_SUB && few_rows &&
         6 * ((size_t)P.sub.n_s << P.sub.m) + 2 * P.sub.cand_list.size() + 4 * P.sub.pid.size() +
                 2 * P.sub.tperm.size() + 64 * 1024 < lds_limit())
         return XDG_OK;
@@ -1285,10 +1352,10 @@ static int build_inner(xdg_basis_s *b, uint32_t *wrong) {
 // The caller's block is complete without the inner one: whatever keeps that from
 // being built (no room, a plan or an index that does not apply) leaves the block
 // in the caller's labels and the thread's last error as it was.
-int basis_build_inner(xdg_basis_s *b) {
+int basis_build_inner(xdg_basis_s *b, bool few_rows) {
     const std::string before = get_error();
     uint32_t wrong = 0;
-    const int rc = build_inner(b, &wrong);
+    const int rc = build_inner(b, few_rows, &wrong);
     if (rc == XDG_OK) return XDG_OK;
     if (wrong) {
         set_error("internal: an orbit of the relabelled sector has no place in the basis");

@@ -11,72 +11,6 @@ using namespace xdg;
 
 namespace xdg {
 int last_timing(double *total, double *apply);
-
-namespace {
-std::mutex g_inner_mu;
-std::vector<xdg_basis_s *> g_inner_of;   // the blocks that have a second labelling
-}  // namespace
-
-void offer_relabelled(xdg_basis_s *b, RelabelledRef in) {
-    std::lock_guard<std::mutex> all(g_inner_mu);
-    std::lock_guard<std::mutex> lock(b->inner_mu);
-    b->inner = std::move(in);
-    b->has_inner = true;
-    g_inner_of.push_back(b);
-}
-
-static void forget_relabelled(xdg_basis_s *b) {
-    if (!b->has_inner) return;
-    std::lock_guard<std::mutex> all(g_inner_mu);
-    g_inner_of.erase(std::remove(g_inner_of.begin(), g_inner_of.end(), b), g_inner_of.end());
-}
-
-RelabelledRef relabelled(const xdg_ham_s *h, hipStream_t st) {
-    xdg_basis_s *b = h->basis;
-    if (!b->has_inner || !h->inner_bonds.d.p) return nullptr;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    bool captured = false;
-    if (st) {
-        captured = hipStreamIsCapturing(st, &cs) != hipSuccess ||
-                   cs != hipStreamCaptureStatusNone;
-    }
-    std::lock_guard<std::mutex> lock(b->inner_mu);
-    b->inner_captured |= captured && b->inner;
-    return b->inner;
-}
-
-std::vector<RelabelledRef> relabelled(int n, xdg_ham_s *const *hams, hipStream_t st) {
-    std::vector<RelabelledRef> in(n);
-    for (int i = 0; i < n; ++i) in[i] = relabelled(hams[i], st);
-    return in;
-}
-
-bool give_up_relabelled() {
-    const uint64_t missing = take_missing_memory();
-    if (!missing) return false;
-    std::vector<RelabelledRef> gone;   // freed after the locks
-    {
-        std::lock_guard<std::mutex> all(g_inner_mu);
-        uint64_t held = 0;
-        for (xdg_basis_s *b : g_inner_of) {
-            std::lock_guard<std::mutex> lock(b->inner_mu);
-            if (b->inner && !b->inner_captured) held += b->inner->bytes;
-        }
-        if (held < missing) return false;
-        for (xdg_basis_s *b : g_inner_of) {
-            std::lock_guard<std::mutex> lock(b->inner_mu);
-            if (!b->inner || b->inner_captured) continue;
-            gone.push_back(std::move(b->inner));
-            b->inner = nullptr;
-            b->has_inner = false;
-        }
-        g_inner_of.erase(std::remove_if(g_inner_of.begin(), g_inner_of.end(),
-                                        [](xdg_basis_s *b) { return !b->has_inner; }),
-                         g_inner_of.end());
-    }
-    return true;
-}
-
 }  // namespace xdg
 
 namespace {
@@ -234,7 +168,7 @@ int xdg_create_basis(int n_sites, int n_up, int n_sym, const int32_t *perm, cons
         if (rc == XDG_OK) rc = basis_build_device(b);
         if (rc == XDG_OK && (!opts || opts->search == XDG_SEARCH_AUTO) &&
             (!opts || opts->n_sublattices == 0))
-            rc = basis_build_inner(b);
+            rc = basis_build_inner(b, below_few_line(b));
         if (rc != XDG_OK) {
             delete b;
             return rc;

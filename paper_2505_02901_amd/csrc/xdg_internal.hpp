@@ -359,7 +359,8 @@ inline void bondx_site(int i, int m, int pb, BondX &x) {
 }
 
 int basis_build_device(xdg_basis_s *b);                 // enumerate + index
-int basis_build_inner(xdg_basis_s *b);                  // b->inner, where it applies
+// b->inner, where it applies (few_rows: see below_few_line)
+int basis_build_inner(xdg_basis_s *b, bool few_rows);
 // The labelling that a launch on `st` uses (null: the caller's); under capture
 // it stays from then on.
 using RelabelledRef = std::shared_ptr<const Relabelled>;
@@ -371,6 +372,7 @@ bool tables_fit(const xdg_ham_s *h, const Relabelled *in);
 // all blocks if what they hold covers what was missing.  True: call again.
 bool give_up_relabelled();
 void offer_relabelled(xdg_basis_s *b, RelabelledRef in);
+void forget_relabelled(xdg_basis_s *b);
 // Bytes that this thread's last failed allocation lacked (0: none since the
 // last call of this).
 uint64_t take_missing_memory();
