@@ -226,7 +226,7 @@ int xdg_ham_dim(xdg_ham h, int64_t *dim, int *is_complex);
  * on the fly; several vectors at once as for a matrix of coefficients).
  *   x, y: device pointers, [dim][nvec], dtype XDG_F64/F32/C128/C64; x != y.
  *   Real dtypes need a real block (xdg_basis_is_complex == 0).
- * One lane owns each output row and writes it once: no atomics, and the
+ * One lane writes each output element, once: no atomics, and the
  * result is bitwise reproducible for any launch configuration.
  * Enqueued on `stream`. */
 int xdg_apply(xdg_ham h, const void *x, void *y, int64_t nvec, int dtype, void *stream);
@@ -246,13 +246,15 @@ typedef struct xdg_launch_cfg {
                           rank-addressed copy (slot = place of the representative among the
                           states whose top block is a minimal top, ordered in the packed
                           form by the contents of their blocks and otherwise by rank;
-                          zeros where the representative is not a basis state), filled by a scatter before
-                          the launch: one random read per term instead of an index word and
+                          zeros where the representative is not a basis state), filled by a
+                          scatter before the launch: one random read per term instead of an index word and
                           x.  The copy is device memory held by the Hamiltonian (slots x the
-                          row's bytes; XDG_ENOMEM when it does not fit), set up by a first call
-                          outside graph capture; calls on other streams wait for the last
-                          launch that read it.  0 = through the rank index.  Elsewhere
-                          ignored.  Both give the same y (up to the sign of zero sums) */
+                          row's bytes, up to eight columns padded to a power of two unless
+                          only the bare row fits; XDG_ENOMEM when that does not), set up by a
+                          first call outside graph capture; calls on other streams wait for
+                          the last launch that read it.  0 = through the rank index.
+                          Elsewhere ignored.  Both give the same y (up to the sign of zero
+                          sums) */
     int reserved[2];   /* must be zero */
 } xdg_launch_cfg;
 
@@ -276,7 +278,7 @@ int xdg_apply_batched(int n, const xdg_ham *hams, const void *const *xs, void *c
  * hipMalloc.  Same arguments, kernels and results (bitwise) as
  * xdg_apply_batched, but it allocates nothing: the queue counter, the tile
  * prefix and the sector descriptors live in one file-scope device array of
- * the library (about 40 KB, held by each GPU the library runs on until the
+ * the library (about 64 KB, held by each GPU the library runs on until the
  * process ends), written by small kernels on `stream` before the launch.
  * Limit: n <= 128 blocks (XDG_EINVAL beyond, before any launch).  Every call
  * on a GPU shares that GPU's array: calls that overlap on one GPU (other

@@ -164,7 +164,8 @@ int form_of(const xdg_basis_s *b, int dtype, int64_t nvec, Form *f) {
 }
 
 // Rank-addressed x: row i of x (spr scalars) goes to the slot of reps[i]
-// (block_slot in the packed form, top_rank otherwise) of xr (`slot` scalars apart); the other slots hold zeros.
+// (block_slot in the packed form, top_rank otherwise) of xr (`slot` scalars
+// apart); the other slots hold zeros.
 template <class W, class T>
 __global__ __launch_bounds__(256) void k_xr_scatter(const W *reps, int64_t dim, int spr, int slot,
                                                    const T *x, T *xr, const uint32_t *rtab,
@@ -262,26 +263,30 @@ int xr_prepare(xdg_ham_s *h, const Relabelled *in, const void *x, const Form &f,
         if (f.single)
             hipLaunchKernelGGL((k_xr_scatter<uint64_t, float>), dim3(g), dim3(256), 0, st,
                                b->reps.as<uint64_t>(), b->dim, spr, slot, (const float *)x,
-                               h->xr_buf.as<float>(), b->xr_rtab.as<uint32_t>(), b->rank, b->xr_bits, top,
+                               h->xr_buf.as<float>(), b->xr_rtab.as<uint32_t>(), b->rank,
+                               b->xr_bits, top,
                                b->xr_slots, umap, b->xb_ent.as<uint32_t>(),
                                b->xb_off.as<uint32_t>(), b->xb_top.as<uint2>());
         else
             hipLaunchKernelGGL((k_xr_scatter<uint64_t, double>), dim3(g), dim3(256), 0, st,
                                b->reps.as<uint64_t>(), b->dim, spr, slot, (const double *)x,
-                               h->xr_buf.as<double>(), b->xr_rtab.as<uint32_t>(), b->rank, b->xr_bits, top,
+                               h->xr_buf.as<double>(), b->xr_rtab.as<uint32_t>(), b->rank,
+                               b->xr_bits, top,
                                b->xr_slots, umap, b->xb_ent.as<uint32_t>(),
                                b->xb_off.as<uint32_t>(), b->xb_top.as<uint2>());
     } else {
         if (f.single)
             hipLaunchKernelGGL((k_xr_scatter<uint32_t, float>), dim3(g), dim3(256), 0, st,
                                b->reps.as<uint32_t>(), b->dim, spr, slot, (const float *)x,
-                               h->xr_buf.as<float>(), b->xr_rtab.as<uint32_t>(), b->rank, b->xr_bits, top,
+                               h->xr_buf.as<float>(), b->xr_rtab.as<uint32_t>(), b->rank,
+                               b->xr_bits, top,
                                b->xr_slots, umap, b->xb_ent.as<uint32_t>(),
                                b->xb_off.as<uint32_t>(), b->xb_top.as<uint2>());
         else
             hipLaunchKernelGGL((k_xr_scatter<uint32_t, double>), dim3(g), dim3(256), 0, st,
                                b->reps.as<uint32_t>(), b->dim, spr, slot, (const double *)x,
-                               h->xr_buf.as<double>(), b->xr_rtab.as<uint32_t>(), b->rank, b->xr_bits, top,
+                               h->xr_buf.as<double>(), b->xr_rtab.as<uint32_t>(), b->rank,
+                               b->xr_bits, top,
                                b->xr_slots, umap, b->xb_ent.as<uint32_t>(),
                                b->xb_off.as<uint32_t>(), b->xb_top.as<uint2>());
     }

@@ -1,7 +1,7 @@
 // The matrix-free application y = H x on a sector (apply, Sec. 3.6; the
 // on-the-fly element loop of Sec. 5.1 and the indexing of Sec. 5.2).
 //
-// Pull form: one lane owns one output row r (a basis state).  For every bond
+// Pull form: every output row r (a basis state) is summed by one lane.  For every bond
 // with unequal spins it forms t = r with both spins exchanged, finds the
 // representative s of t, a group element u with u.t = s (the first one the
 // search meets: when s is in the block, chi is 1 on Stab(s), so every such u
@@ -444,13 +444,6 @@ __device__ __forceinline__ int64_t user_pos(const SectorDesc &d, int64_t k, A &f
     return (int64_t)(v & 0x7FFFFFFFu);
 }
 
-// T: storage type of x and y; A: type of the amplitudes and of the per-row
-// accumulation (each output element is rounded to T once, at the store).
-// XR: the terms read the rank-addressed x (sublattice coding, d.xr set);
-// XR = 2: every character is 1 (the amplitude skips chi(u), a product by
-// exactly 1).  PIPE: each term's gather is added at the next term of the row
-// (or after its last bond), so that its latency overlaps the next search;
-// the same fused multiply-adds in the same order.
 // A row of a block without a group.  All lanes take the same bond, whose data
 // are scalars: neighbouring rows agree in their upper sites, so most of a
 // wave's gathers are consecutive.  Exchanging sites i and i + 1 moves the
@@ -586,7 +579,15 @@ __device__ __forceinline__ void process_row_own(const SectorDesc &d, const Stage
     for (int v = 0; v < NV; ++v) gst(Y + base + v, (T)fmadd<A>(diag, (A)xd[v], acc[v]));
 }
 
-// FORM: as for locate (the packed one comes with its bond records).
+// A row of a block with a group.  FORM: as for locate (the packed one comes with
+// its bond records).
+// T: storage type of x and y; A: type of the amplitudes and of the per-row
+// accumulation (each output element is rounded to T once, at the store).
+// XR: the terms read the rank-addressed x (sublattice coding, d.xr set);
+// XR = 2: every character is 1 (the amplitude skips chi(u), a product by
+// exactly 1).  PIPE: each term's gather is added at the next term of the row
+// (or after its last bond), so that its latency overlaps the next search;
+// the same fused multiply-adds in the same order.
 template <class W, int KIND, class T, class A, bool CPLX, int NV, int XR = 0,
           bool PIPE = false, int FORM = FORM_ANY>
 __device__ __forceinline__ void process_row(const SectorDesc &d, const Staged<A> &S, int64_t row,
@@ -1047,6 +1048,7 @@ template <class W, int KIND, class T, class A, bool CPLX>
 __device__ __forceinline__ void process_few(const SectorDesc &d, const Staged<A> &S, int64_t r0,
                                             int64_t r1, int64_t wave, int64_t waves, int few,
                                             unsigned char *scratch, int64_t nvec) {
+    static_assert(KIND != K_U1, "a term without a group is too cheap to share out");
     using B = typename BondT<A>::type;
     constexpr int C = CPLX ? 2 : 1;
     const int lane = (int)__lane_id();
@@ -1070,14 +1072,10 @@ __device__ __forceinline__ void process_few(const SectorDesc &d, const Staged<A>
                     A hs = bd.h;
                     if constexpr (KIND == K_SUB)
                         if (d.umap) idx = user_pos<A>(d, idx, hs);
-                    A ar = hs;
-                    if constexpr (KIND != K_U1) {
-                        const A f = hs * S.sq[cnt];
-                        const auto c = S.chi[u];
-                        ar = f * c.x;
-                        if constexpr (CPLX) amp[2 * e + 1] = f * c.y;
-                    }
-                    amp[C * e] = ar;
+                    const A f = hs * S.sq[cnt];
+                    const auto c = S.chi[u];
+                    if constexpr (CPLX) amp[2 * e + 1] = f * c.y;
+                    amp[C * e] = f * c.x;
                     at = (uint32_t)idx;
                 }
             }
@@ -1113,16 +1111,15 @@ __device__ __forceinline__ void process_few(const SectorDesc &d, const Staged<A>
                     re = at == NO_TERM ? re : n_;
                 }
             }
-            A rn = A(1);
-            if constexpr (KIND != K_U1) rn = S.rsq[gld(d.stab + row)];
+            A rn = S.rsq[gld(d.stab + row)];
             int64_t orow = row;
             if constexpr (KIND == K_SUB)
                 if (d.umap) orow = user_pos<A>(d, row, rn);
             const size_t base = ((size_t)orow * cols + v) * C;
             const A diag = (A)d.jz_quarter - A(0.5) * junq;
-            gst(Y + base, (T)fmadd<A>(diag, (A)gld(X + base), KIND != K_U1 ? rn * re : re));
+            gst(Y + base, (T)fmadd<A>(diag, (A)gld(X + base), rn * re));
             if constexpr (CPLX)
-                gst(Y + base + 1, (T)fmadd<A>(diag, (A)gld(X + base + 1), KIND != K_U1 ? rn * im : im));
+                gst(Y + base + 1, (T)fmadd<A>(diag, (A)gld(X + base + 1), rn * im));
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
