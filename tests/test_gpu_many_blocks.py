@@ -40,3 +40,22 @@ def test_blocks_do_not_mix(X, name, nvec, prec):
         v1, v2 = X.xdg_tpq_micro_batched([hs[i].handle], 0.5, n_iter, nvec, seed=11 + i, prec=prec)
         assert np.array_equal(u[i], v1[0], equal_nan=True), (name, nvec, i)
         assert np.array_equal(u2[i], v2[0], equal_nan=True), (name, nvec, i)
+
+
+@pytest.mark.parametrize("nvec", [2, 8])
+def test_blocks_of_many_sizes(X, nvec):
+    """Small blocks that share an allocation, blocks that fill one together and a
+    block larger than that (2.7 M rows), in every neighbourhood."""
+    ups = (2, 9, 3, 12, 4, 9, 10, 5, 12, 12, 2, 11, 6)
+    ms = {u: W.chain_model(24, n_up=u) for u in ups}
+    bs = {u: X.Basis.from_model(m) for u, m in ms.items()}
+    hs = {u: X.Hamiltonian.from_model(bs[u], m) for u, m in ms.items()}
+    n_iter = 3
+    H = [hs[u].handle for u in ups]
+    _, al, be = X.xdg_lanczos_eigval_batched(H, nvec, n_iter, seed=11)
+    u1, u2 = X.xdg_tpq_micro_batched(H, 0.5, n_iter, nvec, seed=11)
+    for i, u in enumerate(ups):
+        _, a, b = X.xdg_lanczos_eigval_batched([H[i]], nvec, n_iter, seed=11 + i)
+        assert np.array_equal(al[i], a[0]) and np.array_equal(be[i], b[0]), (u, i)
+        v1, v2 = X.xdg_tpq_micro_batched([H[i]], 0.5, n_iter, nvec, seed=11 + i)
+        assert np.array_equal(u1[i], v1[0]) and np.array_equal(u2[i], v2[0]), (u, i)
