@@ -1135,12 +1135,13 @@ void offer_relabelled(xdg_basis_s *b, RelabelledRef in) {
     std::lock_guard<std::mutex> all(g_inner_mu);
     std::lock_guard<std::mutex> lock(b->inner_mu);
     b->inner = std::move(in);
-    b->has_inner = true;
+    b->has_inner = b->had_inner = true;
     g_inner_of.push_back(b);
 }
 
 void forget_relabelled(xdg_basis_s *b) {
-    if (!b->has_inner) return;
+    if (!b->had_inner) return;
+    // (also where it has been given up: that may still be under way)
     std::lock_guard<std::mutex> all(g_inner_mu);
     g_inner_of.erase(std::remove(g_inner_of.begin(), g_inner_of.end(), b), g_inner_of.end());
 }

@@ -256,6 +256,7 @@ struct xdg_basis_s {
     std::atomic<bool> has_inner{false};   // without the lock: false is final
     std::shared_ptr<const xdg::Relabelled> inner;
     bool inner_captured = false;
+    bool had_inner = false;     // set with the labelling, before others see the block
     // workspace of expect_szsz (which waits for its results), used under the lock
     std::mutex measure_mu;
     xdg::DevBuf measure_ws;
