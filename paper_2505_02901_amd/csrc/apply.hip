@@ -344,6 +344,33 @@ static int64_t few_line(const xdg_basis_s *b, int n_bonds, int64_t cols, bool cp
 static int64_t few_weight(const xdg_basis_s *b) {
     return b->dim * b->n_sites / std::max(1, std::min(b->n_up, b->n_sites - b->n_up));
 }
+// Rows so short that the row loop's chain ends before the few-rows loop has staged
+// its tables (one wave a workgroup does that there): thin fillings of rings and of
+// groups of shifts and mirrors.  `terms`: what a row has at most; both loops' times
+// are about linear in it, in the sites and in the length of a search, and the line
+// below is where the fits cross.  Measured, FP64, row loop against few-rows loop (us):
+//   rings, one vector: 2 up 5.9 and 7.8 (N = 16), 5.8 and 11.2 (32), 8.7 and 15.0
+//     (40); 3 up 7.4 and 8.2 (12), 7.3 and 12.6 (32); 4 up 9.3 and 9.2 (16), 9.9 and
+//     11.6 (24), 10.8 and 11.4 (32); N = 28, 6 up 15.1 and 11.8; next neighbours
+//     too: 2 up 11.7 and 14.4 (32); eight vectors: 3 up 8.4 and 12.6 (32, 155 rows),
+//     4 up 14.9 and 13.6 (28, 735 rows), 17.6 and 10.5 (32, 1128 rows);
+//   with reflections: 3 up 9.3 and 10.9 (20), 4 up 11.9 and 12.5 (24);
+//   mirror: 2 up 5.7 and 6.4 (8), 3 up 6.9 and 6.4 (8), 7.5 and 8.7 (16), 8.7 and 11.6
+//     (32), 15.4 and 11.4 (40), 4 up 10.4 and 9.0 (20);
+//   8 shifts: 2 up 8.6 and 9.5 (16), 3 up 11.2 and 10.1 (16), 12.1 and 14.1 (32).
+static bool short_rows(const xdg_basis_s *b, const BondSet &bonds, int n_bonds, int64_t cols,
+                       bool cplx) {
+    if (b->plan.kind != K_AFF) return false;
+    const int N = b->n_sites, ring = b->plan.ring;
+    const int64_t terms = 2 * (int64_t)n_bonds * std::min(b->n_up, N - b->n_up) / N;
+    const int64_t most = (ring ? 8 : 6) - (b->wide ? 2 : 0);
+    if (terms > most || b->dim * (cols * (cplx ? 2 : 1) - 1) > 3000) return false;
+    const int search = ring == 2 ? 10 : ring ? 8 : 6 + b->n_sym;   // a term's, in tenths of us
+    const int64_t row = terms * ((b->wide ? search * 3 / 2 : search) - 4) +
+                        (bonds.ring ? 0 : n_bonds / 3);
+    const int64_t few = ring ? 8 + 8 * N / 5 : 2 + 8 * N / 5 + 2 * b->n_sym;
+    return row < few;
+}
 bool below_few_line(const xdg_basis_s *b) { return few_weight(b) < few_line(b, 0, 1, false); }
 
 // Blocks without a group: is an exchange of sites that are not neighbouring
@@ -413,8 +440,10 @@ static bool few_shape(int64_t rows, int n_bonds, bool cplx, bool single_acc, siz
     const size_t per_wave = single_acc ? few_bytes<float>(cplx, *few * nb)
                                        : few_bytes<double>(cplx, *few * nb);
     const int64_t waves = (rows + *few - 1) / *few;
-    // a workgroup per compute unit at least, as large as that leaves it
-    int w = 1;
+    // a workgroup per compute unit at least, as large as that leaves it; one wave
+    // that is alone has the others of its workgroup stage the tables (4x6 square,
+    // translations, 1 up: 57 us with none, 16 with fifteen; row loop 24)
+    int w = waves > 1 ? 1 : 16;
     while (w < 16 && (int64_t)w * device_cu_count() < waves) w *= 2;
     while (w > 1 && a16(tables) + w * per_wave > lds_budget()) w /= 2;
     *block = 64 * w;
@@ -602,7 +631,8 @@ int apply_tuned(xdg_ham_s *h, const void *x, void *y, int64_t nvec, int dtype, h
     if (b->dim < (int64_t)1024 * APPLY_BLOCK) {   // small blocks: one row per lane
         LaunchCfg c{APPLY_BLOCK, (int)std::min<int64_t>(need, 1 << 30), 8};
         c.small = 1;
-        c.few = few_weight(b) < few_line(b, h->n_bonds, f.cols, f.cplx_kernel);
+        c.few = few_weight(b) < few_line(b, h->n_bonds, f.cols, f.cplx_kernel) &&
+                !short_rows(b, in ? h->inner_bonds : h->bonds, h->n_bonds, f.cols, f.cplx_kernel);
         h->tuned[key] = c;
         return apply_launch(h, x, y, nvec, dtype, st, &c);
     }

@@ -130,3 +130,44 @@ def test_many_bonds_without_a_group(X, n, n_up, far):
         run(y)
         # up to 6701 terms of size max |x|, each rounded once against a sum of that many
         assert np.max(np.abs(y.cpu().numpy() - want)) < 6701 * 6701 * 1.2e-16 * float(x.abs().max())
+
+
+def shifts(n, step, up):
+    i = np.arange(n)
+    perm = (np.array([i, i[::-1]]) if step is None else
+            np.array([(i + step * k) % n for k in range(n // step)])).astype(np.int32)
+    return W.chain_model(n, n_up=up).with_sector(perm, np.ones(len(perm), complex))
+
+
+THIN = {f"ring{n}_{up}": W.chain_model(n, n_up=up, l=0)
+        for n, up in ((12, 0), (12, 1), (12, 3), (12, 4), (16, 4), (24, 4), (24, 5), (40, 3), (40, 4))}
+THIN |= {f"ring{n}_{up}_k1": W.chain_model(n, n_up=up, l=1) for n, up in ((8, 2), (28, 4))}
+THIN |= {f"dihedral{n}_{up}": W.chain_model(n, n_up=up).with_sector(
+    W.chain_dihedral(n), np.ones(2 * n, complex)) for n, up in ((20, 3), (20, 17), (20, 4))}
+THIN |= {f"mirror{n}_{up}": shifts(n, None, up) for n, up in ((8, 3), (16, 3), (16, 4), (40, 2), (40, 3))}
+THIN |= {f"shifts{n}_{up}": shifts(n, s, up) for n, s, up in ((16, 2, 2), (16, 2, 3), (12, 4, 3))}
+THIN |= {f"square{a[0]}x{b[1]}_{up}": W.torus_model(a, b, 1.0, 0.5, "A1", n_up=up, rotations=False,
+                                                    reflections=False)
+         for a, b in (((4, 0), (0, 4)), ((4, 0), (0, 6))) for up in (0, 1, 2)}
+
+
+@pytest.mark.parametrize("name", sorted(THIN))
+def test_thin_fillings(X, name):
+    """rows of few terms, on both sides of the line between the loops, and blocks
+    of a single wave"""
+    m = THIN[name]
+    b = X.Basis.from_model(m)
+    H = X.Hamiltonian.from_model(b, m)
+    basis = oracle.basis(m)
+    for dt in (torch.float32, torch.float64, torch.complex128):
+        if b.is_complex and not dt.is_complex:
+            continue
+        for nvec in (1, 2, 8):
+            x = torch.randn(b.dim, nvec, dtype=dt, device="cuda")
+            y, z = torch.full_like(x, 3.0), torch.full_like(x, 4.0)
+            H.apply(x, y)
+            X.xdg_apply_with_config(H.handle, x, z)
+            assert torch.equal(y, z), (name, dt, nvec)
+            want = oracle.apply(m, basis, x.cpu().numpy())
+            tol = 2e-6 if dt == torch.float32 else 1e-12
+            assert np.max(np.abs(y.cpu().numpy() - want)) <= tol * max(np.max(np.abs(want)), 1.0)
